@@ -115,15 +115,22 @@ const fl::KernelEntry* find_entry(const fl_variant_desc* d, int dtype, int D, in
   for (int t = 0; t < 5; ++t)
     for (int e = 0; e < r.n[t]; ++e) {
       const fl::KernelEntry& k = r.tab[t][e];
-      if (k.key.dtype != dtype || k.key.diff != (int)d->combine || (k.key.paged != 0) != (paged != nullptr)) continue;
+      if (k.key.dtype != dtype || (k.key.paged != 0) != (paged != nullptr)) continue;
       if (paged != nullptr && (k.key.pack != paged->pack || k.key.nwaves != (paged->wide ? 8 : 4))) continue;
       if (paged == nullptr && k.key.pack != (packed != nullptr ? packed->pack : 1)) continue;
       if (packed != nullptr && k.key.nwaves != (packed->wide ? 8 : 4)) continue;
       if (dtype == FL_F32) {
+        // The smallest head dim that fits; of its shapes the first (fewest key splits) that gives every CU a workgroup, two
+        // under a mask that leaves the query tiles unequal work, else the last.  Measured with 256- / 128- / 64- / 32-row
+        // workgroups: 2 x 8 heads of 1024 rows at D = 64 154 / 83 / 51 / 61 us (64, 128, 256, 512 workgroups), 4 x 16 heads
+        // 162 / 167 / 188 / 225; causal, 2 x 8 heads of 2048 rows 289 / 158 / 105 / 119.
         if (D > k.key.D || Dv > k.key.DV) continue;
-        if (best == nullptr || k.key.D < best->key.D) best = &k;   // smallest register budget that fits
+        const bool fills = best != nullptr && heads * ((Sq + best->bm - 1) / best->bm) >= (mask != 0 ? 512 : 256);
+        if (best == nullptr || k.key.D < best->key.D || (k.key.D == best->key.D && (g_tuning.bm != 0 ? k.bm == g_tuning.bm : heads > 0 && !fills)))
+          best = &k;
         continue;
       }
+      if (k.key.diff != (int)d->combine) continue;
       if (k.key.D != D || k.key.DV != Dv || k.key.mod != (int)d->score_mod || k.key.mask != mask ||
           k.key.nbias != (int)d->n_bias || k.key.epi != (int)d->epilogue)
         continue;
@@ -1174,6 +1181,7 @@ static fl_status forward_call(const fl_tensor* q, const fl_tensor* k, const fl_t
   p.mask = (int)mask;
   p.n_bias = (int)desc->n_bias;
   p.epi = (int)desc->epilogue;
+  p.diff = diff;
   p.n_qtiles = (int)((Sq + ke->bm - 1) / ke->bm);
   if (dtype == FL_BF16) {
     // dynamic LDS: the K/V rings, then two staging buffers per wave and bias for the bias tiles

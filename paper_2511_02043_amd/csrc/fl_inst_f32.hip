@@ -1,21 +1,34 @@
-// fp32-storage kernels: variant switches are runtime values here, only the stream count and the
-// register budget for the head dim are compile-time.
+// fp32-storage kernels: variant switches are runtime values here, only the register budget for the head dim and the
+// workgroup's shape (row groups x key splits) are compile-time.
 #include "fl_registry.hpp"
 #include "fl_kernel_f32.hpp"
 namespace fl {
-template <bool DIFF, int DMAX>
+template <class C>
 static hipError_t launch_f32(const FwdParams& p, int nblocks, hipStream_t stream) {
-  constexpr int kLds = ((DIFF ? 2 : 1) * kF32Keys * DMAX + kF32Keys * DMAX) * 4;
-  hipLaunchKernelGGL((fwd_f32_kernel<DIFF, DMAX>), dim3(nblocks), dim3(256), kLds, stream, p);
+  static std::atomic<bool> done[64];               // the dynamic-LDS limit is per device and sticky, as in launch_bf16
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= 64 || !done[dev].load(std::memory_order_acquire)) {
+    e = hipFuncSetAttribute((const void*)fwd_f32_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
+    if (e != hipSuccess) return e;
+    if (dev >= 0 && dev < 64) done[dev].store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL(fwd_f32_kernel<C>, dim3(nblocks), dim3(C::NT), C::LDS, stream, p);
   return hipGetLastError();
 }
-#define E(DIFF, DMAX)                                                                        \
-  KernelEntry {                                                                              \
-    KernelKey{2, DMAX, DMAX, -1, -1, -1, DIFF ? 1 : 0, -1, 4, 1, kF32Keys, 0, 0, 0, 1}, kF32Rows,           \
-        ((DIFF ? 2 : 1) * kF32Keys * DMAX + kF32Keys * DMAX) * 4, &launch_f32<DIFF, DMAX>    \
-  }
-static const KernelEntry kEntries[] = {E(false, 64), E(false, 128), E(true, 64), E(true, 128)};
-#undef E
+template <int DMAX, int RG, int KS>
+static constexpr KernelEntry entry() {
+  typedef F32Cfg<DMAX, RG, KS> C;
+  static_assert(C::LDS <= kMaxLdsBytes, "LDS of a compute unit");
+  return KernelEntry{KernelKey{2, DMAX, DMAX, -1, -1, -1, -1, -1, RG * KS, KS, kF32Keys, 0, 0, 0, 1}, C::BM, C::LDS, &launch_f32<C>};
+}
+// per head dim in the order of the key splits (find_entry takes the first one that fills the chip)
+static const KernelEntry kEntries[] = {
+    entry<32, 8, 1>(),  entry<32, 4, 2>(),  entry<32, 2, 4>(), entry<32, 1, 8>(),
+    entry<64, 8, 1>(),  entry<64, 4, 2>(),  entry<64, 2, 4>(), entry<64, 1, 8>(),
+    entry<128, 8, 1>(), entry<128, 4, 2>(), entry<128, 1, 4>(),
+};
 const KernelEntry* entries_f32(int* n) {
   *n = (int)(sizeof(kEntries) / sizeof(kEntries[0]));
   return kEntries;

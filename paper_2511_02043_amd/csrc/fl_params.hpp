@@ -79,7 +79,7 @@ struct FwdParams {
   int32_t window, prefix;
   float scale, softcap, rms_eps;
   int32_t out_f32;       // 1: out is float, 0: out has the input dtype
-  int32_t mod, mask, n_bias, epi;   // runtime copy of the descriptor (fp32 kernel reads these)
+  int32_t mod, mask, n_bias, epi, diff;   // runtime copy of the descriptor (fp32 kernel reads these)
   int32_t n_qtiles;      // ceil(Sq / rows per workgroup)
   int32_t order;         // workgroup ordering scheme
   int32_t doc_vec;       // 1: kv_doc rows are 16-byte aligned and Sk % 4 == 0 -> 4 ids per load
