@@ -258,35 +258,48 @@ __global__ void empty_keys_kernel(fl::View out, int out_f32, float* lse, int64_t
 }
 
 struct BwdRegistry {
-  const fl::BwdEntry* tab[2];
-  int n[2];
+  const fl::BwdEntry* tab[3];
+  int n[3];
   BwdRegistry() {
     tab[0] = fl::entries_bwd64(&n[0]);
     tab[1] = fl::entries_bwd128(&n[1]);
+    tab[2] = fl::entries_bwd32(&n[2]);
   }
 };
+
+const BwdRegistry& bwd_registry() {
+  static const BwdRegistry reg;                    // initialised once, also under concurrent first calls
+  return reg;
+}
+
+// The compiled specialisation for exactly these head dims, or null.
+const fl::BwdEntry* find_compiled_bwd(const fl_variant_desc* d, int64_t D, int64_t Dv, int nbias) {
+  const BwdRegistry& reg = bwd_registry();
+  const int mask = (int)canonical_mask(d->mask);
+  for (int t = 0; t < 3; ++t)
+    for (int e = 0; e < reg.n[t]; ++e) {
+      const fl::BwdEntry& k = reg.tab[t][e];
+      if (k.key.D == D && k.key.Dv == Dv && k.key.mod == (int)d->score_mod && k.key.mask == mask && k.key.nbias == nbias) return &k;
+    }
+  return nullptr;
+}
 
 // Can the backward kernel templates be instantiated for this variant at run time (head dim of the core kernels)?
 bool bwd_jit_ok(const fl_variant_desc* d, int D, int nbias) {
   return (D == 64 || D == 128) && d->score_mod <= FL_MOD_SOFTCAP && nbias >= 0 && nbias <= 2;
 }
 
-// The compiled specialisation of the variant; with `instantiate`, otherwise one built from the kernel templates on first
-// use (a few seconds, once per process and variant).
+// The specialisation of the variant at head dim D == Dv: the compiled one or, with `instantiate`, one built from the kernel
+// templates on first use (a few seconds, once per process and variant).
 const fl::BwdEntry* find_bwd_entry(const fl_variant_desc* d, int D, int nbias = 0, bool instantiate = false) {
-  static const BwdRegistry reg;                    // initialised once, also under concurrent first calls
-  const fl::BwdEntry* const* tab = reg.tab;
-  const int* n = reg.n;
-  const int mask = (int)canonical_mask(d->mask);
-  const fl::BwdEntry* same_dim = nullptr;
-  for (int t = 0; t < 2; ++t)
-    for (int e = 0; e < n[t]; ++e) {
-      const fl::BwdEntry& k = tab[t][e];
-      if (k.key.D == D && same_dim == nullptr) same_dim = &k;
-      if (k.key.D == D && k.key.mod == (int)d->score_mod && k.key.mask == mask && k.key.nbias == nbias) return &k;
-    }
-  if (!instantiate || same_dim == nullptr || !bwd_jit_ok(d, D, nbias)) return nullptr;
-  return fl::jit_backward_entry(D, (int)d->score_mod, (uint32_t)mask, nbias, same_dim->prep, same_dim->reduce);
+  const fl::BwdEntry* exact = find_compiled_bwd(d, D, D, nbias);
+  if (exact != nullptr || !instantiate || !bwd_jit_ok(d, D, nbias)) return exact;
+  const BwdRegistry& reg = bwd_registry();
+  for (int t = 0; t < 3; ++t)
+    for (int e = 0; e < reg.n[t]; ++e)
+      if (reg.tab[t][e].key.D == D && reg.tab[t][e].key.Dv == D)
+        return fl::jit_backward_entry(D, (int)d->score_mod, canonical_mask(d->mask), nbias, reg.tab[t][e].prep, reg.tab[t][e].reduce);
+  return nullptr;
 }
 
 hipError_t run_bwd_dq(const fl::BwdEntry* be, const fl::BwdParams& p, int nblocks, hipStream_t stream) {
@@ -394,7 +407,7 @@ struct EpiBwdParams {
   const float* o[2];                // the streams' recomputed outputs, dense [rows, Dv] fp32 (null: not needed)
   const float* lse;                 // [B, ns * G, H, Sq]: stream s of row-axis g at ns * g + s
   int64_t lse_sb, lse_sg, lse_sh;
-  uint16_t* d_o[2];                 // per-stream dO, dense [rows, Dc] bf16, channels past Dv zero
+  uint16_t* d_o[2];                 // per-stream dO, dense [rows, Dvc] bf16, channels past Dv zero (null: dO is dout as it is)
   float* delta[2];                  // per-stream rowsum(dO * O)
   float* lse2[2];                   // per-stream lse * log2(e), +inf for rows without a visible key
   const float* lambda;
@@ -402,7 +415,7 @@ struct EpiBwdParams {
   float* dl_rows;                   // per-row terms of dlambda (summed per head by reduce_dlambda_kernel), or null
   float* dw_part;                   // per-workgroup partial sums of the rms_weight gradient, [workgroups, Dv], or null
   float rms_eps;
-  int32_t B, G, H, Sq, Dv, Dc;
+  int32_t B, G, H, Sq, Dv, Dvc;
   int32_t ns, has_gate, has_rms, dgate_f32;
 };
 
@@ -479,10 +492,10 @@ __global__ void __launch_bounds__(256) epi_bwd_kernel(const EpiBwdParams e) {
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     const int c = lane + 64 * u;
-    if (c < e.Dc) {
+    if (c < e.Dvc && e.d_o[0] != nullptr) {
       const bool ok = c < e.Dv;
-      e.d_o[0][row * e.Dc + c] = ok ? (uint16_t)(fl::pack_bf16(dx[u], 0.f) & 0xFFFFu) : (uint16_t)0;
-      if (e.ns == 2) e.d_o[1][row * e.Dc + c] = ok ? (uint16_t)(fl::pack_bf16(-lam * dx[u], 0.f) & 0xFFFFu) : (uint16_t)0;
+      e.d_o[0][row * e.Dvc + c] = ok ? (uint16_t)(fl::pack_bf16(dx[u], 0.f) & 0xFFFFu) : (uint16_t)0;
+      if (e.ns == 2) e.d_o[1][row * e.Dvc + c] = ok ? (uint16_t)(fl::pack_bf16(-lam * dx[u], 0.f) & 0xFFFFu) : (uint16_t)0;
     }
     d1 += dx[u] * o1[u];
     d2 += -lam * dx[u] * o2[u];
@@ -508,7 +521,7 @@ __global__ void __launch_bounds__(256) epi_bwd_kernel(const EpiBwdParams e) {
 }
 
 // The same with LPR lanes per row, eight channels per lane (16-byte loads and stores), 64 / LPR rows per wave: for tensors
-// whose rows are 16-byte aligned (the host checks).  LPR = Dc / 8; lanes whose channels lie past Dv only write the zero
+// whose rows are 16-byte aligned (the host checks).  LPR = Dvc / 8; lanes whose channels lie past Dv only write the zero
 // padding of the per-stream dO.  The rms_weight partial sums are per workgroup as above, over 4 * 64 / LPR rows.
 template <int LPR>
 __global__ void __launch_bounds__(256) epi_bwd_rows_kernel(const EpiBwdParams e) {
@@ -628,15 +641,15 @@ __global__ void __launch_bounds__(256) epi_bwd_rows_kernel(const EpiBwdParams e)
     d2 += -lam * dx[k] * o2[k];
     dl += -dx[k] * o2[k];
   }
-  if (live && c0 < e.Dc) {
+  if (live && c0 < e.Dvc && e.d_o[0] != nullptr) {
     float z[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) z[k] = ok ? dx[k] : 0.f;
-    *(uint4*)(e.d_o[0] + row * e.Dc + c0) = pack8(z);
+    *(uint4*)(e.d_o[0] + row * e.Dvc + c0) = pack8(z);
     if (e.ns == 2) {
 #pragma unroll
       for (int k = 0; k < 8; ++k) z[k] = ok ? -lam * dx[k] : 0.f;
-      *(uint4*)(e.d_o[1] + row * e.Dc + c0) = pack8(z);
+      *(uint4*)(e.d_o[1] + row * e.Dvc + c0) = pack8(z);
     }
   }
   // without recomputed outputs (one stream, no RMSNorm): delta = rowsum(dy * y) = rowsum(dout * out)
@@ -771,9 +784,9 @@ __global__ void __launch_bounds__(256) pad_rows_kernel(fl::View src, uint16_t* d
   *(uint4*)(dst + row * Dc + c) = v;
 }
 
-// dense fp32 [B, G, H, S, Dc] (optionally the sum of two) -> the first D channels of a [B, G, H, S, D] view, bf16 or fp32
-__global__ void __launch_bounds__(256) scatter_grad_kernel(const float* a, const float* b2, fl::View dst, int dst_f32, int G, int H,
-                                                           int S, int D, int Dc, int64_t rows) {
+// dense fp32 [B, G, H, S, Dc] -> the first D channels of a [B, G, H, S, D] view, bf16 or fp32
+__global__ void __launch_bounds__(256) scatter_grad_kernel(const float* a, fl::View dst, int dst_f32, int G, int H, int S, int D, int Dc,
+                                                           int64_t rows) {
   const int cpr = D / 4;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= rows * cpr) return;
@@ -781,11 +794,7 @@ __global__ void __launch_bounds__(256) scatter_grad_kernel(const float* a, const
   const int c = (int)(idx % cpr) * 4;
   const int i = (int)(row % S), h = (int)((row / S) % H), g = (int)((row / ((int64_t)S * H)) % G);
   const int b = (int)(row / ((int64_t)S * H * G));
-  float4 v = *(const float4*)(a + row * Dc + c);
-  if (b2 != nullptr) {
-    const float4 w = *(const float4*)(b2 + row * Dc + c);
-    v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
-  }
+  const float4 v = *(const float4*)(a + row * Dc + c);
   const int64_t o = b * dst.sb + g * dst.sg + h * dst.sh + (int64_t)i * dst.ss + c;
   if (dst_f32) *(float4*)((float*)dst.ptr + o) = v;
   else *(uint2*)((uint16_t*)dst.ptr + o) = make_uint2(fl::pack_bf16(v.x, v.y), fl::pack_bf16(v.z, v.w));
@@ -852,9 +861,9 @@ PrefillLayout prefill_layout(int64_t B, int64_t Hkv, int64_t D, int64_t max_len)
 
 // Workspace of fl_attn_bwd_ex (byte offsets; every region 256-byte aligned).
 struct ExLayout {
-  int Dc, ns, hsplit;
-  bool need_o, pad_qk, pad_v;
-  size_t stat, o, d_o, qpad, kpad, vpad, gq, gk, gv, sum, part, ds;   // sizes of one region each
+  int Dc, Dvc, ns, hsplit;          // head dims the kernels run at: (D, Dv) where such a kernel is compiled, else core_dim()
+  bool need_o, pad_qk, pad_v, own_do;
+  size_t stat, o, d_o, qpad, kpad, vpad, gq, gk, gv, sum, part_k, part_v, ds;   // sizes of one region each
   size_t off_lse2[2], off_delta[2], off_o[2], off_do[2], off_qpad[2], off_kpad[2], off_vpad, off_gq[2], off_gk[2], off_gv[2],
       off_sum, off_part, off_dl, off_ds, off_dw;
   size_t total;
@@ -864,24 +873,33 @@ ExLayout ex_layout(int64_t B, int64_t G, int64_t H, int64_t Hkv, int64_t Sq, int
   ExLayout L;
   memset(&L, 0, sizeof(L));
   const uint32_t mask = canonical_mask(d->mask);
-  L.Dc = core_dim(D, Dv);
+  L.Dc = L.Dvc = core_dim(D, Dv);
+  if (find_compiled_bwd(d, D, Dv, (int)d->n_bias) != nullptr) {
+    L.Dc = (int)D;
+    L.Dvc = (int)Dv;
+  }
   L.ns = d->combine == FL_DIFFERENTIAL ? 2 : 1;
   L.need_o = L.ns == 2 || (d->epilogue & FL_EPI_RMSNORM) != 0;
   L.pad_qk = D != L.Dc;
-  L.pad_v = Dv != L.Dc;
+  L.pad_v = Dv != L.Dvc;
+  // a dO of its own: the epilogue changes it, a second stream scales it, or it is padded
+  L.own_do = L.ns == 2 || d->epilogue != 0 || L.pad_v;
   const size_t rq = (size_t)(B * G * H * Sq), rk = (size_t)(B * G * Hkv * Sk);
   L.stat = up256(rq * 4);
   L.o = L.need_o ? up256(rq * Dv * 4) : 0;
-  L.d_o = up256(rq * L.Dc * 2);
+  L.d_o = L.own_do ? up256(rq * L.Dvc * 2) : 0;
   L.qpad = L.pad_qk ? up256(rq * L.Dc * 2) : 0;
   L.kpad = L.pad_qk ? up256(rk * L.Dc * 2) : 0;
-  L.vpad = L.pad_v ? up256(rk * L.Dc * 2) : 0;
-  L.gq = up256(rq * L.Dc * 4);
-  L.gk = up256(rk * L.Dc * 4);
-  L.gv = up256(rk * L.Dc * 4);
+  L.vpad = L.pad_v ? up256(rk * L.Dvc * 2) : 0;
+  // fp32 gradients at the kernels' head dims: where these are the caller's, the kernels write the caller's tensors, and only
+  // the first stream's dV is kept, for the second stream's pass to add its own to
+  L.gq = L.pad_qk ? up256(rq * L.Dc * 4) : 0;
+  L.gk = L.pad_qk ? up256(rk * L.Dc * 4) : 0;
+  L.gv = L.pad_v || L.ns == 2 ? up256(rk * L.Dvc * 4) : 0;
   L.sum = up256(workspace_bytes(B, Sq, Sk, mask));
   L.hsplit = choose_hsplit(B, G, H, Hkv, Sq, Sk, mask, clamp_window(d->window, Sq, Sk));
-  L.part = L.hsplit > 1 ? up256((size_t)L.hsplit * rk * L.Dc * 4) : 0;
+  L.part_k = L.hsplit > 1 ? up256((size_t)L.hsplit * rk * L.Dc * 4) : 0;
+  L.part_v = L.hsplit > 1 ? up256((size_t)L.hsplit * rk * L.Dvc * 4) : 0;
   size_t at = 0;
   auto take = [&](size_t n) { const size_t o = at; at += n; return o; };
   for (int s = 0; s < L.ns; ++s) {
@@ -893,11 +911,11 @@ ExLayout ex_layout(int64_t B, int64_t G, int64_t H, int64_t Hkv, int64_t Sq, int
     L.off_kpad[s] = take(L.kpad);
     L.off_gq[s] = take(L.gq);
     L.off_gk[s] = take(L.gk);
-    L.off_gv[s] = take(L.gv);
+    L.off_gv[s] = take(s == 0 ? L.gv : 0);
   }
   L.off_vpad = take(L.vpad);
   L.off_sum = take(L.sum);
-  L.off_part = take(2 * L.part);
+  L.off_part = take(L.part_k + L.part_v);
   L.off_dl = take(L.ns == 2 ? L.stat : 0);
   // bias gradients: dS of every score (bf16), reduced over the broadcast axes afterwards
   L.ds = d->n_bias > 0 ? up256(rq * (size_t)Sk * 2) : 0;
@@ -915,7 +933,8 @@ bool bwd_simple(const fl_variant_desc* d, int64_t D, int64_t Dv) {
 // Can fl_attn_bwd_ex build the variant from the backward kernels?
 bool bwd_ex_ok(const fl_variant_desc* d, int64_t D, int64_t Dv) {
   if (!((D == 32 || D == 64 || D == 128) && (Dv == 32 || Dv == 64 || Dv == 128))) return false;
-  return find_bwd_entry(d, core_dim(D, Dv), (int)d->n_bias) != nullptr || bwd_jit_ok(d, core_dim(D, Dv), (int)d->n_bias);
+  return find_compiled_bwd(d, D, Dv, (int)d->n_bias) != nullptr || find_bwd_entry(d, core_dim(D, Dv), (int)d->n_bias) != nullptr ||
+         bwd_jit_ok(d, core_dim(D, Dv), (int)d->n_bias);
 }
 
 fl::View dense_view(void* ptr, int64_t G, int64_t H, int64_t S, int64_t Dc) {
@@ -1404,7 +1423,7 @@ fl_status fl::backward_call(const fl_tensor* q, const fl_tensor* k, const fl_ten
   p.scale = desc->scale;
   p.softcap = desc->softcap;
   p.dq_f32 = dq->dtype == FL_F32;
-  p.dkv_f32 = dk->dtype == FL_F32;
+  p.dk_f32 = p.dv_f32 = dk->dtype == FL_F32;
   p.n_qtiles = (int)((Sq + be->bm - 1) / be->bm);
   p.n_ktiles = (int)((Sk + be->bm - 1) / be->bm);
   static_assert(fl::BwdCfg<64, 0, 0, 64, 2>::BM == kBwdKeysPerWg, "keys per dK/dV workgroup");
@@ -1483,8 +1502,11 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
   const bool diff = desc->combine == FL_DIFFERENTIAL;
   const bool has_gate = (desc->epilogue & FL_EPI_GATE_SIGMOID) != 0, has_rms = (desc->epilogue & FL_EPI_RMSNORM) != 0;
   const ExLayout L = ex_layout(B, G, H, Hkv, Sq, Sk, D, Dv, desc);
-  const int Dc = L.Dc, ns = L.ns;
-  const fl::BwdEntry* be = find_bwd_entry(desc, Dc, (int)desc->n_bias, true);
+  const int Dc = L.Dc, Dvc = L.Dvc, ns = L.ns;
+  const fl::BwdEntry* be = Dc == Dvc ? find_bwd_entry(desc, Dc, (int)desc->n_bias, true) : find_compiled_bwd(desc, Dc, Dvc, (int)desc->n_bias);
+  if (be == nullptr)
+    return fail(FL_ERR_UNSUPPORTED, "no backward kernels for D=%lld Dv=%lld score_mod=%u mask=0x%x n_bias=%u", (long long)D,
+                (long long)Dv, desc->score_mod, canonical_mask(desc->mask), desc->n_bias);
 
   // ---- tensors
   const int64_t qsz[5] = {B, G, H, Sq, D}, ksz[5] = {B, G, Hkv, Sk, D}, vsz[5] = {B, G, Hkv, Sk, Dv}, osz[5] = {B, G, H, Sq, Dv};
@@ -1561,7 +1583,7 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
     return fail(FL_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", L.total, aux->workspace ? aux->workspace_bytes : (size_t)0);
   if (((uintptr_t)aux->workspace) % 16 != 0) return fail(FL_ERR_ALIGN, "workspace not 16-byte aligned");
   const int64_t rows_q = B * G * H * Sq, rows_k = B * G * Hkv * Sk;
-  if (rows_q * Dc > 0x7fffffff00LL || rows_k * Dc > 0x7fffffff00LL) return fail(FL_ERR_SHAPE, "too many rows");
+  if (rows_q * std::max(Dc, Dvc) > 0x7fffffff00LL || rows_k * std::max(Dc, Dvc) > 0x7fffffff00LL) return fail(FL_ERR_SHAPE, "too many rows");
 
   hipStream_t stream = (hipStream_t)stream_v;
   unsigned char* ws = (unsigned char*)aux->workspace;
@@ -1612,7 +1634,7 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
   ep.lse_sh = lse->size[2] > 1 ? lse->stride[2] : 0;
   for (int s = 0; s < ns; ++s) {
     ep.o[s] = L.need_o ? (const float*)(ws + L.off_o[s]) : nullptr;
-    ep.d_o[s] = (uint16_t*)(ws + L.off_do[s]);
+    ep.d_o[s] = L.own_do ? (uint16_t*)(ws + L.off_do[s]) : nullptr;
     ep.delta[s] = (float*)(ws + L.off_delta[s]);
     ep.lse2[s] = (float*)(ws + L.off_lse2[s]);
   }
@@ -1621,7 +1643,7 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
   ep.dl_rows = diff && extra->dlambda != nullptr ? (float*)(ws + L.off_dl) : nullptr;
   ep.dw_part = has_rms && extra != nullptr && extra->drms_weight != nullptr ? (float*)(ws + L.off_dw) : nullptr;
   ep.rms_eps = desc->rms_eps;
-  ep.B = (int)B; ep.G = (int)G; ep.H = (int)H; ep.Sq = (int)Sq; ep.Dv = (int)Dv; ep.Dc = Dc;
+  ep.B = (int)B; ep.G = (int)G; ep.H = (int)H; ep.Sq = (int)Sq; ep.Dv = (int)Dv; ep.Dvc = Dvc;
   ep.ns = ns; ep.has_gate = has_gate; ep.has_rms = has_rms;
   // rows 16-byte aligned everywhere: several rows per wave, eight channels per lane; else one row per wave
   auto rows_aligned = [](const fl::View& v, int elem_bytes) {
@@ -1631,11 +1653,12 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
   };
   const bool by_rows = rows_aligned(ep.dout, 2) && rows_aligned(ep.out, 2) && rows_aligned(ep.gate, 2) &&
                        rows_aligned(ep.dgate, ep.dgate_f32 ? 4 : 2) && ((uintptr_t)ep.rms_w) % 16 == 0;
-  const int rows_per_wg = by_rows ? 4 * (64 / (Dc / 8)) : 4;
+  const int rows_per_wg = by_rows ? 4 * (64 / (Dvc / 8)) : 4;
   const int64_t epi_wgs = (rows_q + rows_per_wg - 1) / rows_per_wg;
   if (epi_wgs > 0x7fffffffLL) return fail(FL_ERR_SHAPE, "too many rows");
   if (!by_rows) hipLaunchKernelGGL(epi_bwd_kernel, dim3((unsigned)epi_wgs), dim3(256), 0, stream, ep);
-  else if (Dc == 64) hipLaunchKernelGGL(epi_bwd_rows_kernel<8>, dim3((unsigned)epi_wgs), dim3(256), 0, stream, ep);
+  else if (Dvc == 32) hipLaunchKernelGGL(epi_bwd_rows_kernel<4>, dim3((unsigned)epi_wgs), dim3(256), 0, stream, ep);
+  else if (Dvc == 64) hipLaunchKernelGGL(epi_bwd_rows_kernel<8>, dim3((unsigned)epi_wgs), dim3(256), 0, stream, ep);
   else hipLaunchKernelGGL(epi_bwd_rows_kernel<16>, dim3((unsigned)epi_wgs), dim3(256), 0, stream, ep);
   if (ep.dw_part != nullptr)
     hipLaunchKernelGGL(reduce_drms_kernel, dim3((unsigned)Dv), dim3(256), 0, stream, (const float*)ep.dw_part, extra->drms_weight,
@@ -1652,15 +1675,15 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
                        (int)G, (int)Hkv, (int)Sk, (int)D, Dc, rows_k);
   }
   if (L.pad_v)
-    hipLaunchKernelGGL(pad_rows_kernel, blocks(rows_k * (Dc / 8)), dim3(256), 0, stream, make_view(v), (uint16_t*)(ws + L.off_vpad), (int)G,
-                       (int)Hkv, (int)Sk, (int)Dv, Dc, rows_k);
+    hipLaunchKernelGGL(pad_rows_kernel, blocks(rows_k * (Dvc / 8)), dim3(256), 0, stream, make_view(v), (uint16_t*)(ws + L.off_vpad), (int)G,
+                       (int)Hkv, (int)Sk, (int)Dv, Dvc, rows_k);
   const bool want_dbias = dbias[0].ptr != nullptr || dbias[1].ptr != nullptr;
   // under a mask whole blocks are skipped by the dQ kernel: their dS is zero
   if (want_dbias && mask != 0)
     hipLaunchKernelGGL(zero_f32_kernel, blocks((int64_t)(L.ds / 4)), dim3(256), 0, stream, (float*)(ws + L.off_ds), (int64_t)(L.ds / 4));
   if ((e = hipGetLastError()) != hipSuccess) return fail(FL_ERR_LAUNCH, "backward pre-pass launch: %s", hipGetErrorString(e));
 
-  // ---- 4. the backward kernels, once per stream, into dense fp32 gradient buffers
+  // ---- 4. the backward kernels, once per stream, into the caller's gradients or, at a padded head dim, dense fp32 buffers
   fl::BwdParams p;
   memset(&p, 0, sizeof(p));
   p.alibi_slopes = aux->alibi_slopes;
@@ -1672,13 +1695,11 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
   p.q_off = desc->q_offset;
   p.scale = desc->scale;
   p.softcap = desc->softcap;
-  p.dq_f32 = 1;
-  p.dkv_f32 = 1;
   p.n_qtiles = (int)((Sq + be->bm - 1) / be->bm);
   p.n_ktiles = (int)((Sk + be->bm - 1) / be->bm);
   p.hsplit = L.hsplit;
   p.part_dk = (float*)(ws + L.off_part);
-  p.part_dv = (float*)(ws + L.off_part + L.part);
+  p.part_dv = (float*)(ws + L.off_part + L.part_k);
   const int order = g_tuning.order >= 0 ? g_tuning.order : 1;
   p.order_q = order == 1 && (B * G * H) % 8 == 0;
   p.order_k = order == 1 && (B * G * Hkv * p.hsplit) % 8 == 0;
@@ -1694,15 +1715,23 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
     launch_doc_summaries(aux->q_doc_ids, p.q_sum, (int)Sq, nqs, tq, aux->kv_doc_ids, p.kv_sum, (int)Sk, nks, tk, stream);
     if ((e = hipGetLastError()) != hipSuccess) return fail(FL_ERR_LAUNCH, "doc summary launch: %s", hipGetErrorString(e));
   }
-  const fl::View vview = L.pad_v ? dense_view(ws + L.off_vpad, G, Hkv, Sk, Dc) : make_view(v);
+  const fl::View vview = L.pad_v ? dense_view(ws + L.off_vpad, G, Hkv, Sk, Dvc) : make_view(v);
+  fl_tensor* dqs[2] = {dq, diff ? (fl_tensor*)&extra->dq2 : nullptr};
+  fl_tensor* dks[2] = {dk, diff ? (fl_tensor*)&extra->dk2 : nullptr};
   for (int s = 0; s < ns; ++s) {
     p.q = L.pad_qk ? dense_view(ws + L.off_qpad[s], G, H, Sq, Dc) : make_view(qs[s]);
     p.k = L.pad_qk ? dense_view(ws + L.off_kpad[s], G, Hkv, Sk, Dc) : make_view(ks[s]);
     p.v = vview;
-    p.dout = dense_view(ws + L.off_do[s], G, H, Sq, Dc);
-    p.dq = dense_view(ws + L.off_gq[s], G, H, Sq, Dc);
-    p.dk = dense_view(ws + L.off_gk[s], G, Hkv, Sk, Dc);
-    p.dv = dense_view(ws + L.off_gv[s], G, Hkv, Sk, Dc);
+    p.dout = L.own_do ? dense_view(ws + L.off_do[s], G, H, Sq, Dvc) : make_view(dout);
+    p.dq = L.pad_qk ? dense_view(ws + L.off_gq[s], G, H, Sq, Dc) : make_view(dqs[s]);
+    p.dk = L.pad_qk ? dense_view(ws + L.off_gk[s], G, Hkv, Sk, Dc) : make_view(dks[s]);
+    p.dq_f32 = L.pad_qk || dqs[s]->dtype == FL_F32;
+    p.dk_f32 = L.pad_qk || dks[s]->dtype == FL_F32;
+    // dV is one sum over the streams: the first pass leaves its part in fp32, the second adds its own to it
+    const bool own_dv = L.pad_v || s + 1 < ns;
+    p.dv = own_dv ? dense_view(ws + L.off_gv[0], G, Hkv, Sk, Dvc) : make_view(dv);
+    p.dv_f32 = own_dv || dv->dtype == FL_F32;
+    p.dv_add = s > 0 ? (const float*)(ws + L.off_gv[0]) : nullptr;
     p.delta = (float*)(ws + L.off_delta[s]);
     p.lse2 = (float*)(ws + L.off_lse2[s]);
     if ((e = run_bwd_dq(be, p, (int)nb_q, stream)) != hipSuccess) return fail(FL_ERR_LAUNCH, "dq launch: %s", hipGetErrorString(e));
@@ -1724,24 +1753,22 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
       }
     if ((e = run_bwd_dkdv(be, p, (int)nb_k, stream)) != hipSuccess) return fail(FL_ERR_LAUNCH, "dk/dv launch: %s", hipGetErrorString(e));
     if (p.hsplit > 1) {
-      const int64_t chunks = rows_k * (Dc / 4);
+      const int64_t chunks = rows_k * ((Dc > Dvc ? Dc : Dvc) / 4);
       if ((e = be->reduce(p, (int)((chunks + 255) / 256), stream)) != hipSuccess)
         return fail(FL_ERR_LAUNCH, "dk/dv reduction launch: %s", hipGetErrorString(e));
     }
   }
 
-  // ---- 5. into the caller's tensors: first D (Dv) channels, dv summed over the streams
-  fl_tensor* dqs[2] = {dq, diff ? (fl_tensor*)&extra->dq2 : nullptr};
-  fl_tensor* dks[2] = {dk, diff ? (fl_tensor*)&extra->dk2 : nullptr};
-  for (int s = 0; s < ns; ++s) {
+  // ---- 5. from the padded buffers into the caller's tensors: the first D (Dv) channels
+  for (int s = 0; s < ns && L.pad_qk; ++s) {
     hipLaunchKernelGGL(scatter_grad_kernel, blocks(rows_q * (D / 4)), dim3(256), 0, stream, (const float*)(ws + L.off_gq[s]),
-                       (const float*)nullptr, make_view(dqs[s]), (int)(dqs[s]->dtype == FL_F32), (int)G, (int)H, (int)Sq, (int)D, Dc, rows_q);
+                       make_view(dqs[s]), (int)(dqs[s]->dtype == FL_F32), (int)G, (int)H, (int)Sq, (int)D, Dc, rows_q);
     hipLaunchKernelGGL(scatter_grad_kernel, blocks(rows_k * (D / 4)), dim3(256), 0, stream, (const float*)(ws + L.off_gk[s]),
-                       (const float*)nullptr, make_view(dks[s]), (int)(dks[s]->dtype == FL_F32), (int)G, (int)Hkv, (int)Sk, (int)D, Dc, rows_k);
+                       make_view(dks[s]), (int)(dks[s]->dtype == FL_F32), (int)G, (int)Hkv, (int)Sk, (int)D, Dc, rows_k);
   }
-  hipLaunchKernelGGL(scatter_grad_kernel, blocks(rows_k * (Dv / 4)), dim3(256), 0, stream, (const float*)(ws + L.off_gv[0]),
-                     ns == 2 ? (const float*)(ws + L.off_gv[1]) : (const float*)nullptr, make_view(dv), (int)(dv->dtype == FL_F32), (int)G,
-                     (int)Hkv, (int)Sk, (int)Dv, Dc, rows_k);
+  if (L.pad_v)
+    hipLaunchKernelGGL(scatter_grad_kernel, blocks(rows_k * (Dv / 4)), dim3(256), 0, stream, (const float*)(ws + L.off_gv[0]),
+                       make_view(dv), (int)(dv->dtype == FL_F32), (int)G, (int)Hkv, (int)Sk, (int)Dv, Dvc, rows_k);
   if ((e = hipGetLastError()) != hipSuccess) return fail(FL_ERR_LAUNCH, "gradient scatter launch: %s", hipGetErrorString(e));
   return FL_OK;
 }

@@ -50,12 +50,14 @@ struct BwdParams {
   int32_t B, G, H, Hkv, Sq, Sk;
   int32_t window, prefix;
   float scale, softcap;
-  int32_t dq_f32, dkv_f32;         // 1: that output is float, 0: bf16
+  int32_t dq_f32, dk_f32, dv_f32;  // 1: that output is float, 0: bf16
   int32_t n_qtiles, n_ktiles;      // workgroups per (b, g, h) of the dQ kernel / per (b, g, hkv) of the dK/dV kernel
   int32_t order_q, order_k;        // 1: XCD-aware workgroup order (whole (b, g, h) problems per XCD) in that kernel
   int32_t hsplit;                  // dK/dV kernel: the query heads of a group are cut into hsplit subsets, one workgroup each
-  float* part_dk;                  // hsplit > 1: fp32 partial sums [hsplit][B, G, Hkv, Sk, D], summed by bwd_reduce_kv_kernel
+  float* part_dk;                  // hsplit > 1: fp32 partial sums [hsplit][B, G, Hkv, Sk, D | DV], summed by bwd_reduce_kv_kernel
   float* part_dv;
+  const float* dv_add;             // added to dV before it is written, dense fp32 [B, G, Hkv, Sk, DV]: the first softmax
+                                   // stream's dV in the pass over the second stream (null: nothing to add)
   BiasView bias[2];                // the forward pass's additive biases (kernels built with NBIAS > 0), bf16
   int32_t q_off;                   // query row i sits at sequence position i + q_off (positional masks, ALiBi); >= 0
   const void* user_aux[4];         // run-time compiled variants: the caller's device arrays that the expressions read
@@ -68,7 +70,8 @@ struct BwdParams {
 template <int D>
 __device__ __forceinline__ int swz_u(int r) {
   if constexpr (D == 128) return ((r & 3) << 2) | ((r >> 2) & 3);
-  else return (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+  else if constexpr (D == 64) return (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+  else return (r >> 2) & 3;                        // 64-byte rows: four of them are one line of all banks
 }
 
 // Query rows [lo, hi) that can see any key in [j_lo, j_hi] under the positional masks.
@@ -85,39 +88,44 @@ __device__ __forceinline__ void query_range(const uint32_t MASK, int j_lo, int j
   lo = min(lo, hi);
 }
 
-template <int D_, int MOD_, uint32_t MASK_, int BN_, int WPE_, int NBIAS_ = 0>
+// D: channels of Q and K, DV: of V and dO.  The two contractions over D and the two (dK/dV kernel) or one (dQ kernel) over
+// or into DV are tiled separately, so that D != DV and head dim 32 do no matrix work on zero padding.
+template <int D_, int MOD_, uint32_t MASK_, int BN_, int WPE_, int NBIAS_ = 0, int DV_ = D_>
 struct BwdCfg {
-  static constexpr int D = D_, MOD = MOD_, BN = BN_, WPE = WPE_, NBIAS = NBIAS_;
+  static constexpr int D = D_, DV = DV_, MOD = MOD_, BN = BN_, WPE = WPE_, NBIAS = NBIAS_;
   static constexpr uint32_t MASK = MASK_;
   static constexpr int NW = 4, NT = NW * 64;
   static constexpr int BM = NW * 32;               // rows (dQ kernel) or keys (dK/dV kernel) per workgroup
   static constexpr int NB = BN / 32;               // 32-row blocks of a streamed tile
-  static constexpr int KK = D / 16;                // k-steps over the head dim
-  static constexpr int DB = D / 32;                // 32-channel blocks of the head dim
-  static constexpr int ROW = D * 2;                // bytes of a tile row
-  static constexpr int TILE = BN * ROW;            // bytes of one streamed tile
+  static constexpr int KK = D / 16, KV = DV / 16;  // k-steps over the channels of Q / K and of V / dO
+  static constexpr int DB = D / 32, DBV = DV / 32; // 32-channel blocks of them
+  static constexpr int ROW = D * 2, ROWV = DV * 2; // bytes of a tile row
+  static constexpr int TILE = BN * ROW, TILEV = BN * ROWV;   // bytes of one streamed tile (Q or K, V or dO)
   static constexpr int STAT = BN * 4;              // bytes of one per-row statistic of a tile (dK/dV kernel)
-  static constexpr int STAGE_DQ = 2 * TILE;        // K, V
-  static constexpr int STAGE_KV = 2 * TILE + 2 * STAT;   // Q, dO, lse2, delta
-  static constexpr int TILE_INSTR = TILE / 1024;   // 64-lane x 16-byte direct loads per tile
-  static constexpr int RPI = 1024 / ROW;           // tile rows per load instruction
+  static constexpr int STATS = TILE + TILEV;       // offset of the statistics in a stage
+  static constexpr int STAGE_DQ = TILE + TILEV;    // K, V
+  static constexpr int STAGE_KV = STATS + 2 * STAT;      // Q, dO, lse2, delta
+  static constexpr int TILE_INSTR = TILE / 1024, TILEV_INSTR = TILEV / 1024;   // 64-lane x 16-byte direct loads per tile
+  static constexpr int RPI = 1024 / ROW;           // rows of a Q / K tile per load instruction
   static constexpr int GR = WPE == 1 ? 4 : 2;      // dK/dV pipeline: row fragments read ahead (a lone wave per SIMD hides LDS latency itself)
   static constexpr int GT = WPE == 1 ? 4 : 2;      // dK/dV pipeline: transposed fragments read ahead
-  static_assert(D == 64 || D == 128, "head dims of the backward kernels");
-  static_assert(TILE_INSTR % NW == 0, "every wave issues the same number of loads");
-  static_assert((NW * RPI) % 16 == 0, "a lane's destination row keeps its residue mod 16");
+  static_assert((D == 32 || D == 64 || D == 128) && (DV == 32 || DV == 64 || DV == 128), "head dims of the backward kernels");
+  static_assert(TILE_INSTR % NW == 0 && TILEV_INSTR % NW == 0, "every wave issues the same number of loads");
+  static_assert((NW * RPI) % 16 == 0 && (NW * 1024 / ROWV) % 16 == 0, "a lane's destination row keeps its residue mod 16");
 };
 
 // Fragment -> LDS offset maps of the pipelined loops.  RowPair: KK row fragments of the block at
-// OFF0, then KK of the block at OFF1.  TrQuad: DB transposed fragments each of (block at OFF0,
-// rows 0..15), (block at OFF1, rows 0..15), (OFF0, rows 16..31), (OFF1, rows 16..31).
+// OFF0, then those of the block at OFF1.  TrQuad: transposed fragments of (block at OFF0, rows 0..15; DB0 of
+// them), (block at OFF1, rows 0..15; DB1), (OFF0, rows 16..31), (OFF1, rows 16..31).
 template <int OFF0, int OFF1, int KK>
 struct RowPair {
   static constexpr int off(int f) { return f < KK ? OFF0 : OFF1; }
 };
-template <int OFF0, int OFF1, int DB, int ROW>
+template <int OFF0, int OFF1, int DB0, int DB1, int ROW0, int ROW1>
 struct TrQuad {
-  static constexpr int off(int f) { return (((f / DB) % 2) == 0 ? OFF0 : OFF1) + ((f / DB) / 2) * 16 * ROW; }
+  static constexpr int off(int f) {
+    return f % (DB0 + DB1) < DB0 ? OFF0 + (f / (DB0 + DB1)) * 16 * ROW0 : OFF1 + (f / (DB0 + DB1)) * 16 * ROW1;
+  }
 };
 
 template <int OFF>
@@ -131,28 +139,34 @@ struct TrOne {                                     // DB transposed fragments of
 
 template <class C>
 struct BwdWave {
-  static constexpr int D = C::D, KK = C::KK, DB = C::DB, ROW = C::ROW;
+  static constexpr int D = C::D, DV = C::DV, KK = C::KK, DB = C::DB, ROW = C::ROW;
   static constexpr uint32_t MASK = C::MASK;
 
   int lane, half, col;
-  uint32_t ra[C::KK];              // per-lane byte offset of the row-read fragment of k-step kk (row block 0)
+  uint32_t ra[C::KK];              // per-lane byte offset of the row-read fragment of k-step kk (row block 0) of a Q / K tile
   uint32_t ta[C::DB][2];           // per-lane byte offsets of the transposing read of channel block d (rows +0 / +8)
+  uint32_t rv[C::KV], tv[C::DBV][2];   // the same in a V / dO tile
 
   __device__ __forceinline__ void init(int lane_) {
     lane = lane_;
     half = lane >> 5;
     col = lane & 31;
+    lane_offsets<D>(ra, ta);
+    lane_offsets<DV>(rv, tv);
+  }
+  template <int W>
+  __device__ __forceinline__ void lane_offsets(uint32_t (&r_off)[W / 16], uint32_t (&t_off)[W / 32][2]) const {
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) ra[kk] = col * ROW + ((2 * kk + half) ^ swz_u<D>(col)) * 16;
+    for (int kk = 0; kk < W / 16; ++kk) r_off[kk] = col * (W * 2) + ((2 * kk + half) ^ swz_u<W>(col)) * 16;
     const int s16 = lane & 15;
     const int r0 = 4 * half + (s16 >> 2);          // row this lane addresses in the transposing read
 #pragma unroll
-    for (int d = 0; d < DB; ++d) {
+    for (int d = 0; d < W / 32; ++d) {
       const int ch = 32 * d + 16 * ((lane >> 4) & 1) + 4 * (s16 & 3);   // first of its 4 channels
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int r = r0 + 8 * u;
-        ta[d][u] = r * ROW + ((ch >> 3) ^ swz_u<D>(r)) * 16 + (ch & 7) * 2;
+        t_off[d][u] = r * (W * 2) + ((ch >> 3) ^ swz_u<W>(r)) * 16 + (ch & 7) * 2;
       }
     }
   }
@@ -193,17 +207,17 @@ struct BwdWave {
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  // KK row-read fragments (A operand, 32 tile rows x 16 channels each) of the 32-row block at
+  // The row-read fragments (A operand, 32 tile rows x 16 channels each; lane offsets off) of the 32-row block at
   // LDS byte offset OFF, read two ahead; body(kk, fragment).
-  template <int OFF, class Body>
-  __device__ __forceinline__ void row_stream(Body&& body) const {
-    constexpr int G = 2, NG = KK / G;
-    i32x4 fr[KK];
-    static_for<0, G>([&](auto f) __attribute__((always_inline)) { read_b128<OFF>(fr[f], ra[f]); });
+  template <int OFF, int NF, class Body>
+  __device__ __forceinline__ void row_stream(const uint32_t (&off)[NF], Body&& body) const {
+    constexpr int G = 2, NG = NF / G;
+    i32x4 fr[NF];
+    static_for<0, G>([&](auto f) __attribute__((always_inline)) { read_b128<OFF>(fr[f], off[f]); });
     static_for<0, NG>([&](auto gc) __attribute__((always_inline)) {
       constexpr int g = gc;
       if constexpr (g + 1 < NG)
-        static_for<(g + 1) * G, (g + 2) * G>([&](auto f) __attribute__((always_inline)) { read_b128<OFF>(fr[f], ra[f]); });
+        static_for<(g + 1) * G, (g + 2) * G>([&](auto f) __attribute__((always_inline)) { read_b128<OFF>(fr[f], off[f]); });
       wait_lds<(g + 1 < NG) ? G : 0>();
       static_for<g * G, (g + 1) * G>([&](auto f) __attribute__((always_inline)) { body(f, __builtin_bit_cast(bf16x8, fr[f])); });
     });
@@ -234,36 +248,36 @@ struct BwdWave {
   }
 
   // Generic forms for the software-pipelined loops: O::off(f) is the LDS byte offset of fragment
-  // f (a compile-time function), fragments are read G ahead, body(f, fragment) runs in order.
-  template <class O, int NF, int G, class Body>
-  __device__ __forceinline__ void row_stream_g(const uint32_t (&ra)[C::KK], Body&& body) const {
+  // f (a compile-time function), addr(f) the lane's part of it, fragments are read G ahead, body(f, fragment) runs in order.
+  template <class O, int NF, int G, class Addr, class Body>
+  __device__ __forceinline__ void row_stream_g(Addr&& addr, Body&& body) const {
     constexpr int NG = NF / G;
     static_assert(NF % G == 0 && G <= 15, "fragment groups");
     i32x4 fr[NF];
-    static_for<0, G>([&](auto f) __attribute__((always_inline)) { read_b128<O::off(f)>(fr[f], ra[f % KK]); });
+    static_for<0, G>([&](auto f) __attribute__((always_inline)) { read_b128<O::off(f)>(fr[f], addr(f)); });
     static_for<0, NG>([&](auto gc) __attribute__((always_inline)) {
       constexpr int g = gc;
       if constexpr (g + 1 < NG)
-        static_for<(g + 1) * G, (g + 2) * G>([&](auto f) __attribute__((always_inline)) { read_b128<O::off(f)>(fr[f], ra[f % KK]); });
+        static_for<(g + 1) * G, (g + 2) * G>([&](auto f) __attribute__((always_inline)) { read_b128<O::off(f)>(fr[f], addr(f)); });
       wait_lds<(g + 1 < NG) ? G : 0>();
       static_for<g * G, (g + 1) * G>([&](auto f) __attribute__((always_inline)) { body(f, __builtin_bit_cast(bf16x8, fr[f])); });
     });
   }
-  template <class O, int NF, int G, class Body>
-  __device__ __forceinline__ void tr_stream_g(const uint32_t (&ta)[C::DB][2], Body&& body) const {
+  template <class O, int NF, int G, class Addr, class Body>
+  __device__ __forceinline__ void tr_stream_g(Addr&& addr, Body&& body) const {   // addr(f, 0 | 1): rows +0 / +8
     constexpr int NG = NF / G;
     static_assert(NF % G == 0 && 2 * G <= 15, "fragment groups");
     i32x2 lo[NF], hi[NF];
     static_for<0, G>([&](auto f) __attribute__((always_inline)) {
-      read_tr<O::off(f)>(lo[f], ta[f % DB][0]);
-      read_tr<O::off(f)>(hi[f], ta[f % DB][1]);
+      read_tr<O::off(f)>(lo[f], addr(f, 0));
+      read_tr<O::off(f)>(hi[f], addr(f, 1));
     });
     static_for<0, NG>([&](auto gc) __attribute__((always_inline)) {
       constexpr int g = gc;
       if constexpr (g + 1 < NG)
         static_for<(g + 1) * G, (g + 2) * G>([&](auto f) __attribute__((always_inline)) {
-          read_tr<O::off(f)>(lo[f], ta[f % DB][0]);
-          read_tr<O::off(f)>(hi[f], ta[f % DB][1]);
+          read_tr<O::off(f)>(lo[f], addr(f, 0));
+          read_tr<O::off(f)>(hi[f], addr(f, 1));
         });
       wait_lds<(g + 1 < NG) ? 2 * G : 0>();
       static_for<g * G, (g + 1) * G>([&](auto f) __attribute__((always_inline)) {
@@ -273,13 +287,13 @@ struct BwdWave {
   }
 };
 
-// One 64-lane x 16-byte direct load instruction `inst` of a [rows][D] tile whose row 0 is at
+// One 64-lane x 16-byte direct load instruction `inst` of a [rows][W] tile whose row 0 is at
 // `base` (row stride `row_bytes`); rows at or past n_valid are replaced by row n_valid - 1.
-template <class C>
+template <int W>
 __device__ __forceinline__ void tile_load_instr(const unsigned char* base, int64_t row_bytes, int n_valid, int inst,
                                                 int lane, unsigned char* lds_tile) {
-  const int dst_row = inst * C::RPI + lane / (C::D / 8);
-  const int chunk = (lane % (C::D / 8)) ^ swz_u<C::D>(dst_row);
+  const int dst_row = inst * (512 / W) + lane / (W / 8);
+  const int chunk = (lane % (W / 8)) ^ swz_u<W>(dst_row);
   const int row = dst_row < n_valid ? dst_row : n_valid - 1;
   lds_void* dst = (lds_void*)(lds_tile + inst * 1024);
   __builtin_amdgcn_global_load_lds((global_cvoid*)(base + (int64_t)row * row_bytes + chunk * 16), dst, 16, 0, 0);
@@ -372,24 +386,33 @@ struct BiasHead {
   }
 };
 
-// Four consecutive channels of a dK or dV row: to the output tensor, or (grouped-query heads cut
+// Four consecutive channels of a dK (V false) or dV row: to the output tensor, or (grouped-query heads cut
 // over several workgroups) to this workgroup's fp32 partial.
-__device__ __forceinline__ void store_kv_grad(const BwdParams& p, const View& out, float* part, int split, int b, int g,
-                                              int hk, int j, int ch, int D, float x0, float x1, float x2, float x3) {
+template <bool V, int W>
+__device__ __forceinline__ void store_kv_grad(const BwdParams& p, int split, int b, int g, int hk, int j, int ch, float x0,
+                                              float x1, float x2, float x3) {
+  const int64_t dense = (((int64_t)b * p.G + g) * p.Hkv + hk) * p.Sk + j;
   if (p.hsplit > 1) {
-    const int64_t row = ((((int64_t)split * p.B + b) * p.G + g) * p.Hkv + hk) * p.Sk + j;
-    *(float4*)(part + row * D + ch) = make_float4(x0, x1, x2, x3);
+    const int64_t row = (int64_t)split * p.B * p.G * p.Hkv * p.Sk + dense;
+    *(float4*)((V ? p.part_dv : p.part_dk) + row * W + ch) = make_float4(x0, x1, x2, x3);
   } else {
+    if (V && p.dv_add != nullptr) {
+      const float4 a = *(const float4*)(p.dv_add + dense * W + ch);
+      x0 += a.x; x1 += a.y; x2 += a.z; x3 += a.w;
+    }
+    const View& out = V ? p.dv : p.dk;
     const int64_t row = b * out.sb + g * out.sg + hk * out.sh + (int64_t)j * out.ss;
-    if (p.dkv_f32) *(float4*)((float*)out.ptr + row + ch) = make_float4(x0, x1, x2, x3);
+    if (V ? p.dv_f32 : p.dk_f32) *(float4*)((float*)out.ptr + row + ch) = make_float4(x0, x1, x2, x3);
     else *(uint2*)((uint16_t*)out.ptr + row + ch) = make_uint2(pack_bf16(x0, x1), pack_bf16(x2, x3));
   }
 }
 
-// Sum of the hsplit partials of dK and dV, in a fixed order (reproducible), written in the output dtype.
-template <int D>
+// Sum of the hsplit partials of dK and dV, in a fixed order (reproducible), written in the output dtype.  One thread per
+// four channels of a dK row or of a dV row (grid.y).
+template <int D, int DV>
 __global__ void __launch_bounds__(256) bwd_reduce_kv_kernel(const BwdParams p) {
-  constexpr int cpr = D / 4;                       // float4 chunks per row
+  const bool is_v = blockIdx.y != 0;
+  const int W = is_v ? DV : D, cpr = W / 4;        // channels and float4 chunks per row
   const int64_t rows = (int64_t)p.B * p.G * p.Hkv * p.Sk;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= rows * cpr) return;
@@ -399,22 +422,20 @@ __global__ void __launch_bounds__(256) bwd_reduce_kv_kernel(const BwdParams p) {
   const int hk = (int)((row / p.Sk) % p.Hkv);
   const int g = (int)((row / ((int64_t)p.Sk * p.Hkv)) % p.G);
   const int b = (int)(row / ((int64_t)p.Sk * p.Hkv * p.G));
-  float4 k = make_float4(0.f, 0.f, 0.f, 0.f), v = k;
+  const float* part = is_v ? p.part_dv : p.part_dk;
+  float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int s = 0; s < p.hsplit; ++s) {
-    const float4 a = *(const float4*)(p.part_dk + ((int64_t)s * rows + row) * D + ch);
-    const float4 c = *(const float4*)(p.part_dv + ((int64_t)s * rows + row) * D + ch);
-    k.x += a.x; k.y += a.y; k.z += a.z; k.w += a.w;
-    v.x += c.x; v.y += c.y; v.z += c.z; v.w += c.w;
+    const float4 a = *(const float4*)(part + ((int64_t)s * rows + row) * W + ch);
+    x.x += a.x; x.y += a.y; x.z += a.z; x.w += a.w;
   }
-  const int64_t krow = b * p.dk.sb + g * p.dk.sg + hk * p.dk.sh + (int64_t)j * p.dk.ss;
-  const int64_t vrow = b * p.dv.sb + g * p.dv.sg + hk * p.dv.sh + (int64_t)j * p.dv.ss;
-  if (p.dkv_f32) {
-    *(float4*)((float*)p.dk.ptr + krow + ch) = k;
-    *(float4*)((float*)p.dv.ptr + vrow + ch) = v;
-  } else {
-    *(uint2*)((uint16_t*)p.dk.ptr + krow + ch) = make_uint2(pack_bf16(k.x, k.y), pack_bf16(k.z, k.w));
-    *(uint2*)((uint16_t*)p.dv.ptr + vrow + ch) = make_uint2(pack_bf16(v.x, v.y), pack_bf16(v.z, v.w));
+  if (is_v && p.dv_add != nullptr) {
+    const float4 a = *(const float4*)(p.dv_add + row * W + ch);
+    x.x += a.x; x.y += a.y; x.z += a.z; x.w += a.w;
   }
+  const View& out = is_v ? p.dv : p.dk;
+  const int64_t orow = b * out.sb + g * out.sg + hk * out.sh + (int64_t)j * out.ss;
+  if (is_v ? p.dv_f32 : p.dk_f32) *(float4*)((float*)out.ptr + orow + ch) = x;
+  else *(uint2*)((uint16_t*)out.ptr + orow + ch) = make_uint2(pack_bf16(x.x, x.y), pack_bf16(x.z, x.w));
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -456,7 +477,7 @@ __global__ void __launch_bounds__(256) bwd_prep_kernel(const BwdParams p) {
 template <class C>
 __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE, C::WPE)))
 bwd_dq_kernel(const BwdParams p) {
-  constexpr int D = C::D, BN = C::BN, NB = C::NB, KK = C::KK, DB = C::DB, ROW = C::ROW;
+  constexpr int BN = C::BN, NB = C::NB, KK = C::KK, KV = C::KV, DB = C::DB, ROW = C::ROW, ROWV = C::ROWV;
   constexpr uint32_t MASK = C::MASK;
   constexpr uint32_t POS = MASK & ~kMaskDoc;
   typedef BwdWave<C> W;
@@ -494,15 +515,14 @@ bwd_dq_kernel(const BwdParams p) {
   const int64_t srow = ((int64_t)(b * p.G + g) * p.H + h) * p.Sq + ic;
 
   // per-lane operands: Q and dO rows as B fragments, row statistics
-  bf16x8 qf[KK], dof[KK];
+  bf16x8 qf[KK], dof[KV];
   {
     const uint16_t* qp = (const uint16_t*)p.q.ptr + b * p.q.sb + g * p.q.sg + h * p.q.sh + (int64_t)ic * p.q.ss;
     const uint16_t* dp = (const uint16_t*)p.dout.ptr + b * p.dout.sb + g * p.dout.sg + h * p.dout.sh + (int64_t)ic * p.dout.ss;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      qf[kk] = *(const bf16x8*)(qp + 16 * kk + 8 * w.half);
-      dof[kk] = *(const bf16x8*)(dp + 16 * kk + 8 * w.half);
-    }
+    for (int kk = 0; kk < KK; ++kk) qf[kk] = *(const bf16x8*)(qp + 16 * kk + 8 * w.half);
+#pragma unroll
+    for (int kk = 0; kk < KV; ++kk) dof[kk] = *(const bf16x8*)(dp + 16 * kk + 8 * w.half);
   }
   const float lse2 = p.lse2[srow], delta = p.delta[srow];
   const float c_scale = p.scale * kLog2e;
@@ -573,9 +593,10 @@ bwd_dq_kernel(const BwdParams p) {
     const int nvalid = min(BN, p.Sk - t * BN);
     unsigned char* st = lds_raw + stage * C::STAGE_DQ;
 #pragma unroll
-    for (int u = 0; u < C::TILE_INSTR / C::NW; ++u) {
-      tile_load_instr<C>(kbase + (int64_t)(t * BN) * kss, kss, nvalid, wave + u * C::NW, lane, st);
-      tile_load_instr<C>(vbase + (int64_t)(t * BN) * vss, vss, nvalid, wave + u * C::NW, lane, st + C::TILE);
+    for (int u = 0; u < (C::TILE_INSTR > C::TILEV_INSTR ? C::TILE_INSTR : C::TILEV_INSTR) / C::NW; ++u) {
+      if (u < C::TILE_INSTR / C::NW) tile_load_instr<C::D>(kbase + (int64_t)(t * BN) * kss, kss, nvalid, wave + u * C::NW, lane, st);
+      if (u < C::TILEV_INSTR / C::NW)
+        tile_load_instr<C::DV>(vbase + (int64_t)(t * BN) * vss, vss, nvalid, wave + u * C::NW, lane, st + C::TILE);
     }
   };
 
@@ -620,17 +641,17 @@ bwd_dq_kernel(const BwdParams p) {
       }
       if constexpr (C::NBIAS > 0 && nb == 0) load_tile(tn, 1 - decltype(stage_c)::value);
       f32x16 s = W::zero16(), dp = W::zero16();
-      w.template row_stream<ST + nb * 32 * ROW>([&](auto kk, bf16x8 a) __attribute__((always_inline)) {
+      w.template row_stream<ST + nb * 32 * ROW>(w.ra, [&](auto kk, bf16x8 a) __attribute__((always_inline)) {
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], s, 0, 0, 0);
       });
-      w.template row_stream<ST + C::TILE + nb * 32 * ROW>([&](auto kk, bf16x8 a) __attribute__((always_inline)) {
+      w.template row_stream<ST + C::TILE + nb * 32 * ROWV>(w.rv, [&](auto kk, bf16x8 a) __attribute__((always_inline)) {
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dof[kk], dp, 0, 0, 0);
       });
       const int jb = j0 + 32 * nb + 4 * w.half;    // key of register 0
       float bl[C::NBIAS > 0 ? 16 : 1];             // sum of the biases of each score, log2 units
       if constexpr (C::NBIAS > 0) {
         // the first block's values are older than the next tile's loads: all but those have to have landed
-        if constexpr (nb == 0) __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * (C::TILE_INSTR / C::NW)));
+        if constexpr (nb == 0) __builtin_amdgcn_s_waitcnt(0x0F70 | ((C::TILE_INSTR + C::TILEV_INSTR) / C::NW));
         if (bvec) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
@@ -764,7 +785,7 @@ bwd_dq_kernel(const BwdParams p) {
 template <class C>
 __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE, C::WPE)))
 bwd_dkdv_kernel(const BwdParams p) {
-  constexpr int D = C::D, BN = C::BN, NB = C::NB, KK = C::KK, DB = C::DB, ROW = C::ROW;
+  constexpr int BN = C::BN, NB = C::NB, KK = C::KK, KV = C::KV, DB = C::DB, ROW = C::ROW, ROWV = C::ROWV;
   constexpr uint32_t MASK = C::MASK;
   constexpr uint32_t POS = MASK & ~kMaskDoc;
   typedef BwdWave<C> W;
@@ -801,26 +822,25 @@ bwd_dkdv_kernel(const BwdParams p) {
   const int j = jw + w.col, jc = j < p.Sk ? j : p.Sk - 1;
   const FwdParams uctx = user_context(p);          // what a compiled variant's expressions read (unused otherwise)
 
-  bf16x8 kf[KK], vf[KK];
+  bf16x8 kf[KK], vf[KV];
   {
     const uint16_t* kp = (const uint16_t*)p.k.ptr + b * p.k.sb + g * p.k.sg + hk * p.k.sh + (int64_t)jc * p.k.ss;
     const uint16_t* vp = (const uint16_t*)p.v.ptr + b * p.v.sb + g * p.v.sg + hk * p.v.sh + (int64_t)jc * p.v.ss;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      kf[kk] = *(const bf16x8*)(kp + 16 * kk + 8 * w.half);
-      vf[kk] = *(const bf16x8*)(vp + 16 * kk + 8 * w.half);
-    }
+    for (int kk = 0; kk < KK; ++kk) kf[kk] = *(const bf16x8*)(kp + 16 * kk + 8 * w.half);
+#pragma unroll
+    for (int kk = 0; kk < KV; ++kk) vf[kk] = *(const bf16x8*)(vp + 16 * kk + 8 * w.half);
   }
   const float c_scale = p.scale * kLog2e;
   int kdoc = 0;
   if constexpr ((MASK & kMaskDoc) != 0) kdoc = p.kv_doc[(int64_t)b * p.Sk + jc];
 
-  f32x16 dk[DB], dv[DB];
+  constexpr int DBV = C::DBV;
+  f32x16 dk[DB], dv[DBV];
 #pragma unroll
-  for (int d = 0; d < DB; ++d) {
-    dk[d] = W::zero16();
-    dv[d] = W::zero16();
-  }
+  for (int d = 0; d < DB; ++d) dk[d] = W::zero16();
+#pragma unroll
+  for (int d = 0; d < DBV; ++d) dv[d] = W::zero16();
 
   // query rows that can see the workgroup's keys; q-tile skipping for document masks
   const int j_last = (j0 + C::BM < p.Sk ? j0 + C::BM : p.Sk) - 1;
@@ -884,9 +904,9 @@ bwd_dkdv_kernel(const BwdParams p) {
     const unsigned char* qb = (const unsigned char*)((const uint16_t*)p.q.ptr + b * p.q.sb + g * p.q.sg + h * p.q.sh + (int64_t)(t * BN) * p.q.ss);
     const unsigned char* db = (const unsigned char*)((const uint16_t*)p.dout.ptr + b * p.dout.sb + g * p.dout.sg + h * p.dout.sh + (int64_t)(t * BN) * p.dout.ss);
 #pragma unroll
-    for (int u = 0; u < C::TILE_INSTR / C::NW; ++u) {
-      tile_load_instr<C>(qb, p.q.ss * 2, nvalid, wave + u * C::NW, lane, st);
-      tile_load_instr<C>(db, p.dout.ss * 2, nvalid, wave + u * C::NW, lane, st + C::TILE);
+    for (int u = 0; u < (C::TILE_INSTR > C::TILEV_INSTR ? C::TILE_INSTR : C::TILEV_INSTR) / C::NW; ++u) {
+      if (u < C::TILE_INSTR / C::NW) tile_load_instr<C::D>(qb, p.q.ss * 2, nvalid, wave + u * C::NW, lane, st);
+      if (u < C::TILEV_INSTR / C::NW) tile_load_instr<C::DV>(db, p.dout.ss * 2, nvalid, wave + u * C::NW, lane, st + C::TILE);
     }
     // row statistics: 64 rows per instruction, 4 bytes per lane
     const int64_t srow = ((int64_t)(b * p.G + g) * p.H + h) * p.Sq;
@@ -896,7 +916,7 @@ bwd_dkdv_kernel(const BwdParams p) {
       const int row = t * BN + (r < nvalid ? r : nvalid - 1);
       const float* src = (which == 0 ? p.lse2 : p.delta) + srow + row;
       if (BN >= 64 || lane < BN) {
-        lds_void* dst = (lds_void*)(st + 2 * C::TILE + which * C::STAT + blk * 256);
+        lds_void* dst = (lds_void*)(st + C::STATS + which * C::STAT + blk * 256);
         __builtin_amdgcn_global_load_lds((global_cvoid*)src, dst, 4, 0, 0);
       }
     }
@@ -922,14 +942,14 @@ bwd_dkdv_kernel(const BwdParams p) {
     const float slope2 = C::MOD == kModAlibi ? p.alibi_slopes[h] * kLog2e : 0.f;
     const int cls = classify_block(POS, ib + p.q_off, ib + 31 + p.q_off, jw, jw + 31, p.Sk, p.window, p.prefix, make_int2(0, 0), make_int2(0, 0));
     const bool need_mask = (MASK & (kMaskDoc | kMaskCustom)) != 0 || ib + 31 >= p.Sq || cls != kFull;
-    uint32_t ra_n[KK], ta_c[DB][2];
+    // lane addresses: row reads of the next block (Q fragments, then dO), transposing reads of the current one (dO, then Q)
+    uint32_t ra_n[KK + KV], ta_c[DBV + DB][2];
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) ra_n[kk] = w.ra[kk] + base_n;
+    for (int f = 0; f < KK + KV; ++f) ra_n[f] = (f < KK ? w.ra[f < KK ? f : 0] : w.rv[f < KK ? 0 : f - KK]) + base_n;
 #pragma unroll
-    for (int d = 0; d < DB; ++d) {
-      ta_c[d][0] = w.ta[d][0] + base_c;
-      ta_c[d][1] = w.ta[d][1] + base_c;
-    }
+    for (int d = 0; d < DBV + DB; ++d)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) ta_c[d][u] = (d < DBV ? w.tv[d < DBV ? d : 0][u] : w.ta[d < DBV ? 0 : d - DBV][u]) + base_c;
     // row statistics of the current block's 16 rows of this half: quads of lse2 and of delta, read
     // shortly before the element pairs that use them
     const uint32_t stat_addr = (uint32_t)(4 * w.half) * 4 + base_c;
@@ -937,18 +957,20 @@ bwd_dkdv_kernel(const BwdParams p) {
     auto read_stats = [&](auto q_lo, auto q_hi) __attribute__((always_inline)) {   // quads [q_lo, q_hi): rows 8*q .. 8*q + 3 (+ 4*half)
       static_for<decltype(q_lo)::value, decltype(q_hi)::value>([&](auto qc) __attribute__((always_inline)) {
         constexpr int q4 = decltype(qc)::value;
-        W::template read_b128<2 * C::TILE + (32 * QB + 8 * q4) * 4>(st_l[q4], stat_addr);
-        W::template read_b128<2 * C::TILE + C::STAT + (32 * QB + 8 * q4) * 4>(st_d[q4], stat_addr);
+        W::template read_b128<C::STATS + (32 * QB + 8 * q4) * 4>(st_l[q4], stat_addr);
+        W::template read_b128<C::STATS + C::STAT + (32 * QB + 8 * q4) * 4>(st_d[q4], stat_addr);
       });
     };
     if (first) {                                   // the very first block: its scores are not there yet
-      uint32_t ra_c[KK];
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) ra_c[kk] = w.ra[kk] + base_c;
       cur.s = W::zero16();
       cur.dp = W::zero16();
-      w.template row_stream_g<RowPair<QB * 32 * ROW, C::TILE + QB * 32 * ROW, KK>, 2 * KK, 2>(
-          ra_c, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
+      w.template row_stream_g<RowPair<QB * 32 * ROW, C::TILE + QB * 32 * ROWV, KK>, KK + KV, 2>(
+          [&](auto fc) __attribute__((always_inline)) {
+            constexpr int f = decltype(fc)::value;
+            if constexpr (f < KK) return w.ra[f] + base_c;
+            else return w.rv[f - KK] + base_c;
+          },
+          [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
             constexpr int f = decltype(fc)::value;
             if constexpr (f < KK) cur.s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, kf[f], cur.s, 0, 0, 0);
             else cur.dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, vf[f - KK], cur.dp, 0, 0, 0);
@@ -1010,31 +1032,34 @@ bwd_dkdv_kernel(const BwdParams p) {
     // phase A
     nxt.s = W::zero16();
     nxt.dp = W::zero16();
-    w.template row_stream_g<RowPair<QN * 32 * ROW, C::TILE + QN * 32 * ROW, KK>, 2 * KK, C::GR>(
-        ra_n, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
+    w.template row_stream_g<RowPair<QN * 32 * ROW, C::TILE + QN * 32 * ROWV, KK>, KK + KV, C::GR>(
+        [&](auto fc) __attribute__((always_inline)) { return ra_n[decltype(fc)::value]; }, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
           constexpr int f = decltype(fc)::value;
           if constexpr (f < KK) nxt.s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, kf[f], nxt.s, 0, 0, 0);
           else nxt.dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, vf[f - KK], nxt.dp, 0, 0, 0);
-          constexpr int per = (2 * KK) / 4;        // MFMAs per element pair (pairs 0..3 in this phase)
-          if constexpr (f % per == per - 1) ew_pair(f / per);
+          static_for<4 * f / (KK + KV), 4 * (f + 1) / (KK + KV)>([&](auto r2) __attribute__((always_inline)) { ew_pair(r2); });   // pairs 0..3
           __builtin_amdgcn_sched_barrier(0);
         });
     // phase B
     read_stats(std::integral_constant<int, 2>(), std::integral_constant<int, 4>());   // covered by the first wait below
-    w.template tr_stream_g<TrQuad<C::TILE + QB * 32 * ROW, QB * 32 * ROW, DB, ROW>, 4 * DB, C::GT>(
-        ta_c, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
-          constexpr int f = decltype(fc)::value, d = f % DB, grp = f / DB, ks = grp / 2;
-          if constexpr (grp % 2 == 0) {
+    constexpr int NT = DBV + DB;                   // transposed fragments per 16 rows
+    w.template tr_stream_g<TrQuad<C::TILE + QB * 32 * ROWV, QB * 32 * ROW, DBV, DB, ROWV, ROW>, 2 * NT, C::GT>(
+        [&](auto fc, int u) __attribute__((always_inline)) { return ta_c[decltype(fc)::value % NT][u]; },
+        [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
+          constexpr int f = decltype(fc)::value, ks = f / NT;
+          if constexpr (f % NT < DBV) {
+            constexpr int d = f % NT;
             const bf16x8 bop = __builtin_bit_cast(
                 bf16x8, (i32x4){(int)pw[4 * ks], (int)pw[4 * ks + 1], (int)pw[4 * ks + 2], (int)pw[4 * ks + 3]});
             dv[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bop, dv[d], 0, 0, 0);
           } else {
+            constexpr int d = f % NT - DBV;
             const bf16x8 bop = __builtin_bit_cast(
                 bf16x8, (i32x4){(int)dsw[4 * ks], (int)dsw[4 * ks + 1], (int)dsw[4 * ks + 2], (int)dsw[4 * ks + 3]});
             dk[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bop, dk[d], 0, 0, 0);
           }
-          constexpr int per = (2 * DB) / 4;        // MFMAs per element pair (pairs 4..7 during the rows-0..15 half)
-          if constexpr (f < 2 * DB && f % per == per - 1) ew_pair(4 + f / per);
+          if constexpr (f < NT)                    // pairs 4..7 during the rows-0..15 half
+            static_for<4 + 4 * f / NT, 4 + 4 * (f + 1) / NT>([&](auto r2) __attribute__((always_inline)) { ew_pair(r2); });
           __builtin_amdgcn_sched_barrier(0);
         });
   };
@@ -1074,10 +1099,15 @@ bwd_dkdv_kernel(const BwdParams p) {
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) {
         const int ch = 32 * d + 8 * r4 + 4 * w.half;
-        store_kv_grad(p, p.dk, p.part_dk, split, b, g, hk, j, ch, D, dk[d][4 * r4] * p.scale, dk[d][4 * r4 + 1] * p.scale,
-                      dk[d][4 * r4 + 2] * p.scale, dk[d][4 * r4 + 3] * p.scale);
-        store_kv_grad(p, p.dv, p.part_dv, split, b, g, hk, j, ch, D, dv[d][4 * r4], dv[d][4 * r4 + 1], dv[d][4 * r4 + 2],
-                      dv[d][4 * r4 + 3]);
+        store_kv_grad<false, C::D>(p, split, b, g, hk, j, ch, dk[d][4 * r4] * p.scale, dk[d][4 * r4 + 1] * p.scale,
+                                   dk[d][4 * r4 + 2] * p.scale, dk[d][4 * r4 + 3] * p.scale);
+      }
+#pragma unroll
+    for (int d = 0; d < DBV; ++d)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const int ch = 32 * d + 8 * r4 + 4 * w.half;
+        store_kv_grad<true, C::DV>(p, split, b, g, hk, j, ch, dv[d][4 * r4], dv[d][4 * r4 + 1], dv[d][4 * r4 + 2], dv[d][4 * r4 + 3]);
       }
   }
 }
@@ -1096,7 +1126,7 @@ bwd_dkdv_kernel(const BwdParams p) {
 template <class C>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 bwd_dkdv_ws_kernel(const BwdParams p) {
-  constexpr int D = C::D, BN = C::BN, NB = C::NB, KK = C::KK, DB = C::DB, ROW = C::ROW;
+  constexpr int BN = C::BN, NB = C::NB, KK = C::KK, KV = C::KV, DB = C::DB, ROW = C::ROW, ROWV = C::ROWV;
   constexpr uint32_t MASK = C::MASK;
   constexpr uint32_t POS = MASK & ~kMaskDoc;
   static_assert(C::MOD != kModCustom && (MASK & kMaskCustom) == 0, "compiled variants run the plain dK/dV kernel");
@@ -1104,9 +1134,9 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
   constexpr int NSTAGE = 3;
   constexpr int XBUF = 64 * 16 * 4;                // one exchange buffer: 16 floats per lane, [quad][lane][4]
   constexpr int XCH = NSTAGE * C::STAGE_KV;        // exchange buffers [key group][2] follow the tile ring
-  constexpr int PPM = 8 / KK;                      // element pairs per MFMA of phase 1
+  constexpr int DBV = C::DBV;
   static_assert(NB == 2 && BN == 64, "two row blocks per tile");
-  static_assert(C::TILE_INSTR % NWS == 0, "every wave issues the same number of loads");
+  static_assert(C::TILE_INSTR % NWS == 0 && C::TILEV_INSTR % NWS == 0, "every wave issues the same number of loads");
   typedef BwdWave<C> W;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
 
@@ -1197,15 +1227,15 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
     const unsigned char* qb = (const unsigned char*)((const uint16_t*)p.q.ptr + b * p.q.sb + g * p.q.sg + h * p.q.sh + (int64_t)(t * BN) * p.q.ss);
     const unsigned char* db = (const unsigned char*)((const uint16_t*)p.dout.ptr + b * p.dout.sb + g * p.dout.sg + h * p.dout.sh + (int64_t)(t * BN) * p.dout.ss);
 #pragma unroll
-    for (int u = 0; u < C::TILE_INSTR / NWS; ++u) {
-      tile_load_instr<C>(qb, p.q.ss * 2, nvalid, wave + u * NWS, lane, st);
-      tile_load_instr<C>(db, p.dout.ss * 2, nvalid, wave + u * NWS, lane, st + C::TILE);
+    for (int u = 0; u < (C::TILE_INSTR > C::TILEV_INSTR ? C::TILE_INSTR : C::TILEV_INSTR) / NWS; ++u) {
+      if (u < C::TILE_INSTR / NWS) tile_load_instr<C::D>(qb, p.q.ss * 2, nvalid, wave + u * NWS, lane, st);
+      if (u < C::TILEV_INSTR / NWS) tile_load_instr<C::DV>(db, p.dout.ss * 2, nvalid, wave + u * NWS, lane, st + C::TILE);
     }
     if (wave < 2) {                                // row statistics, 4 bytes per lane: wave 0 lse2, wave 1 delta
       const int64_t srow = ((int64_t)(b * p.G + g) * p.H + h) * p.Sq;
       const int row = t * BN + (lane < nvalid ? lane : nvalid - 1);
       const float* src = (wave == 0 ? p.lse2 : p.delta) + srow + row;
-      lds_void* dst = (lds_void*)(st + 2 * C::TILE + wave * C::STAT);
+      lds_void* dst = (lds_void*)(st + C::STATS + wave * C::STAT);
       __builtin_amdgcn_global_load_lds((global_cvoid*)src, dst, 4, 0, 0);
     }
   };
@@ -1241,17 +1271,16 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
     }
     int kdoc = 0;
     if constexpr ((MASK & kMaskDoc) != 0) kdoc = p.kv_doc[(int64_t)b * p.Sk + jc];
-    f32x16 dv[DB];
+    f32x16 dv[DBV];
 #pragma unroll
-    for (int d = 0; d < DB; ++d) dv[d] = W::zero16();
+    for (int d = 0; d < DBV; ++d) dv[d] = W::zero16();
     f32x16 sa = W::zero16(), sb = W::zero16();
     uint32_t pw[8] = {0, 0, 0, 0, 0, 0, 0, 0};     // bf16 pairs of the last block's P, consumed one iteration later
     auto scores = [&](auto off_c, uint32_t base, f32x16& dst) __attribute__((always_inline)) {   // S of one block, no overlap
-      uint32_t ra_b[KK];
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) ra_b[kk] = w.ra[kk] + base;
       dst = W::zero16();
-      w.template row_stream_g<RowOne<decltype(off_c)::value>, KK, 2>(ra_b, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
+      w.template row_stream_g<RowOne<decltype(off_c)::value>, KK, 2>([&](auto fc) __attribute__((always_inline)) {
+        return w.ra[decltype(fc)::value] + base;
+      }, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
         dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, kf[decltype(fc)::value], dst, 0, 0, 0);
       });
     };
@@ -1269,7 +1298,7 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
       for (int kk = 0; kk < KK; ++kk) ra_n[kk] = w.ra[kk] + base_n;
       i32x4 st_l[4];                               // lse2 of the block's 16 rows of this half
       static_for<0, 4>([&](auto qc) __attribute__((always_inline)) {
-        W::template read_b128<2 * C::TILE + (32 * QB + 8 * decltype(qc)::value) * 4>(st_l[decltype(qc)::value], stat_addr + base_c);
+        W::template read_b128<C::STATS + (32 * QB + 8 * decltype(qc)::value) * 4>(st_l[decltype(qc)::value], stat_addr + base_c);
       });
       const int irow = ib + 4 * w.half;            // query row of register 0
       int qd[16];
@@ -1323,10 +1352,12 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
       };
       // phase 1: scores of the next block  ||  P of the current block
       nxt = W::zero16();
-      w.template row_stream_g<RowOne<QN * 32 * ROW>, KK, 2>(ra_n, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
+      w.template row_stream_g<RowOne<QN * 32 * ROW>, KK, 2>([&](auto fc) __attribute__((always_inline)) {
+        return ra_n[decltype(fc)::value];
+      }, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
         constexpr int f = decltype(fc)::value;
         nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, kf[f], nxt, 0, 0, 0);
-        static_for<f * PPM, (f + 1) * PPM>([&](auto r2c) __attribute__((always_inline)) { ew_pair(r2c); });
+        static_for<8 * f / KK, 8 * (f + 1) / KK>([&](auto r2c) __attribute__((always_inline)) { ew_pair(r2c); });
         __builtin_amdgcn_sched_barrier(0);
       });
     };
@@ -1335,14 +1366,16 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
     // runs while the partner is in its pure matrix phase
     auto dv_phase = [&](auto qb_c, uint32_t base_c) __attribute__((always_inline)) {
       constexpr int QB = decltype(qb_c)::value;
-      uint32_t ta_c[DB][2];
+      uint32_t ta_c[DBV][2];
 #pragma unroll
-      for (int d = 0; d < DB; ++d) {
-        ta_c[d][0] = w.ta[d][0] + base_c;
-        ta_c[d][1] = w.ta[d][1] + base_c;
+      for (int d = 0; d < DBV; ++d) {
+        ta_c[d][0] = w.tv[d][0] + base_c;
+        ta_c[d][1] = w.tv[d][1] + base_c;
       }
-      w.template tr_stream_g<TrOne<C::TILE + QB * 32 * ROW, DB, ROW>, 2 * DB, 2>(ta_c, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
-        constexpr int f = decltype(fc)::value, d = f % DB, ks = f / DB;
+      w.template tr_stream_g<TrOne<C::TILE + QB * 32 * ROWV, DBV, ROWV>, 2 * DBV, 2>([&](auto fc, int u) __attribute__((always_inline)) {
+        return ta_c[decltype(fc)::value % DBV][u];
+      }, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
+        constexpr int f = decltype(fc)::value, d = f % DBV, ks = f / DBV;
         const bf16x8 bop = __builtin_bit_cast(
             bf16x8, (i32x4){(int)pw[4 * ks], (int)pw[4 * ks + 1], (int)pw[4 * ks + 2], (int)pw[4 * ks + 3]});
         dv[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bop, dv[d], 0, 0, 0);
@@ -1373,30 +1406,29 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
     }
     if (j < p.Sk) {
 #pragma unroll
-      for (int d = 0; d < DB; ++d)
+      for (int d = 0; d < DBV; ++d)
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4)
-          store_kv_grad(p, p.dv, p.part_dv, split, b, g, hk, j, 32 * d + 8 * r4 + 4 * w.half, D, dv[d][4 * r4],
-                        dv[d][4 * r4 + 1], dv[d][4 * r4 + 2], dv[d][4 * r4 + 3]);
+          store_kv_grad<true, C::DV>(p, split, b, g, hk, j, 32 * d + 8 * r4 + 4 * w.half, dv[d][4 * r4], dv[d][4 * r4 + 1],
+                                     dv[d][4 * r4 + 2], dv[d][4 * r4 + 3]);
     }
   } else {
     // ================= dS wave =================
-    bf16x8 vf[KK];
+    bf16x8 vf[KV];
     {
       const uint16_t* vp = (const uint16_t*)p.v.ptr + b * p.v.sb + g * p.v.sg + hk * p.v.sh + (int64_t)jc * p.v.ss;
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) vf[kk] = *(const bf16x8*)(vp + 16 * kk + 8 * w.half);
+      for (int kk = 0; kk < KV; ++kk) vf[kk] = *(const bf16x8*)(vp + 16 * kk + 8 * w.half);
     }
     f32x16 dk[DB];
 #pragma unroll
     for (int d = 0; d < DB; ++d) dk[d] = W::zero16();
     f32x16 da = W::zero16(), db = W::zero16();
     auto dscores = [&](auto off_c, uint32_t base, f32x16& dst) __attribute__((always_inline)) {  // dP of one block, no overlap
-      uint32_t ra_b[KK];
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) ra_b[kk] = w.ra[kk] + base;
       dst = W::zero16();
-      w.template row_stream_g<RowOne<decltype(off_c)::value>, KK, 2>(ra_b, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
+      w.template row_stream_g<RowOne<decltype(off_c)::value>, KV, 2>([&](auto fc) __attribute__((always_inline)) {
+        return w.rv[decltype(fc)::value] + base;
+      }, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
         dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, vf[decltype(fc)::value], dst, 0, 0, 0);
       });
     };
@@ -1404,9 +1436,9 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
     // block QN at base_n goes to nxt
     auto ds_iter = [&](auto qp_c, auto qn_c, auto xb_c, uint32_t base_p, uint32_t base_n, f32x16& cur, f32x16& nxt) __attribute__((always_inline)) {
       constexpr int QP = decltype(qp_c)::value, QN = decltype(qn_c)::value, XB = decltype(xb_c)::value;
-      uint32_t ra_n[KK], ta_p[DB][2];
+      uint32_t ra_n[KV], ta_p[DB][2];
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) ra_n[kk] = w.ra[kk] + base_n;
+      for (int kk = 0; kk < KV; ++kk) ra_n[kk] = w.rv[kk] + base_n;
 #pragma unroll
       for (int d = 0; d < DB; ++d) {
         ta_p[d][0] = w.ta[d][0] + base_p;
@@ -1416,7 +1448,7 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
       static_for<0, 4>([&](auto qc) __attribute__((always_inline)) {
         constexpr int q4 = decltype(qc)::value;
         W::template read_b128<XB * XBUF + q4 * 1024>(pq[q4], xaddr);
-        W::template read_b128<2 * C::TILE + C::STAT + (32 * QP + 8 * q4) * 4>(st_d[q4], stat_addr + base_p);
+        W::template read_b128<C::STATS + C::STAT + (32 * QP + 8 * q4) * 4>(st_d[q4], stat_addr + base_p);
       });
       uint32_t dsw[8];
       auto ew_pair = [&](auto r2c) __attribute__((always_inline)) {
@@ -1432,14 +1464,18 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
       };
       // phase 1: dP of the next block  ||  dS of the handed-over block
       nxt = W::zero16();
-      w.template row_stream_g<RowOne<C::TILE + QN * 32 * ROW>, KK, 2>(ra_n, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
+      w.template row_stream_g<RowOne<C::TILE + QN * 32 * ROWV>, KV, 2>([&](auto fc) __attribute__((always_inline)) {
+        return ra_n[decltype(fc)::value];
+      }, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
         constexpr int f = decltype(fc)::value;
         nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, vf[f], nxt, 0, 0, 0);
-        static_for<f * PPM, (f + 1) * PPM>([&](auto r2c) __attribute__((always_inline)) { ew_pair(r2c); });
+        static_for<8 * f / KV, 8 * (f + 1) / KV>([&](auto r2c) __attribute__((always_inline)) { ew_pair(r2c); });
         __builtin_amdgcn_sched_barrier(0);
       });
       // phase 2: dK += Q^T dS
-      w.template tr_stream_g<TrOne<QP * 32 * ROW, DB, ROW>, 2 * DB, 2>(ta_p, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
+      w.template tr_stream_g<TrOne<QP * 32 * ROW, DB, ROW>, 2 * DB, 2>([&](auto fc, int u) __attribute__((always_inline)) {
+        return ta_p[decltype(fc)::value % DB][u];
+      }, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
         constexpr int f = decltype(fc)::value, d = f % DB, ks = f / DB;
         const bf16x8 bop = __builtin_bit_cast(
             bf16x8, (i32x4){(int)dsw[4 * ks], (int)dsw[4 * ks + 1], (int)dsw[4 * ks + 2], (int)dsw[4 * ks + 3]});
@@ -1472,8 +1508,8 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
       for (int d = 0; d < DB; ++d)
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4)
-          store_kv_grad(p, p.dk, p.part_dk, split, b, g, hk, j, 32 * d + 8 * r4 + 4 * w.half, D, dk[d][4 * r4] * p.scale,
-                        dk[d][4 * r4 + 1] * p.scale, dk[d][4 * r4 + 2] * p.scale, dk[d][4 * r4 + 3] * p.scale);
+          store_kv_grad<false, C::D>(p, split, b, g, hk, j, 32 * d + 8 * r4 + 4 * w.half, dk[d][4 * r4] * p.scale,
+                                     dk[d][4 * r4 + 1] * p.scale, dk[d][4 * r4 + 2] * p.scale, dk[d][4 * r4 + 3] * p.scale);
     }
   }
 }

@@ -10,9 +10,10 @@
 namespace fl {
 
 struct BwdKey {
-  int D;            // head dim (D == Dv)
+  int D;            // head dim of q and k
   int mod, mask;
   int nbias;        // additive biases the kernels read (and whose gradient the dQ kernel emits)
+  int Dv;           // head dim of v and dout
 };
 
 typedef hipError_t (*BwdLaunchFn)(const BwdParams& p, int nblocks, hipStream_t stream);
@@ -55,9 +56,9 @@ hipError_t launch_bwd_prep(const BwdParams& p, int nblocks, hipStream_t stream) 
   hipLaunchKernelGGL(bwd_prep_kernel<DV>, dim3(nblocks), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
-template <int D>
+template <int D, int DV>
 hipError_t launch_bwd_reduce(const BwdParams& p, int nblocks, hipStream_t stream) {
-  hipLaunchKernelGGL(bwd_reduce_kv_kernel<D>, dim3(nblocks), dim3(256), 0, stream, p);
+  hipLaunchKernelGGL((bwd_reduce_kv_kernel<D, DV>), dim3(nblocks, 2), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 template <class C>
@@ -87,14 +88,14 @@ hipError_t launch_bwd_dkdv_ws(const BwdParams& p, int nblocks, hipStream_t strea
 
 // CQ / CK: the shapes of the dQ kernel and of the dK/dV kernel (streamed tile rows, waves per SIMD).
 // WS: the dK/dV kernel with specialised waves (eight waves, two per SIMD) instead of the plain one.
-template <int D, int MOD, uint32_t MASK, int BN_Q, int WPE_Q, int BN_K, int WPE_K, bool WS, int NBIAS = 0>
+template <int D, int MOD, uint32_t MASK, int BN_Q, int WPE_Q, int BN_K, int WPE_K, bool WS, int NBIAS = 0, int DV = D>
 constexpr BwdEntry bwd_entry() {
-  typedef BwdCfg<D, MOD, MASK, BN_Q, WPE_Q, NBIAS> CQ;
-  typedef BwdCfg<D, MOD, MASK, BN_K, WPE_K, NBIAS> CK;
+  typedef BwdCfg<D, MOD, MASK, BN_Q, WPE_Q, NBIAS, DV> CQ;
+  typedef BwdCfg<D, MOD, MASK, BN_K, WPE_K, NBIAS, DV> CK;
   if constexpr (WS)
-    return BwdEntry{BwdKey{D, MOD, (int)MASK, NBIAS}, CQ::BM, &launch_bwd_prep<D>, &launch_bwd_dq<CQ>, &launch_bwd_dkdv_ws<CK>, &launch_bwd_reduce<D>, nullptr};
+    return BwdEntry{BwdKey{D, MOD, (int)MASK, NBIAS, DV}, CQ::BM, &launch_bwd_prep<DV>, &launch_bwd_dq<CQ>, &launch_bwd_dkdv_ws<CK>, &launch_bwd_reduce<D, DV>, nullptr};
   else
-    return BwdEntry{BwdKey{D, MOD, (int)MASK, NBIAS}, CQ::BM, &launch_bwd_prep<D>, &launch_bwd_dq<CQ>, &launch_bwd_dkdv<CK>, &launch_bwd_reduce<D>, nullptr};
+    return BwdEntry{BwdKey{D, MOD, (int)MASK, NBIAS, DV}, CQ::BM, &launch_bwd_prep<DV>, &launch_bwd_dq<CQ>, &launch_bwd_dkdv<CK>, &launch_bwd_reduce<D, DV>, nullptr};
 }
 
 // The call behind fl_attn_bwd (fl_api.hip).  custom / user_aux: the backward kernels of a variant compiled at run time from
@@ -103,6 +104,7 @@ fl_status backward_call(const fl_tensor* q, const fl_tensor* k, const fl_tensor*
                         const fl_tensor* lse, const fl_variant_desc* desc, const fl_aux* aux, fl_tensor* dq, fl_tensor* dk,
                         fl_tensor* dv, void* stream, const BwdEntry* custom, const void* const* user_aux);
 
+const BwdEntry* entries_bwd32(int* n);             // the entries with head dim 32 and those with D != Dv
 const BwdEntry* entries_bwd64(int* n);
 const BwdEntry* entries_bwd128(int* n);
 

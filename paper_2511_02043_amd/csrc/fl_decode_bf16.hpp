@@ -228,7 +228,9 @@ decode_kernel(const DecodeParams p) {
     for (int cb = 0; cb < CB; ++cb) {
       // scores of the tile's 32 keys for this block's pairs: lane = pair, register r = key 8*(r/4) + 4*half + r%4
       f32x16 s = W::zero16();
-      w.template row_stream_g<RowOne<0>, KK, 2>(ra_b, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
+      w.template row_stream_g<RowOne<0>, KK, 2>([&](auto fc) __attribute__((always_inline)) {
+        return ra_b[decltype(fc)::value];
+      }, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[cb][decltype(fc)::value], s, 0, 0, 0);
       });
       const int lo_key = p.window >= 0 ? pos[cb] - p.window : 0;
@@ -274,7 +276,9 @@ decode_kernel(const DecodeParams p) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) oacc[cb][d][r] *= alpha;
       }
-      w.template tr_stream_g<TrOne<C::TILE, DB, ROW>, 2 * DB, 2>(ta_b, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
+      w.template tr_stream_g<TrOne<C::TILE, DB, ROW>, 2 * DB, 2>([&](auto fc, int u) __attribute__((always_inline)) {
+        return ta_b[decltype(fc)::value % DB][u];
+      }, [&](auto fc, bf16x8 a) __attribute__((always_inline)) {
         constexpr int f = decltype(fc)::value, d = f % DB, ks = f / DB;
         const bf16x8 bop = __builtin_bit_cast(
             bf16x8, (i32x4){(int)pw[4 * ks], (int)pw[4 * ks + 1], (int)pw[4 * ks + 2], (int)pw[4 * ks + 3]});

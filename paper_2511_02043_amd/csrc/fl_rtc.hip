@@ -235,7 +235,7 @@ const BwdEntry* jit_backward_entry(int D, int mod, uint32_t mask, int nbias, Bwd
   j->dkdv.code = j->dq.code;
   j->dq.kernel_name = names[0];
   j->dkdv.kernel_name = names[1];
-  j->entry = BwdEntry{BwdKey{D, mod, (int)mask, nbias}, 128, prep, nullptr, nullptr, reduce, j};
+  j->entry = BwdEntry{BwdKey{D, mod, (int)mask, nbias, D}, 128, prep, nullptr, nullptr, reduce, j};
   cache[key] = j;
   return &j->entry;
 }
@@ -257,7 +257,7 @@ BwdEntry* jit_backward_wrap(const std::vector<char>& code, const std::string& dq
   j->dkdv.code = code;
   j->dq.kernel_name = dq_name;
   j->dkdv.kernel_name = dkdv_name;
-  j->entry = BwdEntry{BwdKey{D, mod, (int)mask, 0}, 128, prep, nullptr, nullptr, reduce, j};
+  j->entry = BwdEntry{BwdKey{D, mod, (int)mask, 0, D}, 128, prep, nullptr, nullptr, reduce, j};
   return &j->entry;
 }
 
