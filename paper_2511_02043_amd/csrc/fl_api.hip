@@ -705,69 +705,140 @@ __global__ void __launch_bounds__(256) reduce_dlambda_kernel(const float* dl_row
   if (threadIdx.x == 0) dlambda[h] = part[0];
 }
 
-// Gradient of one bias from the staged dS (bf16 dense [B, G, H, Sq, Sk]): the sum over the axes the bias
-// broadcasts along (its size-1 axes), one thread per output element, fixed summation order.
-__global__ void __launch_bounds__(256) reduce_dbias_kernel(const uint16_t* ds, fl::BiasView out, int B, int G, int H, int Sq, int Sk,
-                                                           int ob, int og, int oh, int oi, int oj, int64_t total, int accumulate) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= total) return;
-  const int j = (int)(idx % oj), i = (int)((idx / oj) % oi), h = (int)((idx / ((int64_t)oj * oi)) % oh);
-  const int g = (int)((idx / ((int64_t)oj * oi * oh)) % og), b = (int)(idx / ((int64_t)oj * oi * oh * og));
-  const int nb = ob == 1 ? B : 1, ng = og == 1 ? G : 1, nh = oh == 1 ? H : 1, ni = oi == 1 ? Sq : 1, nj = oj == 1 ? Sk : 1;
-  float s = 0.f;
-  for (int bb = 0; bb < nb; ++bb)
-    for (int gg = 0; gg < ng; ++gg)
-      for (int hh = 0; hh < nh; ++hh)
-        for (int ii = 0; ii < ni; ++ii) {
-          const uint16_t* row = ds + ((((int64_t)(b + bb) * G + (g + gg)) * H + (h + hh)) * Sq + (i + ii)) * Sk + j;
-          for (int jj = 0; jj < nj; ++jj) s += fl::bf16_to_f32(row[jj]);
-        }
-  float* dst = (float*)out.ptr + b * out.sb + g * out.sg + h * out.sh + (int64_t)i * out.si + (int64_t)j * out.sj;
-  *dst = accumulate ? *dst + s : s;                // the second softmax stream adds to the first one's sum
-}
+// Gradient of one bias from the staged dS (32 x 32 blocks, see fl::kDsBlock): the sum over the axes the bias broadcasts along
+// (its size-1 axes).  An output block is a sum of staged blocks, register by register; sums along the queries or the keys
+// inside the block follow at the end.  SPLIT: a workgroup per output block, whose four waves take a quarter of the terms each
+// and meet in LDS in a fixed order (enough waves in flight also where few blocks remain); otherwise a wave per output block.
+// Bound by the read of the staged blocks: 302 MB (128 x 8 heads x 384 x 384) in 64 us, 4.7 TB/s; one thread per eight output
+// elements over a row-major dS took 100 us, and a thread per output of a bias broadcast along the queries 1.6 ms.  From 16
+// terms on the split fills the chip; below that its barrier and the idle waves cost more than they give.
+struct DbiasParams {
+  const uint16_t* ds;
+  fl::BiasView out;
+  int B, G, H, Sq, Sk, nqb, nkb;
+  int ob, og, oh, oi, oj;           // sizes of the bias's axes
+  int64_t units;                    // output blocks
+  int accumulate;                   // the second softmax stream adds to the first one's sum
+};
 
-// The same for a bias that is not broadcast along the keys, Sk a multiple of 8 and a gradient tensor with unit key stride
-// and 16-byte aligned rows: eight keys per thread (one 16-byte load per staged row), four rows in flight.  The terms of an
-// output element are added in the same order as above.
-__global__ void __launch_bounds__(256) reduce_dbias_vec8_kernel(const uint16_t* ds, fl::BiasView out, int B, int G, int H, int Sq, int Sk,
-                                                                int ob, int og, int oh, int oi, int64_t total8, int accumulate) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= total8) return;
-  const int oj8 = Sk / 8;
-  const int j = (int)(idx % oj8) * 8, i = (int)((idx / oj8) % oi), h = (int)((idx / ((int64_t)oj8 * oi)) % oh);
-  const int g = (int)((idx / ((int64_t)oj8 * oi * oh)) % og), b = (int)(idx / ((int64_t)oj8 * oi * oh * og));
-  const int nb = ob == 1 ? B : 1, ng = og == 1 ? G : 1, nh = oh == 1 ? H : 1, ni = oi == 1 ? Sq : 1;
-  const int64_t n_terms = (int64_t)nb * ng * nh * ni;
-  auto term = [&](int64_t n) -> const uint4* {     // n-th staged row of this output, in the nesting order b, g, h, i
-    const int ii = (int)(n % ni), hh = (int)((n / ni) % nh), gg = (int)((n / ((int64_t)ni * nh)) % ng);
-    const int bb = (int)(n / ((int64_t)ni * nh * ng));
-    return (const uint4*)(ds + ((((int64_t)(b + bb) * G + (g + gg)) * H + (h + hh)) * Sq + (i + ii)) * Sk + j);
+template <bool SPLIT>
+__global__ void __launch_bounds__(256) reduce_dbias_kernel(const DbiasParams d) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t unit = SPLIT ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
+  if (unit >= d.units) return;                     // (uniform over the workgroup where it has a barrier)
+  const int ui = d.oi == 1 ? 1 : d.nqb, uj = d.oj == 1 ? 1 : d.nkb;
+  const int jb = (int)(unit % uj), ib = (int)((unit / uj) % ui), h = (int)((unit / ((int64_t)uj * ui)) % d.oh);
+  const int g = (int)((unit / ((int64_t)uj * ui * d.oh)) % d.og), b = (int)(unit / ((int64_t)uj * ui * d.oh * d.og));
+  const int nb = d.ob == 1 ? d.B : 1, ng = d.og == 1 ? d.G : 1, nh = d.oh == 1 ? d.H : 1;
+  const int ni = d.oi == 1 ? d.nqb : 1, nj = d.oj == 1 ? d.nkb : 1;
+  const int64_t n_terms = (int64_t)nb * ng * nh * ni * nj;
+  const int64_t n_lo = SPLIT ? n_terms * wave / 4 : 0, n_hi = SPLIT ? n_terms * (wave + 1) / 4 : n_terms;
+  // term n in the nesting order b, g, h, i, j, kept as running indices
+  int64_t rest = n_lo;
+  int jj = (int)(rest % nj);
+  rest /= nj;
+  int ii = (int)(rest % ni);
+  rest /= ni;
+  int hh = (int)(rest % nh);
+  rest /= nh;
+  int gg = (int)(rest % ng), bb = (int)(rest / ng);
+  auto next_block = [&]() -> const uint4* {
+    const int64_t blk = ((((int64_t)(b + bb) * d.G + (g + gg)) * d.H + (h + hh)) * d.nqb + (ib + ii)) * d.nkb + (jb + jj);
+    if (++jj == nj) {
+      jj = 0;
+      if (++ii == ni) {
+        ii = 0;
+        if (++hh == nh) {
+          hh = 0;
+          if (++gg == ng) {
+            gg = 0;
+            ++bb;
+          }
+        }
+      }
+    }
+    return (const uint4*)(d.ds + blk * fl::kDsBlock) + lane;
   };
-  float s[8];
+  float s[16];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) s[k] = 0.f;
-  auto add = [&](const uint4& v) {
+  for (int r = 0; r < 16; ++r) s[r] = 0.f;
+  auto add = [&](const uint4& v, int r0) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      s[2 * k] += __uint_as_float(w[k] << 16);
-      s[2 * k + 1] += __uint_as_float(w[k] & 0xFFFF0000u);
+      s[r0 + 2 * k] += __uint_as_float(w[k] << 16);
+      s[r0 + 2 * k + 1] += __uint_as_float(w[k] & 0xFFFF0000u);
     }
   };
-  int64_t n = 0;
-  for (; n + 4 <= n_terms; n += 4) {
-    const uint4 v0 = *term(n), v1 = *term(n + 1), v2 = *term(n + 2), v3 = *term(n + 3);
-    add(v0); add(v1); add(v2); add(v3);
+  int64_t n = n_lo;
+  for (; n + 4 <= n_hi; n += 4) {                  // 8 KiB per wave in flight
+    uint4 v[8];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint4* src = next_block();
+      v[2 * u] = src[0];
+      v[2 * u + 1] = src[64];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      add(v[2 * u], 0);
+      add(v[2 * u + 1], 8);
+    }
   }
-  for (; n < n_terms; ++n) add(*term(n));
-  float4* dst = (float4*)((float*)out.ptr + b * out.sb + g * out.sg + h * out.sh + (int64_t)i * out.si + j);
-  if (accumulate) {                                // the second softmax stream adds to the first one's sum
-    const float4 a = dst[0], c = dst[1];
-    s[0] += a.x; s[1] += a.y; s[2] += a.z; s[3] += a.w;
-    s[4] += c.x; s[5] += c.y; s[6] += c.z; s[7] += c.w;
+  for (; n < n_hi; ++n) {
+    const uint4* src = next_block();
+    const uint4 v0 = src[0], v1 = src[64];
+    add(v0, 0);
+    add(v1, 8);
   }
-  dst[0] = make_float4(s[0], s[1], s[2], s[3]);
-  dst[1] = make_float4(s[4], s[5], s[6], s[7]);
+  if constexpr (SPLIT) {
+    __shared__ float part[3][16][64];
+    if (wave > 0)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) part[wave - 1][r][lane] = s[r];
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = ((s[r] + part[0][r][lane]) + part[1][r][lane]) + part[2][r][lane];
+  }
+  const int half = lane >> 5, col = lane & 31;
+  if (d.oi == 1)                                   // over the block's 32 query rows
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+      for (int o = 16; o >= 1; o >>= 1) s[r] += __shfl_xor(s[r], o);
+  if (d.oj == 1) {                                 // over its 32 keys
+#pragma unroll
+    for (int r = 1; r < 16; ++r) s[0] += s[r];
+    s[0] += __shfl_xor(s[0], 32);
+  }
+  const int i = d.oi == 1 ? 0 : ib * 32 + col;
+  if (d.oi == 1 ? col != 0 : i >= d.Sq) return;
+  float* row = (float*)d.out.ptr + b * d.out.sb + g * d.out.sg + h * d.out.sh + (int64_t)i * d.out.si;
+  if (d.oj == 1) {
+    if (half == 0) *row = d.accumulate ? *row + s[0] : s[0];
+    return;
+  }
+  const bool vec = d.out.sj == 1 && ((uintptr_t)d.out.ptr) % 16 == 0 && ((d.out.sb | d.out.sg | d.out.sh | d.out.si) & 3) == 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int j = jb * 32 + 4 * half + 8 * q;
+    if (vec && j + 3 < d.Sk) {
+      float4 x = make_float4(s[4 * q], s[4 * q + 1], s[4 * q + 2], s[4 * q + 3]);
+      if (d.accumulate) {
+        const float4 a = *(const float4*)(row + j);
+        x.x += a.x; x.y += a.y; x.z += a.z; x.w += a.w;
+      }
+      *(float4*)(row + j) = x;
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (j + u < d.Sk) {
+          float* dst = row + (int64_t)(j + u) * d.out.sj;
+          *dst = d.accumulate ? *dst + s[4 * q + u] : s[4 * q + u];
+        }
+    }
+  }
 }
 
 // bf16 [B, G, H, S, D] view -> dense [B, G, H, S, Dc] with zero channels past D (8 channels per thread)
@@ -918,7 +989,7 @@ ExLayout ex_layout(int64_t B, int64_t G, int64_t H, int64_t Hkv, int64_t Sq, int
   L.off_part = take(L.part_k + L.part_v);
   L.off_dl = take(L.ns == 2 ? L.stat : 0);
   // bias gradients: dS of every score (bf16), reduced over the broadcast axes afterwards
-  L.ds = d->n_bias > 0 ? up256(rq * (size_t)Sk * 2) : 0;
+  L.ds = d->n_bias > 0 ? up256((size_t)(B * G * H) * ((Sq + 31) / 32) * ((Sk + 31) / 32) * fl::kDsBlock * 2) : 0;
   L.off_ds = take(L.ds);
   // rms_weight gradient: one partial sum per workgroup (four rows) of the epilogue-derivative kernel
   L.off_dw = take((d->epilogue & FL_EPI_RMSNORM) != 0 ? up256(((rq + 3) / 4) * (size_t)Dv * 4) : 0);
@@ -1737,19 +1808,21 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
     if ((e = run_bwd_dq(be, p, (int)nb_q, stream)) != hipSuccess) return fail(FL_ERR_LAUNCH, "dq launch: %s", hipGetErrorString(e));
     for (uint32_t nb = 0; nb < desc->n_bias; ++nb)
       if (dbias[nb].ptr != nullptr) {               // this stream's dS, summed over the axes the bias broadcasts along
-        const fl_tensor* gt = &extra->dbias[nb];
-        const int64_t total = gt->size[0] * gt->size[1] * gt->size[2] * gt->size[3] * gt->size[4];
-        const fl::BiasView& bv = dbias[nb];
-        const bool vec8 = gt->size[4] == Sk && Sk % 8 == 0 && bv.sj == 1 && ((uintptr_t)bv.ptr) % 16 == 0 && bv.sb % 4 == 0 &&
-                          bv.sg % 4 == 0 && bv.sh % 4 == 0 && bv.si % 4 == 0;
-        if (vec8)
-          hipLaunchKernelGGL(reduce_dbias_vec8_kernel, blocks(total / 8), dim3(256), 0, stream, (const uint16_t*)p.ds_stage, bv, (int)B,
-                             (int)G, (int)H, (int)Sq, (int)Sk, (int)gt->size[0], (int)gt->size[1], (int)gt->size[2], (int)gt->size[3],
-                             total / 8, s);
+        const int64_t* gz = extra->dbias[nb].size;
+        DbiasParams dp;
+        dp.ds = p.ds_stage;
+        dp.out = dbias[nb];
+        dp.B = (int)B; dp.G = (int)G; dp.H = (int)H; dp.Sq = (int)Sq; dp.Sk = (int)Sk;
+        dp.nqb = (int)((Sq + 31) / 32);
+        dp.nkb = (int)((Sk + 31) / 32);
+        dp.ob = (int)gz[0]; dp.og = (int)gz[1]; dp.oh = (int)gz[2]; dp.oi = (int)gz[3]; dp.oj = (int)gz[4];
+        dp.units = gz[0] * gz[1] * gz[2] * (gz[3] == 1 ? 1 : dp.nqb) * (gz[4] == 1 ? 1 : dp.nkb);
+        dp.accumulate = s;
+        const int64_t terms = B * G * H * dp.nqb * dp.nkb / dp.units;
+        if (terms >= 16)
+          hipLaunchKernelGGL(reduce_dbias_kernel<true>, dim3((unsigned)dp.units), dim3(256), 0, stream, dp);
         else
-          hipLaunchKernelGGL(reduce_dbias_kernel, blocks(total), dim3(256), 0, stream, (const uint16_t*)p.ds_stage, bv, (int)B, (int)G,
-                             (int)H, (int)Sq, (int)Sk, (int)gt->size[0], (int)gt->size[1], (int)gt->size[2], (int)gt->size[3],
-                             (int)gt->size[4], total, s);
+          hipLaunchKernelGGL(reduce_dbias_kernel<false>, dim3((unsigned)((dp.units + 3) / 4)), dim3(256), 0, stream, dp);
       }
     if ((e = run_bwd_dkdv(be, p, (int)nb_k, stream)) != hipSuccess) return fail(FL_ERR_LAUNCH, "dk/dv launch: %s", hipGetErrorString(e));
     if (p.hsplit > 1) {

@@ -61,9 +61,17 @@ struct BwdParams {
   BiasView bias[2];                // the forward pass's additive biases (kernels built with NBIAS > 0), bf16
   int32_t q_off;                   // query row i sits at sequence position i + q_off (positional masks, ALiBi); >= 0
   const void* user_aux[4];         // run-time compiled variants: the caller's device arrays that the expressions read
-  uint16_t* ds_stage;              // bias gradients wanted: dS of every score, bf16 dense [B, G, H, Sq, Sk]; the host sums it
-                                   // over the axes each bias broadcasts along afterwards (null: not wanted)
+  // Bias gradients wanted: dS of every score in bf16, as the 32 x 32 blocks in which the dQ kernel holds it,
+  // [B, G, H, ceil(Sq / 32), ceil(Sk / 32)][kDsBlock]; the host sums it afterwards over the axes each bias broadcasts along
+  // (null: not wanted).
+  uint16_t* ds_stage;
 };
+
+// One staged block: registers 0..7 of its 64 lanes, then registers 8..15 (lane L and register r are query row L % 32 and
+// key 8 * (r / 4) + 4 * (L / 32) + r % 4 of the block), so that every store and load is 16 bytes per lane and 1 KiB
+// contiguous per wave.  In the row-major order [Sq, Sk] a lane's four consecutive keys were an 8-byte store of their own:
+// the dQ kernel of the Evoformer rows (128 x 8 heads x 384, D = 32) took 200 us that way, 143 us this way.
+constexpr int kDsBlock = 1024;
 
 // chunk swizzle of a tile row (see the header comment): an XOR on the 16-byte chunk index that
 // depends on row % 16 only.
@@ -716,22 +724,14 @@ bwd_dq_kernel(const BwdParams p) {
         dsw[r2] = pack_bf16(dsv[0], dsv[1]);
         if constexpr (kSplit) dbw[r2] = pack_bf16(dbv[0] * pr[0], dbv[1] * pr[1]);
       }
-      if constexpr (C::NBIAS > 0) {                // staged for the host's reduction over the axes each bias broadcasts
-        // along; registers 4q .. 4q + 3 are the four consecutive keys jb + 8q ..
+      if constexpr (C::NBIAS > 0) {                // staged for the host's reduction over the axes each bias broadcasts along
         auto staged = [&](int n) __attribute__((always_inline)) { return kSplit ? dbw[n] : dsw[n]; };
-        if (p.ds_stage != nullptr && i < p.Sq) {
-          uint16_t* row = p.ds_stage + (((int64_t)(b * p.G + g) * p.H + h) * p.Sq + i) * p.Sk;
+        if (p.ds_stage != nullptr && iw < p.Sq) {    // (rows past Sq and keys past Sk inside the block are zeros)
+          const int nqb = (p.Sq + 31) / 32, nkb = (p.Sk + 31) / 32;
+          const int64_t blk = ((((int64_t)(b * p.G + g) * p.H + h) * nqb + iw / 32) * nkb + (j0 / 32 + nb)) * kDsBlock;
 #pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            const int j = jb + 8 * q4;
-            if ((p.Sk & 3) == 0 && j + 3 < p.Sk) {
-              *(uint2*)(row + j) = make_uint2(staged(2 * q4), staged(2 * q4 + 1));
-            } else {
-#pragma unroll
-              for (int u = 0; u < 4; ++u)
-                if (j + u < p.Sk) row[j + u] = (uint16_t)(staged(2 * q4 + (u >> 1)) >> (16 * (u & 1)));
-            }
-          }
+          for (int u = 0; u < 2; ++u)
+            *(uint4*)(p.ds_stage + blk + u * 512 + lane * 8) = make_uint4(staged(4 * u), staged(4 * u + 1), staged(4 * u + 2), staged(4 * u + 3));
         }
       }
       w.template tr_stream<ST + nb * 32 * ROW>([&](auto fc, bf16x8 a) __attribute__((always_inline)) {
@@ -929,13 +929,30 @@ bwd_dkdv_kernel(const BwdParams p) {
   // so the matrix core and the vector ALU of a wave have independent work at the same time.  The
   // Q / dO tiles cycle through a ring of three LDS stages: the tile after next is requested when
   // every wave has left the tile before the current one.
+  constexpr int NBR = C::NBIAS > 0 ? C::NBIAS : 1;
   struct Blk {
     f32x16 s, dp;
+    uint16_t bias[NBR][16];                        // this lane's bias values of the block, as loaded
+  };
+  // Bias values of query block Q of item it (rows past Sq: the last one's): requested a step before they are used, so that
+  // their latency, and that of the tile loads in flight before them, lies behind a whole block's matrix work -- where two
+  // blocks' values fit the registers (two biases at head dim 64 spilled 40 of them), else at the start of their own step.
+  constexpr bool kBiasAhead = C::WPE == 1 || (C::D + C::DV) * C::NBIAS <= 128;
+  auto load_bias = [&](int it, int Q, Blk& blk) __attribute__((always_inline)) {
+    if constexpr (C::NBIAS > 0) {
+      BiasHead<C::NBIAS> bh_;
+      bh_.set(p, b, g, h_first + it / nt);
+      const int i0 = (t_lo + it % nt) * BN + 32 * Q + 4 * w.half;
+#pragma unroll
+      for (int n = 0; n < C::NBIAS; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) blk.bias[n][r] = bh_.raw1(p, n, min(i0 + 8 * (r >> 2) + (r & 3), p.Sq - 1), jc);
+    }
   };
   constexpr int NSTAGE = 3;
   // one step: block QB of the tile in the LDS stage at byte offset base_c is current, block QN of
   // the tile at base_n is next (the same tile, or row block 0 of the following one)
-  auto step = [&](auto qb_c, auto qn_c, uint32_t base_c, uint32_t base_n, int it, bool first, Blk& cur, Blk& nxt) __attribute__((always_inline)) {
+  auto step = [&](auto qb_c, auto qn_c, uint32_t base_c, uint32_t base_n, int it, int it_n, bool first, Blk& cur, Blk& nxt) __attribute__((always_inline)) {
     constexpr int QB = decltype(qb_c)::value, QN = decltype(qn_c)::value;
     const int t = t_lo + it % nt, h = h_first + it / nt;
     const int ib = t * BN + 32 * QB;
@@ -962,6 +979,7 @@ bwd_dkdv_kernel(const BwdParams p) {
       });
     };
     if (first) {                                   // the very first block: its scores are not there yet
+      if constexpr (kBiasAhead) load_bias(it, QB, cur);
       cur.s = W::zero16();
       cur.dp = W::zero16();
       w.template row_stream_g<RowPair<QB * 32 * ROW, C::TILE + QB * 32 * ROWV, KK>, KK + KV, 2>(
@@ -987,16 +1005,8 @@ bwd_dkdv_kernel(const BwdParams p) {
         qd[r] = qdoc[i < p.Sq ? i : p.Sq - 1];
       }
     }
-    float bl[C::NBIAS > 0 ? 16 : 1];               // bias values of the current block's scores of this lane
-    if constexpr (C::NBIAS > 0) {
-      BiasHead<C::NBIAS> bh_;
-      bh_.set(p, b, g, h);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = irow + 8 * (r >> 2) + (r & 3);
-        bl[r] = bh_.value(p, i < p.Sq ? i : p.Sq - 1, jc);
-      }
-    }
+    if constexpr (kBiasAhead) load_bias(it_n, QN, nxt);
+    else load_bias(it, QB, cur);
     uint32_t pw[8], dsw[8];
     auto ew_pair = [&](int r2) __attribute__((always_inline)) {      // P and dS of registers 2*r2, 2*r2 + 1
       float pv[2], dsv[2];
@@ -1009,7 +1019,11 @@ bwd_dkdv_kernel(const BwdParams p) {
         float a;
         if constexpr (C::MOD == kModCustom) a = replay_user<C::MOD>(cur.s[r], p, uctx, lse2, b, g, h, i, j, fac);
         else a = replay_score<C::MOD>(cur.s[r], c_scale, lse2, p.softcap, slope2, (float)(i + p.q_off - j), fac);
-        if constexpr (C::NBIAS > 0) a += bl[r];
+        if constexpr (C::NBIAS > 0) {
+          float sum = bf16_to_f32(cur.bias[0][r]);
+          if constexpr (C::NBIAS > 1) sum += bf16_to_f32(cur.bias[NBR - 1][r]);
+          a = fmaf(sum, kLog2e, a);
+        }
         pv[e] = fast_exp2(a);
         dsv[e] = cur.dp[r] - delta;
         if constexpr (C::MOD == kModSoftcap || C::MOD == kModCustom) dsv[e] *= fac;
@@ -1080,8 +1094,8 @@ bwd_dkdv_kernel(const BwdParams p) {
     while (it0 < n_items) {
       const int stage_n = stage + 1 == NSTAGE ? 0 : stage + 1;
       const uint32_t base_c = stage * C::STAGE_KV, base_n = stage_n * C::STAGE_KV;
-      step(std::integral_constant<int, 0>(), std::integral_constant<int, 1>(), base_c, base_c, it0, first, ba, bb);
-      step(std::integral_constant<int, 1>(), std::integral_constant<int, 0>(), base_c, base_n, it0, false, bb, ba);
+      step(std::integral_constant<int, 0>(), std::integral_constant<int, 1>(), base_c, base_c, it0, it0, first, ba, bb);
+      step(std::integral_constant<int, 1>(), std::integral_constant<int, 0>(), base_c, base_n, it0, it1 < n_items ? it1 : it0, false, bb, ba);
       first = false;
       __builtin_amdgcn_s_waitcnt(0x0F70);          // the tile after next has landed ...
       __syncthreads();                             // ... for everyone, and everyone has left this tile

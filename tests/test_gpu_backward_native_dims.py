@@ -3,10 +3,13 @@ and write the caller's gradients without padded copies: sizes around the edges o
 workgroups, grouped heads (with the group cut over several workgroups, so that partial sums of dK and dV of different widths
 are added), a chunk of queries against more keys, and both gradient types (the second softmax stream adds its dV to the first
 one's in fp32 before the result is rounded).  Oracle and tolerance: as for fl_attn_bwd_ex."""
+import numpy as np
 import pytest
 
+from oracle import attention_backward_oracle as bo
+from oracle import attention_oracle as ao
 from paper_2511_02043_amd import binding as fb
-from paper_2511_02043_amd import inputs
+from paper_2511_02043_amd import inputs, runner
 from tests.test_gpu_backward_ex import compare
 
 pytestmark = pytest.mark.gpu
@@ -39,3 +42,38 @@ def test_bf16_gradients_and_split_groups(name):
         compare(C(S=150, Sk=150, **VARIANTS[name]), "f32", label=name)
     finally:
         fb.fl_set_tuning("bwd_wg_target", 0)
+
+
+def bias_workload(shape):
+    w = C(D=32, n_bias=1, B=2, G=2, H=4, S=100, Sk=70)
+    w.biases = (inputs.normal(shape, inputs.tensor_seed(7, 9), "bf16"),)
+    return w
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 4, 100, 70), (1, 2, 1, 1, 70), (2, 1, 4, 1, 70), (1, 1, 1, 100, 70), (2, 2, 4, 100, 70)])
+def test_bias_gradient_axes(shape):
+    """Bias gradients summed over every kind of axis (batch, rows, heads, queries), at sizes that no 32 x 32 block divides:
+    sums of few and of many staged blocks, along the lanes of a block and across blocks."""
+    compare(bias_workload(shape), "f32", label=f"bias_{shape}")
+
+
+@pytest.mark.parametrize("shape", [(2, 2, 4, 1, 1), (1, 1, 4, 100, 1), (1, 1, 1, 1, 1)])
+def test_bias_gradient_summed_over_the_keys(shape):
+    """A bias that is the same for all keys of a row does not change the softmax: its gradient is zero in real arithmetic.  What
+    may be left is the rounding of dS to bf16 and that of the stored output, which enters delta = rowsum(dout * out): 2^-9 of
+    each term (2^-8 allowed, for the fp32 arithmetic before it)."""
+    w = bias_workload(shape)
+    dout = inputs.dout_for(w)
+    db = runner.upload_backward_ex(w, dout, grad_dtype="f32")
+    db.fwd.run_checked()
+    for t in db.grads["dbias"]:
+        t.fill_(float("nan"))
+    db.run_checked()
+    got = db.grads["dbias"][0].cpu().numpy().astype(np.float64)
+    out, _ = ao.run_workload(w)
+    w.biases = (np.ascontiguousarray(np.broadcast_to(w.biases[0], (2, 2, 4, 100, 70))),)
+    ds = bo.variant_backward(w, dout)["dbias"][0]
+    terms = np.abs(ds).sum(-1, keepdims=True) + np.abs(dout.astype(np.float64) * out).sum(-1, keepdims=True)
+    bound = 2.0 ** -8 * terms.sum(tuple(a for a in range(4) if shape[a] == 1), keepdims=True)
+    assert got.shape == shape
+    assert np.all(np.abs(got) <= bound), (float(np.max(np.abs(got))), float(np.max(bound)))
