@@ -2,7 +2,8 @@
 `decode_attention(...)` for one decode step over a paged cache.
 
 Marshalling only: the forward pass is fl_attn_fwd, the backward pass fl_attn_bwd, both through
-the C-ABI binding; no attention arithmetic happens here and there is no fallback path.  Tensors
+the C ABI (`_fltorch`, compiled from csrc/fl_torch.cpp, fills the descriptors of the calls that are short
+enough for it to count); no attention arithmetic happens here and there is no fallback path.  Tensors
 are [B, H, S, D] (or [B, G, H, S, D] with an extra independent row axis) bf16 CUDA tensors;
 strided views are passed as they are.
 
@@ -18,6 +19,22 @@ from typing import Optional
 import torch
 
 from . import binding as fb
+
+_host_module = None
+
+
+def _host():
+    """The compiled marshalling module (loaded once, after the library)."""
+    global _host_module
+    if _host_module is None:
+        fb.lib()
+        from . import _fltorch
+        _host_module = _fltorch
+    return _host_module
+
+
+def _stream(t: torch.Tensor) -> int:
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
 
 
 def _as5(x: torch.Tensor) -> torch.Tensor:
@@ -49,7 +66,7 @@ def _check_aux(name: str, t: Optional[torch.Tensor], dtype: torch.dtype, shape, 
         raise ValueError(f"{name} must have unit stride along its last axis")
 
 
-def _desc(scale, causal, window, prefix, softcap, alibi_slopes, q_doc_ids, q_offset=0):
+def _mask_bits(causal, window, prefix, q_doc_ids):
     mask = 0
     if causal:
         mask |= fb.FL_MASK_CAUSAL
@@ -59,52 +76,34 @@ def _desc(scale, causal, window, prefix, softcap, alibi_slopes, q_doc_ids, q_off
         mask |= fb.FL_MASK_PREFIX
     if q_doc_ids is not None:
         mask |= fb.FL_MASK_DOC
+    return mask
+
+
+def _score_mod(softcap, alibi_slopes):
     if softcap is not None and alibi_slopes is not None:
         raise ValueError("one score_mod at a time")
-    mod = fb.FL_MOD_SOFTCAP if softcap is not None else (fb.FL_MOD_ALIBI if alibi_slopes is not None else fb.FL_MOD_NONE)
-    return fb.variant_desc(scale=float(scale), score_mod=mod, softcap=float(softcap or 0.0), mask=mask,
-                           window=int(window or 0), prefix_len=int(prefix or 0), q_offset=int(q_offset))
+    return fb.FL_MOD_SOFTCAP if softcap is not None else (fb.FL_MOD_ALIBI if alibi_slopes is not None else fb.FL_MOD_NONE)
 
 
 class _Attention(torch.autograd.Function):
     @staticmethod
     def forward(ctx, q, k, v, scale, causal, window, prefix, softcap, alibi_slopes, q_doc_ids, kv_doc_ids, q_offset):
-        q5, k5, v5 = _as5(q), _as5(k), _as5(v)
-        B, G, H, Sq, _ = q5.shape
-        desc = _desc(scale, causal, window, prefix, softcap, alibi_slopes, q_doc_ids, q_offset)
-        out = torch.empty((B, G, H, Sq, v5.shape[4]), dtype=q.dtype, device=q.device)
-        lse = torch.empty((B, G, H, Sq, 1), dtype=torch.float32, device=q.device)
-        tq, tk, tv, tout, tlse = (fb.tensor_desc(x) for x in (q5, k5, v5, out, lse))
-        ws = None
-        nbytes = fb.fl_attn_fwd_workspace_size(tq, tk, desc)
-        if nbytes:
-            ws = torch.empty(nbytes, dtype=torch.uint8, device=q.device)
-        aux = fb.aux_desc(alibi_slopes=alibi_slopes, q_doc_ids=q_doc_ids, kv_doc_ids=kv_doc_ids, workspace=ws)
-        stream = torch.cuda.current_stream(q.device).cuda_stream
-        fb.check(fb.fl_attn_fwd(tq, tk, tv, desc, aux, tout, tlse, stream))
+        variant = (float(scale), _score_mod(softcap, alibi_slopes), float(softcap or 0.0),
+                   _mask_bits(causal, window, prefix, q_doc_ids), int(window or 0), int(prefix or 0), q_offset,
+                   alibi_slopes, q_doc_ids, kv_doc_ids)
+        status, out, lse = _host().attention_fwd(q, k, v, *variant, _stream(q))
+        if status:
+            fb.check(status)
         ctx.save_for_backward(q, k, v, out, lse)
-        ctx.variant = (scale, causal, window, prefix, softcap, q_offset)
-        ctx.aux_tensors = (alibi_slopes, q_doc_ids, kv_doc_ids)
-        return out if q.dim() == 5 else out.squeeze(1)
+        ctx.variant = variant
+        return out
 
     @staticmethod
     def backward(ctx, dout):
         q, k, v, out, lse = ctx.saved_tensors
-        scale, causal, window, prefix, softcap, q_offset = ctx.variant
-        alibi_slopes, q_doc_ids, kv_doc_ids = ctx.aux_tensors
-        q5, k5, v5, d5 = _as5(q), _as5(k), _as5(v), _as5(dout)
-        if d5.stride(-1) != 1 or any(st % 8 for st in d5.stride()[:-1]):
-            d5 = d5.contiguous()                   # the kernels need unit inner stride and 16-byte aligned rows
-        desc = _desc(scale, causal, window, prefix, softcap, alibi_slopes, q_doc_ids, q_offset)
-        dq, dk, dv = torch.empty_like(q5), torch.empty_like(k5), torch.empty_like(v5)
-        tq, tk, tv, tout, tdo, tlse, tdq, tdk, tdv = (fb.tensor_desc(x) for x in (q5, k5, v5, out, d5, lse, dq, dk, dv))
-        nbytes = fb.fl_attn_bwd_workspace_size(tq, tk, desc)
-        ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=q.device)
-        aux = fb.aux_desc(alibi_slopes=alibi_slopes, q_doc_ids=q_doc_ids, kv_doc_ids=kv_doc_ids, workspace=ws)
-        stream = torch.cuda.current_stream(q.device).cuda_stream
-        fb.check(fb.fl_attn_bwd(tq, tk, tv, tout, tdo, tlse, desc, aux, tdq, tdk, tdv, stream))
-        if q.dim() == 4:
-            dq, dk, dv = dq.squeeze(1), dk.squeeze(1), dv.squeeze(1)
+        status, dq, dk, dv = _host().attention_bwd(q, k, v, out, lse, dout, *ctx.variant, _stream(q))
+        if status:
+            fb.check(status)
         return (dq, dk, dv) + (None,) * 9
 
 
@@ -128,26 +127,17 @@ def attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, *, scale: Optio
         kv_doc_ids = q_doc_ids
     if kv_doc_ids is not None and q_doc_ids is None:
         raise ValueError("kv_doc_ids needs q_doc_ids")
-    q5, k5 = _as5(q), _as5(k)
-    _check_aux("alibi_slopes", alibi_slopes, torch.float32, (q5.shape[2],), q.device)
-    _check_aux("q_doc_ids", q_doc_ids, torch.int32, (q5.shape[0], q5.shape[3]), q.device)
-    _check_aux("kv_doc_ids", kv_doc_ids, torch.int32, (k5.shape[0], k5.shape[3]), q.device)
+    for x in (q, k, v):
+        if x.dim() not in (4, 5):
+            raise ValueError(f"expected [B, H, S, D] or [B, G, H, S, D], got {tuple(x.shape)}")
+    if alibi_slopes is not None:
+        _check_aux("alibi_slopes", alibi_slopes, torch.float32, (q.shape[-3],), q.device)
+    if q_doc_ids is not None:
+        _check_aux("q_doc_ids", q_doc_ids, torch.int32, (q.shape[0], q.shape[-2]), q.device)
+        _check_aux("kv_doc_ids", kv_doc_ids, torch.int32, (k.shape[0], k.shape[-2]), q.device)
     if q_offset < 0:
         raise ValueError("q_offset must be >= 0")
     return _Attention.apply(q, k, v, scale, causal, window, prefix, softcap, alibi_slopes, q_doc_ids, kv_doc_ids, int(q_offset))
-
-
-def _mask_bits(causal, window, prefix, q_doc_ids):
-    mask = 0
-    if causal:
-        mask |= fb.FL_MASK_CAUSAL
-    if window is not None:
-        mask |= fb.FL_MASK_WINDOW | fb.FL_MASK_CAUSAL
-    if prefix is not None:
-        mask |= fb.FL_MASK_PREFIX
-    if q_doc_ids is not None:
-        mask |= fb.FL_MASK_DOC
-    return mask
 
 
 class _VariantAttention(torch.autograd.Function):
@@ -162,8 +152,7 @@ class _VariantAttention(torch.autograd.Function):
         diff = q2 is not None
         biases = [b for b in (bias0, bias1) if b is not None]
         epi = (fb.FL_EPI_RMSNORM if cfg["rmsnorm"] else 0) | (fb.FL_EPI_GATE_SIGMOID if gate is not None else 0)
-        mod = fb.FL_MOD_SOFTCAP if cfg["softcap"] is not None else (fb.FL_MOD_ALIBI if cfg["alibi_slopes"] is not None else fb.FL_MOD_NONE)
-        desc = fb.variant_desc(scale=float(cfg["scale"]), score_mod=mod, softcap=float(cfg["softcap"] or 0.0),
+        desc = fb.variant_desc(scale=float(cfg["scale"]), score_mod=_score_mod(cfg["softcap"], cfg["alibi_slopes"]), softcap=float(cfg["softcap"] or 0.0),
                                mask=_mask_bits(cfg["causal"], cfg["window"], cfg["prefix"], cfg["q_doc_ids"]),
                                window=int(cfg["window"] or 0), prefix_len=int(cfg["prefix"] or 0), n_bias=len(biases),
                                combine=fb.FL_DIFFERENTIAL if diff else fb.FL_SINGLE, epilogue=epi,
@@ -263,6 +252,19 @@ def variant_attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, *, scal
     return _VariantAttention.apply(cfg, q, k, v, q2, k2, lam, gate, b0, b1, rms_weight if rmsnorm else None)
 
 
+def _paged_call(decode, q, k_cache, v_cache, seq_lens, block_table, max_seq_len, scale, window, softcap, alibi_slopes, workspace,
+                return_lse):
+    mask = (fb.FL_MASK_WINDOW | fb.FL_MASK_CAUSAL) if window is not None else fb.FL_MASK_CAUSAL
+    status, need, out, lse = _host().paged(decode, q, k_cache, v_cache, seq_lens, block_table, int(max_seq_len), float(scale),
+                                           _score_mod(softcap, alibi_slopes), float(softcap or 0.0), mask, int(window or 0),
+                                           alibi_slopes, workspace, return_lse, _stream(q))
+    if status:
+        fb.check(status)
+    if workspace is not None and workspace.numel() * workspace.element_size() < need:
+        raise ValueError(f"workspace holds {workspace.numel() * workspace.element_size()} bytes, {need} needed")
+    return (out, lse) if return_lse else out
+
+
 def decode_attention(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.Tensor, seq_lens: torch.Tensor,
                      block_table: Optional[torch.Tensor] = None, *, max_seq_len: Optional[int] = None,
                      scale: Optional[float] = None, window: Optional[int] = None, softcap: Optional[float] = None,
@@ -293,28 +295,8 @@ def decode_attention(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.Tens
         max_seq_len = (block_table.shape[1] if block_table is not None else 1) * page_size
     if scale is None:
         scale = D ** -0.5
-    if softcap is not None and alibi_slopes is not None:
-        raise ValueError("one score_mod at a time")
-    mod = fb.FL_MOD_SOFTCAP if softcap is not None else (fb.FL_MOD_ALIBI if alibi_slopes is not None else fb.FL_MOD_NONE)
-    desc = fb.variant_desc(scale=float(scale), score_mod=mod, softcap=float(softcap or 0.0),
-                           mask=(fb.FL_MASK_WINDOW | fb.FL_MASK_CAUSAL) if window is not None else fb.FL_MASK_CAUSAL,
-                           window=int(window or 0))
-    q5 = q[:, None, :, None, :]
-    k5, v5 = k_cache.permute(0, 2, 1, 3)[:, None], v_cache.permute(0, 2, 1, 3)[:, None]    # [pages, 1, Hkv, page_size, D]
-    out = torch.empty((B, 1, H, 1, D), dtype=torch.bfloat16, device=q.device)
-    lse = torch.empty((B, 1, H, 1, 1), dtype=torch.float32, device=q.device) if return_lse else None
-    kv = fb.paged_kv(block_table=block_table, page_size=page_size, seq_lens=seq_lens, max_seq_len=int(max_seq_len))
-    tq, tk, tv, tout = (fb.tensor_desc(x) for x in (q5, k5, v5, out))
-    tlse = fb.tensor_desc(lse) if return_lse else None
-    need = max(fb.fl_attn_decode_workspace_size(tq, tk, kv), 16)
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    elif workspace.numel() * workspace.element_size() < need:
-        raise ValueError(f"workspace holds {workspace.numel() * workspace.element_size()} bytes, {need} needed")
-    aux = fb.aux_desc(alibi_slopes=alibi_slopes, workspace=workspace)
-    fb.check(fb.fl_attn_decode(tq, tk, tv, kv, desc, aux, tout, tlse, torch.cuda.current_stream(q.device).cuda_stream))
-    out = out[:, 0, :, 0, :]
-    return (out, lse[:, 0, :, 0, 0]) if return_lse else out
+    return _paged_call(True, q, k_cache, v_cache, seq_lens, block_table, max_seq_len, scale, window, softcap, alibi_slopes, workspace,
+                       return_lse)
 
 
 def paged_prefill_attention(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.Tensor, seq_lens: torch.Tensor,
@@ -344,25 +326,5 @@ def paged_prefill_attention(q: torch.Tensor, k_cache: torch.Tensor, v_cache: tor
         max_seq_len = (block_table.shape[1] if block_table is not None else 1) * page_size
     if scale is None:
         scale = D ** -0.5
-    if softcap is not None and alibi_slopes is not None:
-        raise ValueError("one score_mod at a time")
-    mod = fb.FL_MOD_SOFTCAP if softcap is not None else (fb.FL_MOD_ALIBI if alibi_slopes is not None else fb.FL_MOD_NONE)
-    desc = fb.variant_desc(scale=float(scale), score_mod=mod, softcap=float(softcap or 0.0),
-                           mask=(fb.FL_MASK_WINDOW | fb.FL_MASK_CAUSAL) if window is not None else fb.FL_MASK_CAUSAL,
-                           window=int(window or 0))
-    q5 = q[:, None]
-    k5, v5 = k_cache.permute(0, 2, 1, 3)[:, None], v_cache.permute(0, 2, 1, 3)[:, None]    # [pages, 1, Hkv, page_size, D]
-    out = torch.empty((B, 1, H, Sq, D), dtype=torch.bfloat16, device=q.device)
-    lse = torch.empty((B, 1, H, Sq, 1), dtype=torch.float32, device=q.device) if return_lse else None
-    kv = fb.paged_kv(block_table=block_table, page_size=page_size, seq_lens=seq_lens, max_seq_len=int(max_seq_len))
-    tq, tk, tv, tout = (fb.tensor_desc(x) for x in (q5, k5, v5, out))
-    tlse = fb.tensor_desc(lse) if return_lse else None
-    need = max(fb.fl_attn_prefill_paged_workspace_size(tq, tk, kv), 16)
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    elif workspace.numel() * workspace.element_size() < need:
-        raise ValueError(f"workspace holds {workspace.numel() * workspace.element_size()} bytes, {need} needed")
-    aux = fb.aux_desc(alibi_slopes=alibi_slopes, workspace=workspace)
-    fb.check(fb.fl_attn_prefill_paged(tq, tk, tv, kv, desc, aux, tout, tlse, torch.cuda.current_stream(q.device).cuda_stream))
-    out = out[:, 0]
-    return (out, lse[:, 0, :, :, 0]) if return_lse else out
+    return _paged_call(False, q, k_cache, v_cache, seq_lens, block_table, max_seq_len, scale, window, softcap, alibi_slopes, workspace,
+                       return_lse)

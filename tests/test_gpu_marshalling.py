@@ -1,0 +1,52 @@
+"""The compiled marshalling of the PyTorch entry points: 4-D and 5-D tensors, strided views, an expanded output gradient and a
+caller's workspace reach the C ABI as the tensors they are, and what it does not take is refused before a launch."""
+import pytest
+import torch
+
+from paper_2511_02043_amd import functional as F
+
+pytestmark = pytest.mark.gpu
+
+
+def normal(*shape, seed=0):
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(seed)
+    return torch.randn(shape, generator=gen, device="cuda:0").bfloat16()
+
+
+def grads(q, k, v, **kw):
+    x = [t.detach().requires_grad_(True) for t in (q, k, v)]
+    out = F.attention(*x, **kw)
+    return (out.detach(),) + torch.autograd.grad(out.sum(), x)      # (the gradient of a sum arrives as an expanded scalar)
+
+
+def test_ranks_and_views_agree():
+    """The kernels see the same values whatever the layout, so the results are the same to the bit."""
+    q, k, v = normal(2, 4, 65, 64), normal(2, 2, 65, 64, seed=1), normal(2, 2, 65, 64, seed=2)
+    ref = grads(q, k, v, causal=True, softcap=8.0)
+    rows = lambda t: t.transpose(1, 2).contiguous().transpose(1, 2)                 # storage [B, S, H, D]
+    part = lambda t: torch.cat([t, t], dim=-1)[..., :64]                            # rows of a wider tensor
+    for view in (rows, part):
+        for a, b in zip(ref, grads(view(q), view(k), view(v), causal=True, softcap=8.0)):
+            assert a.shape == b.shape and torch.equal(a, b)
+    for a, b in zip(ref, grads(q[:, None], k[:, None], v[:, None], causal=True, softcap=8.0)):
+        assert torch.equal(a[:, None], b)
+
+
+def test_refusals():
+    q = normal(1, 2, 16, 64)
+    with pytest.raises(KeyError):
+        F.attention(q, q.half(), q)
+    with pytest.raises(ValueError):
+        F.attention(q, q, q[0])
+    with pytest.raises(Exception, match="size"):
+        F.attention(q, q, q[:, :, :8])
+    cache = normal(4, 16, 2, 64)
+    lens = torch.tensor([20], dtype=torch.int32, device="cuda:0")
+    table = torch.tensor([[1, 3]], dtype=torch.int32, device="cuda:0")
+    want = F.decode_attention(q[:, :, 0], cache, cache, lens, table)
+    with pytest.raises(ValueError, match="workspace"):
+        F.decode_attention(q[:, :, 0], cache, cache, lens, table, workspace=torch.empty(8, dtype=torch.uint8, device="cuda:0"))
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda:0")
+    got, lse = F.decode_attention(q[:, :, 0], cache, cache, lens, table, workspace=ws, return_lse=True)
+    assert torch.equal(got, want) and lse.shape == (1, 2) and bool(torch.isfinite(lse).all())
