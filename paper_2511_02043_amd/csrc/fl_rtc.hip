@@ -70,9 +70,13 @@ bool expression_ok(const char* e) {
 
 
 // Compiles `src` (which instantiates the kernels named by the expressions `insts`) for gfx950 with the
-// library's own flags; returns the code object and the lowered kernel names.
+// library's own flags; returns the code object and the lowered kernel names.  batch_loads: schedule for instruction-level
+// parallelism.  The default strategy keeps source order where scalar registers run short, which these kernels' do: of the
+// loads that an expression does for the 32 scores of a lane it then waits for each before the next one.
 fl_status compile_program(const std::string& src, const std::vector<std::string>& insts, const char* what,
-                          std::vector<char>* code, std::vector<std::string>* kernel_names) {
+                          std::vector<char>* code, std::vector<std::string>* kernel_names, bool batch_loads = false) {
+  static std::mutex mu;                            // the compiler's own options are global while it runs: one compilation at a time
+  std::lock_guard<std::mutex> lock(mu);
   const char* headers[] = {kParamsHpp, kKernelHpp, kBwdHpp};
   const char* names[] = {"fl_params.hpp", "fl_kernel_bf16.hpp", "fl_bwd_bf16.hpp"};
   hiprtcProgram prog;
@@ -82,8 +86,9 @@ fl_status compile_program(const std::string& src, const std::vector<std::string>
   for (const std::string& i : insts) exprs.push_back("&" + i);
   for (const std::string& e : exprs) hiprtcAddNameExpression(prog, e.c_str());
   // gfx950 only, packed fp32 instructions off
-  const char* opts[] = {"--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"};
-  const hiprtcResult r = hiprtcCompileProgram(prog, (int)(sizeof(opts) / sizeof(opts[0])), opts);
+  std::vector<const char*> opts = {"--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"};
+  if (batch_loads) opts.insert(opts.end(), {"-mllvm", "-amdgpu-sched-strategy=iterative-ilp"});
+  const hiprtcResult r = hiprtcCompileProgram(prog, (int)opts.size(), opts.data());
   if (r != HIPRTC_SUCCESS) {
     size_t n = 0;
     hiprtcGetProgramLogSize(prog, &n);
@@ -387,7 +392,7 @@ fl_status fl_compile_variant_grad(const char* score_mod_expr, const char* score_
   }
 
   std::vector<std::string> names;
-  fl_status st = compile_program(src, insts, "expression does not compile", &v->code, &names);
+  fl_status st = compile_program(src, insts, "expression does not compile", &v->code, &names, captures);
   // a derivative expression is given by callers who want the backward pass: its kernels are compiled now, so that an
   // error in that expression is reported here
   if (st == FL_OK && score_mod_grad_expr != nullptr) st = compile_backward(v);
