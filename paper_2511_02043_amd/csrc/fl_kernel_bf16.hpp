@@ -1327,7 +1327,7 @@ fwd_bf16_kernel(const FwdParams call) {
           if (tl[2] < t_hi) w.template bias_dma<N % 2>(tl[2] * BN);
         }
         const int tk = tl[SPB + 1] < t_hi ? tl[SPB + 1] : t_hi - 1, tv = tl[SPB] < t_hi ? tl[SPB] : t_hi - 1;
-        if constexpr ((MASK & kMaskDoc) != 0) {    // tiles may be skipped: no fixed stride between them
+        if constexpr ((MASK & (kMaskDoc | kMaskCustom)) != 0) {   // tiles may be skipped: no fixed stride between them
 #pragma unroll
           for (int s = 0; s < NS; ++s) kb[s] = k_tile_base(s, tk);
           vb = v_tile_base(tv);
@@ -1372,7 +1372,7 @@ fwd_bf16_kernel(const FwdParams call) {
         }
         tl[NTL - 1] = after(tl[NTL - 1], tks[NTL - 1], tbw[NTL - 1], std::integral_constant<bool, false>());
         full0 = fulln;
-        if constexpr ((MASK & kMaskDoc) == 0) {    // consecutive tiles: advance the bases until the list ends
+        if constexpr ((MASK & (kMaskDoc | kMaskCustom)) == 0) {   // consecutive tiles: advance the bases until the list ends
           if (tl[SPB] < t_hi) vb += vstep;
 #pragma unroll
           for (int s = 0; s < NS; ++s)

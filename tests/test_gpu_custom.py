@@ -244,3 +244,20 @@ def test_tile_skipping_with_a_window_base_mask_and_errors():
     assert fb.fl_attn_fwd_custom_skip(mod_only.handle, dw.tq, dw.tk, dw.tv, float(w.scale), [], None, dw.tout, dw.tlse) == fb.FL_OK
     torch.cuda.synchronize()
     mod_only.release()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_tile_skipping_with_hidden_tiles_between_visible_ones(D):
+    """Global keys and a band around the diagonal: a row's visible tiles are the first few and a late run, in key
+    ranges longer than the 64 tiles whose classes a workgroup looks at together."""
+    import torch
+    w = inputs.causal_bf16(B=1, H=2, S=300, Sk=4700, D=D, causal=False, salt=13)
+    var = fb.CustomVariant(None, "j >= 300 && (j - 15 * i > 90 || 15 * i - j > 90)", D)
+    dw = runner.upload(w, out_dtype="f32")
+    (plain, skip), _ = run_both_ways(var, dw, float(w.scale))
+    assert np.array_equal(plain[0], skip[0]) and np.array_equal(plain[1], skip[1])
+    ref, ref_lse = ao.attention_custom(w.q, w.k, w.v, scale=w.scale, score_mod=None,
+                                       mask=lambda b, g, h, i, j: (j >= 300) & ((j - 15 * i > 90) | (15 * i - j > 90)))
+    assert float(np.max(np.abs(skip[0] - ref))) <= 1e-2
+    assert float(np.max(np.abs(skip[1] - ref_lse))) <= 1e-3
+    var.release()
