@@ -111,8 +111,10 @@ struct BwdCfg {
   static constexpr int TILE = BN * ROW, TILEV = BN * ROWV;   // bytes of one streamed tile (Q or K, V or dO)
   static constexpr int STAT = BN * 4;              // bytes of one per-row statistic of a tile (dK/dV kernel)
   static constexpr int STATS = TILE + TILEV;       // offset of the statistics in a stage
-  static constexpr int STAGE_DQ = TILE + TILEV;    // K, V
-  static constexpr int STAGE_KV = STATS + 2 * STAT;      // Q, dO, lse2, delta
+  static constexpr bool DOC = (MASK_ & kMaskDoc) != 0;   // the document ids of a tile's keys / rows are staged with the tile
+  static constexpr int STAGE_DQ = TILE + TILEV + (DOC ? STAT : 0);   // K, V, key ids
+  static constexpr int STAGE_KV = STATS + (DOC ? 3 : 2) * STAT;      // Q, dO, lse2, delta, row ids
+  static_assert(!DOC || BN == 64, "one 4-byte load instruction fetches a tile's ids");
   static constexpr int TILE_INSTR = TILE / 1024, TILEV_INSTR = TILEV / 1024;   // 64-lane x 16-byte direct loads per tile
   static constexpr int RPI = 1024 / ROW;           // rows of a Q / K tile per load instruction
   static constexpr int GR = WPE == 1 ? 4 : 2;      // dK/dV pipeline: row fragments read ahead (a lone wave per SIMD hides LDS latency itself)
@@ -208,6 +210,9 @@ struct BwdWave {
   static __device__ __forceinline__ void write_b128(uint32_t addr, i32x4 v) {
     asm volatile("ds_write_b128 %0, %1 offset:%2" : : "v"(addr), "v"(v), "n"(OFF) : "memory");
   }
+  // Values read by hand that only a branch uses: keeps their registers theirs until the reads have landed (called behind
+  // the wait that covers them), also on the path around the branch.
+  static __device__ __forceinline__ void landed(const i32x4& a, const i32x4& b) { asm volatile("" : : "v"(a), "v"(b)); }
   template <int N>
   static __device__ __forceinline__ void wait_lds() {
     static_assert(N >= 0 && N <= 15, "lgkmcnt is a 4-bit counter");
@@ -306,6 +311,38 @@ __device__ __forceinline__ void tile_load_instr(const unsigned char* base, int64
   lds_void* dst = (lds_void*)(lds_tile + inst * 1024);
   __builtin_amdgcn_global_load_lds((global_cvoid*)(base + (int64_t)row * row_bytes + chunk * 16), dst, 16, 0, 0);
 }
+
+// The tile skipper's view of 64 consecutive tiles of a list, one per lane: the range of document ids in tile base + lane, and
+// which of them hold something visible to the workgroup.  One memory round trip serves 64 tiles; finding the next visible
+// tile is a bit scan and its id range a lane read.
+// The ids of a tile's keys (dQ) or rows (dK / dV) arrive in LDS with the tile, and a tile in which the wave's rows and keys are
+// all of one document skips the mask.  Before, every block fetched its 16 ids per lane from global memory behind the loads of
+// the next tile, and so waited for that tile, and every step waited for the next tile's summary.  Windows and packed
+// documents, 8 x 16 heads x 2048 rows, D = 64: dQ 110 -> 88 us, dK / dV 167 -> 154 us; 4 x 32 / 8 heads x 4096, D = 128, the
+// whole training step 1193 -> 1018 us.
+struct TileWindow {
+  int base;
+  int2 ids;
+  unsigned long long vis;
+  __device__ __forceinline__ int2 at(int t) const {      // base <= t < base + 64, uniform
+    return make_int2(__builtin_amdgcn_readlane(ids.x, t - base), __builtin_amdgcn_readlane(ids.y, t - base));
+  }
+};
+// Smallest and largest id of NB consecutive 32-element blocks from block s0 (n blocks in all)
+template <int NB>
+__device__ __forceinline__ int2 merge_summaries(const int2* sum, int s0, int n) {
+  int2 r = sum[min(s0, n - 1)];
+#pragma unroll
+  for (int u = 1; u < NB; ++u) {
+    const int2 x = sum[min(s0 + u, n - 1)];
+    r.x = min(r.x, x.x);
+    r.y = max(r.y, x.y);
+  }
+  return r;
+}
+// Do two id ranges hold one and the same document (nothing is masked) / none in common (everything is)?
+__device__ __forceinline__ bool same_document(int2 a, int2 b) { return a.x == a.y && b.x == b.y && a.x == b.x; }
+__device__ __forceinline__ bool no_common_document(int2 a, int2 b) { return a.y < b.x || b.y < a.x; }
 
 // The score pipeline of the forward pass replayed on one raw dot product x = <q_i, k_j>:
 // returns the log2-domain exponent argument a (P = exp2(a)) and the soft-cap derivative factor.
@@ -551,44 +588,40 @@ bwd_dq_kernel(const BwdParams p) {
   key_range(MASK, i0 + p.q_off, i_last + p.q_off, p.Sk, p.window, p.prefix, k_lo, k_hi);   // rows by their positions
   const int t_lo = k_lo / BN, t_hi = (k_hi + BN - 1) / BN;
   const int nks = (p.Sk + kSumBlock - 1) / kSumBlock;
-  int2 qs_wg = make_int2(0, 0);
-  if constexpr ((MASK & kMaskDoc) != 0) {
+  int2 qs_wg = make_int2(0, 0), qs_wave = make_int2(0, 0);
+  TileWindow win = {t_lo, make_int2(0, 0), 0};
+  auto load_window = [&](int t) __attribute__((always_inline)) {   // what the skipper knows about tiles t .. t + 63
+    win.base = t;
+    win.ids = merge_summaries<NB>(p.kv_sum + (int64_t)b * nks, (t + lane) * NB, nks);
+  };
+  auto scan_window = [&]() __attribute__((always_inline)) {
+    const int tt = win.base + lane;
+    win.vis = __builtin_amdgcn_ballot_w64(
+        tt < t_hi && classify_block(MASK, i0 + p.q_off, i_last + p.q_off, tt * BN, tt * BN + BN - 1, p.Sk, p.window, p.prefix, qs_wg, win.ids) != kSkip);
+  };
+  if (C::DOC && t_lo < t_hi) {                     // (without keys there are no summaries)
     const int nqs = (p.Sq + kSumBlock - 1) / kSumBlock;
     const int2* qsum = p.q_sum + (int64_t)b * nqs;
-    qs_wg = qsum[i0 / kSumBlock];
-    for (int u = 1; u < C::BM / kSumBlock; ++u)
-      if (i0 / kSumBlock + u < nqs) {
-        const int2 t = qsum[i0 / kSumBlock + u];
-        qs_wg.x = min(qs_wg.x, t.x);
-        qs_wg.y = max(qs_wg.y, t.y);
-      }
+    load_window(t_lo);
+    qs_wg = merge_summaries<C::BM / kSumBlock>(qsum, i0 / kSumBlock, nqs);
+    qs_wave = qsum[min(iw / kSumBlock, nqs - 1)];
+    scan_window();
   }
-  // does key tile t hold anything visible to the workgroup's rows?  (document-id summaries)
-  auto tile_visible = [&](int t) __attribute__((always_inline)) -> bool {
-    const int2* ksum = p.kv_sum + (int64_t)b * nks;
-    int2 ks = ksum[min(t * NB, nks - 1)];
-    for (int u = 1; u < NB; ++u)
-      if (t * NB + u < nks) {
-        const int2 x = ksum[t * NB + u];
-        ks.x = min(ks.x, x.x);
-        ks.y = max(ks.y, x.y);
-      }
-    return classify_block(MASK, i0 + p.q_off, i_last + p.q_off, t * BN, t * BN + BN - 1, p.Sk, p.window, p.prefix, qs_wg, ks) != kSkip;
-  };
-  auto next_tile = [&](int t) __attribute__((always_inline)) -> int {
-    if constexpr ((MASK & kMaskDoc) != 0) {
-      if (t < t_hi && !tile_visible(t)) {            // a run of hidden tiles: 64 per round, one per lane
-        ++t;
-        while (t < t_hi) {
-          const int tt = t + lane;
-          const unsigned long long found = __builtin_amdgcn_ballot_w64(tt < t_hi && tile_visible(tt));
-          if (found != 0) {
-            t += __builtin_ctzll(found);
-            break;
-          }
-          t += 64;
+  // first tile at or after t that holds something visible to the workgroup's rows (t_hi if none), and its id range
+  auto next_tile = [&](int t, int2& ks) __attribute__((always_inline)) -> int {
+    if constexpr (C::DOC) {
+      while (t < t_hi) {
+        if (t >= win.base + 64) {
+          load_window(t);
+          scan_window();
         }
-        t = __builtin_amdgcn_readfirstlane(t < t_hi ? t : t_hi);
+        const unsigned long long rest = win.vis >> (t - win.base);
+        if (rest != 0) {
+          t += __builtin_ctzll(rest);
+          ks = win.at(t);
+          return t;
+        }
+        t = min(win.base + 64, t_hi);
       }
     }
     return t;
@@ -606,12 +639,19 @@ bwd_dq_kernel(const BwdParams p) {
       if (u < C::TILEV_INSTR / C::NW)
         tile_load_instr<C::DV>(vbase + (int64_t)(t * BN) * vss, vss, nvalid, wave + u * C::NW, lane, st + C::TILE);
     }
+    if constexpr (C::DOC) {
+      if (wave == 0) {
+        lds_void* dst = (lds_void*)(st + C::TILE + C::TILEV);
+        __builtin_amdgcn_global_load_lds((global_cvoid*)(p.kv_doc + (int64_t)b * p.Sk + t * BN + (lane < nvalid ? lane : nvalid - 1)), dst, 4, 0, 0);
+      }
+    }
   };
 
   // (tn: the tile to request into the other stage while this one is worked on; with biases its loads are issued behind
   // the first block's bias loads, so that waiting for those -- vector loads return in order -- leaves them in flight)
-  auto compute = [&](auto stage_c, int t, int tn) __attribute__((always_inline)) {
+  auto compute = [&](auto stage_c, int t, int tn, int2 ks) __attribute__((always_inline)) {   // ks: the id range of tile t
     constexpr int ST = decltype(stage_c)::value * C::STAGE_DQ;
+    const bool doc_mask = C::DOC && !same_document(qs_wave, ks), doc_skip = C::DOC && no_common_document(qs_wave, ks);   // uniform
     if constexpr (C::NBIAS == 0) load_tile(tn, 1 - decltype(stage_c)::value);
     const int j0 = t * BN;
     static_for<0, NB>([&](auto nbc) __attribute__((always_inline)) {
@@ -619,11 +659,11 @@ bwd_dq_kernel(const BwdParams p) {
       // the wave's 32 rows against this block's 32 keys under the positional masks (uniform)
       const int cls = classify_block(POS, iw + p.q_off, iw + 31 + p.q_off, j0 + 32 * nb, j0 + 32 * nb + 31, p.Sk, p.window, p.prefix,
                                      make_int2(0, 0), make_int2(0, 0));
-      if (cls == kSkip) {                          // nothing visible: dS = 0
+      if (cls == kSkip || doc_skip) {              // nothing visible: dS = 0
         if constexpr (C::NBIAS > 0 && nb == 0) load_tile(tn, 1 - decltype(stage_c)::value);
         return;
       }
-      const bool need_mask = (MASK & (kMaskDoc | kMaskCustom)) != 0 || iw + 31 >= p.Sq || cls != kFull;
+      const bool need_mask = doc_mask || (MASK & kMaskCustom) != 0 || iw + 31 >= p.Sq || cls != kFull;
       // This lane's bias values of the block: requested before the matrix work and left untouched until after it (a
       // conversion right here would put the wait for them, and for the tile loads issued before them, in front of the
       // MFMAs); four keys per load where the rows allow it.
@@ -648,6 +688,11 @@ bwd_dq_kernel(const BwdParams p) {
         }
       }
       if constexpr (C::NBIAS > 0 && nb == 0) load_tile(tn, 1 - decltype(stage_c)::value);
+      i32x4 kd[4];                                 // the block's key ids, covered by the waits of the streams below
+      if constexpr (C::DOC)
+        static_for<0, 4>([&](auto qc) __attribute__((always_inline)) {
+          W::template read_b128<ST + C::TILE + C::TILEV + (32 * nb + 8 * decltype(qc)::value) * 4>(kd[decltype(qc)::value], 16 * w.half);
+        });
       f32x16 s = W::zero16(), dp = W::zero16();
       w.template row_stream<ST + nb * 32 * ROW>(w.ra, [&](auto kk, bf16x8 a) __attribute__((always_inline)) {
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], s, 0, 0, 0);
@@ -655,6 +700,10 @@ bwd_dq_kernel(const BwdParams p) {
       w.template row_stream<ST + C::TILE + nb * 32 * ROWV>(w.rv, [&](auto kk, bf16x8 a) __attribute__((always_inline)) {
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dof[kk], dp, 0, 0, 0);
       });
+      if constexpr (C::DOC) {
+        W::landed(kd[0], kd[1]);
+        W::landed(kd[2], kd[3]);
+      }
       const int jb = j0 + 32 * nb + 4 * w.half;    // key of register 0
       float bl[C::NBIAS > 0 ? 16 : 1];             // sum of the biases of each score, log2 units
       if constexpr (C::NBIAS > 0) {
@@ -679,15 +728,6 @@ bwd_dq_kernel(const BwdParams p) {
             for (int n = 0; n < C::NBIAS; ++n) sum += bf16_to_f32(b1[n][r]);
             bl[r] = sum * kLog2e;
           }
-        }
-      }
-      int kd[16];
-      if constexpr ((MASK & kMaskDoc) != 0) {
-        const int32_t* kdoc = p.kv_doc + (int64_t)b * p.Sk;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = jb + 8 * (r >> 2) + (r & 3);
-          kd[r] = kdoc[j < p.Sk ? j : p.Sk - 1];
         }
       }
       // dsw: the gradient of the raw scaled score (what dQ contracts with K); dbw: the gradient of the score after the
@@ -716,7 +756,7 @@ bwd_dq_kernel(const BwdParams p) {
           for (int e = 0; e < 2; ++e) {
             const int r = 2 * r2 + e;
             const int j = jb + 8 * (r >> 2) + (r & 3);
-            if (hidden_user<MASK>(i, j, p, uctx, b, g, h, qdoc, (MASK & kMaskDoc) ? kd[r] : 0)) pr[e] = 0.f;
+            if (hidden_user<MASK>(i, j, p, uctx, b, g, h, qdoc, C::DOC ? kd[r >> 2][r & 3] : 0)) pr[e] = 0.f;
           }
         }
         dsv[0] *= pr[0];
@@ -743,7 +783,8 @@ bwd_dq_kernel(const BwdParams p) {
     });
   };
 
-  int t = next_tile(t_lo);
+  int2 ks = make_int2(0, 0), ks_n = make_int2(0, 0);
+  int t = next_tile(t_lo, ks);
   if (t < t_hi) {
     load_tile(t, 0);
     __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0)
@@ -752,11 +793,12 @@ bwd_dq_kernel(const BwdParams p) {
       bool done = false;
       static_for<0, 2>([&](auto sc) __attribute__((always_inline)) {
         if (!done) {
-          const int tn = next_tile(t + 1);
-          compute(sc, t, tn < t_hi ? tn : t);      // (past the last tile: the current one again, into the stage nobody reads)
+          const int tn = next_tile(t + 1, ks_n);
+          compute(sc, t, tn < t_hi ? tn : t, ks);  // (past the last tile: the current one again, into the stage nobody reads)
           __builtin_amdgcn_s_waitcnt(0x0F70);
           __syncthreads();
           t = tn;
+          ks = ks_n;
           done = t >= t_hi;
         }
       });
@@ -852,46 +894,44 @@ bwd_dkdv_kernel(const BwdParams p) {
   const int nt = t_hi - t_lo;                      // q-tiles per head
   const int n_items = nt > 0 ? nt * group : 0;     // (head of the group, q-tile), head-major
   const int nqs = (p.Sq + kSumBlock - 1) / kSumBlock;
-  int2 ks_wg = make_int2(0, 0);
-  if constexpr ((MASK & kMaskDoc) != 0) {
+  int2 ks_wg = make_int2(0, 0), ks_wave = make_int2(0, 0);
+  TileWindow win = {0, make_int2(0, 0), 0};        // over the q-tiles t_lo + 0, 1, ... of a head: the ids do not depend on it
+  auto load_window = [&](int t) __attribute__((always_inline)) {
+    win.base = t;
+    win.ids = merge_summaries<NB>(p.q_sum + (int64_t)b * nqs, (t_lo + t + lane) * NB, nqs);
+  };
+  auto scan_window = [&]() __attribute__((always_inline)) {
+    const int tt = t_lo + win.base + lane;
+    const int q_last = (tt * BN + BN < p.Sq ? tt * BN + BN : p.Sq) - 1;
+    win.vis = __builtin_amdgcn_ballot_w64(
+        win.base + lane < nt && classify_block(MASK, tt * BN + p.q_off, q_last + p.q_off, j0, j0 + C::BM - 1, p.Sk, p.window, p.prefix, win.ids, ks_wg) != kSkip);
+  };
+  if (C::DOC && n_items > 0) {                     // (without rows there are no summaries)
     const int nks = (p.Sk + kSumBlock - 1) / kSumBlock;
     const int2* ksum = p.kv_sum + (int64_t)b * nks;
-    ks_wg = ksum[j0 / kSumBlock];
-    for (int u = 1; u < C::BM / kSumBlock; ++u)
-      if (j0 / kSumBlock + u < nks) {
-        const int2 x = ksum[j0 / kSumBlock + u];
-        ks_wg.x = min(ks_wg.x, x.x);
-        ks_wg.y = max(ks_wg.y, x.y);
-      }
+    load_window(0);
+    ks_wg = merge_summaries<C::BM / kSumBlock>(ksum, j0 / kSumBlock, nks);
+    ks_wave = ksum[min(jw / kSumBlock, nks - 1)];
+    scan_window();
   }
-  // does the q-tile of item `it` hold a row that sees any of the workgroup's keys?  (document-id summaries)
-  auto item_visible = [&](int it) __attribute__((always_inline)) -> bool {
-    const int2* qsum = p.q_sum + (int64_t)b * nqs;
-    const int t = t_lo + it % nt;
-    int2 qs = qsum[min(t * NB, nqs - 1)];
-    for (int u = 1; u < NB; ++u)
-      if (t * NB + u < nqs) {
-        const int2 x = qsum[t * NB + u];
-        qs.x = min(qs.x, x.x);
-        qs.y = max(qs.y, x.y);
-      }
-    const int q_last = (t * BN + BN < p.Sq ? t * BN + BN : p.Sq) - 1;
-    return classify_block(MASK, t * BN + p.q_off, q_last + p.q_off, j0, j0 + C::BM - 1, p.Sk, p.window, p.prefix, qs, ks_wg) != kSkip;
-  };
-  auto next_item = [&](int it) __attribute__((always_inline)) -> int {
-    if constexpr ((MASK & kMaskDoc) != 0) {
-      if (it < n_items && !item_visible(it)) {       // a run of hidden q-tiles: 64 per round, one per lane
-        ++it;
-        while (it < n_items) {
-          const int ii = it + lane;
-          const unsigned long long found = __builtin_amdgcn_ballot_w64(ii < n_items && item_visible(ii));
-          if (found != 0) {
-            it += __builtin_ctzll(found);
-            break;
-          }
-          it += 64;
+  // first item at or after `it` whose q-tile holds a row that sees any of the workgroup's keys (n_items if none), and whether
+  // the wave's keys need the document mask in it
+  auto next_item = [&](int it, bool& doc_mask) __attribute__((always_inline)) -> int {
+    doc_mask = false;
+    if constexpr (C::DOC) {
+      while (it < n_items) {
+        const int r = it % nt;
+        if (r < win.base || r >= win.base + 64) {
+          load_window(r);
+          scan_window();
         }
-        it = __builtin_amdgcn_readfirstlane(it < n_items ? it : n_items);
+        const unsigned long long rest = win.vis >> (r - win.base);
+        if (rest != 0) {
+          const int step = __builtin_ctzll(rest);
+          doc_mask = !same_document(win.at(r + step), ks_wave);
+          return it + step;
+        }
+        it += min(win.base + 64, nt) - r;
       }
     }
     return it;
@@ -910,6 +950,12 @@ bwd_dkdv_kernel(const BwdParams p) {
     }
     // row statistics: 64 rows per instruction, 4 bytes per lane
     const int64_t srow = ((int64_t)(b * p.G + g) * p.H + h) * p.Sq;
+    if constexpr (C::DOC) {
+      if (wave == 2) {                             // document ids of the rows
+        lds_void* dst = (lds_void*)(st + C::STATS + 2 * C::STAT);
+        __builtin_amdgcn_global_load_lds((global_cvoid*)(p.q_doc + (int64_t)b * p.Sq + t * BN + (lane < nvalid ? lane : nvalid - 1)), dst, 4, 0, 0);
+      }
+    }
     for (int u = wave; u < 2 * (BN / 64 > 0 ? BN / 64 : 1); u += C::NW) {
       const int which = u % 2, blk = u / 2;        // 0: lse2, 1: delta
       const int r = blk * 64 + lane;
@@ -952,13 +998,13 @@ bwd_dkdv_kernel(const BwdParams p) {
   constexpr int NSTAGE = 3;
   // one step: block QB of the tile in the LDS stage at byte offset base_c is current, block QN of
   // the tile at base_n is next (the same tile, or row block 0 of the following one)
-  auto step = [&](auto qb_c, auto qn_c, uint32_t base_c, uint32_t base_n, int it, int it_n, bool first, Blk& cur, Blk& nxt) __attribute__((always_inline)) {
+  auto step = [&](auto qb_c, auto qn_c, uint32_t base_c, uint32_t base_n, int it, int it_n, bool doc_mask, bool first, Blk& cur, Blk& nxt) __attribute__((always_inline)) {
     constexpr int QB = decltype(qb_c)::value, QN = decltype(qn_c)::value;
     const int t = t_lo + it % nt, h = h_first + it / nt;
     const int ib = t * BN + 32 * QB;
     const float slope2 = C::MOD == kModAlibi ? p.alibi_slopes[h] * kLog2e : 0.f;
     const int cls = classify_block(POS, ib + p.q_off, ib + 31 + p.q_off, jw, jw + 31, p.Sk, p.window, p.prefix, make_int2(0, 0), make_int2(0, 0));
-    const bool need_mask = (MASK & (kMaskDoc | kMaskCustom)) != 0 || ib + 31 >= p.Sq || cls != kFull;
+    const bool need_mask = doc_mask || (MASK & kMaskCustom) != 0 || ib + 31 >= p.Sq || cls != kFull;
     // lane addresses: row reads of the next block (Q fragments, then dO), transposing reads of the current one (dO, then Q)
     uint32_t ra_n[KK + KV], ta_c[DBV + DB][2];
 #pragma unroll
@@ -970,12 +1016,13 @@ bwd_dkdv_kernel(const BwdParams p) {
     // row statistics of the current block's 16 rows of this half: quads of lse2 and of delta, read
     // shortly before the element pairs that use them
     const uint32_t stat_addr = (uint32_t)(4 * w.half) * 4 + base_c;
-    i32x4 st_l[4], st_d[4];
+    i32x4 st_l[4], st_d[4], qd[4];                 // (qd: the rows' document ids)
     auto read_stats = [&](auto q_lo, auto q_hi) __attribute__((always_inline)) {   // quads [q_lo, q_hi): rows 8*q .. 8*q + 3 (+ 4*half)
       static_for<decltype(q_lo)::value, decltype(q_hi)::value>([&](auto qc) __attribute__((always_inline)) {
         constexpr int q4 = decltype(qc)::value;
         W::template read_b128<C::STATS + (32 * QB + 8 * q4) * 4>(st_l[q4], stat_addr);
         W::template read_b128<C::STATS + C::STAT + (32 * QB + 8 * q4) * 4>(st_d[q4], stat_addr);
+        if constexpr (C::DOC) W::template read_b128<C::STATS + 2 * C::STAT + (32 * QB + 8 * q4) * 4>(qd[q4], stat_addr);
       });
     };
     if (first) {                                   // the very first block: its scores are not there yet
@@ -996,15 +1043,6 @@ bwd_dkdv_kernel(const BwdParams p) {
     }
     read_stats(std::integral_constant<int, 0>(), std::integral_constant<int, 2>());   // for the pairs of phase A
     const int irow = ib + 4 * w.half;              // query row of register 0
-    int qd[16];
-    if constexpr ((MASK & kMaskDoc) != 0) {
-      const int32_t* qdoc = p.q_doc + (int64_t)b * p.Sq;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = irow + 8 * (r >> 2) + (r & 3);
-        qd[r] = qdoc[i < p.Sq ? i : p.Sq - 1];
-      }
-    }
     if constexpr (kBiasAhead) load_bias(it_n, QN, nxt);
     else load_bias(it, QB, cur);
     uint32_t pw[8], dsw[8];
@@ -1034,7 +1072,7 @@ bwd_dkdv_kernel(const BwdParams p) {
         for (int e = 0; e < 2; ++e) {
           const int r = 2 * r2 + e;
           const int i = irow + 8 * (r >> 2) + (r & 3);
-          if (hidden_user<MASK>(i, j, p, uctx, b, g, h, (MASK & kMaskDoc) ? qd[r] : 0, kdoc)) pv[e] = 0.f;
+          if (hidden_user<MASK>(i, j, p, uctx, b, g, h, C::DOC ? qd[r >> 2][r & 3] : 0, kdoc)) pv[e] = 0.f;
         }
       }
       dsv[0] *= pv[0];
@@ -1054,6 +1092,7 @@ bwd_dkdv_kernel(const BwdParams p) {
           static_for<4 * f / (KK + KV), 4 * (f + 1) / (KK + KV)>([&](auto r2) __attribute__((always_inline)) { ew_pair(r2); });   // pairs 0..3
           __builtin_amdgcn_sched_barrier(0);
         });
+    if constexpr (C::DOC) W::landed(qd[0], qd[1]);
     // phase B
     read_stats(std::integral_constant<int, 2>(), std::integral_constant<int, 4>());   // covered by the first wait below
     constexpr int NT = DBV + DB;                   // transposed fragments per 16 rows
@@ -1076,13 +1115,15 @@ bwd_dkdv_kernel(const BwdParams p) {
             static_for<4 + 4 * f / NT, 4 + 4 * (f + 1) / NT>([&](auto r2) __attribute__((always_inline)) { ew_pair(r2); });
           __builtin_amdgcn_sched_barrier(0);
         });
+    if constexpr (C::DOC) W::landed(qd[2], qd[3]);
   };
   static_assert(NB == 2, "a tile is two row blocks: the two score register sets swap roles twice per tile");
 
-  int it0 = next_item(0);
+  bool dm0 = false, dm1 = false, dm2 = false;      // do items it0, it1, it2 need the document mask?
+  int it0 = next_item(0, dm0);
   if (it0 < n_items) {
-    int it1 = next_item(it0 + 1);
-    int it2 = it1 < n_items ? next_item(it1 + 1) : n_items;
+    int it1 = next_item(it0 + 1, dm1);
+    int it2 = it1 < n_items ? next_item(it1 + 1, dm2) : n_items;
     load_item(it0, 0);
     if (it1 < n_items) load_item(it1, 1);
     __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0)
@@ -1094,14 +1135,16 @@ bwd_dkdv_kernel(const BwdParams p) {
     while (it0 < n_items) {
       const int stage_n = stage + 1 == NSTAGE ? 0 : stage + 1;
       const uint32_t base_c = stage * C::STAGE_KV, base_n = stage_n * C::STAGE_KV;
-      step(std::integral_constant<int, 0>(), std::integral_constant<int, 1>(), base_c, base_c, it0, it0, first, ba, bb);
-      step(std::integral_constant<int, 1>(), std::integral_constant<int, 0>(), base_c, base_n, it0, it1 < n_items ? it1 : it0, false, bb, ba);
+      step(std::integral_constant<int, 0>(), std::integral_constant<int, 1>(), base_c, base_c, it0, it0, dm0, first, ba, bb);
+      step(std::integral_constant<int, 1>(), std::integral_constant<int, 0>(), base_c, base_n, it0, it1 < n_items ? it1 : it0, dm0, false, bb, ba);
       first = false;
       __builtin_amdgcn_s_waitcnt(0x0F70);          // the tile after next has landed ...
       __syncthreads();                             // ... for everyone, and everyone has left this tile
       it0 = it1;
+      dm0 = dm1;
       it1 = it2;
-      it2 = it2 < n_items ? next_item(it2 + 1) : n_items;
+      dm1 = dm2;
+      it2 = it2 < n_items ? next_item(it2 + 1, dm2) : n_items;
       if (it2 < n_items) load_item(it2, stage);
       stage = stage_n;
     }
@@ -1190,50 +1233,49 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
   const int nt = t_hi - t_lo;                      // q-tiles per head
   const int n_items = nt > 0 ? nt * group : 0;     // (head of the group, q-tile), head-major
   const int nqs = (p.Sq + kSumBlock - 1) / kSumBlock;
-  int2 ks_wg = make_int2(0, 0);
-  if constexpr ((MASK & kMaskDoc) != 0) {
+  int2 ks_wg = make_int2(0, 0), ks_wave = make_int2(0, 0);
+  TileWindow win = {0, make_int2(0, 0), 0};        // over the q-tiles t_lo + 0, 1, ... of a head: the ids do not depend on it
+  auto load_window = [&](int t) __attribute__((always_inline)) {
+    win.base = t;
+    win.ids = merge_summaries<NB>(p.q_sum + (int64_t)b * nqs, (t_lo + t + lane) * NB, nqs);
+  };
+  auto scan_window = [&]() __attribute__((always_inline)) {
+    const int tt = t_lo + win.base + lane;
+    const int q_last = (tt * BN + BN < p.Sq ? tt * BN + BN : p.Sq) - 1;
+    win.vis = __builtin_amdgcn_ballot_w64(
+        win.base + lane < nt && classify_block(MASK, tt * BN + p.q_off, q_last + p.q_off, j0, j0 + C::BM - 1, p.Sk, p.window, p.prefix, win.ids, ks_wg) != kSkip);
+  };
+  if (C::DOC && n_items > 0) {                     // (without rows there are no summaries)
     const int nks = (p.Sk + kSumBlock - 1) / kSumBlock;
     const int2* ksum = p.kv_sum + (int64_t)b * nks;
-    ks_wg = ksum[j0 / kSumBlock];
-    for (int u = 1; u < C::BM / kSumBlock; ++u)
-      if (j0 / kSumBlock + u < nks) {
-        const int2 x = ksum[j0 / kSumBlock + u];
-        ks_wg.x = min(ks_wg.x, x.x);
-        ks_wg.y = max(ks_wg.y, x.y);
-      }
+    load_window(0);
+    ks_wg = merge_summaries<C::BM / kSumBlock>(ksum, j0 / kSumBlock, nks);
+    ks_wave = ksum[min(jw / kSumBlock, nks - 1)];
+    scan_window();
   }
-  // does the q-tile of item `it` hold a row that sees any of the workgroup's keys?  (document-id summaries)
-  auto item_visible = [&](int it) __attribute__((always_inline)) -> bool {
-    const int2* qsum = p.q_sum + (int64_t)b * nqs;
-    const int t = t_lo + it % nt;
-    int2 qs = qsum[min(t * NB, nqs - 1)];
-    for (int u = 1; u < NB; ++u)
-      if (t * NB + u < nqs) {
-        const int2 x = qsum[t * NB + u];
-        qs.x = min(qs.x, x.x);
-        qs.y = max(qs.y, x.y);
-      }
-    const int q_last = (t * BN + BN < p.Sq ? t * BN + BN : p.Sq) - 1;
-    return classify_block(MASK, t * BN + p.q_off, q_last + p.q_off, j0, j0 + C::BM - 1, p.Sk, p.window, p.prefix, qs, ks_wg) != kSkip;
-  };
-  auto next_item = [&](int it) __attribute__((always_inline)) -> int {
-    if constexpr ((MASK & kMaskDoc) != 0) {
-      if (it < n_items && !item_visible(it)) {       // a run of hidden q-tiles: 64 per round, one per lane
-        ++it;
-        while (it < n_items) {
-          const int ii = it + lane;
-          const unsigned long long found = __builtin_amdgcn_ballot_w64(ii < n_items && item_visible(ii));
-          if (found != 0) {
-            it += __builtin_ctzll(found);
-            break;
-          }
-          it += 64;
+  // first item at or after `it` whose q-tile holds a row that sees any of the workgroup's keys (n_items if none), and whether
+  // the wave's keys need the document mask in it
+  auto next_item = [&](int it, bool& doc_mask) __attribute__((always_inline)) -> int {
+    doc_mask = false;
+    if constexpr (C::DOC) {
+      while (it < n_items) {
+        const int r = it % nt;
+        if (r < win.base || r >= win.base + 64) {
+          load_window(r);
+          scan_window();
         }
-        it = __builtin_amdgcn_readfirstlane(it < n_items ? it : n_items);
+        const unsigned long long rest = win.vis >> (r - win.base);
+        if (rest != 0) {
+          const int step = __builtin_ctzll(rest);
+          doc_mask = !same_document(win.at(r + step), ks_wave);
+          return it + step;
+        }
+        it += min(win.base + 64, nt) - r;
       }
     }
     return it;
   };
+
   auto load_item = [&](int it, int stage) __attribute__((always_inline)) {
     const int t = t_lo + it % nt, h = h_first + it / nt;
     const int nvalid = min(BN, p.Sq - t * BN);
@@ -1252,6 +1294,12 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
       lds_void* dst = (lds_void*)(st + C::STATS + wave * C::STAT);
       __builtin_amdgcn_global_load_lds((global_cvoid*)src, dst, 4, 0, 0);
     }
+    if constexpr (C::DOC) {
+      if (wave == 2) {                             // document ids of the rows
+        lds_void* dst = (lds_void*)(st + C::STATS + 2 * C::STAT);
+        __builtin_amdgcn_global_load_lds((global_cvoid*)(p.q_doc + (int64_t)b * p.Sq + t * BN + (lane < nvalid ? lane : nvalid - 1)), dst, 4, 0, 0);
+      }
+    }
   };
   // end of an iteration: this wave's LDS traffic (and, when `loads`, its tile loads) is complete, then
   // the workgroup barrier.  No fence beyond that: every LDS access of the loop is issued by hand.
@@ -1264,9 +1312,10 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
   };
 
   // window of the tile list: items at list positions P - 1, P, P + 1, P + 2 (n_items = none)
-  int itm1 = n_items, it0 = next_item(0);
-  int itp1 = it0 < n_items ? next_item(it0 + 1) : n_items;
-  int itp2 = itp1 < n_items ? next_item(itp1 + 1) : n_items;
+  bool dm0 = false, dmp1 = false, dmp2 = false;    // do the items at P, P + 1, P + 2 need the document mask?
+  int itm1 = n_items, it0 = next_item(0, dm0);
+  int itp1 = it0 < n_items ? next_item(it0 + 1, dmp1) : n_items;
+  int itp2 = itp1 < n_items ? next_item(itp1 + 1, dmp2) : n_items;
   if (it0 < n_items) load_item(it0, 0);
   if (itp1 < n_items) load_item(itp1, 1);
   if (itp2 < n_items) load_item(itp2, 2);
@@ -1306,24 +1355,17 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
       const int ib = t * BN + 32 * QB;
       const float slope2 = C::MOD == kModAlibi ? p.alibi_slopes[h] * kLog2e : 0.f;
       const int cls = classify_block(POS, ib + p.q_off, ib + 31 + p.q_off, jw, jw + 31, p.Sk, p.window, p.prefix, make_int2(0, 0), make_int2(0, 0));
-      const bool need_mask = (MASK & kMaskDoc) != 0 || ib + 31 >= p.Sq || cls != kFull;
+      const bool need_mask = dm0 || ib + 31 >= p.Sq || cls != kFull;
       uint32_t ra_n[KK];
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) ra_n[kk] = w.ra[kk] + base_n;
-      i32x4 st_l[4];                               // lse2 of the block's 16 rows of this half
+      i32x4 st_l[4], qd[4];                        // lse2 and document ids of the block's 16 rows of this half
       static_for<0, 4>([&](auto qc) __attribute__((always_inline)) {
         W::template read_b128<C::STATS + (32 * QB + 8 * decltype(qc)::value) * 4>(st_l[decltype(qc)::value], stat_addr + base_c);
+        if constexpr (C::DOC)
+          W::template read_b128<C::STATS + 2 * C::STAT + (32 * QB + 8 * decltype(qc)::value) * 4>(qd[decltype(qc)::value], stat_addr + base_c);
       });
       const int irow = ib + 4 * w.half;            // query row of register 0
-      int qd[16];
-      if constexpr ((MASK & kMaskDoc) != 0) {
-        const int32_t* qdoc = p.q_doc + (int64_t)b * p.Sq;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int i = irow + 8 * (r >> 2) + (r & 3);
-          qd[r] = qdoc[i < p.Sq ? i : p.Sq - 1];
-        }
-      }
       float bl[C::NBIAS > 0 ? 16 : 1];             // bias values of the current block's scores of this lane
       if constexpr (C::NBIAS > 0) {
         BiasHead<C::NBIAS> bh_;
@@ -1353,7 +1395,7 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
           for (int e = 0; e < 2; ++e) {
             const int r = 2 * r2 + e;
             const int i = irow + 8 * (r >> 2) + (r & 3);
-            if (hidden<MASK>(i, j, p.Sq, p.Sk, p.q_off, p.window, p.prefix, (MASK & kMaskDoc) ? qd[r] : 0, kdoc)) pv[e] = 0.f;
+            if (hidden<MASK>(i, j, p.Sq, p.Sk, p.q_off, p.window, p.prefix, C::DOC ? qd[r >> 2][r & 3] : 0, kdoc)) pv[e] = 0.f;
           }
         }
         pw[r2] = pack_bf16(pv[0], pv[1]);
@@ -1374,6 +1416,10 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
         static_for<8 * f / KK, 8 * (f + 1) / KK>([&](auto r2c) __attribute__((always_inline)) { ew_pair(r2c); });
         __builtin_amdgcn_sched_barrier(0);
       });
+      if constexpr (C::DOC) {
+        W::landed(qd[0], qd[1]);
+        W::landed(qd[2], qd[3]);
+      }
     };
     // dV += dO^T P for the block whose P (bf16 pairs in pw) the previous iteration formed: it runs
     // first in an iteration, while the partner wave is in its mixed phase, and the mixed phase above
@@ -1414,8 +1460,10 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
       iteration_end(false);
       itm1 = it0;
       it0 = itp1;
+      dm0 = dmp1;
       itp1 = itp2;
-      itp2 = itp2 < n_items ? next_item(itp2 + 1) : n_items;
+      dmp1 = dmp2;
+      itp2 = itp2 < n_items ? next_item(itp2 + 1, dmp2) : n_items;
       s0 = s0 + 1 == NSTAGE ? 0 : s0 + 1;
     }
     if (j < p.Sk) {
@@ -1513,8 +1561,10 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
       iteration_end(false);
       itm1 = it0;
       it0 = itp1;
+      dm0 = dmp1;
       itp1 = itp2;
-      itp2 = itp2 < n_items ? next_item(itp2 + 1) : n_items;
+      dmp1 = dmp2;
+      itp2 = itp2 < n_items ? next_item(itp2 + 1, dmp2) : n_items;
       s0 = s0 + 1 == NSTAGE ? 0 : s0 + 1;
     }
     if (j < p.Sk) {
