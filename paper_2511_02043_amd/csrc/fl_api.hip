@@ -1300,7 +1300,6 @@ static fl_status forward_call(const fl_tensor* q, const fl_tensor* k, const fl_t
   int order = g_tuning.order >= 0 ? g_tuning.order : 1;
   if (order == 1 && nbh % 8 != 0) order = 0;
   p.order = order;
-  p.doc_vec = (mask & FL_MASK_DOC) && Sk % 4 == 0 && ((uintptr_t)aux->kv_doc_ids) % 16 == 0;
 
   hipStream_t stream = (hipStream_t)stream_v;
   if (Sk == 0) {

@@ -133,7 +133,13 @@ struct Bf16Cfg {
   static_assert(RING_ == 2 || (NBIAS_ == 0 && !DIFF_), "bias staging and the two-stream loop wait for their loads every step");
   static constexpr int K_RING = 0;                 // LDS layout: K ring [RING][NS][K_BYTES], V ring [RING][V_BYTES]
   static constexpr int V_RING = RING * NS * K_BYTES;
-  static constexpr int RING_BYTES = V_RING + RING * V_BYTES;
+  // document masks: the key ids of a tile travel with its V tile (slot n % RING), so that masking a tile reads them from LDS (fetched
+  // from memory where the mask needs them they cost a round trip per masked tile: causal with 60 / 12 documents in 4096 rows,
+  // 4 x 16 heads, D = 64: 69 / 97 us that way, 65 / 92 us this way)
+  static constexpr bool DOC = (MASK_ & kMaskDoc) != 0;
+  static constexpr int ID_BYTES = DOC ? BN * 4 : 0;
+  static constexpr int ID_RING = V_RING + RING * V_BYTES;
+  static constexpr int RING_BYTES = ID_RING + RING * ID_BYTES;
   static constexpr int XCH_BYTES = DIFF ? NROWG * 64 * DVB * 16 * 4 : 0;   // epilogue exchange of the differential variant
   static constexpr int LDS_BYTES = RING_BYTES > XCH_BYTES ? RING_BYTES : XCH_BYTES;
   static constexpr int K_INSTR = K_BYTES / 1024;   // 64-lane x 16-byte direct loads per K tile
@@ -416,8 +422,19 @@ struct Wave {
   // i - j > window) -- one or two compares per score instead of evaluating every mask on (i, j).
   // `word` (mask expressions with a precomputed map only): bit 16*nb + r set = this lane's score register r of key block
   // nb is hidden; then nothing is evaluated here.
+  // ID_OFF (document masks): LDS offset of the tile's key ids.
+  template <int ID_OFF>
   __device__ __forceinline__ void mask(Scores& sc, int j0, uint32_t word = 0) const {
     constexpr uint32_t MASK = C::MASK;
+    i32x4 kd[NB][4];                               // ids of this lane's keys: register r of block nb is kd[nb][r / 4][r % 4]
+    if constexpr (C::DOC) {
+      const uint32_t a = 16u * (uint32_t)half;
+      static_for<0, NB * 4>([&](auto qc) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value;
+        read_k<ID_OFF + (32 * (q / 4) + 8 * (q % 4)) * 4>(kd[q / 4][q % 4], a);
+      });
+      wait_lds<0>();
+    }
     if constexpr ((MASK & kMaskCustom) != 0) {
       if (p.block_bits != nullptr) {               // uniform
 #pragma unroll
@@ -443,24 +460,6 @@ struct Wave {
     }
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      int kd[16];
-      if constexpr ((MASK & kMaskDoc) != 0) {
-        const int32_t* kdoc = p.kv_doc + (int64_t)b * p.Sk;
-        const int jb = jl + 32 * nb;
-        if (p.doc_vec && j0 + C::BN <= p.Sk) {     // uniform: four ids per load
-#pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4) {
-            const int4 q4 = *(const int4*)(kdoc + jb + 8 * r4);
-            kd[4 * r4] = q4.x; kd[4 * r4 + 1] = q4.y; kd[4 * r4 + 2] = q4.z; kd[4 * r4 + 3] = q4.w;
-          }
-        } else {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int j = jb + 8 * (r >> 2) + (r & 3);
-            kd[r] = kdoc[j < p.Sk ? j : p.Sk - 1];
-          }
-        }
-      }
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -468,7 +467,7 @@ struct Wave {
           const int c = 32 * nb + 8 * (r >> 2) + (r & 3);
           bool hide = c > d_hi[rb];
           if constexpr ((MASK & kMaskWindow) != 0) hide = hide || c < d_lo[rb];
-          if constexpr ((MASK & kMaskDoc) != 0) hide = hide || kd[r] != qdoc[rb];
+          if constexpr ((MASK & kMaskDoc) != 0) hide = hide || kd[nb][r >> 2][r & 3] != qdoc[rb];
           if constexpr ((MASK & kMaskCustom) != 0)  // (valid indices only, as for the score_mod; a key past Sk is hidden already)
             hide = hide || fl_user_mask(b, g, h, ic[rb] + p.q_off, FL_USER_CLAMP && jl + c >= p.Sk ? p.Sk - 1 : jl + c, p);
           if (hide) sc[rb][nb][r] = -INFINITY;
@@ -1140,6 +1139,16 @@ fwd_bf16_kernel(const FwdParams call) {
     lds_void* dst = (lds_void*)(lds_raw + lds_off + v_instr(u) * 1024);
     __builtin_amdgcn_global_load_lds((global_cvoid*)(tile_base + v_off[u]), dst, 16, 0, 0);
   };
+  // the key ids of tile t, 4 bytes per lane, by the last wave (a key past Sk repeats the last one's and is masked anyway)
+  auto issue_ids = [&](int t, int slot) __attribute__((always_inline)) {
+    if constexpr (C::DOC) {
+      static_assert(BN <= 64, "one load instruction fetches a tile's ids");
+      if (wave == C::NWAVES - 1 && lane < BN) {
+        lds_void* dst = (lds_void*)(lds_raw + C::ID_RING + slot * C::ID_BYTES);
+        __builtin_amdgcn_global_load_lds((global_cvoid*)(p.kv_doc + (int64_t)b * p.Sk + min(t * BN + lane, p.Sk - 1)), dst, 4, 0, 0);
+      }
+    }
+  };
   auto k_tile_base = [&](int s, int t) __attribute__((always_inline)) { return kbase[s] + (int64_t)(t * BN) * kss[s]; };
   auto v_tile_base = [&](int t) __attribute__((always_inline)) { return vbase + (int64_t)(t * BN) * vss; };
   // whole-tile loads in one burst (prologue, two-stream loop)
@@ -1168,6 +1177,7 @@ fwd_bf16_kernel(const FwdParams call) {
 #pragma unroll
     for (int u = 0; u < VPW; ++u)
       issue_v(u, C::PAGED ? pb[u < KPW ? u : 0] : v_tile_base(t), C::V_RING + buf * C::V_BYTES);
+    issue_ids(t, buf);
   };
   auto wait_loads_and_sync = [&]() __attribute__((always_inline)) {
     __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): this wave's direct loads have landed
@@ -1266,7 +1276,7 @@ fwd_bf16_kernel(const FwdParams call) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) cur[rb][nb][r] = -INFINITY;
           } else {
-            w.mask(cur, t0 * BN, tbw[0]);
+            w.template mask<C::ID_RING + slot_vc * C::ID_BYTES>(cur, t0 * BN, tbw[0]);
             w.rowmax(cur, mx);
             w.advance_max(mx);
           }
@@ -1294,6 +1304,7 @@ fwd_bf16_kernel(const FwdParams call) {
           paged_bases(p.k, tk, pgk, kbp);
           paged_bases(p.v, tv, pgv, vbp);
         }
+        issue_ids(tv, slot_vl);
         w.template phase_a<C::K_RING + slot_kn * NS * C::K_BYTES>(
             nxt, cur, ps, tn * BN, br, [&](auto fc) __attribute__((always_inline)) {
               constexpr int f = decltype(fc)::value, NF = NB * KK;

@@ -171,8 +171,9 @@ const KernelEntry* jit_forward_entry(const JitRequest& r) {
   const int nw = (r.diff || r.wide) ? 8 : 4;
   const int ns = r.diff ? 2 : 1;
   int bn = 64;
-  if (2 * bn * 2 * (ns * r.D + r.DV) > 65536) bn = 32;
-  const int lds = 2 * bn * 2 * (ns * r.D + r.DV);
+  const int ids = (r.mask & kMaskDoc) != 0 ? 2 * 4 : 0;   // bytes per key of the id ring of a document mask
+  if (bn * (4 * (ns * r.D + r.DV) + ids) > 65536) bn = 32;
+  const int lds = bn * (4 * (ns * r.D + r.DV) + ids);
   const int xch = r.diff ? (nw / 2) * 64 * (r.DV / 32) * 16 * 4 : 0;
   char inst[320];
   snprintf(inst, sizeof(inst), "fl::fwd_bf16_kernel<fl::Bf16Cfg<%d, %d, %d, 1, %d, 2, %d, %uu, %d, %s, %uu, 2, %s, %d>>", r.D, r.DV, nw, bn,
