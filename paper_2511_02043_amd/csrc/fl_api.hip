@@ -108,16 +108,6 @@ const fl::KernelEntry* find_entry(const fl_variant_desc* d, int dtype, int D, in
                                   int64_t Sq = 0, const PagedShape* paged = nullptr, const PagedShape* packed = nullptr) {
   const Registry& r = registry();
   const int mask = (int)canonical_mask(d->mask);
-  // a soft-cap that bounds every exponent runs without a running maximum where such a kernel is listed
-  int mod = (int)d->score_mod;
-  if (mod == FL_MOD_SOFTCAP && d->softcap * fl::kLog2e <= fl::kFixedRefLog2 && paged == nullptr && packed == nullptr)
-    for (int t = 0; t < 5; ++t)
-      for (int e = 0; e < r.n[t]; ++e) {
-        const fl::KernelKey& k = r.tab[t][e].key;
-        if (k.mod == fl::kModSoftcapFixed && k.dtype == dtype && k.D == D && k.DV == Dv && k.mask == mask && k.nbias == (int)d->n_bias &&
-            k.epi == (int)d->epilogue && k.diff == (int)d->combine)
-          mod = fl::kModSoftcapFixed;
-      }
   const fl::KernelEntry* best = nullptr;
   const fl::KernelEntry* short_loop = nullptr;    // the variant's 32-key-tile shape at three or four waves per SIMD, if listed
   const fl::KernelEntry* four_waves = nullptr;    // a 4-wave, one-row-block shape of the variant (128 query rows per workgroup)
@@ -141,7 +131,7 @@ const fl::KernelEntry* find_entry(const fl_variant_desc* d, int dtype, int D, in
         continue;
       }
       if (k.key.diff != (int)d->combine) continue;
-      if (k.key.D != D || k.key.DV != Dv || k.key.mod != mod || k.key.mask != mask ||
+      if (k.key.D != D || k.key.DV != Dv || k.key.mod != (int)d->score_mod || k.key.mask != mask ||
           k.key.nbias != (int)d->n_bias || k.key.epi != (int)d->epilogue)
         continue;
       // shape preference: tuning request if it exists, else the first listed

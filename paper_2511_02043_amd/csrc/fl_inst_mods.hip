@@ -14,9 +14,6 @@ static const KernelEntry kEntries[] = {
     bf16_entry<64, 64, 4, 1, 32, 3, kModNone, CW | kMaskDoc, 0, false, 0>(),
     E(64, kModNone, CW),   E(64, kModNone, CW | kMaskDoc),  E(64, kModNone, kMaskDoc),
     E(64, kModNone, kMaskCausal | kMaskDoc),
-    // soft-caps small enough to need no running maximum: the shapes of the general ones
-    E(64, kModSoftcapFixed, 0), E(64, kModSoftcapFixed, kMaskCausal), E(128, kModSoftcapFixed, 0),
-    bf16_entry<64, 64, 4, 1, 32, 4, kModSoftcapFixed, 0, 0, false, 0>(),
     bf16_entry<64, 64, 4, 2, 32, 2, kModNone, kMaskPrefix, 0, false, 0>(),   // long key loops: two row blocks per wave, as for plain / causal
     E(64, kModNone, kMaskPrefix), E(64, kModNone, kMaskPrefix | kMaskDoc),
     // 32-key tiles for the short key loops of other variants (chosen by the host for Sk <= 2048, where they

@@ -104,13 +104,6 @@ struct Bf16Cfg {
   static constexpr int D = D_, DV = DV_, NWAVES = NWAVES_, RB = RB_, BN = BN_, MOD = MOD_, NBIAS = NBIAS_;
   static constexpr uint32_t MASK = MASK_, EPI = EPI_;
   static constexpr bool DIFF = DIFF_;
-  static constexpr bool SOFTCAP = MOD_ == kModSoftcap || MOD_ == kModSoftcapFixed;
-  // Scores bounded by the variant itself: the exponent's reference is settled with the first tile.  The kernel is bound by the
-  // vector ALU there (three transcendentals per score), and following the running maximum -- a maximum and a subtraction per
-  // score, the update per tile -- is a fifth of its instructions; the reference folds into the soft-cap's own constant.
-  // 8 x 16 heads x 1999 rows, D = 64, no mask: 241 -> 212 us.
-  static constexpr bool FIXED_REF = MOD_ == kModSoftcapFixed;
-  static_assert(!FIXED_REF || (NBIAS_ == 0 && !DIFF_), "an additive bias would leave the bound");
   // Differential + RMSNorm divides a nearly cancelling difference by its own rms, which
   // amplifies the bf16 rounding of the probabilities; there P is split into a bf16 high part
   // and a bf16 remainder and the second contraction runs on both.
@@ -210,7 +203,6 @@ struct Wave {
   uint32_t va[C::DVB];          // per-lane byte offset of the V^T fragment of channel block d (key block 0)
   bf16x8 qf[C::RB][C::KK];      // Q fragments of the wave's rows (of its own stream, differential variant)
   f32x16 oacc[C::RB][C::DVB];
-  float cap_ref[C::RB];         // FIXED_REF: cap * log2(e) less the row's reference once that is settled
   float m_run[C::RB], l_run[C::RB];                // log2-domain running max; per-lane partial sum
 
   __device__ __forceinline__ Wave(const FwdParams& p_) : p(p_) {}
@@ -318,11 +310,11 @@ struct Wave {
       return x;
     } else {
       const int j = j0 + 32 * nb + 4 * half + 8 * (r >> 2) + (r & 3);   // key of register r
-      if constexpr (C::SOFTCAP) {
+      if constexpr (C::MOD == kModSoftcap) {
         // cap*tanh(x*scale/cap) in the log2 domain; tanh(y) = 1 - 2/(exp(2y)+1)
         const float e = fast_exp2(x * (2.f * c_scale / p.softcap));
         const float cl = p.softcap * kLog2e;
-        x = fmaf(fast_rcp(e + 1.f), -2.f * cl, C::FIXED_REF ? cap_ref[rb] : cl);
+        x = fmaf(fast_rcp(e + 1.f), -2.f * cl, cl);
       } else if constexpr (C::MOD == kModAlibi) {
         // slope * |i - j| with j = (j0 + 32*nb + 4*half) + c, c the register's compile-time key
         // offset: one per-lane term per key block minus a uniform constant per register, then one FMA
@@ -524,31 +516,11 @@ struct Wave {
     }
   }
 
-  // ---- FIXED_REF: the reference of every row from the (masked) scores of its first tile, which are brought to it; a row
-  // whose first tile is all hidden gets the lowest one.
-  __device__ __forceinline__ void settle_ref(Scores& sc) {
-    float mx[C::RB];
-    rowmax(sc, mx);
-    const float cl = p.softcap * kLog2e;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      cap_ref[rb] = cl - fmaxf(mx[rb], cl - kFixedRefLog2);
-      m_run[rb] = cl - cap_ref[rb];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sc[rb][nb][r] -= m_run[rb];
-    }
-  }
-
   // ---- one probability pair: p = exp2(s - m); then running row sum and bf16 pair (and remainder)
   __device__ __forceinline__ void exp_only(float s0, float s1, float m_safe, float& p0, float& p1) const {
     if constexpr (kPlain) {
       p0 = fast_exp2(fmaf(s0, c_scale, -m_safe));
       p1 = fast_exp2(fmaf(s1, c_scale, -m_safe));
-    } else if constexpr (C::FIXED_REF) {
-      p0 = fast_exp2(s0);
-      p1 = fast_exp2(s1);
     } else {
       p0 = fast_exp2(s0 - m_safe);
       p1 = fast_exp2(s1 - m_safe);
@@ -616,7 +588,7 @@ struct Wave {
     const float x1 = transform_one(nxt[rb][nb][r + 1], j1, rb, nb, r + 1, br);
     nxt[rb][nb][r] = x0;
     nxt[rb][nb][r + 1] = x1;
-    if constexpr (!C::FIXED_REF) ps.mx[rb] = fmaxf(fmaxf(ps.mx[rb], x0), x1);
+    ps.mx[rb] = fmaxf(fmaxf(ps.mx[rb], x0), x1);
   }
 
   // hook(f) runs after the work of fragment f: the caller's tile loads.
@@ -702,11 +674,6 @@ struct Wave {
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
           for (int r = 0; r < 16; r += 2) ps.mx[rb] = fmaxf(fmaxf(ps.mx[rb], nxt[rb][nb][r]), nxt[rb][nb][r + 1]);
-    }
-    if constexpr (C::FIXED_REF) {                  // no running maximum: the row sums are all there is to carry
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) l_run[rb] += ps.psum[rb];
-      return;
     }
     // the tile's row sums are complete; fold the next tile's row maxima into the running state
     float alpha[RB];
@@ -829,7 +796,6 @@ fwd_bf16_kernel(const FwdParams call) {
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     w.m_run[rb] = -INFINITY;
-    w.cap_ref[rb] = C::FIXED_REF ? p.softcap * kLog2e : 0.f;
     w.l_run[rb] = 0.f;
 #pragma unroll
     for (int d = 0; d < DVB; ++d) w.oacc[rb][d] = W::zero16();
@@ -1257,14 +1223,9 @@ fwd_bf16_kernel(const FwdParams call) {
       w.transform(sa, tl[0] * BN, br);
       float mx[RB];
       bool full0 = wave_full(tl[0], tks[0]);
-      bool settled = full0;                        // FIXED_REF: has the first tile set the reference?  (uniform)
       if (full0) {
-        if constexpr (C::FIXED_REF) {
-          w.settle_ref(sa);
-        } else {
-          w.rowmax(sa, mx);
-          w.advance_max(mx);
-        }
+        w.rowmax(sa, mx);
+        w.advance_max(mx);
       }
       __syncthreads();                             // everyone is done with K ring slot 0
       // uniform state of the tile stream: the ragged tile (if any) and the bases of the next K and
@@ -1316,14 +1277,8 @@ fwd_bf16_kernel(const FwdParams call) {
                 for (int r = 0; r < 16; ++r) cur[rb][nb][r] = -INFINITY;
           } else {
             w.template mask<C::ID_RING + slot_vc * C::ID_BYTES>(cur, t0 * BN, tbw[0]);
-            if constexpr (!C::FIXED_REF) {
-              w.rowmax(cur, mx);
-              w.advance_max(mx);
-            }
-          }
-          if (C::FIXED_REF && !settled) {
-            w.settle_ref(cur);
-            settled = true;
+            w.rowmax(cur, mx);
+            w.advance_max(mx);
           }
         }
         if constexpr (C::NBIAS > 0) {

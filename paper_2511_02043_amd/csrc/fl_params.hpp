@@ -35,11 +35,6 @@ namespace fl {
 // Mask bits / enums mirror include/fl_attn.h (kept numerically identical; checked in fl_api.hip).
 constexpr uint32_t kMaskCausal = 1, kMaskWindow = 2, kMaskDoc = 4, kMaskPrefix = 8;
 constexpr int kModNone = 0, kModAlibi = 1, kModSoftcap = 2;
-// The soft-cap where cap * log2(e) <= kFixedRefLog2: the exponents of a row then differ by a bounded amount, so the forward
-// kernel takes the first tile's row maximum as the reference for good, raised where a later score could pass it by more than
-// 2^kFixedRefLog2 (sums of up to 2^31 such terms, of values up to 2^36, stay inside fp32's range).
-constexpr int kModSoftcapFixed = 4;
-constexpr float kFixedRefLog2 = 60.f;
 // Variants compiled at run time from user expressions (fl_compile_variant): the score_mod and the
 // mask predicate are the two functions below, defined by the generated translation unit.  The
 // library's own kernels never instantiate these values, so the functions need no definition there.
