@@ -78,6 +78,13 @@ struct F32Vec<1> {
   }
 };
 
+// 16 zero bytes to LDS, in order with this wave's reads
+__device__ __forceinline__ void f32_clear16(uint32_t addr) {
+  const F32Vec<4>::type z = {0.f, 0.f, 0.f, 0.f};
+  asm volatile("ds_write_b128 %0, %1" : : "v"(addr), "v"(z) : "memory");
+}
+static __device__ const float4 kF32Zero = {0.f, 0.f, 0.f, 0.f};
+
 // until at most N younger vector memory operations of this wave are in flight
 template <int N>
 __device__ __forceinline__ void f32_wait_mem() {
@@ -177,26 +184,52 @@ fwd_f32_kernel(const FwdParams p) {
     const float* kp = (const float*)kv.ptr + b * kv.sb + g * kv.sg + hk * kv.sh;
     const float* vp = (const float*)p.v.ptr + b * p.v.sb + g * p.v.sg + hk * p.v.sh;
     // K or V tile t of this wave's split into its buffer `buf`: the split's RG waves share the load instructions.  A chunk
-    // past the head dim is replaced by the row's first (its products are with zeros, or end in channels nobody stores), a
-    // row past Sk by the last one (its scores are masked).
+    // past the head dim is replaced by the row's first (V's end in channels nobody stores), a row past Sk by the last one (its
+    // scores are masked).
     // (The offsets inside a tile are formed again for every tile, from an opaque copy of the lane id: hoisted out of the loop
     // they would hold the registers that two waves per SIMD do not have.)
-    auto load_tile = [&](const float* head, int64_t ss, int dim, bool swizzled, int t, int lds_off) __attribute__((always_inline)) {
+    auto load_tile = [&](const float* head, int64_t ss, int dim, auto is_k, int t, int lds_off) __attribute__((always_inline)) {
+      constexpr bool kKeys = decltype(is_k)::value;   // K rows are swizzled
       const int last = p.Sk - 1 - t * kF32Keys;    // last row of the tile that exists (uniform)
       const unsigned char* base = (const unsigned char*)(head + (int64_t)(t * kF32Keys) * ss);
-      int ln = lane;
+      auto issue = [&](auto zeros) __attribute__((always_inline)) {
+        int ln = lane;
+#pragma unroll
+        for (int u = 0; u < (C::NINSTR + RG - 1) / RG; ++u) {
+          asm volatile("" : "+v"(ln));
+          const int inst = (rg + u * RG) % C::NINSTR;
+          const int row = inst * (64 / C::CH) + ln / C::CH, pos = ln % C::CH;
+          const int c = (kKeys ? pos ^ swz_f32<C::CH>(row) : pos) * 4;
+          const uint32_t off = ((uint32_t)min(row, last) * (uint32_t)ss + (uint32_t)(c < dim ? c : 0)) * 4u;
+          const unsigned char* src = base + off;
+          if (decltype(zeros)::value && c >= dim) src = (const unsigned char*)&kF32Zero;
+          __builtin_amdgcn_global_load_lds((global_cvoid*)src, (lds_void*)(lds_raw + lds_off + inst * 1024), 16, 0, 0);
+        }
+      };
+      if (kKeys && RG == 1 && dim < DMAX) issue(std::integral_constant<bool, true>());
+      else issue(std::integral_constant<bool, false>());
+    };
+    // Stand-ins that would meet a zero: K's chunks past D the zeros of Q, V's rows past Sk a weight of zero.  What they stand in
+    // for may be infinite, so each lane clears those that it loaded, once they have landed and before anyone reads them.  (One
+    // wave per split has a whole tile to clear, and reads K's from zeros instead: 2 x 8 heads of 1000 rows at D = 68 take 102
+    // us with the stand-ins as they are, 106 us read from zeros and 114 us cleared; two and more waves 1 % either way.)
+    auto clear_tile = [&](auto is_k, int t, int lds_off) __attribute__((always_inline)) {
 #pragma unroll
       for (int u = 0; u < (C::NINSTR + RG - 1) / RG; ++u) {
-        asm volatile("" : "+v"(ln));
         const int inst = (rg + u * RG) % C::NINSTR;
-        const int row = inst * (64 / C::CH) + ln / C::CH, pos = ln % C::CH;
-        const int c = (swizzled ? pos ^ swz_f32<C::CH>(row) : pos) * 4;
-        const uint32_t off = ((uint32_t)min(row, last) * (uint32_t)ss + (uint32_t)(c < dim ? c : 0)) * 4u;
-        __builtin_amdgcn_global_load_lds((global_cvoid*)(base + off), (lds_void*)(lds_raw + lds_off + inst * 1024), 16, 0, 0);
+        const int row = inst * (64 / C::CH) + lane / C::CH, pos = lane % C::CH;
+        if (decltype(is_k)::value ? (pos ^ swz_f32<C::CH>(row)) * 4 >= p.D : t * kF32Keys + row >= p.Sk)
+          f32_clear16(lds_off + inst * 1024 + lane * 16);
       }
     };
-    auto load_k = [&](int t, int buf) __attribute__((always_inline)) { load_tile(kp, kv.ss, p.D, true, t, (ks * C::NBUF + buf) * C::STAGE); };
-    auto load_v = [&](int t, int buf) __attribute__((always_inline)) { load_tile(vp, p.v.ss, p.Dv, false, t, (ks * C::NBUF + buf) * C::STAGE + C::TILE); };
+    auto clear_k = [&](int t, int buf) __attribute__((always_inline)) {
+      if (RG > 1 && p.D < DMAX) clear_tile(std::integral_constant<bool, true>(), t, (ks * C::NBUF + buf) * C::STAGE);
+    };
+    auto clear_v = [&](int t, int buf) __attribute__((always_inline)) {
+      if ((t + 1) * kF32Keys > p.Sk) clear_tile(std::integral_constant<bool, false>(), t, (ks * C::NBUF + buf) * C::STAGE + C::TILE);
+    };
+    auto load_k = [&](int t, int buf) __attribute__((always_inline)) { load_tile(kp, kv.ss, p.D, std::integral_constant<bool, true>(), t, (ks * C::NBUF + buf) * C::STAGE); };
+    auto load_v = [&](int t, int buf) __attribute__((always_inline)) { load_tile(vp, p.v.ss, p.Dv, std::integral_constant<bool, false>(), t, (ks * C::NBUF + buf) * C::STAGE + C::TILE); };
     auto wanted = [&](int t) __attribute__((always_inline)) -> bool {
       return t < t_hi && classify(t, i0, i_max, qs_wg, tile_ids(t)) != kSkip;
     };
@@ -347,6 +380,7 @@ fwd_f32_kernel(const FwdParams p) {
              [&]() __attribute__((always_inline)) {
                if (tn < t_hi) f32_wait_mem<C::NINSTR>();
                else f32_wait_mem<0>();
+               clear_v(t, 0);
              });
         if (tn < t_hi) load_v(tn, 0);
         t = tn;
@@ -359,6 +393,9 @@ fwd_f32_kernel(const FwdParams p) {
       for (int it = 0; it < n_iter; ++it) {
         const int t = t_lo + it * KS + ks;
         f32_wait_mem<0>();                         // this wave's loads of tile t have landed ...
+        clear_k(t, it & 1);
+        clear_v(t, it & 1);
+        f32_wait_lds<0>();
         __syncthreads();                           // ... and everyone's; the other buffer is free
         if (it + 1 < n_iter && wanted(t + KS)) {
           load_k(t + KS, (it + 1) & 1);
