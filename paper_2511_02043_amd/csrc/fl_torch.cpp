@@ -75,6 +75,14 @@ fl_aux aux_of(const OptTensor& slopes, const OptTensor& q_ids, const OptTensor& 
   return a;
 }
 
+// An output gradient in a layout that the kernels read: unit inner stride, 16-byte aligned rows and base, no broadcast axis
+// (autograd hands over a sum over an outer axis as one).
+Tensor readable(const Tensor& t) {
+  bool ok = t.stride(-1) == 1 && (uintptr_t)t.data_ptr() % 16 == 0;
+  for (int64_t a = 0; a + 1 < t.dim(); ++a) ok = ok && (t.size(a) == 1 || (t.stride(a) != 0 && t.stride(a) % 8 == 0));
+  return ok ? t : t.clone(at::MemoryFormat::Contiguous);
+}
+
 Tensor bytes(size_t n, const Tensor& like) { return at::empty({(int64_t)n}, like.options().dtype(at::kByte)); }
 
 // out [B, (G,) H, Sq, Dv] in q's dtype and rank, lse [B, G, H, Sq, 1]
@@ -105,9 +113,7 @@ std::tuple<int, Tensor, Tensor, Tensor> attention_bwd(const Tensor& q, const Ten
                                                       const Tensor& lse, const Tensor& dout_in, double scale, int mod, double softcap,
                                                       int mask, int window, int prefix, int q_offset, const OptTensor& slopes,
                                                       const OptTensor& q_ids, const OptTensor& kv_ids, int64_t stream) {
-  bool ok = dout_in.stride(-1) == 1;               // the kernels need unit inner stride and 16-byte aligned rows
-  for (int64_t a = 0; a + 1 < dout_in.dim(); ++a) ok = ok && dout_in.stride(a) % 8 == 0;
-  const Tensor dout = ok ? dout_in : dout_in.contiguous();
+  const Tensor dout = readable(dout_in);
   const fl_tensor tq = desc(q), tk = desc(k), tv = desc(v), tout = desc(out), tlse = desc(lse), tdo = desc(dout);
   const fl_variant_desc d = variant(scale, mod, softcap, mask, window, prefix, q_offset);
   Tensor dq = at::empty_like(q), dk = at::empty_like(k), dv = at::empty_like(v);
@@ -168,4 +174,5 @@ PYBIND11_MODULE(_fltorch, m) {
   m.def("attention_fwd", &attention_fwd);
   m.def("attention_bwd", &attention_bwd);
   m.def("paged", &paged);
+  m.def("readable", &readable);
 }

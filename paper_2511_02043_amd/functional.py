@@ -179,9 +179,7 @@ class _VariantAttention(torch.autograd.Function):
         q, k, v, q2, k2, lam, gate, bias0, bias1, rms_weight, out, lse = ctx.saved_tensors
         cfg, desc = ctx.cfg, ctx.desc
         dev = q.device
-        q5, k5, v5, d5 = _as5(q), _as5(k), _as5(v), _as5(dout)
-        if d5.stride(-1) != 1 or any(st % 8 for st in d5.stride()[:-1]):
-            d5 = d5.contiguous()
+        q5, k5, v5, d5 = _as5(q), _as5(k), _as5(v), _as5(_host().readable(dout))
         five = lambda x: None if x is None else _as5(x)
         biases = [b for b in (bias0, bias1) if b is not None]
         dq, dk, dv = torch.empty_like(q5), torch.empty_like(k5), torch.empty_like(v5)

@@ -33,6 +33,35 @@ def test_ranks_and_views_agree():
         assert torch.equal(a[:, None], b)
 
 
+def shifted(t):
+    """The same values at a base address that is 2 bytes off 16."""
+    room = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+    return room[1:].view(t.shape).copy_(t)
+
+
+GRADIENTS = {                                        # as autograd hands them over, for an output [2, 3, 65, 64]
+    "sum over the batch": lambda: normal(1, 3, 65, 64, seed=7).expand(2, 3, 65, 64),
+    "mean over the heads": lambda: normal(2, 1, 65, 64, seed=8).expand(2, 3, 65, 64),
+    "sum over the rows": lambda: normal(2, 3, 1, 64, seed=9).expand(2, 3, 65, 64),
+    "sum over the channels": lambda: normal(2, 3, 65, 1, seed=10).expand(2, 3, 65, 64),
+    "unaligned base": lambda: shifted(normal(2, 3, 65, 64, seed=11)),
+    "unaligned rows": lambda: normal(2, 3, 65, 70, seed=12)[..., :64],
+}
+
+
+@pytest.mark.parametrize("name", list(GRADIENTS))
+@pytest.mark.parametrize("entry", ["attention", "variant_attention"])
+def test_output_gradients_of_any_layout(name, entry):
+    """An output gradient that the kernels cannot read as it lies (broadcast or unaligned) gives what its dense copy gives."""
+    x = [normal(2, 3, 65, 64, seed=n).requires_grad_(True) for n in range(3)]
+    more = {} if entry == "attention" else dict(biases=[normal(1, 1, 3, 65, 65, seed=4)])
+    out = getattr(F, entry)(*x, causal=True, **more)
+    dout = GRADIENTS[name]()
+    want = torch.autograd.grad(out, x, dout.contiguous().clone(), retain_graph=True)
+    for a, b in zip(torch.autograd.grad(out, x, dout), want):
+        assert torch.equal(a, b)
+
+
 def test_refusals():
     q = normal(1, 2, 16, 64)
     with pytest.raises(KeyError):
