@@ -49,6 +49,10 @@
 #ifndef FL_USER_CLAMP
 #define FL_USER_CLAMP 1
 #endif
+// 1: the score_mod reads captured arrays with cheap arithmetic around the loads (see Wave::kLate)
+#ifndef FL_USER_LATE
+#define FL_USER_LATE 0
+#endif
 
 namespace fl {
 
@@ -553,12 +557,15 @@ struct Wave {
     float mx[C::RB];               // row maxima of the next tile so far
   };
   static constexpr int NPAIR = C::RB * C::NB * 8;  // probability pairs of a tile per lane
-  // A score_mod given as an expression that may read captured arrays: the scheduling barriers between the MFMAs would let two
+  // A score_mod given as an expression that reads captured arrays: the scheduling barriers between the MFMAs would let two
   // scores' loads out at a time and wait for each pair, and with it for the tile loads issued before (vector loads return
   // in order).  Its transform is left to the end of phase B instead, for the whole tile at once: all loads of a tile are in
-  // flight together and one wait covers them.  (Document mask and a learned distance bias, 4 x 16 heads x 4096 rows, D = 64:
-  // 214 us interleaved, 152 us this way.)
-  static constexpr bool kLate = C::MOD == kModCustom && FL_USER_CLAMP;
+  // flight together and one wait covers them.  Causal, 2 x 16 heads x 4096 rows, D = 64 / 128: a learned bias by head and
+  // clipped distance 231 / 468 us interleaved, 178 / 309 us this way; a bias whose rows scatter over many cache lines, where
+  // the rate of the loads counts and not their latency, 292 / 538 and 302 / 549.  Arithmetic wants the interleaving: without
+  // a load 0.2 * sinf(...) takes 350 / 878 us there and 690 / 1970 at the end, and sinf of a captured value 472 / 1100 and 793 /
+  // 2140.  Which of the two an expression is, the host reads from its text (loads_bound in fl_rtc.hip).
+  static constexpr bool kLate = C::MOD == kModCustom && FL_USER_LATE;
   static_assert(NB == 1 || NB == 2, "the pipeline splits a tile into at most two key blocks");
 
   // pair q in the order the second contraction needs them: (key block, k-step) major, then row block
@@ -855,9 +862,10 @@ fwd_bf16_kernel(const FwdParams call) {
   // (32-row query block, BN-key tile) -- 0 nothing visible, 1 some, 2 all -- stored [problem][tile][query block] so that
   // the blocks of a workgroup are bytes of one aligned 8-byte word.  Without a map every tile counts as "some".
   constexpr bool kMapped = (MASK & kMaskCustom) != 0;
-  constexpr bool kSkips = kMapped || (MASK & kMaskDoc) != 0;   // tiles between two visible ones may be hidden
+  static_assert(!kMapped || !C::DOC, "the base mask of an expression has no document ids");
   static_assert(!kMapped || (RB == 1 && !C::DIFF && C::NROWG <= 8), "tile-class bytes: one per wave, at most eight per workgroup");
   const bool mapped = kMapped && p.block_map != nullptr;
+  const bool gaps = C::DOC || mapped;              // tiles between two visible ones may be hidden (uniform)
   const unsigned char* mrow = nullptr;             // the word of this workgroup's query blocks in tile 0
   const uint32_t* brow_bits = nullptr;             // this lane's word of hidden-score bits in tile 0 (if the map has them)
   int map_shift = 0;
@@ -909,9 +917,25 @@ fwd_bf16_kernel(const FwdParams call) {
   int wbase = t_lo;
   int2 kwin = make_int2(0, 0);
   unsigned long long wvis = 0;                     // tiles of the window that hold something visible to the workgroup
-  uint32_t bpre = 0;                               // the lane's hidden-score bits of tile tpre (mapped expressions)
-  int tpre = -1;
-  if constexpr (kSkips) kwin = tile_keys_lane(t_lo + lane);
+  if constexpr (C::DOC || kMapped) kwin = tile_keys_lane(t_lo + lane);
+  // Mask expressions find their first tiles that way.  From then on the answer for the tile that the stream will most likely
+  // take next, and the lane's hidden-score bits of it, are fetched a whole step ahead with ordinary vector loads (every lane
+  // reads the same class bytes).  Vector memory operations complete in order and every step of these kernels ends with a wait
+  // for all of this wave's loads, so the answer has arrived by the time it is needed, without a wait of its own.  On dense
+  // lists the window's scalar work in every step costs more than that: hidden where j > i && j > 200, 2 x 16 heads x 4096 rows,
+  // D = 64 / 128, 176 / 257 us with the window throughout, 157 / 236 this way; with the expression evaluated by the kernel
+  // itself, without a map, 409 / 475 and 398 / 460.
+  int2 kpre = make_int2(0, 0);                     // what those loads return
+  uint32_t bpre = 0;
+  int tpre = -1;                                   // the tile they belong to (uniform)
+  auto prefetch_keys = [&](int t) __attribute__((always_inline)) {
+    tpre = t;
+    kpre = tile_keys_lane(t);
+    bpre = tile_bits_lane(t);
+  };
+  auto uniform = [](int2 ks) __attribute__((always_inline)) -> int2 {
+    return make_int2(__builtin_amdgcn_readfirstlane(ks.x), __builtin_amdgcn_readfirstlane(ks.y));
+  };
   if constexpr ((MASK & kMaskDoc) != 0) {
     qs_wg = qraw_wg[0];
 #pragma unroll
@@ -935,13 +959,13 @@ fwd_bf16_kernel(const FwdParams call) {
     const int tt = wbase + w.lane;
     wvis = __builtin_amdgcn_ballot_w64(tt < t_hi && !tile_hidden(tt, kwin));
   };
-  if constexpr (kSkips) scan_window();
+  if constexpr (C::DOC || kMapped) scan_window();
   // First tile at or after t with something visible to the workgroup (t_hi if none), and what the skipper knows about it.
-  // (setup: called while the first tile list is built; there the bits of each tile are requested and not waited for)
+  // (setup: called while the first tile list is built)
   auto next_tile = [&](int t, int2& ks, uint32_t& bw, auto setup) __attribute__((always_inline)) -> int {   // uniform over the workgroup
     ks = make_int2(0, 0);
     bw = 0;
-    if constexpr (kSkips) {
+    if constexpr (C::DOC || (kMapped && decltype(setup)::value)) {
       while (t < t_hi) {
         if (t >= wbase + 64) {                     // the next 64 tiles
           wbase = t;
@@ -954,19 +978,37 @@ fwd_bf16_kernel(const FwdParams call) {
           ks.x = __builtin_amdgcn_readlane(kwin.x, t - wbase);
           ks.y = __builtin_amdgcn_readlane(kwin.y, t - wbase);
           if constexpr (kMapped) {
-            // The bits of the tile after this one are fetched a whole step ahead.  Vector memory operations complete in
-            // order and every step of these kernels ends with a wait for all of this wave's loads, so they have arrived
-            // by the time they are needed, without a wait of their own.
-            bw = !decltype(setup)::value && t == tpre ? bpre : tile_bits_lane(t);
-            if constexpr (!decltype(setup)::value) {
-              const unsigned long long later = rest >> __builtin_ctzll(rest) >> 1;
-              tpre = t + 1 + (later != 0 ? __builtin_ctzll(later) : 0);
-              bpre = tile_bits_lane(tpre);
-            }
+            bw = tile_bits_lane(t);
+            prefetch_keys(t + 1);
           }
           return t;
         }
         t = min(wbase + 64, t_hi);
+      }
+    } else if constexpr (kMapped) {
+      if (t < t_hi) {
+        bw = t == tpre ? bpre : tile_bits_lane(t);
+        ks = t == tpre ? uniform(kpre) : uniform(tile_keys_lane(t));   // (made uniform on either side of the choice)
+        // the usual case first: tile t itself has something visible (one uniform check)
+        if (tile_hidden(t, ks)) {
+          // a run of hidden tiles: 64 per round, one per lane
+          ++t;
+          while (t < t_hi) {
+            const int tt = t + w.lane;
+            const unsigned long long found = __builtin_amdgcn_ballot_w64(tt < t_hi && !tile_hidden(tt, tile_keys_lane(tt)));
+            if (found != 0) {
+              t += __builtin_ctzll(found);
+              break;
+            }
+            t += 64;
+          }
+          t = __builtin_amdgcn_readfirstlane(t < t_hi ? t : t_hi);
+          if (t < t_hi) {
+            ks = uniform(tile_keys_lane(t));
+            bw = tile_bits_lane(t);
+          }
+        }
+        if (t < t_hi) prefetch_keys(t + 1);
       }
     }
     return t;                                      // positional masks are already in [t_lo, t_hi)
@@ -1289,7 +1331,7 @@ fwd_bf16_kernel(const FwdParams call) {
           if (tl[2] < t_hi) w.template bias_dma<N % 2>(tl[2] * BN);
         }
         const int tk = tl[SPB + 1] < t_hi ? tl[SPB + 1] : t_hi - 1, tv = tl[SPB] < t_hi ? tl[SPB] : t_hi - 1;
-        if constexpr (kSkips) {                    // no fixed stride between the tiles of the list
+        if (gaps) {                                // no fixed stride between the tiles of the list
 #pragma unroll
           for (int s = 0; s < NS; ++s) kb[s] = k_tile_base(s, tk);
           vb = v_tile_base(tv);
@@ -1335,7 +1377,7 @@ fwd_bf16_kernel(const FwdParams call) {
         }
         tl[NTL - 1] = after(tl[NTL - 1], tks[NTL - 1], tbw[NTL - 1], std::integral_constant<bool, false>());
         full0 = fulln;
-        if constexpr (!kSkips) {                   // consecutive tiles: advance the bases until the list ends
+        if (!gaps) {                               // consecutive tiles: advance the bases until the list ends
           if (tl[SPB] < t_hi) vb += vstep;
 #pragma unroll
           for (int s = 0; s < NS; ++s)

@@ -61,6 +61,33 @@ bool mentions(const char* e, const char* name) {
   return false;
 }
 
+// Is the time of a score_mod that of its loads from captured arrays?  It reads at least one, and every function it calls is a
+// few instructions without a branch; anything else keeps its arithmetic between the matrix instructions (Wave::kLate has
+// the times of both).
+bool loads_bound(const char* e) {
+  bool reads = false;
+  for (const char* a : {"aux0", "aux1", "aux2", "aux3"}) reads = reads || mentions(e, a);
+  if (!reads) return false;
+  auto word = [](char c) { return (c >= 'a' && c <= 'z') || (c >= 'A' && c <= 'Z') || (c >= '0' && c <= '9') || c == '_'; };
+  static const char* const cheap[] = {"abs", "fabsf", "min", "max", "fminf", "fmaxf", "fmaf", "tanhf", "__expf", "float", "int"};
+  for (const char* c = e; *c;) {
+    if (!word(*c)) {
+      ++c;
+      continue;
+    }
+    const char* start = c;
+    while (word(*c)) ++c;
+    const std::string name(start, c);
+    const char* after = c;
+    while (*after == ' ') ++after;
+    if (*after != '(') continue;
+    bool ok = false;
+    for (const char* f : cheap) ok = ok || name == f;
+    if (!ok) return false;
+  }
+  return true;
+}
+
 bool expression_ok(const char* e) {
   // one C expression: no statement separators, braces, preprocessor lines or string literals
   for (const char* c = e; *c; ++c)
@@ -72,7 +99,8 @@ bool expression_ok(const char* e) {
 // Compiles `src` (which instantiates the kernels named by the expressions `insts`) for gfx950 with the
 // library's own flags; returns the code object and the lowered kernel names.  batch_loads: schedule for instruction-level
 // parallelism.  The default strategy keeps source order where scalar registers run short, which these kernels' do: of the
-// loads that an expression does for the 32 scores of a lane it then waits for each before the next one.
+// loads that an expression does for the 32 scores of a lane it then waits for each before the next one.  For score_mods bound by
+// such loads only: a mask expression that reads ids takes 720 us that way and 657 with the default (2 x 16 heads x 4096, D = 64).
 fl_status compile_program(const std::string& src, const std::vector<std::string>& insts, const char* what,
                           std::vector<char>* code, std::vector<std::string>* kernel_names, bool batch_loads = false) {
   static std::mutex mu;                            // the compiler's own options are global while it runs: one compilation at a time
@@ -380,7 +408,8 @@ fl_status fl_compile_variant_grad(const char* score_mod_expr, const char* score_
   if (mask_expr) v->mask_expr = mask_expr;
   bool captures = false;
   for (int n = 0; n < 4; ++n) captures = captures || adt[n] != 0;
-  std::string src = std::string("#define FL_USER_CLAMP ") + (captures ? "1" : "0") + "\n#include \"fl_kernel_bf16.hpp\"\n" + hook_source(v, false);
+  const bool late = score_mod_expr != nullptr && loads_bound(score_mod_expr);
+  std::string src = std::string("#define FL_USER_CLAMP ") + (captures ? "1" : "0") + "\n#define FL_USER_LATE " + (late ? "1" : "0") + "\n#include \"fl_kernel_bf16.hpp\"\n" + hook_source(v, false);
   src += "template __global__ void ";
   src += inst;
   src += "(const fl::FwdParams);\n";
@@ -393,7 +422,7 @@ fl_status fl_compile_variant_grad(const char* score_mod_expr, const char* score_
   }
 
   std::vector<std::string> names;
-  fl_status st = compile_program(src, insts, "expression does not compile", &v->code, &names, captures);
+  fl_status st = compile_program(src, insts, "expression does not compile", &v->code, &names, late);
   // a derivative expression is given by callers who want the backward pass: its kernels are compiled now, so that an
   // error in that expression is reported here
   if (st == FL_OK && score_mod_grad_expr != nullptr) st = compile_backward(v);

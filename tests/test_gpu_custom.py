@@ -261,3 +261,30 @@ def test_tile_skipping_with_hidden_tiles_between_visible_ones(D):
     assert float(np.max(np.abs(skip[0] - ref))) <= 1e-2
     assert float(np.max(np.abs(skip[1] - ref_lse))) <= 1e-3
     var.release()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("c_mod,np_mod", [
+    ("s * 0.5f", lambda s, t, h, i, j: s * 0.5),                                                     # reads no array
+    ("s + 0.2f * sinf(0.01f * (float)(i - j))", lambda s, t, h, i, j: s + 0.2 * np.sin(0.01 * (i - j))),
+    ("s + 0.2f * sinf((float)aux2[h * 64 + (j & 63)])", lambda s, t, h, i, j: s + 0.2 * np.sin(t[h][j & 63])),
+    ("s + fmaxf((float)aux2[h * 64 + (j & 63)], 0.f)", lambda s, t, h, i, j: s + np.maximum(t[h][j & 63], 0.0)),
+    (None, None)], ids=["arithmetic", "sine", "sine_of_a_load", "load", "mask_only"])
+def test_transforms_of_every_schedule(D, c_mod, np_mod):
+    """A score_mod is transformed between the matrix instructions or a tile at a time, as its text says, under a mask that reads
+    arrays, with and without the pre-pass over the tiles; key counts up to the end of a tile and past 64 tiles."""
+    import torch
+    for Sq, Sk in ((70, 64), (40, 4200)):
+        w = inputs.causal_bf16(B=1, H=2, S=Sq, Sk=Sk, D=D, causal=False, salt=15)
+        table = inputs.normal((2, 64), inputs.tensor_seed(9, 8), "bf16")
+        kinds = (np.arange(Sk) // 300 % 3).astype(np.int32)[None]                  # long runs of hidden keys between visible ones
+        t_table = torch.from_numpy(table.astype(np.float32)).to("cuda:0", torch.bfloat16)
+        t_kinds = torch.from_numpy(kinds).to("cuda:0")
+        var = fb.CustomVariant(c_mod, "aux0[j] == 1", D, aux=[t_kinds, None, t_table])
+        dw = runner.upload(w, out_dtype="f32")
+        (plain, skip), _ = run_both_ways(var, dw, float(w.scale))
+        assert np.array_equal(plain[0], skip[0]) and np.array_equal(plain[1], skip[1])
+        mod = None if np_mod is None else lambda s, b, g, h, i, j: np_mod(s, table.astype(np.float64), h, i, j)
+        ref, ref_lse = ao.attention_custom(w.q, w.k, w.v, scale=w.scale, score_mod=mod, mask=lambda b, g, h, i, j: (kinds[0][j] == 1) & (i >= 0))
+        assert float(np.max(np.abs(skip[0] - ref))) <= 1e-2 and float(np.max(np.abs(skip[1] - ref_lse))) <= 1e-3
+        var.release()
