@@ -78,6 +78,28 @@ def test_backward_ex_matches_oracle(name):
     compare(CASES[name](), "f32", label=name)
 
 
+@pytest.mark.parametrize("B,G,S", [(1200, 1, 1), (70, 1, 33), (9, 5, 64), (3, 2, 511), (2, 1, 513), (1, 1, 1500)])
+def test_dlambda_of_short_and_long_rows(B, G, S):
+    """The sum of a head's dlambda over many short rows, and on both sides of the length from which a row fills the workgroup.
+    Values and output gradients are positive, so that no terms cancel: a row's term is off by the 2^-9 of its rounded
+    probabilities at most, with a random sign, and the sum over n rows by 2^-9 / sqrt(n) of itself (four times that allowed);
+    a row left out or counted twice changes it by 1 / n."""
+    import torch
+    w = C(D=64, pos_mask="causal", diff=True, B=B, G=G, H=2, S=S)
+    w.v = np.abs(w.v) + np.float32(0.5)
+    w.v = inputs.round_to_bf16(w.v)
+    dout = inputs.round_to_bf16(np.abs(inputs.dout_for(w)) + np.float32(0.5))
+    db = runner.upload_backward_ex(w, dout)
+    db.fwd.run_checked()
+    db.grads["dlambda"].fill_(float("nan"))
+    db.run_checked()
+    torch.cuda.synchronize()
+    ref = bo.variant_backward(w, dout)["dlambda"]
+    rel = np.abs(db.grads["dlambda"].cpu().numpy().astype(np.float64) - ref) / np.abs(ref)
+    print(f"dlambda {B}x{G}x{S}: {rel}", flush=True)
+    assert np.all(rel <= 4 * 2.0 ** -9 / np.sqrt(B * G * S))
+
+
 def test_bf16_gradient_outputs():
     compare(C(D=64, pos_mask="causal", n_bias=1, gate=True, S=200), "bf16", label="bias_gate_bf16_grads")
     compare(inputs.differential_bf16(B=1, H=2, S=200), "bf16", label="diff_rms_bf16_grads")
