@@ -209,7 +209,8 @@ typedef struct {
   fl_tensor dq2, dk2;      /* FL_DIFFERENTIAL: gradients of aux->q2 / aux->k2; shapes and dtypes as dq / dk; required */
   fl_tensor dbias[2];      /* gradient of aux->bias[n]: f32 with the sizes of aux->bias[n] (an axis of size 1 that
                               broadcasts holds the sum over that axis); ptr NULL: not computed.  The workspace then
-                              holds dS of every score in bf16 (2 bytes each, Sq and Sk rounded up to 32) until it is summed  */
+                              holds dS of every score in bf16 (2 bytes each; Sk, and an Sq above 32, rounded up to 32)
+                              until it is summed  */
   fl_tensor dgate;         /* FL_EPI_GATE_SIGMOID: gradient of aux->gate, shape of out, bf16 or f32; ptr NULL: not computed */
   float*    dlambda;       /* FL_DIFFERENTIAL: [H] f32 device; NULL: not computed                              */
   float*    drms_weight;   /* FL_EPI_RMSNORM: gradient of aux->rms_weight (of the implied all-ones weight when that is

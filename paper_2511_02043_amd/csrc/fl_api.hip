@@ -717,7 +717,7 @@ __global__ void __launch_bounds__(1024) reduce_dlambda_kernel(const float* dl_ro
   if (threadIdx.x == 0) dlambda[h] = part[0];
 }
 
-// Gradient of one bias from the staged dS (32 x 32 blocks, see fl::kDsBlock): the sum over the axes the bias broadcasts along
+// Gradient of one bias from the staged dS (32 x 32 blocks, see fl::ds_block): the sum over the axes the bias broadcasts along
 // (its size-1 axes).  An output block is a sum of staged blocks, register by register; sums along the queries or the keys
 // inside the block follow at the end.  SPLIT: a workgroup per output block, whose four waves take a quarter of the terms each
 // and meet in LDS in a fixed order (enough waves in flight also where few blocks remain); otherwise a wave per output block.
@@ -728,6 +728,7 @@ struct DbiasParams {
   const uint16_t* ds;
   fl::BiasView out;
   int B, G, H, Sq, Sk, nqb, nkb;
+  int rows;                         // query rows kept of a staged block, see fl::ds_rows
   int ob, og, oh, oi, oj;           // sizes of the bias's axes
   int64_t units;                    // output blocks
   int accumulate;                   // the second softmax stream adds to the first one's sum
@@ -745,6 +746,9 @@ __global__ void __launch_bounds__(256) reduce_dbias_kernel(const DbiasParams d) 
   const int ni = d.oi == 1 ? d.nqb : 1, nj = d.oj == 1 ? d.nkb : 1;
   const int64_t n_terms = (int64_t)nb * ng * nh * ni * nj;
   const int64_t n_lo = SPLIT ? n_terms * wave / 4 : 0, n_hi = SPLIT ? n_terms * (wave + 1) / 4 : n_terms;
+  // (a lane whose row is not kept reads the last one's values: its own are not summed or stored)
+  const int half = lane >> 5, col = lane & 31;
+  const int slot = half * d.rows + min(col, d.rows - 1);
   // term n in the nesting order b, g, h, i, j, kept as running indices
   int64_t rest = n_lo;
   int jj = (int)(rest % nj);
@@ -769,7 +773,7 @@ __global__ void __launch_bounds__(256) reduce_dbias_kernel(const DbiasParams d) 
         }
       }
     }
-    return (const uint4*)(d.ds + blk * fl::kDsBlock) + lane;
+    return (const uint4*)(d.ds + blk * (32 * d.rows)) + slot;
   };
   float s[16];
 #pragma unroll
@@ -789,7 +793,7 @@ __global__ void __launch_bounds__(256) reduce_dbias_kernel(const DbiasParams d) 
     for (int u = 0; u < 4; ++u) {
       const uint4* src = next_block();
       v[2 * u] = src[0];
-      v[2 * u + 1] = src[64];
+      v[2 * u + 1] = src[2 * d.rows];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -799,7 +803,7 @@ __global__ void __launch_bounds__(256) reduce_dbias_kernel(const DbiasParams d) 
   }
   for (; n < n_hi; ++n) {
     const uint4* src = next_block();
-    const uint4 v0 = src[0], v1 = src[64];
+    const uint4 v0 = src[0], v1 = src[2 * d.rows];
     add(v0, 0);
     add(v1, 8);
   }
@@ -813,12 +817,13 @@ __global__ void __launch_bounds__(256) reduce_dbias_kernel(const DbiasParams d) 
 #pragma unroll
     for (int r = 0; r < 16; ++r) s[r] = ((s[r] + part[0][r][lane]) + part[1][r][lane]) + part[2][r][lane];
   }
-  const int half = lane >> 5, col = lane & 31;
   if (d.oi == 1)                                   // over the block's 32 query rows
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
+    for (int r = 0; r < 16; ++r) {
+      if (col >= d.rows) s[r] = 0.f;
 #pragma unroll
       for (int o = 16; o >= 1; o >>= 1) s[r] += __shfl_xor(s[r], o);
+    }
   if (d.oj == 1) {                                 // over its 32 keys
 #pragma unroll
     for (int r = 1; r < 16; ++r) s[0] += s[r];
@@ -1001,7 +1006,7 @@ ExLayout ex_layout(int64_t B, int64_t G, int64_t H, int64_t Hkv, int64_t Sq, int
   L.off_part = take(L.part_k + L.part_v);
   L.off_dl = take(L.ns == 2 ? L.stat : 0);
   // bias gradients: dS of every score (bf16), reduced over the broadcast axes afterwards
-  L.ds = d->n_bias > 0 ? up256((size_t)(B * G * H) * ((Sq + 31) / 32) * ((Sk + 31) / 32) * fl::kDsBlock * 2) : 0;
+  L.ds = d->n_bias > 0 ? up256((size_t)(B * G * H) * ((Sq + 31) / 32) * ((Sk + 31) / 32) * fl::ds_block(Sq) * 2) : 0;
   L.off_ds = take(L.ds);
   // rms_weight gradient: one partial sum per workgroup (four rows) of the epilogue-derivative kernel
   L.off_dw = take((d->epilogue & FL_EPI_RMSNORM) != 0 ? up256(((rq + 3) / 4) * (size_t)Dv * 4) : 0);
@@ -1824,6 +1829,7 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
         dp.ds = p.ds_stage;
         dp.out = dbias[nb];
         dp.B = (int)B; dp.G = (int)G; dp.H = (int)H; dp.Sq = (int)Sq; dp.Sk = (int)Sk;
+        dp.rows = fl::ds_rows(Sq);
         dp.nqb = (int)((Sq + 31) / 32);
         dp.nkb = (int)((Sk + 31) / 32);
         dp.ob = (int)gz[0]; dp.og = (int)gz[1]; dp.oh = (int)gz[2]; dp.oi = (int)gz[3]; dp.oj = (int)gz[4];

@@ -62,7 +62,7 @@ struct BwdParams {
   int32_t q_off;                   // query row i sits at sequence position i + q_off (positional masks, ALiBi); >= 0
   const void* user_aux[4];         // run-time compiled variants: the caller's device arrays that the expressions read
   // Bias gradients wanted: dS of every score in bf16, as the 32 x 32 blocks in which the dQ kernel holds it,
-  // [B, G, H, ceil(Sq / 32), ceil(Sk / 32)][kDsBlock]; the host sums it afterwards over the axes each bias broadcasts along
+  // [B, G, H, ceil(Sq / 32), ceil(Sk / 32)][ds_block(Sq)]; the host sums it afterwards over the axes each bias broadcasts along
   // (null: not wanted).
   uint16_t* ds_stage;
 };
@@ -71,7 +71,9 @@ struct BwdParams {
 // key 8 * (r / 4) + 4 * (L / 32) + r % 4 of the block), so that every store and load is 16 bytes per lane and 1 KiB
 // contiguous per wave.  In the row-major order [Sq, Sk] a lane's four consecutive keys were an 8-byte store of their own:
 // the dQ kernel of the Evoformer rows (128 x 8 heads x 384, D = 32) took 200 us that way, 143 us this way.
-constexpr int kDsBlock = 1024;
+// A call of fewer than 32 query rows keeps only the lanes of rows that exist: a block is [2][2 halves][rows][8].
+__host__ __device__ inline int ds_rows(int64_t Sq) { return Sq < 32 ? (int)Sq : 32; }
+__host__ __device__ inline int ds_block(int64_t Sq) { return 32 * ds_rows(Sq); }
 
 // chunk swizzle of a tile row (see the header comment): an XOR on the 16-byte chunk index that
 // depends on row % 16 only.
@@ -766,12 +768,13 @@ bwd_dq_kernel(const BwdParams p) {
       }
       if constexpr (C::NBIAS > 0) {                // staged for the host's reduction over the axes each bias broadcasts along
         auto staged = [&](int n) __attribute__((always_inline)) { return kSplit ? dbw[n] : dsw[n]; };
-        if (p.ds_stage != nullptr && iw < p.Sq) {    // (rows past Sq and keys past Sk inside the block are zeros)
+        const int rows = ds_rows(p.Sq);
+        if (p.ds_stage != nullptr && iw < p.Sq && w.col < rows) {    // (rows past Sq and keys past Sk inside the block are zeros)
           const int nqb = (p.Sq + 31) / 32, nkb = (p.Sk + 31) / 32;
-          const int64_t blk = ((((int64_t)(b * p.G + g) * p.H + h) * nqb + iw / 32) * nkb + (j0 / 32 + nb)) * kDsBlock;
+          const int64_t blk = ((((int64_t)(b * p.G + g) * p.H + h) * nqb + iw / 32) * nkb + (j0 / 32 + nb)) * (32 * rows);
 #pragma unroll
           for (int u = 0; u < 2; ++u)
-            *(uint4*)(p.ds_stage + blk + u * 512 + lane * 8) = make_uint4(staged(4 * u), staged(4 * u + 1), staged(4 * u + 2), staged(4 * u + 3));
+            *(uint4*)(p.ds_stage + blk + ((2 * u + w.half) * rows + w.col) * 8) = make_uint4(staged(4 * u), staged(4 * u + 1), staged(4 * u + 2), staged(4 * u + 3));
         }
       }
       w.template tr_stream<ST + nb * 32 * ROW>([&](auto fc, bf16x8 a) __attribute__((always_inline)) {

@@ -3,6 +3,9 @@ import ctypes
 import os
 import re
 
+import pytest
+import torch
+
 from paper_2511_02043_amd import binding as fb
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -242,3 +245,16 @@ def test_noalloc_entry_point_rejects_sizes_beyond_its_built_in_buffer():
     assert fb.fl_attn_fwd_noalloc(t, t, t, d, fb.aux_desc(), t, None) == fb.FL_ERR_WORKSPACE
     assert "scratch" in fb.fl_last_error_detail()
     assert fb.fl_attn_fwd_noalloc(t, t, t, None, None, t, None) == fb.FL_ERR_NULL
+
+
+@pytest.mark.parametrize("Sq", [1, 7, 32, 33, 64])
+def test_bias_gradient_workspace_follows_the_query_rows(Sq):
+    """The backward workspace holds dS in bf16 for the call's query rows (from 32 on: rounded up to 32) and its keys rounded up
+    to 32, on top of what the call needs without a bias."""
+    B, H, Sk, D = 2, 3, 1000, 64
+    q, k = torch.zeros(B, 1, H, Sq, D, dtype=torch.bfloat16), torch.zeros(B, 1, H, Sk, D, dtype=torch.bfloat16)
+    size = lambda n: fb.fl_attn_bwd_ex_workspace_size(fb.tensor_desc(q), fb.tensor_desc(k), fb.tensor_desc(k),
+                                                      fb.variant_desc(scale=0.1, n_bias=n, epilogue=fb.FL_EPI_GATE_SIGMOID))
+    rows = Sq if Sq < 32 else (Sq + 31) // 32 * 32
+    staged = B * H * rows * 1024 * 2
+    assert staged <= size(1) - size(0) < staged + 256

@@ -10,7 +10,7 @@ from oracle import attention_backward_oracle as bo
 from oracle import attention_oracle as ao
 from paper_2511_02043_amd import binding as fb
 from paper_2511_02043_amd import inputs, runner
-from tests.test_gpu_backward_ex import compare
+from tests.test_gpu_backward_ex import REL_L2, compare
 
 pytestmark = pytest.mark.gpu
 
@@ -55,6 +55,27 @@ def test_bias_gradient_axes(shape):
     """Bias gradients summed over every kind of axis (batch, rows, heads, queries), at sizes that no 32 x 32 block divides:
     sums of few and of many staged blocks, along the lanes of a block and across blocks."""
     compare(bias_workload(shape), "f32", label=f"bias_{shape}")
+
+
+@pytest.mark.parametrize("S", [1, 5, 31, 32])
+@pytest.mark.parametrize("variant", [dict(D=32), dict(D=64), dict(D=64, pos_mask="prefix")], ids=["d32", "d64", "d64_prefix"])
+def test_bias_gradients_of_few_query_rows(S, variant):
+    """Staged blocks of as many rows as the call has: a bias per query and key, and one that is summed over the queries; under a
+    mask (every row sees the 45 keys of the prefix) with the blocks cleared first."""
+    w = C(S=S, Sk=70, n_bias=2, G=2, **variant)
+    dout = inputs.dout_for(w)
+    db = runner.upload_backward_ex(w, dout, grad_dtype="f32")
+    db.fwd.run_checked()
+    for t in db.grads["dbias"]:
+        t.fill_(float("nan"))
+    db.run_checked()
+    for t, r in zip(db.grads["dbias"], bo.variant_backward(w, dout)["dbias"]):
+        # relative L2 as for fl_attn_bwd_ex; no bound per element, since the rounding of one row's few terms does not average
+        # out (see above)
+        got = t.cpu().numpy().astype(np.float64)
+        rel = float(np.sqrt(np.sum((got - r) ** 2) / np.sum(r * r)))
+        print(f"bias2_{S}x70: rel_l2={rel:.3e}", flush=True)
+        assert got.shape == r.shape and rel <= REL_L2
 
 
 @pytest.mark.parametrize("shape", [(2, 2, 4, 1, 1), (1, 1, 4, 100, 1), (1, 1, 1, 1, 1)])
