@@ -28,7 +28,11 @@ def _host():
     global _host_module
     if _host_module is None:
         fb.lib()
-        from . import _fltorch
+        try:
+            from . import _fltorch
+        except ImportError as e:
+            raise ImportError("_fltorch.so is missing or was built for another interpreter or torch: run "
+                              "make -C paper_2511_02043_amd/csrc PYTHON=<this interpreter>") from e
         _host_module = _fltorch
     return _host_module
 
