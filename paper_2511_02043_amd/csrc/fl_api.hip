@@ -728,14 +728,14 @@ struct DbiasParams {
   const uint16_t* ds;
   fl::BiasView out;
   int B, G, H, Sq, Sk, nqb, nkb;
-  int rows;                         // query rows kept of a staged block, see fl::ds_rows
   int ob, og, oh, oi, oj;           // sizes of the bias's axes
   int64_t units;                    // output blocks
   int accumulate;                   // the second softmax stream adds to the first one's sum
 };
 
-template <bool SPLIT>
+template <bool SPLIT, bool FEW>    // FEW: fewer than 32 query rows
 __global__ void __launch_bounds__(256) reduce_dbias_kernel(const DbiasParams d) {
+  const int rows = FEW ? d.Sq : 32;                // query rows kept of a staged block, see fl::ds_rows
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t unit = SPLIT ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
   if (unit >= d.units) return;                     // (uniform over the workgroup where it has a barrier)
@@ -748,7 +748,7 @@ __global__ void __launch_bounds__(256) reduce_dbias_kernel(const DbiasParams d) 
   const int64_t n_lo = SPLIT ? n_terms * wave / 4 : 0, n_hi = SPLIT ? n_terms * (wave + 1) / 4 : n_terms;
   // (a lane whose row is not kept reads the last one's values: its own are not summed or stored)
   const int half = lane >> 5, col = lane & 31;
-  const int slot = half * d.rows + min(col, d.rows - 1);
+  const int slot = FEW ? half * rows + min(col, rows - 1) : lane;
   // term n in the nesting order b, g, h, i, j, kept as running indices
   int64_t rest = n_lo;
   int jj = (int)(rest % nj);
@@ -773,7 +773,7 @@ __global__ void __launch_bounds__(256) reduce_dbias_kernel(const DbiasParams d) 
         }
       }
     }
-    return (const uint4*)(d.ds + blk * (32 * d.rows)) + slot;
+    return (const uint4*)(d.ds + blk * (32 * rows)) + slot;
   };
   float s[16];
 #pragma unroll
@@ -793,7 +793,7 @@ __global__ void __launch_bounds__(256) reduce_dbias_kernel(const DbiasParams d) 
     for (int u = 0; u < 4; ++u) {
       const uint4* src = next_block();
       v[2 * u] = src[0];
-      v[2 * u + 1] = src[2 * d.rows];
+      v[2 * u + 1] = src[2 * rows];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -803,7 +803,7 @@ __global__ void __launch_bounds__(256) reduce_dbias_kernel(const DbiasParams d) 
   }
   for (; n < n_hi; ++n) {
     const uint4* src = next_block();
-    const uint4 v0 = src[0], v1 = src[2 * d.rows];
+    const uint4 v0 = src[0], v1 = src[2 * rows];
     add(v0, 0);
     add(v1, 8);
   }
@@ -820,7 +820,7 @@ __global__ void __launch_bounds__(256) reduce_dbias_kernel(const DbiasParams d) 
   if (d.oi == 1)                                   // over the block's 32 query rows
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      if (col >= d.rows) s[r] = 0.f;
+      if (col >= rows) s[r] = 0.f;
 #pragma unroll
       for (int o = 16; o >= 1; o >>= 1) s[r] += __shfl_xor(s[r], o);
     }
@@ -1829,17 +1829,18 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
         dp.ds = p.ds_stage;
         dp.out = dbias[nb];
         dp.B = (int)B; dp.G = (int)G; dp.H = (int)H; dp.Sq = (int)Sq; dp.Sk = (int)Sk;
-        dp.rows = fl::ds_rows(Sq);
         dp.nqb = (int)((Sq + 31) / 32);
         dp.nkb = (int)((Sk + 31) / 32);
         dp.ob = (int)gz[0]; dp.og = (int)gz[1]; dp.oh = (int)gz[2]; dp.oi = (int)gz[3]; dp.oj = (int)gz[4];
         dp.units = gz[0] * gz[1] * gz[2] * (gz[3] == 1 ? 1 : dp.nqb) * (gz[4] == 1 ? 1 : dp.nkb);
         dp.accumulate = s;
         const int64_t terms = B * G * H * dp.nqb * dp.nkb / dp.units;
-        if (terms >= 16)
-          hipLaunchKernelGGL(reduce_dbias_kernel<true>, dim3((unsigned)dp.units), dim3(256), 0, stream, dp);
-        else
-          hipLaunchKernelGGL(reduce_dbias_kernel<false>, dim3((unsigned)((dp.units + 3) / 4)), dim3(256), 0, stream, dp);
+        const bool split = terms >= 16, few = Sq < 32;
+        const dim3 grid((unsigned)(split ? dp.units : (dp.units + 3) / 4));
+        if (split && few) hipLaunchKernelGGL((reduce_dbias_kernel<true, true>), grid, dim3(256), 0, stream, dp);
+        else if (split) hipLaunchKernelGGL((reduce_dbias_kernel<true, false>), grid, dim3(256), 0, stream, dp);
+        else if (few) hipLaunchKernelGGL((reduce_dbias_kernel<false, true>), grid, dim3(256), 0, stream, dp);
+        else hipLaunchKernelGGL((reduce_dbias_kernel<false, false>), grid, dim3(256), 0, stream, dp);
       }
     if ((e = run_bwd_dkdv(be, p, (int)nb_k, stream)) != hipSuccess) return fail(FL_ERR_LAUNCH, "dk/dv launch: %s", hipGetErrorString(e));
     if (p.hsplit > 1) {

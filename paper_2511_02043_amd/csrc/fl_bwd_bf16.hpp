@@ -768,13 +768,19 @@ bwd_dq_kernel(const BwdParams p) {
       }
       if constexpr (C::NBIAS > 0) {                // staged for the host's reduction over the axes each bias broadcasts along
         auto staged = [&](int n) __attribute__((always_inline)) { return kSplit ? dbw[n] : dsw[n]; };
-        const int rows = ds_rows(p.Sq);
-        if (p.ds_stage != nullptr && iw < p.Sq && w.col < rows) {    // (rows past Sq and keys past Sk inside the block are zeros)
+        if (p.ds_stage != nullptr && iw < p.Sq) {    // (rows past Sq and keys past Sk inside the block are zeros)
           const int nqb = (p.Sq + 31) / 32, nkb = (p.Sk + 31) / 32;
-          const int64_t blk = ((((int64_t)(b * p.G + g) * p.H + h) * nqb + iw / 32) * nkb + (j0 / 32 + nb)) * (32 * rows);
+          const int64_t blk = (((int64_t)(b * p.G + g) * p.H + h) * nqb + iw / 32) * nkb + (j0 / 32 + nb);
+          if (p.Sq >= 32) {                        // uniform; whole blocks, with nothing to work out per lane
 #pragma unroll
-          for (int u = 0; u < 2; ++u)
-            *(uint4*)(p.ds_stage + blk + ((2 * u + w.half) * rows + w.col) * 8) = make_uint4(staged(4 * u), staged(4 * u + 1), staged(4 * u + 2), staged(4 * u + 3));
+            for (int u = 0; u < 2; ++u)
+              *(uint4*)(p.ds_stage + blk * 1024 + u * 512 + lane * 8) = make_uint4(staged(4 * u), staged(4 * u + 1), staged(4 * u + 2), staged(4 * u + 3));
+          } else if (w.col < p.Sq) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+              *(uint4*)(p.ds_stage + blk * ds_block(p.Sq) + ((2 * u + w.half) * p.Sq + w.col) * 8) =
+                  make_uint4(staged(4 * u), staged(4 * u + 1), staged(4 * u + 2), staged(4 * u + 3));
+          }
         }
       }
       w.template tr_stream<ST + nb * 32 * ROW>([&](auto fc, bf16x8 a) __attribute__((always_inline)) {
