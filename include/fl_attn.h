@@ -229,8 +229,10 @@ typedef struct {
  * and then the softmax / contraction derivative of fl_attn_bwd per stream (dv sums both streams).
  * It is composed from the same kernels: the streams' outputs O1, O2 are recomputed with the forward kernel
  * where RMSNorm or the second stream need them, one elementwise kernel turns dout into the per-stream dO,
- * delta and the epilogue gradients, tensors whose head dim the backward kernels do not take are zero-padded
- * into the workspace (D = 32 -> 64, D = 64 with Dv = 128 -> 128), and the backward kernels run once per stream.
+ * delta and the epilogue gradients, and the backward kernels run once per stream, on the caller's tensors and into its
+ * gradients at (D, Dv) = (64, 64), (128, 128), (32, 32) without a mask (also causal without a bias) and (64, 128) without a
+ * bias, unmasked or causal; other head dims run at the next one of the kernels', on copies zero-padded into the workspace.
+ * Gradients may be written before every input has been read: they overlap no input and not each other.
  *
  *   out, lse   what fl_attn_fwd wrote (lse [B, 2G, H, Sq, 1] for FL_DIFFERENTIAL)
  *   aux        as for fl_attn_fwd, with aux->workspace of fl_attn_bwd_ex_workspace_size bytes (16-byte aligned)
