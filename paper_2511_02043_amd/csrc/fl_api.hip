@@ -1317,6 +1317,11 @@ static fl_status forward_call(const fl_tensor* q, const fl_tensor* k, const fl_t
   int order = g_tuning.order >= 0 ? g_tuning.order : 1;
   if (order == 1 && nbh % 8 != 0) order = 0;
   p.order = order;
+  // grouped-query heads: the heads of a kv head stay on one XCD, so that its L2 fetches their keys and values once (where
+  // every XCD still gets whole kv heads; causal training step, 2 x 32 / 8 heads x 8192 rows, D = 128: 4974 -> 4903 us with the
+  // dQ kernel in the same order).
+  const int64_t share = H / Hkv / ke->key.pack;
+  p.order_heads = order == 1 && dtype == FL_BF16 && (nbh / share) % 8 == 0 && g_tuning.order < 0 ? (int)share : 1;
 
   hipStream_t stream = (hipStream_t)stream_v;
   if (Sk == 0) {
@@ -1519,6 +1524,7 @@ fl_status fl::backward_call(const fl_tensor* q, const fl_tensor* k, const fl_ten
   p.part_dv = (float*)((unsigned char*)p.part_dk + wsz.part_bytes);
   const int order = g_tuning.order >= 0 ? g_tuning.order : 1;
   p.order_q = order == 1 && (B * G * H) % 8 == 0;
+  p.order_heads = p.order_q && (B * G * Hkv) % 8 == 0 && g_tuning.order < 0 ? (int)(H / Hkv) : 1;
   p.order_k = order == 1 && (B * G * Hkv * p.hsplit) % 8 == 0;
   const int64_t nb_q = B * G * H * p.n_qtiles, nb_k = B * G * Hkv * p.hsplit * p.n_ktiles;
   const int64_t rows = B * G * H * Sq;
@@ -1789,6 +1795,7 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
   p.part_dv = (float*)(ws + L.off_part + L.part_k);
   const int order = g_tuning.order >= 0 ? g_tuning.order : 1;
   p.order_q = order == 1 && (B * G * H) % 8 == 0;
+  p.order_heads = p.order_q && (B * G * Hkv) % 8 == 0 && g_tuning.order < 0 ? (int)(H / Hkv) : 1;
   p.order_k = order == 1 && (B * G * Hkv * p.hsplit) % 8 == 0;
   for (int nb = 0; nb < 2; ++nb) p.bias[nb] = bias[nb];
   p.ds_stage = want_dbias ? (uint16_t*)(ws + L.off_ds) : nullptr;

@@ -53,6 +53,7 @@ struct BwdParams {
   int32_t dq_f32, dk_f32, dv_f32;  // 1: that output is float, 0: bf16
   int32_t n_qtiles, n_ktiles;      // workgroups per (b, g, h) of the dQ kernel / per (b, g, hkv) of the dK/dV kernel
   int32_t order_q, order_k;        // 1: XCD-aware workgroup order (whole (b, g, h) problems per XCD) in that kernel
+  int32_t order_heads;             // dQ kernel, order_q 1: heads with the same keys that an XCD takes one after the other (FwdParams)
   int32_t hsplit;                  // dK/dV kernel: the query heads of a group are cut into hsplit subsets, one workgroup each
   float* part_dk;                  // hsplit > 1: fp32 partial sums [hsplit][B, G, Hkv, Sk, D | DV], summed by bwd_reduce_kv_kernel
   float* part_dv;
@@ -546,10 +547,11 @@ bwd_dq_kernel(const BwdParams p) {
   int qt, bh;
   if (p.order_q == 1) {
     // consecutive workgroup ids go round-robin to the 8 XCDs: give each XCD whole heads, so that a
-    // head's K / V tiles stay in one L2 (the host checks that the head count is a multiple of 8)
-    const int idx = blockIdx.x >> 3;
-    bh = (idx / nq) * 8 + (blockIdx.x & 7);
-    qt = nq - 1 - idx % nq;
+    // head's K / V tiles stay in one L2 (the host checks that the head count is a multiple of 8), with the heads that read
+    // the same K / V side by side
+    const int share = p.order_heads, idx = blockIdx.x >> 3, inner = idx % (nq * share);
+    bh = ((idx / (nq * share)) * 8 + (blockIdx.x & 7)) * share + inner % share;
+    qt = nq - 1 - inner / share;
   } else {
     qt = nq - 1 - (int)(blockIdx.x % nq);
     bh = blockIdx.x / nq;

@@ -730,11 +730,12 @@ fwd_bf16_kernel(const FwdParams call) {
   int pi, bh;
   if (call.order == 1) {
     // XCD-aware: consecutive workgroup ids go round-robin to the 8 XCDs; give each XCD whole
-    // (b, g, h) problems so that a head's K/V stay in one L2 (host checks (B*G*H) % 8 == 0).
-    const int xcd = bid & 7;
-    const int idx = bid >> 3;
-    bh = (idx / npairs) * 8 + xcd;
-    pi = idx % npairs;
+    // (b, g, h) problems so that a head's K/V stay in one L2 (host checks (B*G*H) % 8 == 0), and all order_heads problems
+    // that read the same K/V one after the other (grouped-query heads; 1 where that leaves XCDs without work).
+    const int xcd = bid & 7, share = call.order_heads;
+    const int idx = bid >> 3, inner = idx % (npairs * share);
+    bh = ((idx / (npairs * share)) * 8 + xcd) * share + inner % share;
+    pi = inner / share;
   } else {
     pi = bid % npairs;
     bh = bid / npairs;
@@ -746,7 +747,26 @@ fwd_bf16_kernel(const FwdParams call) {
   const int heads_wg = call.H / C::PACK;
   FwdParams p = call;
   if (call.kv_lens != nullptr) {
-    const int len = max(0, min(call.kv_lens[bh / (heads_wg * call.G)], call.Sk));
+    const int seq_wgs = heads_wg * call.G;
+    int b = bh / seq_wgs, len;
+    if (call.B > 1 && call.B <= 64) {
+      // Sequences go out longest first: the launch has a few workgroups per compute unit at most, and the one that takes
+      // the last long sequence would end long after the rest.  A lane ranks one sequence (ties by index).  (8 sequences of
+      // 4096 - 8192 tokens, 512 rows, 32 / 8 heads,
+      // D = 128: 422 -> 399 us; more than 64 sequences are many workgroups anyway)
+      const int ln = tid & 63;
+      const int mine = ln < call.B ? max(0, min(call.kv_lens[ln], call.Sk)) : -1;
+      int rank = 0;
+      for (int m = 0; m < call.B; ++m) {
+        const int other = __builtin_amdgcn_readlane(mine, m);
+        rank += other > mine || (other == mine && m < ln);
+      }
+      const int seq = __builtin_ctzll(__builtin_amdgcn_ballot_w64(ln < call.B && rank == b));   // ranks are a permutation
+      bh += (seq - b) * seq_wgs;
+      len = __builtin_amdgcn_readlane(mine, seq);
+    } else {
+      len = max(0, min(call.kv_lens[b], call.Sk));
+    }
     p.Sk = len;
     p.q_off = len - call.Sq;
   }

@@ -571,6 +571,7 @@ static fl_status custom_forward(fl_custom_variant* v, const fl_tensor* q, const 
   p.lds_bytes = 4 * kBN * (int)D * 2;              // K ring and V ring of two 64-key tiles each
   const int64_t nbh = B * G * H;
   p.order = nbh % 8 == 0 ? 1 : 0;
+  p.order_heads = 1;
   // under a causal / prefix base mask without a window a workgroup takes a long and a short q-tile
   const bool tri = (v->mask & (FL_MASK_CAUSAL | FL_MASK_PREFIX)) != 0 && (v->mask & FL_MASK_WINDOW) == 0;
   p.pair = tri && nbh * ((p.n_qtiles + 1) / 2) >= 512;

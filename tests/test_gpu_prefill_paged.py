@@ -72,6 +72,11 @@ CASES = {
                                                          seq_lens=[4, 5, 6, 32, 36, 37, 777], salt=13),
     "few_mha_d64_q40": lambda: inputs.prefill_paged_bf16(H=2, Hkv=2, D=64, Sq=40, page_size=32,
                                                          seq_lens=[39, 40, 41, 100, 1500], salt=14),
+    # sequences go out longest first: equal lengths, empty ones, and as many as are ranked (64) and more
+    "ranked_64_ties_d64_q70": lambda: inputs.prefill_paged_bf16(H=2, Hkv=1, D=64, Sq=70, page_size=16,
+                                                                seq_lens=[(37 * n) % 16 * 13 for n in range(64)], salt=17),
+    "unranked_65_d64_q70": lambda: inputs.prefill_paged_bf16(H=2, Hkv=1, D=64, Sq=70, page_size=16,
+                                                             seq_lens=[(37 * n) % 16 * 13 for n in range(65)], salt=18),
     "few_gqa4_d128_q3": lambda: inputs.prefill_paged_bf16(H=4, Hkv=1, D=128, Sq=3, page_size=64, seq_lens=[2, 3, 4, 64, 66, 2100], salt=15),
     "d32_p16_q40": lambda: inputs.prefill_paged_bf16(H=4, Hkv=2, D=32, Sq=40, page_size=16, seq_lens=[40, 41, 200]),
 }
