@@ -175,6 +175,12 @@ template <class C>
 struct Wave {
   static constexpr int D = C::D, DV = C::DV, NB = C::NB, KK = C::KK, DVB = C::DVB, NS = C::NS, RB = C::RB;
   static constexpr bool kPlain = (C::MOD == kModNone && C::NBIAS == 0);
+  // Soft-cap without biases: the score registers hold t = 1 / (exp(2 z) + 1), z the score over the cap, instead of the capped
+  // score cap * (1 - 2 t).  The row max is that of -t, and the step from t to the exponent's argument and the subtraction
+  // of the row's reference are one FMA.  A hidden score is t = +inf.  (The kernel is bound by its vector instructions:
+  // 8 x 16 heads x 1999 rows, D = 64: 247 -> 228 us with the error against fp64 unchanged.)
+  static constexpr bool kCapT = (C::MOD == kModSoftcap && C::NBIAS == 0);
+  static constexpr float kHidden = kCapT ? INFINITY : -INFINITY;   // what a hidden score's register holds
   typedef f32x16 Scores[C::RB][C::NB];
   // Raw bias values of one tile for this lane: for bias n, row block rb, key block nb and
   // register group r4, the four bf16 values of keys jb + 8*r4 .. +3 (loaded ahead of their use).
@@ -202,6 +208,7 @@ struct Wave {
   int i[C::RB], ic[C::RB];      // this lane's query rows (unclamped / clamped), one per row block
   int qdoc[C::RB];
   float c_scale, slope_l2;
+  float cap_in, cap_l2;         // soft-cap, uniform: raw score -> exponent of exp(2 z); the cap in log2 units
   float alibi_c[16];            // ALiBi, uniform: slope * key offset of score register r inside its 32-key block
   uint32_t ka[C::KK];           // per-lane byte offset of the K fragment of k-step kk (block 0)
   uint32_t va[C::DVB];          // per-lane byte offset of the V^T fragment of channel block d (key block 0)
@@ -308,17 +315,15 @@ struct Wave {
 
   // ---- variant transform (Eq. 4 score_mod, additive biases) of one score register.
   // Leaves the score in the domain exp_only() expects: raw for the plain variants (the scale is
-  // folded into the exponent's FMA), log2-scaled otherwise.  j0 is the tile's first key.
+  // folded into the exponent's FMA), t for the soft-cap (kCapT), log2-scaled otherwise.  j0 is the tile's first key.
   __device__ __forceinline__ float transform_one(float x, int j0, int rb, int nb, int r, const BiasRegs& br) const {
     if constexpr (kPlain) {
       return x;
     } else {
       const int j = j0 + 32 * nb + 4 * half + 8 * (r >> 2) + (r & 3);   // key of register r
       if constexpr (C::MOD == kModSoftcap) {
-        // cap*tanh(x*scale/cap) in the log2 domain; tanh(y) = 1 - 2/(exp(2y)+1)
-        const float e = fast_exp2(x * (2.f * c_scale / p.softcap));
-        const float cl = p.softcap * kLog2e;
-        x = fmaf(fast_rcp(e + 1.f), -2.f * cl, cl);
+        x = fast_rcp(fast_exp2(x * cap_in) + 1.f);
+        if constexpr (!kCapT) x = fmaf(x, -2.f * cap_l2, cap_l2);
       } else if constexpr (C::MOD == kModAlibi) {
         // slope * |i - j| with j = (j0 + 32*nb + 4*half) + c, c the register's compile-time key
         // offset: one per-lane term per key block minus a uniform constant per register, then one FMA
@@ -447,7 +452,7 @@ struct Wave {
           for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              if ((word >> (16 * nb + r)) & 1u) sc[rb][nb][r] = -INFINITY;
+              if ((word >> (16 * nb + r)) & 1u) sc[rb][nb][r] = kHidden;
         return;
       }
     }
@@ -474,11 +479,21 @@ struct Wave {
           if constexpr ((MASK & kMaskDoc) != 0) hide = hide || kd[nb][r >> 2][r & 3] != qdoc[rb];
           if constexpr ((MASK & kMaskCustom) != 0)  // (valid indices only, as for the score_mod; a key past Sk is hidden already)
             hide = hide || fl_user_mask(b, g, h, ic[rb] + p.q_off, FL_USER_CLAMP && jl + c >= p.Sk ? p.Sk - 1 : jl + c, p);
-          if (hide) sc[rb][nb][r] = -INFINITY;
+          if (hide) sc[rb][nb][r] = kHidden;
         }
     }
   }
 
+  // A row's largest register value (kCapT: of -t) in log2 units
+  __device__ __forceinline__ float max_log2(float m) const {
+    if constexpr (kPlain) return m * c_scale;      // scale > 0 (checked on the host)
+    else if constexpr (kCapT) {
+      // rounded so that cap - reference, which the exponents use, is exact (one of the two subtractions always is): the
+      // saved lse then carries no error that the probabilities do not (5e-7 rms at cap 30; 9e-7 with the maximum itself)
+      return cap_l2 - (cap_l2 - fmaf(m, 2.f * cap_l2, cap_l2));
+    }
+    else return m;
+  }
   // ---- row max of the tile in log2 units, one per row block
   __device__ __forceinline__ void rowmax(const Scores& sc, float (&mx)[C::RB]) const {
 #pragma unroll
@@ -487,10 +502,8 @@ struct Wave {
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) m = fmaxf(m, sc[rb][nb][r]);
-      m = half_swap_max(m);
-      if constexpr (kPlain) m *= c_scale;          // scale > 0 (checked on the host)
-      mx[rb] = m;
+        for (int r = 0; r < 16; ++r) m = fmaxf(m, kCapT ? -sc[rb][nb][r] : sc[rb][nb][r]);
+      mx[rb] = max_log2(half_swap_max(m));
     }
   }
 
@@ -525,6 +538,9 @@ struct Wave {
     if constexpr (kPlain) {
       p0 = fast_exp2(fmaf(s0, c_scale, -m_safe));
       p1 = fast_exp2(fmaf(s1, c_scale, -m_safe));
+    } else if constexpr (kCapT) {                  // (m_safe is the reference minus the cap)
+      p0 = fast_exp2(fmaf(s0, -2.f * cap_l2, -m_safe));
+      p1 = fast_exp2(fmaf(s1, -2.f * cap_l2, -m_safe));
     } else {
       p0 = fast_exp2(s0 - m_safe);
       p1 = fast_exp2(s1 - m_safe);
@@ -595,7 +611,7 @@ struct Wave {
     const float x1 = transform_one(nxt[rb][nb][r + 1], j1, rb, nb, r + 1, br);
     nxt[rb][nb][r] = x0;
     nxt[rb][nb][r + 1] = x1;
-    ps.mx[rb] = fmaxf(fmaxf(ps.mx[rb], x0), x1);
+    ps.mx[rb] = fmaxf(fmaxf(ps.mx[rb], kCapT ? -x0 : x0), kCapT ? -x1 : x1);
   }
 
   // hook(f) runs after the work of fragment f: the caller's tile loads.
@@ -609,6 +625,7 @@ struct Wave {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       ps.m_safe[rb] = m_run[rb] == -INFINITY ? 0.f : m_run[rb];
+      if constexpr (kCapT) ps.m_safe[rb] -= cap_l2;
       ps.psum[rb] = 0.f;
       ps.mx[rb] = -INFINITY;
     }
@@ -688,8 +705,7 @@ struct Wave {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       l_run[rb] += ps.psum[rb];
-      float mxs = half_swap_max(ps.mx[rb]);
-      if constexpr (kPlain) mxs *= c_scale;        // scale > 0 (checked on the host)
+      const float mxs = max_log2(half_swap_max(ps.mx[rb]));
       const float m_old = m_run[rb];
       float m_new = (mxs - m_old > kLazyMaxLog2) ? mxs : m_old;   // false for NaN (-inf - -inf)
       m_new = advance ? m_new : m_old;
@@ -829,6 +845,12 @@ fwd_bf16_kernel(const FwdParams call) {
   }
   w.c_scale = p.scale * kLog2e;                    // raw score -> log2 domain
   w.slope_l2 = 0.f;
+  w.cap_in = w.cap_l2 = 0.f;
+  if constexpr (C::MOD == kModSoftcap) {
+    // cap * tanh(z) with z = x * scale / cap, in the log2 domain; tanh(z) = 1 - 2 / (exp(2 z) + 1)
+    w.cap_in = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(2.f * w.c_scale / p.softcap)));
+    w.cap_l2 = p.softcap * kLog2e;
+  }
   if constexpr (C::MOD == kModAlibi) {
     w.slope_l2 = p.alibi_slopes[h] * kLog2e;
 #pragma unroll
@@ -1336,7 +1358,7 @@ fwd_bf16_kernel(const FwdParams call) {
 #pragma unroll
               for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) cur[rb][nb][r] = -INFINITY;
+                for (int r = 0; r < 16; ++r) cur[rb][nb][r] = W::kHidden;
           } else {
             w.template mask<C::ID_RING + slot_vc * C::ID_BYTES>(cur, t0 * BN, tbw[0]);
             w.rowmax(cur, mx);
