@@ -13,6 +13,7 @@
 #include "fl_bwd_registry.hpp"
 #include "fl_host.hpp"
 #include "fl_decode_registry.hpp"
+#include "fl_pair_registry.hpp"
 #include "fl_registry.hpp"
 
 static_assert(FL_MASK_CAUSAL == fl::kMaskCausal && FL_MASK_WINDOW == fl::kMaskWindow &&
@@ -44,6 +45,7 @@ struct Tuning {
   int prefill_gather = 0;          // fl_attn_prefill_paged: 1 always copies the pages into dense tensors first, 2 never
                                    // (where the pages allow it); 0: by chunk length
   int bwd_wg_target = 0;           // 0: the default of choose_hsplit
+  int pair_bias = 0;               // fl_attn_bwd_ex: 1 never takes the stationary-bias kernels
 };
 thread_local Tuning g_tuning;
 
@@ -416,6 +418,7 @@ struct EpiBwdParams {
   const float* rms_w;
   float* dl_rows;                   // per-row terms of dlambda (summed per head by reduce_dlambda_kernel), or null
   float* dw_part;                   // per-workgroup partial sums of the rms_weight gradient, [workgroups, Dv], or null
+  float lse2_mul, delta_mul;        // factors of the stored lse2 and delta (stationary-bias kernels: -1 / (scale log2(e)) and -1)
   float rms_eps;
   int32_t B, G, H, Sq, Dv, Dvc;
   int32_t ns, has_gate, has_rms, dgate_f32;
@@ -510,14 +513,14 @@ __global__ void __launch_bounds__(256) epi_bwd_kernel(const EpiBwdParams e) {
     dl = wsum(dl);
   }
   if (lane == 0) {
-    e.delta[0][row] = d1;
+    e.delta[0][row] = d1 * e.delta_mul;
     if (e.ns == 2) {
       e.delta[1][row] = d2;
       if (e.dl_rows != nullptr) e.dl_rows[row] = dl;
     }
     for (int s = 0; s < e.ns; ++s) {
       const float l = e.lse[b * e.lse_sb + (int64_t)(e.ns * g + s) * e.lse_sg + h * e.lse_sh + i];
-      e.lse2[s][row] = l == -INFINITY ? INFINITY : l * fl::kLog2e;
+      e.lse2[s][row] = (l == -INFINITY ? INFINITY : l * fl::kLog2e) * e.lse2_mul;
     }
   }
 }
@@ -661,14 +664,14 @@ __global__ void __launch_bounds__(256) epi_bwd_rows_kernel(const EpiBwdParams e)
     dl = gsum(dl);
   }
   if (live && sub == 0) {
-    e.delta[0][row] = d1;
+    e.delta[0][row] = d1 * e.delta_mul;
     if (e.ns == 2) {
       e.delta[1][row] = d2;
       if (e.dl_rows != nullptr) e.dl_rows[row] = dl;
     }
     for (int s = 0; s < e.ns; ++s) {
       const float l = e.lse[b * e.lse_sb + (int64_t)(e.ns * g + s) * e.lse_sg + h * e.lse_sh + i];
-      e.lse2[s][row] = l == -INFINITY ? INFINITY : l * fl::kLog2e;
+      e.lse2[s][row] = (l == -INFINITY ? INFINITY : l * fl::kLog2e) * e.lse2_mul;
     }
   }
 }
@@ -858,6 +861,84 @@ __global__ void __launch_bounds__(256) reduce_dbias_kernel(const DbiasParams d) 
   }
 }
 
+// Pair bias gradient from the stationary-bias dQ kernel: the sum of its partial blocks over the chunks of the row axis and over
+// the axes the bias broadcasts along.  One wave per 32 x 32 output block; fixed order.
+struct PairBiasParams {
+  const float* part;                // [chunks][B][H][nqb][nkb][quad][lane][4]
+  fl::BiasView out;
+  int chunks, B, H, nqb, nkb, ob, oh, Sq, Sk;
+  int64_t units;                    // ob * oh * nqb * nkb
+};
+__global__ void __launch_bounds__(256) reduce_pair_bias_kernel(const PairBiasParams d) {
+  const int64_t unit = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (unit >= d.units) return;
+  const int kb = (int)(unit % d.nkb), qb = (int)((unit / d.nkb) % d.nqb);
+  const int h = (int)((unit / ((int64_t)d.nkb * d.nqb)) % d.oh), b = (int)(unit / ((int64_t)d.nkb * d.nqb * d.oh));
+  const int nb = d.ob == 1 ? d.B : 1, nh = d.oh == 1 ? d.H : 1, terms = d.chunks * nb * nh;
+  float s[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll 4
+  for (int n = 0; n < terms; ++n) {
+    const int hh = n % nh, bb = (n / nh) % nb, c = n / (nh * nb);
+    const float4* src = (const float4*)(d.part + (((((int64_t)c * d.B + b + bb) * d.H + h + hh) * d.nqb + qb) * d.nkb + kb) * 1024) + lane;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 x = src[q * 64];
+      s[4 * q] += x.x; s[4 * q + 1] += x.y; s[4 * q + 2] += x.z; s[4 * q + 3] += x.w;
+    }
+  }
+  const int i = 32 * qb + (lane & 31);
+  if (i >= d.Sq) return;
+  float* row = (float*)d.out.ptr + b * d.out.sb + h * d.out.sh + (int64_t)i * d.out.si;
+  const bool vec = d.out.sj == 1 && ((uintptr_t)d.out.ptr) % 16 == 0 && ((d.out.sb | d.out.sh | d.out.si) & 3) == 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int j = 32 * kb + 8 * q + 4 * (lane >> 5);
+    if (vec && j + 3 < d.Sk) {
+      *(float4*)(row + j) = make_float4(s[4 * q], s[4 * q + 1], s[4 * q + 2], s[4 * q + 3]);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (j + u < d.Sk) row[(int64_t)(j + u) * d.out.sj] = s[4 * q + u];
+    }
+  }
+}
+
+// Key bias of the stationary-bias kernels: bias * log2(e) / c in fp32, [b][g][h] rows of n_key (zeros past Sk); b, g, h run over the
+// bias's own axes.
+__global__ void __launch_bounds__(256) fold_key_bias_kernel(const fl::BiasView bias, float* dst, int og, int oh, int Sk, int n_key, float mul, int64_t total) {
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= total) return;
+  const int j = (int)(idx % n_key);
+  const int64_t row = idx / n_key;
+  const int h = (int)(row % oh), g = (int)((row / oh) % og), b = (int)(row / ((int64_t)oh * og));
+  dst[idx] = j < Sk ? fl::bf16_to_f32(((const uint16_t*)bias.ptr)[b * bias.sb + g * bias.sg + h * bias.sh + (int64_t)j * bias.sj]) * mul : 0.f;
+}
+
+// Key bias gradient: the sums over the query rows [B, G, H, Sk], added over the axes the bias broadcasts along (sizes ob, og, oh).
+// A workgroup takes 64 keys of an output row; its four waves take a quarter of the terms each and meet in LDS (fixed order).
+__global__ void __launch_bounds__(256) reduce_key_bias_kernel(const float* part, const fl::BiasView out, int B, int G, int H, int Sk, int ob, int og, int oh) {
+  __shared__ float s4[4][64];
+  const int nkb = (Sk + 63) / 64, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = (int)(blockIdx.x % nkb) * 64 + lane;
+  const int row = blockIdx.x / nkb, h = row % oh, g = (row / oh) % og, b = row / (oh * og);
+  const int nb = ob == 1 ? B : 1, ng = og == 1 ? G : 1, nh = oh == 1 ? H : 1;
+  const int64_t terms = (int64_t)nb * ng * nh, lo = terms * wave / 4, hi = terms * (wave + 1) / 4;
+  float s = 0.f;
+  if (j < Sk)
+#pragma unroll 4
+    for (int64_t n = lo; n < hi; ++n) {
+      const int hh = (int)(n % nh), gg = (int)((n / nh) % ng), bb = (int)(n / ((int64_t)nh * ng));
+      s += part[((((int64_t)(b + bb)) * G + g + gg) * H + h + hh) * Sk + j];
+    }
+  s4[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && j < Sk)
+    ((float*)out.ptr)[b * out.sb + g * out.sg + h * out.sh + (int64_t)j * out.sj] = ((s4[0][lane] + s4[1][lane]) + s4[2][lane]) + s4[3][lane];
+}
+
 // bf16 [B, G, H, S, D] view -> dense [B, G, H, S, Dc] with zero channels past D (8 channels per thread)
 __global__ void __launch_bounds__(256) pad_rows_kernel(fl::View src, uint16_t* dst, int G, int H, int S, int D, int Dc, int64_t rows) {
   const int cpr = Dc / 8;
@@ -947,6 +1028,47 @@ PrefillLayout prefill_layout(int64_t B, int64_t Hkv, int64_t D, int64_t max_len)
   return L;
 }
 
+// The stationary-bias kernels (fl_bwd_pair.hpp) by sizes alone: how many ranges the row axis is cut into, one workgroup per 64
+// owned rows, (b, h) and range.  Few, long ranges load the bias seldom and leave small partial gradients; the launch should fill
+// the 256 compute units (one workgroup each) a whole number of times.  A range costs about two problems of start-up (128 x 8 heads
+// x 384, D = 32, dQ / dK and dV: 5 ranges 77 / 86 us, 8 97 / 106, 16 96 / 96, 32 116 / 113).
+int pair_chunks(int64_t B, int64_t G, int64_t H, int64_t S_own) {
+  const int64_t base = B * H * ((S_own + 63) / 64);
+  int64_t best = 1, best_cost = 0;
+  for (int64_t c = 1; c <= G; ++c) {
+    const int64_t cost = ((base * c + 255) / 256) * ((G + c - 1) / c + 2);
+    if (c == 1 || cost < best_cost) {
+      best = c;
+      best_cost = cost;
+    }
+  }
+  return (int)best;
+}
+// ... whether they can take a call of these sizes at all (the biases' shapes decide the rest), and the part of the workspace they need
+// Head dim 32 up to 512 rows, 64 up to 384: past that a wave's blocks do not fit its registers (128 x 8 heads x 500, D = 64: 853
+// against 708 us with the general kernels; x 384: 400 against 424; D = 32, x 500: 310 against 578).
+bool pair_sizes_ok(int64_t G, int64_t H, int64_t Hkv, int64_t Sq, int64_t Sk, int64_t D, int64_t Dv, const fl_variant_desc* d) {
+  return d->n_bias > 0 && d->score_mod == FL_MOD_NONE && d->mask == 0 && d->combine == FL_SINGLE && H == Hkv && D == Dv && (D == 32 || D == 64) &&
+         G >= 2 && Sq >= 1 && Sk >= 1 && std::max(Sq, Sk) <= (D == 32 ? 512 : 384) && d->scale > 1e-20f && d->scale < 1e20f;
+}
+struct PairLayout {
+  int chunks_q, chunks_k, nqb, nkb, n_key;
+  size_t off_part, off_key_part, off_key, total;
+};
+PairLayout pair_layout(int64_t B, int64_t G, int64_t H, int64_t Sq, int64_t Sk) {
+  PairLayout P;
+  P.chunks_q = pair_chunks(B, G, H, Sq);
+  P.chunks_k = pair_chunks(B, G, H, Sk);
+  P.nqb = (int)((Sq + 31) / 32);
+  P.nkb = (int)((Sk + 31) / 32);
+  P.n_key = (int)((Sk + 127) / 128 * 128);
+  P.off_part = 0;
+  P.off_key_part = up256((size_t)P.chunks_q * (B * H) * P.nqb * P.nkb * 4096);
+  P.off_key = P.off_key_part + up256((size_t)(B * G * H) * Sk * 4);
+  P.total = P.off_key + up256((size_t)(B * G * H) * P.n_key * 4);
+  return P;
+}
+
 // Workspace of fl_attn_bwd_ex (byte offsets; every region 256-byte aligned).
 struct ExLayout {
   int Dc, Dvc, ns, hsplit;          // head dims the kernels run at: (D, Dv) where such a kernel is compiled, else core_dim()
@@ -1007,6 +1129,7 @@ ExLayout ex_layout(int64_t B, int64_t G, int64_t H, int64_t Hkv, int64_t Sq, int
   L.off_dl = take(L.ns == 2 ? L.stat : 0);
   // bias gradients: dS of every score (bf16), reduced over the broadcast axes afterwards
   L.ds = d->n_bias > 0 ? up256((size_t)(B * G * H) * ((Sq + 31) / 32) * ((Sk + 31) / 32) * fl::ds_block(Sq) * 2) : 0;
+  if (pair_sizes_ok(G, H, Hkv, Sq, Sk, D, Dv, d)) L.ds = std::max(L.ds, pair_layout(B, G, H, Sq, Sk).total);
   L.off_ds = take(L.ds);
   // rms_weight gradient: one partial sum per workgroup (four rows) of the epilogue-derivative kernel
   L.off_dw = take((d->epilogue & FL_EPI_RMSNORM) != 0 ? up256(((rq + 3) / 4) * (size_t)Dv * 4) : 0);
@@ -1023,6 +1146,58 @@ bool bwd_ex_ok(const fl_variant_desc* d, int64_t D, int64_t Dv) {
   if (!((D == 32 || D == 64 || D == 128) && (Dv == 32 || Dv == 64 || Dv == 128))) return false;
   return find_compiled_bwd(d, D, Dv, (int)d->n_bias) != nullptr || find_bwd_entry(d, core_dim(D, Dv), (int)d->n_bias) != nullptr ||
          bwd_jit_ok(d, core_dim(D, Dv), (int)d->n_bias);
+}
+
+// dQ, dK, dV and the bias gradients by the stationary-bias kernels; pair / keyb: the indices of the two biases (keyb -1: none).
+hipError_t run_pair_bwd(const fl::BwdParams& call, int D, int pair, int keyb, const fl_aux* aux, const fl_bwd_extra* extra, const fl::BiasView* dbias,
+                        unsigned char* ws, hipStream_t stream) {
+  const int B = call.B, G = call.G, H = call.H, Sq = call.Sq, Sk = call.Sk;
+  const PairLayout P = pair_layout(B, G, H, Sq, Sk);
+  fl::PairParams p;
+  memset(&p, 0, sizeof(p));
+  p.b = call;
+  p.b.bias[0] = call.bias[pair];
+  auto blocks = [](int64_t n, int64_t per) { return dim3((unsigned)((n + per - 1) / per)); };
+  if (keyb >= 0) {
+    const int64_t* z = aux->bias[keyb].size;
+    const int64_t total = z[0] * z[1] * z[2] * P.n_key;
+    float* key = (float*)(ws + P.off_key);
+    hipLaunchKernelGGL(fold_key_bias_kernel, blocks(total, 256), dim3(256), 0, stream, call.bias[keyb], key, (int)z[1], (int)z[2], Sk, P.n_key,
+                       1.f / call.scale, total);       // log2(e) / (scale log2(e))
+    p.key = key;
+    p.key_sh = z[2] == 1 ? 0 : P.n_key;
+    p.key_sg = z[1] == 1 ? 0 : z[2] * P.n_key;
+    p.key_sb = z[0] == 1 ? 0 : z[1] * z[2] * P.n_key;
+  }
+  auto launch = [&](int role, int own, int streamed, int chunks) {
+    p.chunks = chunks;
+    p.n_own = (own + 63) / 64;
+    const int64_t units = (int64_t)B * H * chunks;
+    p.xcd = units % 8 == 0;
+    return (D == 32 ? fl::launch_pair32 : fl::launch_pair64)((streamed + 127) / 128, role, keyb >= 0, p, (int)(units * p.n_own), stream);
+  };
+  p.bias_part = dbias[pair].ptr != nullptr ? (float*)(ws + P.off_part) : nullptr;
+  hipError_t e = launch(0, Sq, Sk, P.chunks_q);
+  if (e != hipSuccess) return e;
+  if (p.bias_part != nullptr) {
+    PairBiasParams d;
+    d.part = p.bias_part;
+    d.out = dbias[pair];
+    d.chunks = P.chunks_q; d.B = B; d.H = H; d.nqb = P.nqb; d.nkb = P.nkb; d.Sq = Sq; d.Sk = Sk;
+    d.ob = (int)extra->dbias[pair].size[0];
+    d.oh = (int)extra->dbias[pair].size[2];
+    d.units = (int64_t)d.ob * d.oh * P.nqb * P.nkb;
+    hipLaunchKernelGGL(reduce_pair_bias_kernel, blocks(d.units, 4), dim3(256), 0, stream, d);
+  }
+  p.key_part = keyb >= 0 && dbias[keyb].ptr != nullptr ? (float*)(ws + P.off_key_part) : nullptr;
+  if ((e = launch(1, Sk, Sq, P.chunks_k)) != hipSuccess) return e;
+  if (p.key_part != nullptr) {
+    const int64_t* z = extra->dbias[keyb].size;
+    const int64_t wgs = z[0] * z[1] * z[2] * ((Sk + 63) / 64);
+    hipLaunchKernelGGL(reduce_key_bias_kernel, blocks(wgs, 1), dim3(256), 0, stream, (const float*)p.key_part, dbias[keyb], B, G, H, Sk,
+                       (int)z[0], (int)z[1], (int)z[2]);
+  }
+  return hipGetLastError();
 }
 
 fl::View dense_view(void* ptr, int64_t G, int64_t H, int64_t S, int64_t Dc) {
@@ -1075,6 +1250,7 @@ fl_status fl_set_tuning(const char* key, int value) {
   else if (!strcmp(key, "prefill_pack")) g_tuning.prefill_pack = value;
   else if (!strcmp(key, "prefill_gather")) g_tuning.prefill_gather = value;
   else if (!strcmp(key, "bwd_wg_target")) g_tuning.bwd_wg_target = value;
+  else if (!strcmp(key, "pair_bias")) g_tuning.pair_bias = value;
   else return fail(FL_ERR_UNSUPPORTED, "unknown tuning key '%s'", key);
   return FL_OK;
 }
@@ -1738,6 +1914,18 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
   ep.rms_eps = desc->rms_eps;
   ep.B = (int)B; ep.G = (int)G; ep.H = (int)H; ep.Sq = (int)Sq; ep.Dv = (int)Dv; ep.Dvc = Dvc;
   ep.ns = ns; ep.has_gate = has_gate; ep.has_rms = has_rms;
+  // Stationary-bias kernels: a pair bias that every row problem g shares and, beside it, at most a key bias.
+  int pair = -1, keyb = -1;
+  if (pair_sizes_ok(G, H, Hkv, Sq, Sk, D, Dv, desc) && Dc == (int)D && g_tuning.pair_bias != 1) {
+    for (int nb = 0; nb < (int)desc->n_bias; ++nb) {
+      const int64_t* z = aux->bias[nb].size;
+      if (z[1] == 1 && z[3] == Sq && z[4] == Sk && pair < 0) pair = nb;
+      else if (z[3] == 1 && z[4] == Sk && keyb < 0) keyb = nb;
+    }
+    if ((pair >= 0) + (keyb >= 0) != (int)desc->n_bias) pair = -1;
+  }
+  ep.lse2_mul = pair >= 0 ? -1.f / (desc->scale * fl::kLog2e) : 1.f;
+  ep.delta_mul = pair >= 0 ? -1.f : 1.f;
   // rows 16-byte aligned everywhere: several rows per wave, eight channels per lane; else one row per wave
   auto rows_aligned = [](const fl::View& v, int elem_bytes) {
     if (v.ptr == nullptr) return true;
@@ -1772,7 +1960,7 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
                        (int)Hkv, (int)Sk, (int)Dv, Dvc, rows_k);
   const bool want_dbias = dbias[0].ptr != nullptr || dbias[1].ptr != nullptr;
   // under a mask whole blocks are skipped by the dQ kernel: their dS is zero
-  if (want_dbias && mask != 0)
+  if (want_dbias && mask != 0)           // (the stationary-bias kernels take no mask)
     hipLaunchKernelGGL(zero_f32_kernel, blocks((int64_t)(L.ds / 4)), dim3(256), 0, stream, (float*)(ws + L.off_ds), (int64_t)(L.ds / 4));
   if ((e = hipGetLastError()) != hipSuccess) return fail(FL_ERR_LAUNCH, "backward pre-pass launch: %s", hipGetErrorString(e));
 
@@ -1828,6 +2016,11 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
     p.dv_add = s > 0 ? (const float*)(ws + L.off_gv[0]) : nullptr;
     p.delta = (float*)(ws + L.off_delta[s]);
     p.lse2 = (float*)(ws + L.off_lse2[s]);
+    if (pair >= 0) {
+      if ((e = run_pair_bwd(p, Dc, pair, keyb, aux, extra, dbias, ws + L.off_ds, stream)) != hipSuccess)
+        return fail(FL_ERR_LAUNCH, "backward launch: %s", hipGetErrorString(e));
+      continue;
+    }
     if ((e = run_bwd_dq(be, p, (int)nb_q, stream)) != hipSuccess) return fail(FL_ERR_LAUNCH, "dq launch: %s", hipGetErrorString(e));
     for (uint32_t nb = 0; nb < desc->n_bias; ++nb)
       if (dbias[nb].ptr != nullptr) {               // this stream's dS, summed over the axes the bias broadcasts along
