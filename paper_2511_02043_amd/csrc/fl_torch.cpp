@@ -1,9 +1,10 @@
-// Marshalling of the PyTorch entry points whose device work takes a few microseconds (attention and its backward pass, a decode
+// Marshalling of the PyTorch entry points (attention and its backward pass, with and without the variants' extra tensors, a decode
 // step, a chunk of a paged prefill): torch tensors in, C-ABI descriptors filled, outputs and workspace taken from torch's
 // allocator, one call of libflattn.so, the fl_status and the outputs back.  No attention arithmetic and no kernel is here.
 //
 // The same in Python (ctypes structures filled field by field) cost 20 us of a 31 us causal call on [1, 8, 128, 64] and of
-// a 31 us decode step of one sequence, whose kernels take 8 and 10 us.
+// a 31 us decode step of one sequence, whose kernels take 8 and 10 us; a training step with a bias and a gate on
+// [1, 16, 4, 64, 32] took 252 us that way and takes 117 this way, most of it in the autograd engine.
 #include <torch/extension.h>
 
 #include <optional>
@@ -128,6 +129,99 @@ std::tuple<int, Tensor, Tensor, Tensor> attention_bwd(const Tensor& q, const Ten
   return {status, dq, dk, dv};
 }
 
+// The tensors of a variant beyond q, k and v (absent ones are None), as variant_fwd and variant_bwd take them.
+struct Extras {
+  const OptTensor &q2, &k2, &lam, &gate, &bias0, &bias1, &rms_weight;
+  int n_bias() const { return (int)bias0.has_value() + (int)bias1.has_value(); }
+  fl_variant_desc describe(fl_variant_desc d, bool rmsnorm, double rms_eps) const {
+    d.n_bias = (uint32_t)n_bias();
+    d.combine = q2.has_value() ? FL_DIFFERENTIAL : FL_SINGLE;
+    d.epilogue = (rmsnorm ? FL_EPI_RMSNORM : 0) | (gate.has_value() ? FL_EPI_GATE_SIGMOID : 0);
+    d.rms_eps = rmsnorm ? (float)rms_eps : 0.f;
+    return d;
+  }
+  fl_aux fill(fl_aux a) const {
+    int n = 0;
+    for (const OptTensor* b : {&bias0, &bias1})
+      if (b->has_value()) a.bias[n++] = desc(**b);
+    if (gate.has_value()) a.gate = desc(*gate);
+    if (q2.has_value()) a.q2 = desc(*q2);
+    if (k2.has_value()) a.k2 = desc(*k2);
+    a.lambda = ptr<const float>(lam);
+    a.rms_weight = ptr<const float>(rms_weight);
+    return a;
+  }
+};
+
+// out in q's dtype and rank, lse [B, G or 2 G (two streams), H, Sq, 1]
+std::tuple<int, Tensor, Tensor> variant_fwd(const Tensor& q, const Tensor& k, const Tensor& v, const OptTensor& q2, const OptTensor& k2,
+                                            const OptTensor& lam, const OptTensor& gate, const OptTensor& bias0, const OptTensor& bias1,
+                                            const OptTensor& rms_weight, double scale, int mod, double softcap, int mask, int window,
+                                            int prefix, int q_offset, bool rmsnorm, double rms_eps, const OptTensor& slopes,
+                                            const OptTensor& q_ids, const OptTensor& kv_ids, int64_t stream) {
+  const Extras x{q2, k2, lam, gate, bias0, bias1, rms_weight};
+  const fl_tensor tq = desc(q), tk = desc(k), tv = desc(v);
+  const fl_variant_desc d = x.describe(variant(scale, mod, softcap, mask, window, prefix, q_offset), rmsnorm, rms_eps);
+  std::vector<int64_t> size(q.sizes().begin(), q.sizes().end());
+  size.back() = tv.size[4];
+  Tensor out = at::empty(size, q.options());
+  Tensor lse = at::empty({tq.size[0], (q2.has_value() ? 2 : 1) * tq.size[1], tq.size[2], tq.size[3], 1}, q.options().dtype(at::kFloat));
+  fl_tensor tout = desc(out), tlse = desc(lse);
+  Tensor ws;
+  const size_t need = fl_attn_fwd_workspace_size(&tq, &tk, &d);
+  if (need != 0) ws = bytes(need, q);
+  const fl_aux a = x.fill(aux_of(slopes, q_ids, kv_ids, ws));
+  int status;
+  {
+    py::gil_scoped_release nogil;
+    status = fl_attn_fwd(&tq, &tk, &tv, &d, &a, &tout, &tlse, (void*)stream);
+  }
+  return {status, out, lse};
+}
+
+// The status and the gradients of q, k, v, q2, k2, lam, gate, bias0, bias1, rms_weight in their layouts (None where absent).  The
+// kernels sum bias gradients in fp32; they are rounded to the biases' dtype here.
+std::tuple<int, std::vector<OptTensor>> variant_bwd(const Tensor& q, const Tensor& k, const Tensor& v, const OptTensor& q2,
+                                                    const OptTensor& k2, const OptTensor& lam, const OptTensor& gate,
+                                                    const OptTensor& bias0, const OptTensor& bias1, const OptTensor& rms_weight,
+                                                    const Tensor& out, const Tensor& lse, const Tensor& dout_in, double scale, int mod,
+                                                    double softcap, int mask, int window, int prefix, int q_offset, bool rmsnorm,
+                                                    double rms_eps, const OptTensor& slopes, const OptTensor& q_ids,
+                                                    const OptTensor& kv_ids, int64_t stream) {
+  const Extras x{q2, k2, lam, gate, bias0, bias1, rms_weight};
+  const Tensor dout = readable(dout_in);
+  const fl_tensor tq = desc(q), tk = desc(k), tv = desc(v), tout = desc(out), tlse = desc(lse), tdo = desc(dout);
+  const fl_variant_desc d = x.describe(variant(scale, mod, softcap, mask, window, prefix, q_offset), rmsnorm, rms_eps);
+  auto like = [](const OptTensor& t) { return t.has_value() ? OptTensor(at::empty_like(*t)) : OptTensor(); };
+  auto fp32 = [](const OptTensor& t) { return t.has_value() ? OptTensor(at::empty(t->sizes(), t->options().dtype(at::kFloat))) : OptTensor(); };
+  Tensor dq = at::empty_like(q), dk = at::empty_like(k), dv = at::empty_like(v);
+  const OptTensor dq2 = like(q2), dk2 = like(k2), dlam = like(lam), dgate = like(gate), drms = fp32(rms_weight);
+  OptTensor dbias0 = fp32(bias0), dbias1 = fp32(bias1);
+  fl_bwd_extra e = {};
+  e.struct_size = sizeof(e);
+  if (dq2.has_value()) e.dq2 = desc(*dq2);
+  if (dk2.has_value()) e.dk2 = desc(*dk2);
+  if (dgate.has_value()) e.dgate = desc(*dgate);
+  int n = 0;
+  for (const OptTensor* b : {&dbias0, &dbias1})
+    if (b->has_value()) e.dbias[n++] = desc(**b);
+  e.dlambda = ptr<float>(dlam);
+  e.drms_weight = ptr<float>(drms);
+  fl_tensor tdq = desc(dq), tdk = desc(dk), tdv = desc(dv);
+  const Tensor ws = bytes(std::max<size_t>(fl_attn_bwd_ex_workspace_size(&tq, &tk, &tv, &d), 16), q);
+  const fl_aux a = x.fill(aux_of(slopes, q_ids, kv_ids, ws));
+  int status;
+  {
+    py::gil_scoped_release nogil;
+    status = fl_attn_bwd_ex(&tq, &tk, &tv, &tout, &tdo, &tlse, &d, &a, &tdq, &tdk, &tdv, &e, (void*)stream);
+  }
+  if (status == 0) {
+    if (dbias0.has_value()) dbias0 = dbias0->to(bias0->scalar_type());
+    if (dbias1.has_value()) dbias1 = dbias1->to(bias1->scalar_type());
+  }
+  return {status, {dq, dk, dv, dq2, dk2, dlam, dgate, dbias0, dbias1, drms}};
+}
+
 // A decode step (q [B, H, D]) or a chunk of a paged prefill (q [B, H, Sq, D]) over caches [pages, page_size, Hkv, D].  Returns
 // the status, the workspace bytes the call needs, out (q's shape) and lse ([B, H] or [B, H, Sq]; undefined unless wanted).  A
 // workspace that is too small is reported by the second value alone: nothing has been launched then.
@@ -173,6 +267,7 @@ std::tuple<int, int64_t, Tensor, OptTensor> paged(bool decode, const Tensor& q, 
 PYBIND11_MODULE(_fltorch, m) {
   m.def("attention_fwd", &attention_fwd);
   m.def("attention_bwd", &attention_bwd);
+  m.def("variant_fwd", &variant_fwd);
+  m.def("variant_bwd", &variant_bwd);
   m.def("paged", &paged);
-  m.def("readable", &readable);
 }

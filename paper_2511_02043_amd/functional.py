@@ -2,8 +2,7 @@
 `decode_attention(...)` for one decode step over a paged cache.
 
 Marshalling only: the forward pass is fl_attn_fwd, the backward pass fl_attn_bwd, both through
-the C ABI (`_fltorch`, compiled from csrc/fl_torch.cpp, fills the descriptors of the calls that are short
-enough for it to count); no attention arithmetic happens here and there is no fallback path.  Tensors
+the C ABI (`_fltorch`, compiled from csrc/fl_torch.cpp, fills the descriptors); no attention arithmetic happens here and there is no fallback path.  Tensors
 are [B, H, S, D] (or [B, G, H, S, D] with an extra independent row axis) bf16 CUDA tensors;
 strided views are passed as they are.
 
@@ -149,63 +148,22 @@ class _VariantAttention(torch.autograd.Function):
     Tensor inputs: q, k, v, q2, k2, lam, gate, bias0, bias1, rms_weight (absent ones are None)."""
 
     @staticmethod
-    def forward(ctx, cfg, q, k, v, q2, k2, lam, gate, bias0, bias1, rms_weight):
-        dev = q.device
-        q5, k5, v5 = _as5(q), _as5(k), _as5(v)
-        B, G, H, Sq, _ = q5.shape
-        diff = q2 is not None
-        biases = [b for b in (bias0, bias1) if b is not None]
-        epi = (fb.FL_EPI_RMSNORM if cfg["rmsnorm"] else 0) | (fb.FL_EPI_GATE_SIGMOID if gate is not None else 0)
-        desc = fb.variant_desc(scale=float(cfg["scale"]), score_mod=_score_mod(cfg["softcap"], cfg["alibi_slopes"]), softcap=float(cfg["softcap"] or 0.0),
-                               mask=_mask_bits(cfg["causal"], cfg["window"], cfg["prefix"], cfg["q_doc_ids"]),
-                               window=int(cfg["window"] or 0), prefix_len=int(cfg["prefix"] or 0), n_bias=len(biases),
-                               combine=fb.FL_DIFFERENTIAL if diff else fb.FL_SINGLE, epilogue=epi,
-                               rms_eps=float(cfg["rms_eps"]) if cfg["rmsnorm"] else 0.0, q_offset=int(cfg["q_offset"]))
-        out = torch.empty((B, G, H, Sq, v5.shape[4]), dtype=q.dtype, device=dev)
-        lse = torch.empty((B, 2 * G if diff else G, H, Sq, 1), dtype=torch.float32, device=dev)
-        tq, tk, tv, tout, tlse = (fb.tensor_desc(x) for x in (q5, k5, v5, out, lse))
-        ws = None
-        nbytes = fb.fl_attn_fwd_workspace_size(tq, tk, desc)
-        if nbytes:
-            ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
-        five = lambda x: None if x is None else _as5(x)
-        aux = fb.aux_desc(alibi_slopes=cfg["alibi_slopes"], q_doc_ids=cfg["q_doc_ids"], kv_doc_ids=cfg["kv_doc_ids"],
-                          biases=biases, gate=five(gate), q2=five(q2), k2=five(k2), lambda_=lam,
-                          rms_weight=rms_weight, workspace=ws)
-        stream = torch.cuda.current_stream(dev).cuda_stream
-        fb.check(fb.fl_attn_fwd(tq, tk, tv, desc, aux, tout, tlse, stream))
-        ctx.save_for_backward(q, k, v, q2, k2, lam, gate, bias0, bias1, rms_weight, out, lse)
-        ctx.cfg, ctx.desc = cfg, desc
-        return out if q.dim() == 5 else out.squeeze(1)
+    def forward(ctx, variant, q, k, v, q2, k2, lam, gate, bias0, bias1, rms_weight):
+        tensors = (q, k, v, q2, k2, lam, gate, bias0, bias1, rms_weight)
+        status, out, lse = _host().variant_fwd(*tensors, *variant, _stream(q))
+        if status:
+            fb.check(status)
+        ctx.save_for_backward(*tensors, out, lse)
+        ctx.variant = variant
+        return out
 
     @staticmethod
     def backward(ctx, dout):
-        q, k, v, q2, k2, lam, gate, bias0, bias1, rms_weight, out, lse = ctx.saved_tensors
-        cfg, desc = ctx.cfg, ctx.desc
-        dev = q.device
-        q5, k5, v5, d5 = _as5(q), _as5(k), _as5(v), _as5(_host().readable(dout))
-        five = lambda x: None if x is None else _as5(x)
-        biases = [b for b in (bias0, bias1) if b is not None]
-        dq, dk, dv = torch.empty_like(q5), torch.empty_like(k5), torch.empty_like(v5)
-        dq2 = None if q2 is None else torch.empty_like(five(q2))
-        dk2 = None if k2 is None else torch.empty_like(five(k2))
-        dlam = None if lam is None else torch.empty_like(lam)
-        dgate = None if gate is None else torch.empty_like(five(gate))
-        dbias = [torch.empty(tuple(b.shape), dtype=torch.float32, device=dev) for b in biases]
-        tq, tk, tv, tout, tdo, tlse, tdq, tdk, tdv = (fb.tensor_desc(x) for x in (q5, k5, v5, out, d5, lse, dq, dk, dv))
-        ws = torch.empty(max(fb.fl_attn_bwd_ex_workspace_size(tq, tk, tv, desc), 16), dtype=torch.uint8, device=dev)
-        aux = fb.aux_desc(alibi_slopes=cfg["alibi_slopes"], q_doc_ids=cfg["q_doc_ids"], kv_doc_ids=cfg["kv_doc_ids"],
-                          biases=biases, gate=five(gate), q2=five(q2), k2=five(k2), lambda_=lam,
-                          rms_weight=rms_weight, workspace=ws)
-        drms = torch.empty(v5.shape[4], dtype=torch.float32, device=dev) if (cfg["rmsnorm"] and rms_weight is not None) else None
-        extra = fb.bwd_extra(dq2=dq2, dk2=dk2, dbias=dbias, dgate=dgate, dlambda=dlam, drms_weight=drms)
-        stream = torch.cuda.current_stream(dev).cuda_stream
-        fb.check(fb.fl_attn_bwd_ex(tq, tk, tv, tout, tdo, tlse, desc, aux, tdq, tdk, tdv, extra, stream))
-        sq = (lambda x: x) if q.dim() == 5 else (lambda x: None if x is None else x.squeeze(1))
-        gb = [g.to(b.dtype) for g, b in zip(dbias, biases)] + [None] * (2 - len(biases))
-        if bias0 is None and bias1 is not None:
-            gb = [None, gb[0]]
-        return (None, sq(dq), sq(dk), sq(dv), sq(dq2), sq(dk2), dlam, sq(dgate), gb[0], gb[1], drms)
+        saved = ctx.saved_tensors
+        status, grads = _host().variant_bwd(*saved, dout, *ctx.variant, _stream(saved[0]))
+        if status:
+            fb.check(status)
+        return (None, *grads)
 
 
 def variant_attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, *, scale: Optional[float] = None,
@@ -246,12 +204,12 @@ def variant_attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, *, scal
     for n, b in enumerate(biases):
         if b.dim() != 5 or b.dtype != torch.bfloat16 or b.device != q.device:
             raise ValueError(f"biases[{n}] must be a 5-D bf16 tensor on {q.device}")
-    cfg = dict(scale=q.shape[-1] ** -0.5 if scale is None else scale, causal=causal, window=window, prefix=prefix,
-               softcap=softcap, alibi_slopes=alibi_slopes, q_doc_ids=q_doc_ids, kv_doc_ids=kv_doc_ids, q_offset=q_offset,
-               rmsnorm=rmsnorm, rms_eps=rms_eps)
+    variant = (float(q.shape[-1] ** -0.5 if scale is None else scale), _score_mod(softcap, alibi_slopes), float(softcap or 0.0),
+               _mask_bits(causal, window, prefix, q_doc_ids), int(window or 0), int(prefix or 0), int(q_offset), bool(rmsnorm),
+               float(rms_eps), alibi_slopes, q_doc_ids, kv_doc_ids)
     b0 = biases[0] if len(biases) > 0 else None
     b1 = biases[1] if len(biases) > 1 else None
-    return _VariantAttention.apply(cfg, q, k, v, q2, k2, lam, gate, b0, b1, rms_weight if rmsnorm else None)
+    return _VariantAttention.apply(variant, q, k, v, q2, k2, lam, gate, b0, b1, rms_weight if rmsnorm else None)
 
 
 def _paged_call(decode, q, k_cache, v_cache, seq_lens, block_table, max_seq_len, scale, window, softcap, alibi_slopes, workspace,

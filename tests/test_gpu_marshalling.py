@@ -79,3 +79,31 @@ def test_refusals():
     ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda:0")
     got, lse = F.decode_attention(q[:, :, 0], cache, cache, lens, table, workspace=ws, return_lse=True)
     assert torch.equal(got, want) and lse.shape == (1, 2) and bool(torch.isfinite(lse).all())
+
+
+def variant_step(q, k, v, **kw):
+    named = {n: t for n, t in kw.items() if isinstance(t, torch.Tensor)}
+    x = [t.detach().requires_grad_(True) for t in (q, k, v, *named.values())]
+    biases = [b.detach().requires_grad_(True) for b in kw.pop("biases", ())]
+    rest = {n: t for n, t in kw.items() if n not in named}
+    out = F.variant_attention(*x[:3], **dict(zip(named, x[3:])), biases=biases, **rest)
+    return (out.detach(),) + torch.autograd.grad(out, x + biases, torch.ones_like(out))
+
+
+@pytest.mark.parametrize("form", ["gate_bias", "two_streams", "norm_without_weight"])
+def test_variant_ranks_agree(form):
+    """[B, H, S, D] and [B, 1, H, S, D] reach the kernels as the same tensors, output and every gradient in its input's layout."""
+    q, k, v = (normal(2, 3, 70, 64, seed=n) for n in range(3))
+    if form == "gate_bias":
+        kw = dict(gate=normal(2, 3, 70, 64, seed=5), biases=[normal(1, 1, 3, 70, 70, seed=6), normal(2, 1, 1, 1, 70, seed=7)])
+    elif form == "two_streams":
+        kw = dict(q2=normal(2, 3, 70, 64, seed=5), k2=normal(2, 3, 70, 64, seed=6), lam=torch.linspace(0.2, 0.9, 3, device="cuda:0"),
+                  rms_weight=torch.linspace(0.5, 1.5, 64, device="cuda:0"), rmsnorm=True, causal=True)
+    else:
+        kw = dict(rmsnorm=True, gate=normal(2, 3, 70, 64, seed=5))
+    five = {n: t[:, None] if isinstance(t, torch.Tensor) and t.dim() == 4 else t for n, t in kw.items()}
+    for a, b in zip(variant_step(q, k, v, **dict(kw)), variant_step(q[:, None], k[:, None], v[:, None], **five)):
+        assert torch.isfinite(a).all()
+        assert torch.equal(a, b if a.dim() == b.dim() else b[:, 0])
+    with pytest.raises(ValueError, match="expected"):
+        F.variant_attention(q, k[0], v, **kw)
