@@ -302,7 +302,7 @@ const fl::BwdEntry* find_bwd_entry(const fl_variant_desc* d, int D, int nbias = 
   for (int t = 0; t < 3; ++t)
     for (int e = 0; e < reg.n[t]; ++e)
       if (reg.tab[t][e].key.D == D && reg.tab[t][e].key.Dv == D)
-        return fl::jit_backward_entry(D, (int)d->score_mod, canonical_mask(d->mask), nbias, reg.tab[t][e].prep, reg.tab[t][e].reduce);
+        return fl::jit_backward_entry(D, (int)d->score_mod, canonical_mask(d->mask), nbias, reg.tab[t][e].reduce);
   return nullptr;
 }
 
@@ -1717,9 +1717,6 @@ fl_status fl::backward_call(const fl_tensor* q, const fl_tensor* k, const fl_ten
     if ((e = hipGetLastError()) != hipSuccess) return fail(FL_ERR_LAUNCH, "doc summary launch: %s", hipGetErrorString(e));
   }
   if (!no_rows) {
-    const int lanes_per_row = (int)Dv / 8;
-    const int64_t nb_prep = (rows * lanes_per_row + 255) / 256;
-    if ((e = be->prep(p, (int)nb_prep, stream)) != hipSuccess) return fail(FL_ERR_LAUNCH, "pre-pass launch: %s", hipGetErrorString(e));
     // Sk == 0: the key loop is empty and dq comes out as zeros
     if ((e = run_bwd_dq(be, p, (int)nb_q, stream)) != hipSuccess) return fail(FL_ERR_LAUNCH, "dq launch: %s", hipGetErrorString(e));
   }

@@ -21,20 +21,20 @@ typedef hipError_t (*BwdLaunchFn)(const BwdParams& p, int nblocks, hipStream_t s
 struct BwdEntry {
   BwdKey key;
   int bm;           // query rows per workgroup of the dQ kernel = keys per workgroup of the dK/dV kernel
-  BwdLaunchFn prep, dq, dkdv, reduce;   // reduce: sum of the head-subset partials of dK / dV (nblocks of 256 threads)
+  BwdLaunchFn dq, dkdv, reduce;   // reduce: sum of the head-subset partials of dK / dV (nblocks of 256 threads)
   void* jit;        // entries instantiated at run time: their dq / dkdv are null and launched through jit_backward_launch
 };
 
 // A backward specialisation outside the compiled table, instantiated from the same kernel templates with hipRTC
-// on first use and kept for the life of the process (null if it does not compile).  prep / reduce: the compiled
-// pre-pass and partial-sum kernels of that head dim, which do not depend on the variant.
-const BwdEntry* jit_backward_entry(int D, int mod, uint32_t mask, int nbias, BwdLaunchFn prep, BwdLaunchFn reduce);
+// on first use and kept for the life of the process (null if it does not compile).  reduce: the compiled
+// partial-sum kernel of that head dim, which does not depend on the variant.
+const BwdEntry* jit_backward_entry(int D, int mod, uint32_t mask, int nbias, BwdLaunchFn reduce);
 // which: 0 = the dQ kernel, 1 = the dK/dV kernel
 hipError_t jit_backward_launch(const BwdEntry& e, int which, const BwdParams& p, int nblocks, hipStream_t stream);
 // A run-time entry around an already compiled code object with the two kernels (variants compiled from expressions);
 // owned by the caller, released with jit_backward_release.
 BwdEntry* jit_backward_wrap(const std::vector<char>& code, const std::string& dq_name, const std::string& dkdv_name, int D, int mod,
-                            uint32_t mask, BwdLaunchFn prep, BwdLaunchFn reduce);
+                            uint32_t mask, BwdLaunchFn reduce);
 void jit_backward_release(BwdEntry* e);
 
 template <class K>
@@ -51,11 +51,6 @@ hipError_t raise_lds_limit(K kernel) {
   return hipSuccess;
 }
 
-template <int DV>
-hipError_t launch_bwd_prep(const BwdParams& p, int nblocks, hipStream_t stream) {
-  hipLaunchKernelGGL(bwd_prep_kernel<DV>, dim3(nblocks), dim3(256), 0, stream, p);
-  return hipGetLastError();
-}
 template <int D, int DV>
 hipError_t launch_bwd_reduce(const BwdParams& p, int nblocks, hipStream_t stream) {
   hipLaunchKernelGGL((bwd_reduce_kv_kernel<D, DV>), dim3(nblocks, 2), dim3(256), 0, stream, p);
@@ -93,9 +88,9 @@ constexpr BwdEntry bwd_entry() {
   typedef BwdCfg<D, MOD, MASK, BN_Q, WPE_Q, NBIAS, DV> CQ;
   typedef BwdCfg<D, MOD, MASK, BN_K, WPE_K, NBIAS, DV> CK;
   if constexpr (WS)
-    return BwdEntry{BwdKey{D, MOD, (int)MASK, NBIAS, DV}, CQ::BM, &launch_bwd_prep<DV>, &launch_bwd_dq<CQ>, &launch_bwd_dkdv_ws<CK>, &launch_bwd_reduce<D, DV>, nullptr};
+    return BwdEntry{BwdKey{D, MOD, (int)MASK, NBIAS, DV}, CQ::BM, &launch_bwd_dq<CQ>, &launch_bwd_dkdv_ws<CK>, &launch_bwd_reduce<D, DV>, nullptr};
   else
-    return BwdEntry{BwdKey{D, MOD, (int)MASK, NBIAS, DV}, CQ::BM, &launch_bwd_prep<DV>, &launch_bwd_dq<CQ>, &launch_bwd_dkdv<CK>, &launch_bwd_reduce<D, DV>, nullptr};
+    return BwdEntry{BwdKey{D, MOD, (int)MASK, NBIAS, DV}, CQ::BM, &launch_bwd_dq<CQ>, &launch_bwd_dkdv<CK>, &launch_bwd_reduce<D, DV>, nullptr};
 }
 
 // The call behind fl_attn_bwd (fl_api.hip).  custom / user_aux: the backward kernels of a variant compiled at run time from

@@ -246,7 +246,7 @@ struct JitBackward {
 };
 }  // namespace
 
-const BwdEntry* jit_backward_entry(int D, int mod, uint32_t mask, int nbias, BwdLaunchFn prep, BwdLaunchFn reduce) {
+const BwdEntry* jit_backward_entry(int D, int mod, uint32_t mask, int nbias, BwdLaunchFn reduce) {
   typedef std::tuple<int, int, uint32_t, int> Key;
   static std::mutex mu;
   static std::map<Key, JitBackward*> cache;       // entries live until the process ends
@@ -275,7 +275,7 @@ const BwdEntry* jit_backward_entry(int D, int mod, uint32_t mask, int nbias, Bwd
   j->dkdv.code = j->dq.code;
   j->dq.kernel_name = names[0];
   j->dkdv.kernel_name = names[1];
-  j->entry = BwdEntry{BwdKey{D, mod, (int)mask, nbias, D}, 128, prep, nullptr, nullptr, reduce, j};
+  j->entry = BwdEntry{BwdKey{D, mod, (int)mask, nbias, D}, 128, nullptr, nullptr, reduce, j};
   cache[key] = j;
   return &j->entry;
 }
@@ -291,13 +291,13 @@ hipError_t jit_backward_launch(const BwdEntry& e, int which, const BwdParams& p,
 }
 
 BwdEntry* jit_backward_wrap(const std::vector<char>& code, const std::string& dq_name, const std::string& dkdv_name, int D, int mod,
-                            uint32_t mask, BwdLaunchFn prep, BwdLaunchFn reduce) {
+                            uint32_t mask, BwdLaunchFn reduce) {
   JitBackward* j = new JitBackward;
   j->dq.code = code;
   j->dkdv.code = code;
   j->dq.kernel_name = dq_name;
   j->dkdv.kernel_name = dkdv_name;
-  j->entry = BwdEntry{BwdKey{D, mod, (int)mask, 0, D}, 128, prep, nullptr, nullptr, reduce, j};
+  j->entry = BwdEntry{BwdKey{D, mod, (int)mask, 0, D}, 128, nullptr, nullptr, reduce, j};
   return &j->entry;
 }
 
@@ -368,7 +368,7 @@ static fl_status compile_backward(fl_custom_variant* v) {
   if (st != FL_OK) return st;
   int n = 0;
   const fl::BwdEntry* tab = v->D == 128 ? fl::entries_bwd128(&n) : fl::entries_bwd64(&n);
-  v->bwd = fl::jit_backward_wrap(code, names[0], names[1], v->D, mod, v->mask, tab[0].prep, tab[0].reduce);
+  v->bwd = fl::jit_backward_wrap(code, names[0], names[1], v->D, mod, v->mask, tab[0].reduce);
   return FL_OK;
 }
 
