@@ -762,7 +762,8 @@ fwd_bf16_kernel(const FwdParams call) {
   // (packed heads: bh counts groups of PACK heads)
   const int heads_wg = call.H / C::PACK;
   FwdParams p = call;
-  if (call.kv_lens != nullptr) {
+  constexpr bool kv_counts = (C::MASK & (kMaskDoc | kMaskCustom)) == 0 && C::MOD != kModCustom;   // the host passes none with these
+  if (kv_counts && call.kv_lens != nullptr) {
     const int seq_wgs = heads_wg * call.G;
     int b = bh / seq_wgs, len;
     if (call.B > 1 && call.B <= 64) {
