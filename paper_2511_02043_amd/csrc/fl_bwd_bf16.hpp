@@ -24,8 +24,8 @@
 //     accumulators fill a SIMD's registers) splits it over two specialised waves per SIMD.
 //     With grouped heads and few workgroups, the group's heads are cut over several workgroups
 //     whose fp32 partials bwd_reduce_kv_kernel adds in a fixed order.
-// A small pre-pass writes delta and the log2-scaled lse (+inf for rows without a visible key, so
-// that their probabilities come out as exactly 0).
+// The row statistics are delta and the log2-scaled lse (+inf for rows without a visible key, so that their probabilities come out
+// as exactly 0).
 //
 // LDS tiles are row-major [rows][D] bf16 with one 16-byte-chunk swizzle that serves both access
 // patterns without bank conflicts: the row read (32 consecutive rows, one chunk per lane) and
@@ -971,10 +971,11 @@ bwd_dkdv_kernel(const BwdParams p) {
     ks_wave = ksum[min(jw / kSumBlock, nks - 1)];
     scan_window();
   }
-  // first item at or after `it` whose q-tile holds a row that sees any of the workgroup's keys, and whether the wave's keys
-  // need the document mask in it
-  auto next_item = [&](Item it, bool& doc_mask) __attribute__((always_inline)) -> Item {
-    doc_mask = false;
+  // first item at or after `it` whose q-tile holds a row that sees any of the workgroup's keys, and what its document ids say
+  // about the wave's keys (Docs)
+  enum Docs { kDocsSame, kDocsMask, kDocsNone };   // all of one document; some; no row sees any of them
+  auto next_item = [&](Item it, int& docs) __attribute__((always_inline)) -> Item {
+    docs = kDocsSame;
     if constexpr (C::DOC) {
       while (it.h < group) {
         if (it.r < win.base || it.r >= win.base + 64) {
@@ -984,7 +985,7 @@ bwd_dkdv_kernel(const BwdParams p) {
         const unsigned long long rest = win.vis >> (it.r - win.base);
         if (rest != 0) {
           it.r += __builtin_ctzll(rest);
-          doc_mask = !same_document(win.at(it.r), ks_wave);
+          docs = same_document(win.at(it.r), ks_wave) ? kDocsSame : no_common_document(win.at(it.r), ks_wave) ? kDocsNone : kDocsMask;
           return it;
         }
         it.r = win.base + 64;
@@ -993,10 +994,10 @@ bwd_dkdv_kernel(const BwdParams p) {
     }
     return it;
   };
-  auto item_after = [&](Item it, bool& doc_mask) __attribute__((always_inline)) -> Item {
-    doc_mask = false;
+  auto item_after = [&](Item it, int& docs) __attribute__((always_inline)) -> Item {
+    docs = kDocsSame;
     if (it.h >= group) return it;
-    return next_item(it.r + 1 < nt ? Item{it.r + 1, it.h} : Item{0, it.h + 1}, doc_mask);
+    return next_item(it.r + 1 < nt ? Item{it.r + 1, it.h} : Item{0, it.h + 1}, docs);
   };
 
   // A whole tile's addresses: a uniform base and what this lane adds to it, the same for each of its load instructions (their rows
@@ -1205,7 +1206,7 @@ bwd_dkdv_kernel(const BwdParams p) {
   };
   static_assert(NB == 2, "a tile is two row blocks: the two score register sets swap roles twice per tile");
 
-  bool dm0 = false, dm1 = false, dm2 = false;      // do items it0, it1, it2 need the document mask?
+  int dm0 = 0, dm1 = 0, dm2 = 0;                   // Docs of it0, it1, it2
   Item it0 = nt > 0 ? next_item(Item{0, 0}, dm0) : Item{0, group};
   if (it0.h < group) {
     Item it1 = item_after(it0, dm1), it2 = item_after(it1, dm2);
@@ -1220,9 +1221,17 @@ bwd_dkdv_kernel(const BwdParams p) {
     while (it0.h < group) {
       const int stage_n = stage + 1 == NSTAGE ? 0 : stage + 1;
       const uint32_t base_c = stage * C::STAGE_KV, base_n = stage_n * C::STAGE_KV;
-      step(std::integral_constant<int, 0>(), std::integral_constant<int, 1>(), base_c, base_c, it0, it0, dm0, first, ba, bb);
-      step(std::integral_constant<int, 1>(), std::integral_constant<int, 0>(), base_c, base_n, it0, it1.h < group ? it1 : it0, dm0, false, bb, ba);
-      first = false;
+      // A tile of which this wave's keys are hidden is passed over (the workgroup's four waves walk one list, but the last wave's
+      // keys start 96 rows later, and may be of another document); the next one's first scores are then formed on entry.
+      // (windows and packed documents, 8 x 16 heads x 2048 rows, D = 64: 124 -> 121 us)
+      const int pos0 = (t_lo + it0.r) * BN + p.q_off;
+      const bool none = dm0 == kDocsNone ||
+                        classify_block(POS, pos0, pos0 + BN - 1, jw, jw + 31, p.Sk, p.window, p.prefix, make_int2(0, 0), make_int2(0, 0)) == kSkip;
+      if (!none) {
+        step(std::integral_constant<int, 0>(), std::integral_constant<int, 1>(), base_c, base_c, it0, it0, dm0 != kDocsSame, first, ba, bb);
+        step(std::integral_constant<int, 1>(), std::integral_constant<int, 0>(), base_c, base_n, it0, it1.h < group ? it1 : it0, dm0 != kDocsSame, false, bb, ba);
+      }
+      first = none;
       __builtin_amdgcn_s_waitcnt(0x0F70);          // the tile after next has landed ...
       __syncthreads();                             // ... for everyone, and everyone has left this tile
       it0 = it1;
