@@ -769,7 +769,8 @@ fwd_bf16_kernel(const FwdParams call) {
     // XCD-aware: consecutive workgroup ids go round-robin to the 8 XCDs; give each XCD whole
     // (b, g, h) problems so that a head's K/V stay in one L2 (host checks (B*G*H) % 8 == 0), and all order_heads problems
     // that read the same K/V one after the other (grouped-query heads; 1 where that leaves XCDs without work).
-    const int xcd = bid & 7, share = call.order_heads;
+    constexpr bool user = C::MOD == kModCustom || (C::MASK & kMaskCustom) != 0;   // (the host sets 1: no divisions by it)
+    const int xcd = bid & 7, share = user ? 1 : call.order_heads;
     const int idx = bid >> 3, inner = idx % (npairs * share);
     bh = ((idx / (npairs * share)) * 8 + xcd) * share + inner % share;
     pi = inner / share;
