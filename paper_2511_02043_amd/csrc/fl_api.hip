@@ -418,7 +418,7 @@ struct EpiBwdParams {
   const float* rms_w;
   float* dl_rows;                   // per-row terms of dlambda (summed per head by reduce_dlambda_kernel), or null
   float* dw_part;                   // per-workgroup partial sums of the rms_weight gradient, [workgroups, Dv], or null
-  float lse2_mul, delta_mul;        // factors of the stored lse2 and delta (stationary-bias kernels: -1 / (scale log2(e)) and -1)
+  float delta_mul;                  // factor of the stored delta (stationary-bias kernels: -1)
   float rms_eps;
   int32_t B, G, H, Sq, Dv, Dvc;
   int32_t ns, has_gate, has_rms, dgate_f32;
@@ -520,7 +520,7 @@ __global__ void __launch_bounds__(256) epi_bwd_kernel(const EpiBwdParams e) {
     }
     for (int s = 0; s < e.ns; ++s) {
       const float l = e.lse[b * e.lse_sb + (int64_t)(e.ns * g + s) * e.lse_sg + h * e.lse_sh + i];
-      e.lse2[s][row] = (l == -INFINITY ? INFINITY : l * fl::kLog2e) * e.lse2_mul;
+      e.lse2[s][row] = l == -INFINITY ? INFINITY : l * fl::kLog2e;
     }
   }
 }
@@ -671,7 +671,7 @@ __global__ void __launch_bounds__(256) epi_bwd_rows_kernel(const EpiBwdParams e)
     }
     for (int s = 0; s < e.ns; ++s) {
       const float l = e.lse[b * e.lse_sb + (int64_t)(e.ns * g + s) * e.lse_sg + h * e.lse_sh + i];
-      e.lse2[s][row] = (l == -INFINITY ? INFINITY : l * fl::kLog2e) * e.lse2_mul;
+      e.lse2[s][row] = l == -INFINITY ? INFINITY : l * fl::kLog2e;
     }
   }
 }
@@ -906,15 +906,14 @@ __global__ void __launch_bounds__(256) reduce_pair_bias_kernel(const PairBiasPar
   }
 }
 
-// Key bias of the stationary-bias kernels: bias * log2(e) / c in fp32, [b][g][h] rows of n_key (zeros past Sk); b, g, h run over the
-// bias's own axes.
-__global__ void __launch_bounds__(256) fold_key_bias_kernel(const fl::BiasView bias, float* dst, int og, int oh, int Sk, int n_key, float mul, int64_t total) {
+// Key bias of the stationary-bias kernels in fp32, [b][g][h] rows of n_key (zeros past Sk); b, g, h run over the bias's own axes.
+__global__ void __launch_bounds__(256) widen_key_bias_kernel(const fl::BiasView bias, float* dst, int og, int oh, int Sk, int n_key, int64_t total) {
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= total) return;
   const int j = (int)(idx % n_key);
   const int64_t row = idx / n_key;
   const int h = (int)(row % oh), g = (int)((row / oh) % og), b = (int)(row / ((int64_t)oh * og));
-  dst[idx] = j < Sk ? fl::bf16_to_f32(((const uint16_t*)bias.ptr)[b * bias.sb + g * bias.sg + h * bias.sh + (int64_t)j * bias.sj]) * mul : 0.f;
+  dst[idx] = j < Sk ? fl::bf16_to_f32(((const uint16_t*)bias.ptr)[b * bias.sb + g * bias.sg + h * bias.sh + (int64_t)j * bias.sj]) : 0.f;
 }
 
 // Key bias gradient: the sums over the query rows [B, G, H, Sk], added over the axes the bias broadcasts along (sizes ob, og, oh).
@@ -1049,7 +1048,7 @@ int pair_chunks(int64_t B, int64_t G, int64_t H, int64_t S_own) {
 // against 708 us with the general kernels; x 384: 400 against 424; D = 32, x 500: 310 against 578).
 bool pair_sizes_ok(int64_t G, int64_t H, int64_t Hkv, int64_t Sq, int64_t Sk, int64_t D, int64_t Dv, const fl_variant_desc* d) {
   return d->n_bias > 0 && d->score_mod == FL_MOD_NONE && d->mask == 0 && d->combine == FL_SINGLE && H == Hkv && D == Dv && (D == 32 || D == 64) &&
-         G >= 2 && Sq >= 1 && Sk >= 1 && std::max(Sq, Sk) <= (D == 32 ? 512 : 384) && d->scale > 1e-20f && d->scale < 1e20f;
+         G >= 2 && Sq >= 1 && Sk >= 1 && std::max(Sq, Sk) <= (D == 32 ? 512 : 384);
 }
 struct PairLayout {
   int chunks_q, chunks_k, nqb, nkb, n_key;
@@ -1162,8 +1161,8 @@ hipError_t run_pair_bwd(const fl::BwdParams& call, int D, int pair, int keyb, co
     const int64_t* z = aux->bias[keyb].size;
     const int64_t total = z[0] * z[1] * z[2] * P.n_key;
     float* key = (float*)(ws + P.off_key);
-    hipLaunchKernelGGL(fold_key_bias_kernel, blocks(total, 256), dim3(256), 0, stream, call.bias[keyb], key, (int)z[1], (int)z[2], Sk, P.n_key,
-                       1.f / call.scale, total);       // log2(e) / (scale log2(e))
+    hipLaunchKernelGGL(widen_key_bias_kernel, blocks(total, 256), dim3(256), 0, stream, call.bias[keyb], key, (int)z[1], (int)z[2], Sk, P.n_key,
+                       total);
     p.key = key;
     p.key_sh = z[2] == 1 ? 0 : P.n_key;
     p.key_sg = z[1] == 1 ? 0 : z[2] * P.n_key;
@@ -1921,7 +1920,6 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
     }
     if ((pair >= 0) + (keyb >= 0) != (int)desc->n_bias) pair = -1;
   }
-  ep.lse2_mul = pair >= 0 ? -1.f / (desc->scale * fl::kLog2e) : 1.f;
   ep.delta_mul = pair >= 0 ? -1.f : 1.f;
   // rows 16-byte aligned everywhere: several rows per wave, eight channels per lane; else one row per wave
   auto rows_aligned = [](const fl::View& v, int elem_bytes) {

@@ -20,16 +20,16 @@
 // general kernels took 140 + 64 (reduction of the staged dS) / 146 us.
 // The accumulators of a problem are partial over kq: the four waves of a row group meet in LDS, each sums and stores a quarter of
 // the channels, in a fixed order (bitwise reproducible, no atomics).
-// The row statistics come folded into the accumulators' starting values: s = <k, q> - lse / scale, dp = <v, dO> - delta, so that
-// P = exp2(s * c + bias) and dS = P * dp take one instruction each beside the exponential.
+// delta comes folded into the accumulator's starting value, dp = <v, dO> - delta.  lse does not: it meets the bias in log2 units, as
+// in the general dQ kernel (pair_exponent).
 #pragma once
 #include "fl_decode_bf16.hpp"
 
 namespace fl {
 
 struct PairParams {
-  BwdParams b;                     // bias[0]: the pair bias (sg unused); lse2: -lse / scale (-inf: dead row); delta: -delta
-  const float* key;                // key bias times log2(e) / c in fp32, [.., n_key] (n_key: Sk rounded up to 128), or null
+  BwdParams b;                     // bias[0]: the pair bias (sg unused); delta: -delta
+  const float* key;                // key bias in fp32, [.., n_key] (n_key: Sk rounded up to 128), or null
   int64_t key_sb, key_sg, key_sh;
   float* bias_part;                // dQ kernel, or null: partial bias gradients [chunks][B][H][ceil(Sq / 32)][ceil(Sk / 32)][1024]
   float* key_part;                 // dK/dV kernel, or null: sums of dS over the query rows, [B, G, H, Sk]
@@ -50,11 +50,11 @@ struct PairCfg : BwdCfg<D_, kModNone, 0, 128, 2, 1> {
   // for the end of the step.  Two stages at head dim 32 (one: 90 / 96 us instead of 77 / 86); at 64 the LDS holds one.
   static constexpr int NSTG = D_ == 32 ? 2 : 1;
   static constexpr int STEP_TILE = 32 * Base::ROW;                   // 32 rows of one streamed tensor
-  static constexpr int STEP_STAT = 2 * STEP_TILE;                    // role 1: -lse / scale, -delta of the rows
+  static constexpr int STEP_STAT = 2 * STEP_TILE;                    // role 1: lse2, -delta of the rows
   static constexpr int STEP = STEP_STAT + (ROLE == 1 ? 256 : 0);
   static constexpr int WAVE_RING = NSTG * STEP;
   static constexpr int OWN_TILE = 64 * Base::ROW;                    // the owned rows of a problem: Q, dO (role 0) or K, V
-  static constexpr int OWN_STAT = 2 * OWN_TILE;                      // role 0: -lse / scale, -delta of the rows
+  static constexpr int OWN_STAT = 2 * OWN_TILE;                      // role 0: lse2, -delta of the rows
   static constexpr int OWN_KEY = OWN_STAT + (ROLE == 0 ? 2 * 64 * 4 : 0);
   static constexpr int OWN = OWN_KEY + (KEYB ? (ROLE == 0 ? NBLK * 128 * 4 : 64 * 4) : 0);
   static constexpr int OWN_RING = 8 * WAVE_RING;
@@ -68,8 +68,9 @@ struct PairCfg : BwdCfg<D_, kModNone, 0, 128, 2, 1> {
   static constexpr int NSPACE = D_ == 32 ? NX : 1;
   static constexpr int XSUM = XCH + (XTWICE ? 2 : 1) * NSPACE * XBLK;
   static constexpr int LDS = XSUM + (ROLE == 1 && KEYB ? 8 * 256 : 0);
-  // the bias in fp32, ready for the exponent, where the registers allow it; else as bf16 pairs (two instructions more per score)
-  static constexpr bool BIAS_F32 = ROLE == 1 ? D_ == 32 || NBLK <= 2 : NBLK <= (D_ == 32 ? 3 : 2);
+  // the bias in fp32, in log2 units unless a key bias is added first, where the registers allow it; else as bf16 pairs (one or two
+  // instructions more per score)
+  static constexpr bool BIAS_F32 = ROLE == 1 ? D_ == 32 || NBLK <= (KEYB ? 1 : 2) : NBLK <= (D_ == 32 ? 3 : 2);
   static constexpr bool OWN_REGS = D_ == 32;                         // the owned rows' fragments stay in registers for a problem
   static constexpr int STEP_INSTR = 2 * (STEP_TILE / 1024) + (ROLE == 1 ? 1 : 0);   // vector memory loads per wave and step
 };
@@ -85,6 +86,21 @@ __device__ __forceinline__ void read_b32(float& dst, uint32_t addr) {   // by ha
   asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
 }
 __device__ __forceinline__ void write_b32(uint32_t addr, float v) { asm volatile("ds_write_b32 %0, %1" : : "v"(addr), "v"(v) : "memory"); }
+
+// The sum of a score's biases in log2 units, a rounding of its own: never half of an FMA (pair_exponent)
+__device__ __forceinline__ float bias_log2(float sum) {
+#pragma clang fp contract(off)
+  return sum * kLog2e;
+}
+// The argument of P = exp2(s c + bias - lse), lse2 and bl (the biases) in log2 units, in the order of the general dQ kernel.  A row
+// problem all of whose keys are hidden by a large finite bias has lse = bias up to its rounding, and the two have to cancel:
+// the rounded bl against the rounded lse2.  What is left can still be a few units in the last place of numbers like 1e9, in either
+// direction, so that the argument is bounded by what it is mathematically, P <= 1.  NaN stays NaN.
+__device__ __forceinline__ float pair_exponent(float s, float c_scale, float lse2, float bl) {
+#pragma clang fp contract(off)
+  const float a = fmaf(s, c_scale, -lse2) + bl;
+  return __builtin_elementwise_minimum(a, 0.f);
+}
 
 template <class C>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -158,8 +174,9 @@ bwd_pair_kernel(const PairParams pp) {
 #pragma unroll
       for (int r2 = 0; r2 < 8; ++r2) {
         if constexpr (C::BIAS_F32) {
-          blf[t][2 * r2] = __uint_as_float(raw[t][r2] << 16) * kLog2e;
-          blf[t][2 * r2 + 1] = __uint_as_float(raw[t][r2] & 0xFFFF0000u) * kLog2e;
+          const float x0 = __uint_as_float(raw[t][r2] << 16), x1 = __uint_as_float(raw[t][r2] & 0xFFFF0000u);
+          blf[t][2 * r2] = C::KEYB ? x0 : bias_log2(x0);
+          blf[t][2 * r2 + 1] = C::KEYB ? x1 : bias_log2(x1);
           asm volatile("" : "+v"(blf[t][2 * r2]), "+v"(blf[t][2 * r2 + 1]));   // (worked out here, not again in every step)
         } else {
           blp[t][r2] = raw[t][r2];
@@ -265,7 +282,7 @@ bwd_pair_kernel(const PairParams pp) {
 #pragma unroll
     for (int t = 0; t < NBLK; ++t) db[t] = W::zero16();
   // A operands: the identity over rows 0 .. 15 and 16 .. 31 of a block (element e of half h is row 8 (e / 4) + 4 h + e % 4 of
-  // the sixteen), and ones in contraction indices 0 .. 2, which adds the three bf16 parts of a statistic to every score.
+  // the sixteen), and ones in contraction indices 0 .. 2, which adds the three bf16 parts of -delta to every dP.
   bf16x8 eye[2], ones;
   if constexpr (ROLE == 0) {
 #pragma unroll
@@ -280,14 +297,15 @@ bwd_pair_kernel(const PairParams pp) {
     }
     ones = __builtin_bit_cast(bf16x8, (i32x4){w.half == 0 ? 0x3F803F80 : 0, w.half == 0 ? 0x3F80 : 0, 0, 0});
   }
-  // a statistic as the sum of three bf16 values (24 bits in all), contraction indices 0 .. 2 of the B operand.  A dead row's
-  // -inf becomes the lowest bf16 value: its P is 0 all the same, and no part of the split is -inf - -inf.
+  // x as the sum of three bf16 values of eight bits each, cut and not rounded (rounded, the first could overflow), in contraction
+  // indices 0 .. 2 of the B operand.  An infinity or NaN leaves NaN in the sum.
   auto three = [&](float x) __attribute__((always_inline)) -> bf16x8 {
-    x = fmaxf(x, -3.3895313892515355e38f);
-    const float hi = __uint_as_float(pack_bf16(x, 0.f) << 16), r1 = x - hi;
-    const float mid = __uint_as_float(pack_bf16(r1, 0.f) << 16), lo = r1 - mid;
+    const uint32_t hi = __float_as_uint(x) & 0xFFFF0000u;
+    const float r1 = x - __uint_as_float(hi);
+    const uint32_t mid = __float_as_uint(r1) & 0xFFFF0000u;
+    const uint32_t lo = __float_as_uint(r1 - __uint_as_float(mid)) >> 16;
     const bool on = w.half == 0;
-    return __builtin_bit_cast(bf16x8, (i32x4){on ? (int)pack_bf16(hi, mid) : 0, on ? (int)pack_bf16(lo, 0.f) : 0, 0, 0});
+    return __builtin_bit_cast(bf16x8, (i32x4){on ? (int)((hi >> 16) | mid) : 0, on ? (int)lo : 0, 0, 0});
   };
 
   // ---- hand-over at the end of a problem: register quad o of every channel block goes to wave o of the row group
@@ -405,8 +423,8 @@ bwd_pair_kernel(const PairParams pp) {
     const int g = g_lo + n;
     const uint32_t par = n & 1, ob = par * C::OWN;
     bf16x8 uf[C::OWN_REGS ? KK : 1], vf[C::OWN_REGS ? KK : 1];         // the owned rows as B operands
-    bf16x8 s3, d3;                                 // role 0: -lse / scale and -delta of this lane's row
-    float kb = 0.f;                                // role 1: this lane's key bias, log2 units
+    bf16x8 d3;                                     // role 0: -delta of this lane's row
+    float st0 = 0.f;                               // role 0: lse2 of this lane's row; 1: the bias of its key
     static_for<0, NBLK>([&](auto tc) __attribute__((always_inline)) {
       constexpr int t = decltype(tc)::value;
       if constexpr (t == 0) {
@@ -418,7 +436,7 @@ bwd_pair_kernel(const PairParams pp) {
             W::template read_b128<0>(fr[kk], ur[kk] + ob);
             W::template read_b128<C::OWN_TILE>(fr[KK + kk], ur[kk] + ob);
           });
-        float st0 = 0.f, st1 = 0.f;
+        float st1 = 0.f;
         const uint32_t sa = C::OWN_RING + ob + (32 * rg + w.col) * 4;
         if constexpr (ROLE == 0) {
           read_b32<C::OWN_STAT>(st0, sa);
@@ -433,11 +451,7 @@ bwd_pair_kernel(const PairParams pp) {
             uf[kk] = __builtin_bit_cast(bf16x8, fr[kk]);
             vf[kk] = __builtin_bit_cast(bf16x8, fr[KK + kk]);
           }
-        kb = st0 * c_scale;
-        if constexpr (ROLE == 0) {
-          s3 = three(st0);
-          d3 = three(st1);
-        }
+        if constexpr (ROLE == 0) d3 = three(st1);
         ksum = 0.f;
         if (n > 0) take_all(g - 1, par ^ 1);
       }
@@ -445,32 +459,28 @@ bwd_pair_kernel(const PairParams pp) {
       asm volatile("" ::: "memory");
       {
         i32x4 ql[4], qd[4], fx[C::OWN_REGS ? 2 * KK : 1];
-        if constexpr (ROLE == 1) {                 // starting values of the accumulators: the rows' statistics
-          const uint32_t sa = wave * C::WAVE_RING + base + w.half * 16;
+        const uint32_t stat_a = wave * C::WAVE_RING + base + w.half * 16;
+        if constexpr (ROLE == 1)                   // the rows' -delta
           static_for<0, 4>([&](auto qc) __attribute__((always_inline)) {
-            W::template read_b128<C::STEP_STAT + decltype(qc)::value * 32>(ql[decltype(qc)::value], sa);
-            W::template read_b128<C::STEP_STAT + 128 + decltype(qc)::value * 32>(qd[decltype(qc)::value], sa);
+            W::template read_b128<C::STEP_STAT + 128 + decltype(qc)::value * 32>(qd[decltype(qc)::value], stat_a);
           });
-        } else if constexpr (C::KEYB) {
-          const uint32_t sa = C::OWN_RING + ob + (32 * kq + 4 * w.half) * 4;
+        // role 1: the rows' lse2; 0: the keys' biases.  Behind the matrix work: there is no room for them beside its operands
+        auto read_terms = [&]() __attribute__((always_inline)) {
+          __builtin_amdgcn_sched_barrier(0);
+          const uint32_t key_a = C::OWN_RING + ob + (32 * kq + 4 * w.half) * 4;
           static_for<0, 4>([&](auto qc) __attribute__((always_inline)) {
-            W::template read_b128<C::OWN_KEY + t * 512 + decltype(qc)::value * 32>(ql[decltype(qc)::value], sa);
+            constexpr int q = decltype(qc)::value;
+            if constexpr (ROLE == 1) W::template read_b128<C::STEP_STAT + q * 32>(ql[q], stat_a);
+            else if constexpr (C::KEYB) W::template read_b128<C::OWN_KEY + t * 512 + q * 32>(ql[q], key_a);
           });
-        }
+        };
         f32x16 sc = W::zero16(), dp = W::zero16();
-        auto start = [&]() __attribute__((always_inline)) {             // behind the wait that covers ql, qd
+        auto start = [&]() __attribute__((always_inline)) {             // behind the wait that covers qd: dp starts at -delta
           if constexpr (ROLE == 1) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              sc[r] = __int_as_float(ql[r >> 2][r & 3]);
-              dp[r] = __int_as_float(qd[r >> 2][r & 3]);
-            }
+            for (int r = 0; r < 16; ++r) dp[r] = __int_as_float(qd[r >> 2][r & 3]);
           } else {
-            if constexpr (C::KEYB)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) sc[r] = __int_as_float(ql[r >> 2][r & 3]);
             asm volatile("" : "+v"(ones));         // (formed anew for every block: a copy of sixteen registers costs more)
-            sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, s3, sc, 0, 0, 0);
             dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, d3, dp, 0, 0, 0);
           }
         };
@@ -514,6 +524,7 @@ bwd_pair_kernel(const PairParams pp) {
               });
           read_transposed();
         }
+        read_terms();
         W::template wait_lds<0>();                 // every fragment is in registers: the stage takes the step NSTG ahead
         next_load(std::integral_constant<int, (t + NSTG) % NBLK>(), base);
         if constexpr (NSTG > 1) base = base == (NSTG - 1) * C::STEP ? 0 : base + C::STEP;
@@ -526,9 +537,13 @@ bwd_pair_kernel(const PairParams pp) {
             const int r = 2 * r2 + e;
             float bl;
             if constexpr (C::BIAS_F32) bl = blf[C::BIAS_F32 ? t : 0][r];
-            else bl = __uint_as_float(e ? (blp[C::BIAS_F32 ? 0 : t][r2] & 0xFFFF0000u) : (blp[C::BIAS_F32 ? 0 : t][r2] << 16)) * kLog2e;
-            if constexpr (ROLE == 1 && C::KEYB) bl += kb;
-            pv[e] = fast_exp2(fmaf(sc[r], c_scale, bl));
+            // (by hand: the compiler would unpack all of them in front of the loop over the problems and run out of registers)
+            else if (e == 0) asm volatile("v_lshlrev_b32 %0, 16, %1" : "=v"(bl) : "v"(blp[C::BIAS_F32 ? 0 : t][r2]));
+            else asm volatile("v_and_b32 %0, 0xffff0000, %1" : "=v"(bl) : "v"(blp[C::BIAS_F32 ? 0 : t][r2]));
+            const float st_r = ROLE == 1 || C::KEYB ? __int_as_float(ql[r >> 2][r & 3]) : 0.f;
+            if constexpr (C::KEYB) bl += ROLE == 0 ? st_r : st0;
+            if constexpr (C::KEYB || !C::BIAS_F32) bl = bias_log2(bl);
+            pv[e] = fast_exp2(pair_exponent(sc[r], c_scale, ROLE == 0 ? st0 : st_r, bl));
             ds[e] = pv[e] * dp[r];
             if constexpr (ROLE == 1 && C::KEYB) ksum += ds[e];
           }

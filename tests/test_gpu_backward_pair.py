@@ -87,3 +87,59 @@ def test_hidden_keys(hide):
     old = _grads(w, inputs.dout_for(w), 1)
     for n in g:
         assert np.linalg.norm(g[n] - old[n]) <= 4e-3 * np.linalg.norm(old[n]), n
+
+
+def _workload_with_hidden(D, value, by):
+    """Six row problems; all keys of row problem 4 (by a key bias) or of query row 7 (by the pair bias) get `value`, the rest of both
+    biases as drawn."""
+    w = inputs.evoformer_bf16(B=1, Nseq=6, Nres=150, H=2, D=D, two_biases=True, salt=9)
+    pair, key = (x.copy() for x in w.biases)
+    if by == "key":
+        key[0, 4] = value
+    else:
+        pair[0, 0, :, 7] = value
+    w.biases = (inputs.round_to_bf16(pair), inputs.round_to_bf16(key))
+    dout = inputs.dout_for(w)
+    rows = (0, 4) if by == "key" else (0, slice(None), slice(None), 7)     # of q, dq and dout
+    return w, dout, rows
+
+
+# bf16 numbers at which lse * log2(e) and bias * log2(e) differ by up to a unit in the last place of numbers of that size (128 near
+# 1e9, far beyond what exp2 takes), larger ones, and half of the type's lowest value
+LARGE = [-1e4, -1e9, -7.93e8, -3.1e9, -1e10, -1e20, -1e38, -1.69e38]
+
+
+@pytest.mark.parametrize("by", ["key", "pair"])
+@pytest.mark.parametrize("value", LARGE)
+@pytest.mark.parametrize("D", [32, 64])
+def test_rows_hidden_by_finite_bias(D, value, by):
+    """A row all of whose keys are hidden by a large finite bias (padding).  Its lse is that bias up to rounding; P is at most 1 all
+    the same.  Where its dO is zero it contributes nothing to any gradient; else the contribution is finite and bounded."""
+    w, dout, rows = _workload_with_hidden(D, value, by)
+    full = _grads(w, dout, 0)
+    silent = dout.copy()
+    silent[rows] = 0
+    got = _grads(w, silent, 0)
+    dead, _, _ = _workload_with_hidden(D, -np.inf, by)
+    want = _grads(dead, silent, 0)                 # P = 0 there: the sums over the other rows alone
+    for n in got:
+        assert np.all(np.isfinite(full[n])) and np.all(np.isfinite(got[n])), n
+        assert np.array_equal(got[n], want[n]), n
+    assert np.all(got["dq0"][rows] == 0)
+    if by == "key":                                # |dV| <= sum over the queries of P |dO| with P <= 1, dO and P rounded to bf16
+        bound = np.abs(dout[0, 4]).sum(axis=1, keepdims=True)
+        assert np.all(np.abs(full["dv0"][0, 4]) <= bound * (1 + 2.0 ** -6))
+
+
+def test_nan_stays_where_it_is():
+    """A NaN bias value and a NaN in V spoil the same gradients as with the general kernels, no more and no fewer."""
+    w = inputs.evoformer_bf16(B=1, Nseq=4, Nres=70, H=2, D=32, salt=3)
+    pair, v = w.biases[0].copy(), w.v.copy()
+    pair[0, 0, 0, 5, 9] = np.nan
+    v[0, 2, 1, 40, 3] = np.nan
+    w.biases, w.v = (pair,), v
+    dout = inputs.dout_for(w)
+    new, old = _grads(w, dout, 0), _grads(w, dout, 1)
+    for n in new:
+        assert np.array_equal(np.isnan(new[n]), np.isnan(old[n])), n
+    assert np.isnan(new["dq0"][0, 0, 0, 5]).all() and not np.isnan(new["dq0"][0, 0, 0, 6]).any()
