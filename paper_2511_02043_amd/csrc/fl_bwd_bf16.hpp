@@ -439,6 +439,20 @@ __device__ __forceinline__ bool hidden(bool outside, int i, int j, const BwdPara
   return false;
 }
 
+// The sum of a score's biases in log2 units, a rounding of its own: never half of an FMA (biased_exponent)
+__device__ __forceinline__ float bias_log2(float sum) {
+#pragma clang fp contract(off)
+  return sum * kLog2e;
+}
+// The argument of P = exp2(score + biases - lse) from a = score - lse and the biases, in log2 units.  A row all of whose keys are hidden
+// by a large finite bias has lse = bias up to its rounding, and the two have to cancel: the rounded biases against the rounded lse.
+// What is left can still be a few units in the last place of numbers like 1e9, in either direction, so that the argument is
+// bounded by what it is mathematically, P <= 1.  NaN stays NaN.
+__device__ __forceinline__ float biased_exponent(float a, float bl) {
+#pragma clang fp contract(off)
+  return __builtin_elementwise_minimum(a + bl, 0.f);
+}
+
 // Offsets of the (b, g, h) slice of each bias / bias gradient (elements).
 template <int NBIAS>
 struct BiasHead {
@@ -470,7 +484,7 @@ struct BiasHead {
 #pragma unroll
     for (int n = 0; n < NBIAS; ++n)
       s += bf16_to_f32(((const uint16_t*)p.bias[n].ptr)[off[n] + (int64_t)i * p.bias[n].si + (int64_t)j * p.bias[n].sj]);
-    return s * kLog2e;
+    return bias_log2(s);
   }
 };
 
@@ -757,7 +771,7 @@ bwd_dq_kernel(const BwdParams p) {
               const uint32_t wd = (r & 2) ? bq[n][r >> 2].y : bq[n][r >> 2].x;
               sum += __uint_as_float((r & 1) ? (wd & 0xFFFF0000u) : (wd << 16));
             }
-            bl[r] = sum * kLog2e;
+            bl[r] = bias_log2(sum);
           }
         } else {
 #pragma unroll
@@ -765,7 +779,7 @@ bwd_dq_kernel(const BwdParams p) {
             float sum = 0.f;
 #pragma unroll
             for (int n = 0; n < C::NBIAS; ++n) sum += bf16_to_f32(b1[n][r]);
-            bl[r] = sum * kLog2e;
+            bl[r] = bias_log2(sum);
           }
         }
       }
@@ -792,7 +806,7 @@ bwd_dq_kernel(const BwdParams p) {
           float a;
           if constexpr (C::MOD == kModCustom) a = replay_user<C::MOD>(s[r], p, uctx, lse2, b, g, h, i, j, fac);
           else a = replay_score<C::MOD>(s[r], c_scale, lse2, p.softcap, slope2, (float)(i + p.q_off - j), fac);
-          if constexpr (C::NBIAS > 0) a += bl[r];
+          if constexpr (C::NBIAS > 0) a = biased_exponent(a, bl[r]);
           pr[e] = fast_exp2(a);
           dbv[e] = dp[r] - delta;
           dsv[e] = (C::MOD == kModSoftcap || C::MOD == kModCustom) ? dbv[e] * fac : dbv[e];
@@ -1147,7 +1161,7 @@ bwd_dkdv_kernel(const BwdParams p) {
         if constexpr (C::NBIAS > 0) {
           float sum = bf16_to_f32(cur.bias[0][r]);
           if constexpr (C::NBIAS > 1) sum += bf16_to_f32(cur.bias[NBR - 1][r]);
-          a = fmaf(sum, kLog2e, a);
+          a = biased_exponent(a, bias_log2(sum));
         }
         pv[e] = fast_exp2(a);
         dsv[e] = cur.dp[r] - delta;
@@ -1481,7 +1495,7 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
           const int i = irow + 8 * (r >> 2) + (r & 3);
           const float lse2 = __int_as_float(st_l[r >> 2][r & 3]);
           float a = replay_score<C::MOD>(cur[r], c_scale, lse2, p.softcap, slope2, (float)(i + p.q_off - j), fc2[e]);
-          if constexpr (C::NBIAS > 0) a += bl[r];
+          if constexpr (C::NBIAS > 0) a = biased_exponent(a, bl[r]);
           pv[e] = fast_exp2(a);
         }
         if (need_mask) {                           // uniform; kept a branch: most blocks need no mask

@@ -21,7 +21,7 @@
 // The accumulators of a problem are partial over kq: the four waves of a row group meet in LDS, each sums and stores a quarter of
 // the channels, in a fixed order (bitwise reproducible, no atomics).
 // delta comes folded into the accumulator's starting value, dp = <v, dO> - delta.  lse does not: it meets the bias in log2 units, as
-// in the general dQ kernel (pair_exponent).
+// in the general kernels (biased_exponent).
 #pragma once
 #include "fl_decode_bf16.hpp"
 
@@ -86,21 +86,6 @@ __device__ __forceinline__ void read_b32(float& dst, uint32_t addr) {   // by ha
   asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
 }
 __device__ __forceinline__ void write_b32(uint32_t addr, float v) { asm volatile("ds_write_b32 %0, %1" : : "v"(addr), "v"(v) : "memory"); }
-
-// The sum of a score's biases in log2 units, a rounding of its own: never half of an FMA (pair_exponent)
-__device__ __forceinline__ float bias_log2(float sum) {
-#pragma clang fp contract(off)
-  return sum * kLog2e;
-}
-// The argument of P = exp2(s c + bias - lse), lse2 and bl (the biases) in log2 units, in the order of the general dQ kernel.  A row
-// problem all of whose keys are hidden by a large finite bias has lse = bias up to its rounding, and the two have to cancel:
-// the rounded bl against the rounded lse2.  What is left can still be a few units in the last place of numbers like 1e9, in either
-// direction, so that the argument is bounded by what it is mathematically, P <= 1.  NaN stays NaN.
-__device__ __forceinline__ float pair_exponent(float s, float c_scale, float lse2, float bl) {
-#pragma clang fp contract(off)
-  const float a = fmaf(s, c_scale, -lse2) + bl;
-  return __builtin_elementwise_minimum(a, 0.f);
-}
 
 template <class C>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -543,7 +528,7 @@ bwd_pair_kernel(const PairParams pp) {
             const float st_r = ROLE == 1 || C::KEYB ? __int_as_float(ql[r >> 2][r & 3]) : 0.f;
             if constexpr (C::KEYB) bl += ROLE == 0 ? st_r : st0;
             if constexpr (C::KEYB || !C::BIAS_F32) bl = bias_log2(bl);
-            pv[e] = fast_exp2(pair_exponent(sc[r], c_scale, ROLE == 0 ? st0 : st_r, bl));
+            pv[e] = fast_exp2(biased_exponent(fmaf(sc[r], c_scale, ROLE == 0 ? -st0 : -st_r), bl));
             ds[e] = pv[e] * dp[r];
             if constexpr (ROLE == 1 && C::KEYB) ksum += ds[e];
           }

@@ -109,19 +109,20 @@ def _workload_with_hidden(D, value, by):
 LARGE = [-1e4, -1e9, -7.93e8, -3.1e9, -1e10, -1e20, -1e38, -1.69e38]
 
 
+@pytest.mark.parametrize("tune", [0, 1])           # these kernels, the general ones
 @pytest.mark.parametrize("by", ["key", "pair"])
 @pytest.mark.parametrize("value", LARGE)
 @pytest.mark.parametrize("D", [32, 64])
-def test_rows_hidden_by_finite_bias(D, value, by):
+def test_rows_hidden_by_finite_bias(D, value, by, tune):
     """A row all of whose keys are hidden by a large finite bias (padding).  Its lse is that bias up to rounding; P is at most 1 all
     the same.  Where its dO is zero it contributes nothing to any gradient; else the contribution is finite and bounded."""
     w, dout, rows = _workload_with_hidden(D, value, by)
-    full = _grads(w, dout, 0)
+    full = _grads(w, dout, tune)
     silent = dout.copy()
     silent[rows] = 0
-    got = _grads(w, silent, 0)
+    got = _grads(w, silent, tune)
     dead, _, _ = _workload_with_hidden(D, -np.inf, by)
-    want = _grads(dead, silent, 0)                 # P = 0 there: the sums over the other rows alone
+    want = _grads(dead, silent, tune)               # P = 0 there: the sums over the other rows alone
     for n in got:
         assert np.all(np.isfinite(full[n])) and np.all(np.isfinite(got[n])), n
         assert np.array_equal(got[n], want[n]), n
@@ -129,6 +130,23 @@ def test_rows_hidden_by_finite_bias(D, value, by):
     if by == "key":                                # |dV| <= sum over the queries of P |dO| with P <= 1, dO and P rounded to bf16
         bound = np.abs(dout[0, 4]).sum(axis=1, keepdims=True)
         assert np.all(np.abs(full["dv0"][0, 4]) <= bound * (1 + 2.0 ** -6))
+
+
+@pytest.mark.parametrize("offset", [0.0, -30.0, -1e4])
+@pytest.mark.parametrize("D,n_bias", [(32, 1), (32, 2), (64, 1), (64, 2)])
+def test_exponents_are_those_of_the_general_kernels(D, n_bias, offset):
+    """The exponent of every score is formed as in the general kernels, so an offset that all keys of a row share costs no more
+    than it does there.  What may differ: delta enters in front of the sum over the channels instead of behind it, 2^-24 of
+    |delta| + |dP|, which turns the bf16 rounding (2^-8 apart) of about one dS in 2^14 by 2^-8: 2^-15 of the norm; bound 1e-4."""
+    w = inputs.evoformer_bf16(B=1, Nseq=5, Nres=150, H=2, D=D, two_biases=n_bias == 2, salt=4)
+    if offset:                                     # (-1e4 and normal numbers have no sum in bf16: the last bias is the offset alone)
+        w.biases = w.biases[:-1] + (inputs.round_to_bf16(np.full_like(w.biases[-1], offset)),)
+    dout = inputs.dout_for(w)
+    new, old = _grads(w, dout, 0), _grads(w, dout, 1)
+    for n in ("dq0", "dk0", "dv0", "dbias0"):
+        rel = np.linalg.norm(new[n] - old[n]) / np.linalg.norm(old[n])
+        print(f"D {D} biases {n_bias} offset {offset} {n}: {rel:.2e}", flush=True)
+        assert rel <= 1e-4, n
 
 
 def test_nan_stays_where_it_is():
