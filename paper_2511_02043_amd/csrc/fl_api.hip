@@ -1044,11 +1044,12 @@ int pair_chunks(int64_t B, int64_t G, int64_t H, int64_t S_own) {
   return (int)best;
 }
 // ... whether they can take a call of these sizes at all (the biases' shapes decide the rest), and the part of the workspace they need
-// Head dim 32 up to 512 rows, 64 up to 384: past that a wave's blocks do not fit its registers (128 x 8 heads x 500, D = 64: 853
-// against 708 us with the general kernels; x 384: 400 against 424; D = 32, x 500: 310 against 578).
+// Head dim 32 up to 512 rows, 64 up to 384 with one bias and 256 with two: past that a wave's blocks do not fit its registers (the
+// build refuses instances with scratch).  Backward, 128 x 8 heads, against the general kernels: D = 32, x 500 290 / 606 us with one
+// bias, 327 / 773 with two; D = 64, x 384 349 / 445, x 250 165 / 264 and 178 / 319.
 bool pair_sizes_ok(int64_t G, int64_t H, int64_t Hkv, int64_t Sq, int64_t Sk, int64_t D, int64_t Dv, const fl_variant_desc* d) {
   return d->n_bias > 0 && d->score_mod == FL_MOD_NONE && d->mask == 0 && d->combine == FL_SINGLE && H == Hkv && D == Dv && (D == 32 || D == 64) &&
-         G >= 2 && Sq >= 1 && Sk >= 1 && std::max(Sq, Sk) <= (D == 32 ? 512 : 384);
+         G >= 2 && Sq >= 1 && Sk >= 1 && std::max(Sq, Sk) <= (D == 32 ? 512 : d->n_bias == 1 ? 384 : 256);
 }
 struct PairLayout {
   int chunks_q, chunks_k, nqb, nkb, n_key;

@@ -25,14 +25,18 @@ hipError_t launch_pair_any(int nblk, int role, bool keyb, const PairParams& p, i
   switch (nblk) {
     case 1: return launch_pair_steps<D, 1>(role, keyb, p, nblocks, stream);
     case 2: return launch_pair_steps<D, 2>(role, keyb, p, nblocks, stream);
-    case 3: return launch_pair_steps<D, 3>(role, keyb, p, nblocks, stream);
   }
-  if constexpr (D == 32)
+  if constexpr (D == 32) {
+    if (nblk == 3) return launch_pair_steps<D, 3>(role, keyb, p, nblocks, stream);
     if (nblk == 4) return launch_pair_steps<D, 4>(role, keyb, p, nblocks, stream);
+  } else if (nblk == 3 && !keyb) {
+    return role == 0 ? launch_pair<PairCfg<D, 3, 0, false>>(p, nblocks, stream) : launch_pair<PairCfg<D, 3, 1, false>>(p, nblocks, stream);
+  }
   return hipErrorInvalidValue;
 }
 
-// role 0: dQ and bias_part; 1: dK, dV and key_part.  nblk: ceil(streamed rows / 128): 1 .. 4 at head dim 32, 1 .. 3 at 64.
+// role 0: dQ and bias_part; 1: dK, dV and key_part.  nblk: ceil(streamed rows / 128): 1 .. 4 at head dim 32, 1 .. 3 (with a key bias
+// 1 .. 2) at 64.
 hipError_t launch_pair32(int nblk, int role, bool keyb, const PairParams& p, int nblocks, hipStream_t stream);
 hipError_t launch_pair64(int nblk, int role, bool keyb, const PairParams& p, int nblocks, hipStream_t stream);
 

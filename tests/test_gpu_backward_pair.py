@@ -17,7 +17,7 @@ C = inputs.combination_bf16
 
 @pytest.mark.parametrize("n_bias", [1, 2])
 @pytest.mark.parametrize("D,Sq,Sk,G,H", [(32, 1, 1, 2, 1), (32, 31, 33, 3, 2), (32, 64, 128, 9, 1), (32, 65, 129, 2, 2), (32, 257, 200, 3, 1), (32, 384, 300, 2, 2),
-                                         (32, 385, 511, 2, 1), (32, 512, 40, 2, 1), (64, 33, 64, 5, 2), (64, 128, 65, 2, 2), (64, 129, 256, 3, 1), (64, 300, 384, 2, 1)])
+                                         (32, 385, 511, 2, 1), (32, 512, 40, 2, 1), (64, 33, 64, 5, 2), (64, 128, 65, 2, 2), (64, 129, 256, 3, 1), (64, 256, 257, 2, 1), (64, 300, 384, 2, 1)])
 def test_sizes(D, Sq, Sk, G, H, n_bias):
     compare(C(D=D, n_bias=n_bias, S=Sq, Sk=Sk, G=G, B=2, H=H), "f32", label=f"D {D} {Sq} x {Sk} G {G} H {H} biases {n_bias}")
 

@@ -22,3 +22,13 @@ def test_default_builds_the_module_for_the_interpreter_it_is_given():
 def test_the_c_library_needs_no_torch(args):
     out = commands(*args)
     assert "-o ../libflattn.so" in out and "-o ../libflbench.so" in out and "_fltorch" not in out
+
+
+@pytest.mark.parametrize("scratch", [False, True], ids=["registers", "scratch"])
+def test_stationary_bias_kernels_are_built_without_scratch(tmp_path, scratch):
+    """The rule of fl_inst_pair*.hip refuses an instance that the compiler gives scratch memory."""
+    body = "float a[64]; for (int i = 0; i < 64; ++i) a[i] = x[i * n]; x[0] = a[n];" if scratch else "x[threadIdx.x] += n;"
+    (tmp_path / "fl_inst_pairtest.hip").write_text("#include <hip/hip_runtime.h>\n__global__ void k(float* x, int n) { %s }\n" % body)
+    r = subprocess.run(["make", "-f", os.path.join(CSRC, "Makefile"), "-C", str(tmp_path), "HDRS=", "_build/fl_inst_pairtest.o"], capture_output=True, text=True)
+    assert (r.returncode != 0) == scratch, r.stdout + r.stderr
+    assert (tmp_path / "_build" / "fl_inst_pairtest.o").exists() == (not scratch)
