@@ -1034,12 +1034,16 @@ PrefillLayout prefill_layout(int64_t B, int64_t Hkv, int64_t D, int64_t max_len)
 int pair_chunks(int64_t B, int64_t G, int64_t H, int64_t S_own) {
   const int64_t base = B * H * ((S_own + 63) / 64);
   int64_t best = 1, best_cost = 0;
-  for (int64_t c = 1; c <= G; ++c) {
-    const int64_t cost = ((base * c + 255) / 256) * ((G + c - 1) / c + 2);
-    if (c == 1 || cost < best_cost) {
-      best = c;
+  // `rounds` of 256 workgroups hold 256 * rounds / base ranges of a unit.  The problems alone take base * G / 256 and every round two
+  // start-ups more, so that the search ends after a few rounds (about the root of G at worst).
+  for (int64_t rounds = (base + 255) / 256; best_cost == 0 || base * G / 256 + 2 * rounds < best_cost; ++rounds) {
+    const int64_t most = std::min(G, 256 * rounds / base), per = (G + most - 1) / most;
+    const int64_t cost = rounds * (per + 2);
+    if (best_cost == 0 || cost < best_cost) {
+      best = (G + per - 1) / per;                  // the fewest ranges of at most `per` problems
       best_cost = cost;
     }
+    if (most == G) break;
   }
   return (int)best;
 }
@@ -1074,6 +1078,8 @@ struct ExLayout {
   int Dc, Dvc, ns, hsplit;          // head dims the kernels run at: (D, Dv) where such a kernel is compiled, else core_dim()
   bool need_o, pad_qk, pad_v, own_do;
   size_t stat, o, d_o, qpad, kpad, vpad, gq, gk, gv, sum, part_k, part_v, ds;   // sizes of one region each
+  bool pair;                        // the stationary-bias kernels take calls of these sizes, with this part of the ds region:
+  PairLayout pair_at;
   size_t off_lse2[2], off_delta[2], off_o[2], off_do[2], off_qpad[2], off_kpad[2], off_vpad, off_gq[2], off_gk[2], off_gv[2],
       off_sum, off_part, off_dl, off_ds, off_dw;
   size_t total;
@@ -1129,7 +1135,11 @@ ExLayout ex_layout(int64_t B, int64_t G, int64_t H, int64_t Hkv, int64_t Sq, int
   L.off_dl = take(L.ns == 2 ? L.stat : 0);
   // bias gradients: dS of every score (bf16), reduced over the broadcast axes afterwards
   L.ds = d->n_bias > 0 ? up256((size_t)(B * G * H) * ((Sq + 31) / 32) * ((Sk + 31) / 32) * fl::ds_block(Sq) * 2) : 0;
-  if (pair_sizes_ok(G, H, Hkv, Sq, Sk, D, Dv, d)) L.ds = std::max(L.ds, pair_layout(B, G, H, Sq, Sk).total);
+  L.pair = pair_sizes_ok(G, H, Hkv, Sq, Sk, D, Dv, d);
+  if (L.pair) {
+    L.pair_at = pair_layout(B, G, H, Sq, Sk);
+    L.ds = std::max(L.ds, L.pair_at.total);
+  }
   L.off_ds = take(L.ds);
   // rms_weight gradient: one partial sum per workgroup (four rows) of the epilogue-derivative kernel
   L.off_dw = take((d->epilogue & FL_EPI_RMSNORM) != 0 ? up256(((rq + 3) / 4) * (size_t)Dv * 4) : 0);
@@ -1149,10 +1159,9 @@ bool bwd_ex_ok(const fl_variant_desc* d, int64_t D, int64_t Dv) {
 }
 
 // dQ, dK, dV and the bias gradients by the stationary-bias kernels; pair / keyb: the indices of the two biases (keyb -1: none).
-hipError_t run_pair_bwd(const fl::BwdParams& call, int D, int pair, int keyb, const fl_aux* aux, const fl_bwd_extra* extra, const fl::BiasView* dbias,
+hipError_t run_pair_bwd(const fl::BwdParams& call, const PairLayout& P, int D, int pair, int keyb, const fl_aux* aux, const fl_bwd_extra* extra, const fl::BiasView* dbias,
                         unsigned char* ws, hipStream_t stream) {
   const int B = call.B, G = call.G, H = call.H, Sq = call.Sq, Sk = call.Sk;
-  const PairLayout P = pair_layout(B, G, H, Sq, Sk);
   fl::PairParams p;
   memset(&p, 0, sizeof(p));
   p.b = call;
@@ -1913,7 +1922,7 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
   ep.ns = ns; ep.has_gate = has_gate; ep.has_rms = has_rms;
   // Stationary-bias kernels: a pair bias that every row problem g shares and, beside it, at most a key bias.
   int pair = -1, keyb = -1;
-  if (pair_sizes_ok(G, H, Hkv, Sq, Sk, D, Dv, desc) && Dc == (int)D && g_tuning.pair_bias != 1) {
+  if (L.pair && Dc == (int)D && g_tuning.pair_bias != 1) {
     for (int nb = 0; nb < (int)desc->n_bias; ++nb) {
       const int64_t* z = aux->bias[nb].size;
       if (z[1] == 1 && z[3] == Sq && z[4] == Sk && pair < 0) pair = nb;
@@ -2013,7 +2022,7 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
     p.delta = (float*)(ws + L.off_delta[s]);
     p.lse2 = (float*)(ws + L.off_lse2[s]);
     if (pair >= 0) {
-      if ((e = run_pair_bwd(p, Dc, pair, keyb, aux, extra, dbias, ws + L.off_ds, stream)) != hipSuccess)
+      if ((e = run_pair_bwd(p, L.pair_at, Dc, pair, keyb, aux, extra, dbias, ws + L.off_ds, stream)) != hipSuccess)
         return fail(FL_ERR_LAUNCH, "backward launch: %s", hipGetErrorString(e));
       continue;
     }

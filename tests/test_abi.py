@@ -258,3 +258,18 @@ def test_bias_gradient_workspace_follows_the_query_rows(Sq):
     rows = Sq if Sq < 32 else (Sq + 31) // 32 * 32
     staged = B * H * rows * 1024 * 2
     assert staged <= size(1) - size(0) < staged + 256
+
+
+def test_workspace_query_does_not_walk_the_row_axis():
+    """The split of the row axis G over workgroups is found in about the root of G steps (a walk over every split took 60 ms here)."""
+    import time
+    t = fb.fl_tensor()
+    t.ptr, t.dtype = 16, fb.FL_BF16
+    t.size[:] = (1, 1 << 22, 3, 200, 32)
+    t.stride[:] = (0, 3 * 200 * 32, 200 * 32, 32, 1)
+    d = fb.variant_desc(scale=0.125, n_bias=1)
+    fb.fl_attn_bwd_ex_workspace_size(t, t, t, d)
+    start = time.perf_counter()
+    for _ in range(20):
+        assert fb.fl_attn_bwd_ex_workspace_size(t, t, t, d) > 0
+    assert time.perf_counter() - start < 0.2
