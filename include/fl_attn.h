@@ -210,7 +210,8 @@ typedef struct {
   fl_tensor dbias[2];      /* gradient of aux->bias[n]: f32 with the sizes of aux->bias[n] (an axis of size 1 that
                               broadcasts holds the sum over that axis); ptr NULL: not computed.  The workspace then
                               holds dS of every score in bf16 (2 bytes each; Sk, and an Sq above 32, rounded up to 32)
-                              until it is summed  */
+                              until it is summed, and is reserved for it also
+                              where the calls' biases let the library sum it without (a bias shared along G)  */
   fl_tensor dgate;         /* FL_EPI_GATE_SIGMOID: gradient of aux->gate, shape of out, bf16 or f32; ptr NULL: not computed */
   float*    dlambda;       /* FL_DIFFERENTIAL: [H] f32 device; NULL: not computed                              */
   float*    drms_weight;   /* FL_EPI_RMSNORM: gradient of aux->rms_weight (of the implied all-ones weight when that is
@@ -444,7 +445,9 @@ const char* fl_last_error_detail(void);
  * query heads into subsets; both change the workspace size the matching *_workspace_size reports),
  * "prefill_gather" (fl_attn_prefill_paged: 1 = always copy the pages first, 2 = always read them in place with the
  * forward kernel; either also keeps chunks of a few rows away from the decode kernels), "prefill_pack" (1 = never
- * pack the query heads of a kv head into one workgroup of the in-place kernel).
+ * pack the query heads of a kv head into one workgroup of the in-place kernel), "pair_bias" (fl_attn_bwd_ex with a bias shared
+ * along G: 1 = never the kernels that keep it in registers, 2 = always where they can, which may enlarge the workspace
+ * that the query reports).
  * Value 0 restores the built-in choice.  Returns FL_OK or FL_ERR_UNSUPPORTED.  The requests are kept
  * per host thread: they change the later calls of the calling thread only, so this call is as
  * thread-safe as the others and no state is shared between threads.                          */

@@ -45,7 +45,7 @@ struct Tuning {
   int prefill_gather = 0;          // fl_attn_prefill_paged: 1 always copies the pages into dense tensors first, 2 never
                                    // (where the pages allow it); 0: by chunk length
   int bwd_wg_target = 0;           // 0: the default of choose_hsplit
-  int pair_bias = 0;               // fl_attn_bwd_ex: 1 never takes the stationary-bias kernels
+  int pair_bias = 0;               // fl_attn_bwd_ex: 1 never takes the stationary-bias kernels, 2 always where they can
 };
 thread_local Tuning g_tuning;
 
@@ -1031,23 +1031,24 @@ PrefillLayout prefill_layout(int64_t B, int64_t Hkv, int64_t D, int64_t max_len)
 // owned rows, (b, h) and range.  Few, long ranges load the bias seldom and leave small partial gradients; the launch should fill
 // the 256 compute units (one workgroup each) a whole number of times.  A range costs about two problems of start-up (128 x 8 heads
 // x 384, D = 32, dQ / dK and dV: 5 ranges 77 / 86 us, 8 97 / 106, 16 96 / 96, 32 116 / 113).
-int pair_chunks(int64_t B, int64_t G, int64_t H, int64_t S_own) {
+// At most `limit` ranges.
+int pair_chunks(int64_t B, int64_t G, int64_t H, int64_t S_own, int64_t limit) {
   const int64_t base = B * H * ((S_own + 63) / 64);
   int64_t best = 1, best_cost = 0;
   // `rounds` of 256 workgroups hold 256 * rounds / base ranges of a unit.  The problems alone take base * G / 256 and every round two
   // start-ups more, so that the search ends after a few rounds (about the root of G at worst).
   for (int64_t rounds = (base + 255) / 256; best_cost == 0 || base * G / 256 + 2 * rounds < best_cost; ++rounds) {
-    const int64_t most = std::min(G, 256 * rounds / base), per = (G + most - 1) / most;
+    const int64_t most = std::min(limit, 256 * rounds / base), per = (G + most - 1) / most;
     const int64_t cost = rounds * (per + 2);
     if (best_cost == 0 || cost < best_cost) {
       best = (G + per - 1) / per;                  // the fewest ranges of at most `per` problems
       best_cost = cost;
     }
-    if (most == G) break;
+    if (most == limit) break;
   }
   return (int)best;
 }
-// ... whether they can take a call of these sizes at all (the biases' shapes decide the rest), and the part of the workspace they need
+// ... whether they can take a call of these sizes at all (the biases' shapes decide the rest).
 // Head dim 32 up to 512 rows, 64 up to 384 with one bias and 256 with two: past that a wave's blocks do not fit its registers (the
 // build refuses instances with scratch).  Backward, 128 x 8 heads, against the general kernels: D = 32, x 500 290 / 606 us with one
 // bias, 327 / 773 with two; D = 64, x 384 349 / 445, x 250 165 / 264 and 178 / 319.
@@ -1055,21 +1056,28 @@ bool pair_sizes_ok(int64_t G, int64_t H, int64_t Hkv, int64_t Sq, int64_t Sk, in
   return d->n_bias > 0 && d->score_mod == FL_MOD_NONE && d->mask == 0 && d->combine == FL_SINGLE && H == Hkv && D == Dv && (D == 32 || D == 64) &&
          G >= 2 && Sq >= 1 && Sk >= 1 && std::max(Sq, Sk) <= (D == 32 ? 512 : d->n_bias == 1 ? 384 : 256);
 }
+// ... and what they keep in the workspace: partial pair bias gradients, 4 KB per 32 x 32 block and range, and with two biases the key
+// bias in fp32 and its gradient's sums over the query rows.  It takes the place of the general kernels' staged dS, `room` bytes, which the
+// workspace query reserves for either route (it does not see the biases' shapes): the ranges of the dQ kernel are limited by it.
 struct PairLayout {
-  int chunks_q, chunks_k, nqb, nkb, n_key;
+  int chunks_q, chunks_k, nqb, nkb, n_key;         // (chunks_q 0: no room)
   size_t off_part, off_key_part, off_key, total;
 };
-PairLayout pair_layout(int64_t B, int64_t G, int64_t H, int64_t Sq, int64_t Sk) {
+PairLayout pair_layout(int64_t B, int64_t G, int64_t H, int64_t Sq, int64_t Sk, bool two_biases, size_t room) {
   PairLayout P;
-  P.chunks_q = pair_chunks(B, G, H, Sq);
-  P.chunks_k = pair_chunks(B, G, H, Sk);
+  memset(&P, 0, sizeof(P));
   P.nqb = (int)((Sq + 31) / 32);
   P.nkb = (int)((Sk + 31) / 32);
   P.n_key = (int)((Sk + 127) / 128 * 128);
-  P.off_part = 0;
-  P.off_key_part = up256((size_t)P.chunks_q * (B * H) * P.nqb * P.nkb * 4096);
-  P.off_key = P.off_key_part + up256((size_t)(B * G * H) * Sk * 4);
-  P.total = P.off_key + up256((size_t)(B * G * H) * P.n_key * 4);
+  const size_t range = (size_t)(B * H) * P.nqb * P.nkb * 4096;     // partial gradients of one range
+  P.off_key = two_biases ? up256((size_t)(B * G * H) * Sk * 4) : 0;
+  P.off_part = P.off_key + (two_biases ? up256((size_t)(B * G * H) * P.n_key * 4) : 0);
+  const int64_t limit = room < P.off_part ? 0 : std::min<int64_t>(G, (int64_t)((room - P.off_part) / range));
+  if (limit > 0) {
+    P.chunks_q = pair_chunks(B, G, H, Sq, limit);
+    P.chunks_k = pair_chunks(B, G, H, Sk, G);
+  }
+  P.total = P.off_part + P.chunks_q * range;
   return P;
 }
 
@@ -1135,10 +1143,12 @@ ExLayout ex_layout(int64_t B, int64_t G, int64_t H, int64_t Hkv, int64_t Sq, int
   L.off_dl = take(L.ns == 2 ? L.stat : 0);
   // bias gradients: dS of every score (bf16), reduced over the broadcast axes afterwards
   L.ds = d->n_bias > 0 ? up256((size_t)(B * G * H) * ((Sq + 31) / 32) * ((Sk + 31) / 32) * fl::ds_block(Sq) * 2) : 0;
-  L.pair = pair_sizes_ok(G, H, Hkv, Sq, Sk, D, Dv, d);
+  L.pair = g_tuning.pair_bias != 1 && pair_sizes_ok(G, H, Hkv, Sq, Sk, D, Dv, d);
   if (L.pair) {
-    L.pair_at = pair_layout(B, G, H, Sq, Sk);
-    L.ds = std::max(L.ds, L.pair_at.total);
+    const bool always = g_tuning.pair_bias == 2;
+    L.pair_at = pair_layout(B, G, H, Sq, Sk, d->n_bias == 2, always ? SIZE_MAX : L.ds);
+    L.pair = L.pair_at.chunks_q > 0;
+    if (always) L.ds = std::max(L.ds, up256(L.pair_at.total));
   }
   L.off_ds = take(L.ds);
   // rms_weight gradient: one partial sum per workgroup (four rows) of the epilogue-derivative kernel
@@ -1922,7 +1932,7 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
   ep.ns = ns; ep.has_gate = has_gate; ep.has_rms = has_rms;
   // Stationary-bias kernels: a pair bias that every row problem g shares and, beside it, at most a key bias.
   int pair = -1, keyb = -1;
-  if (L.pair && Dc == (int)D && g_tuning.pair_bias != 1) {
+  if (L.pair && Dc == (int)D) {
     for (int nb = 0; nb < (int)desc->n_bias; ++nb) {
       const int64_t* z = aux->bias[nb].size;
       if (z[1] == 1 && z[3] == Sq && z[4] == Sk && pair < 0) pair = nb;

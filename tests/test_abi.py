@@ -273,3 +273,23 @@ def test_workspace_query_does_not_walk_the_row_axis():
     for _ in range(20):
         assert fb.fl_attn_bwd_ex_workspace_size(t, t, t, d) > 0
     assert time.perf_counter() - start < 0.2
+
+
+@pytest.mark.parametrize("sizes", [(1, 128, 8, 1, 384), (4, 2, 16, 1, 512), (1, 8, 4, 70, 200), (2, 3, 5, 512, 40), (1, 128, 8, 384, 384), (1, 16, 1, 129, 130)])
+@pytest.mark.parametrize("D,n_bias", [(32, 1), (32, 2), (64, 1), (64, 2)])
+def test_bias_gradients_ask_for_no_more_than_the_staged_scores(sizes, D, n_bias):
+    """fl_attn_bwd_ex with biases: the rows' statistics and 2 bytes per score (rows and keys rounded up as the header says), whichever
+    kernels the call takes."""
+    B, G, H, Sq, Sk = sizes
+    up = lambda n: (n + 255) // 256 * 256
+    rows = B * G * H * Sq
+
+    def tensor(S):
+        t = fb.fl_tensor()
+        t.ptr, t.dtype = 16, fb.FL_BF16
+        t.size[:] = (B, G, H, S, D)
+        t.stride[:] = (G * H * S * D, H * S * D, S * D, D, 1)
+        return t
+    ds = B * G * H * ((Sk + 31) // 32 * 32) * (Sq if Sq <= 32 else (Sq + 31) // 32 * 32) * 2
+    d = fb.variant_desc(scale=0.125, n_bias=n_bias)
+    assert fb.fl_attn_bwd_ex_workspace_size(tensor(Sq), tensor(Sk), tensor(Sk), d) <= 2 * up(4 * rows) + up(ds)

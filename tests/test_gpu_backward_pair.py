@@ -1,6 +1,6 @@
 """The stationary-bias backward kernels (a pair bias shared by the row problems, with or without a key bias): dQ, dK, dV and both
 bias gradients against the fp64 oracle where tiles end -- 32-row blocks, 64 owned rows, steps of 128 streamed rows, ranges of the
-row axis -- and against the general kernels, which take the same calls with the tuning switch.  Tolerance: fl_attn_bwd_ex's
+row axis -- and against the general kernels; the tuning switch selects either for calls of any size.  Tolerance: fl_attn_bwd_ex's
 (P and dS in bf16, fp32 sums; relative L2 <= 5e-3)."""
 import numpy as np
 import pytest
@@ -13,12 +13,20 @@ from test_gpu_backward_ex import compare
 pytestmark = pytest.mark.gpu
 
 C = inputs.combination_bf16
+PAIR, GENERAL = 2, 1                               # the tuning switch: always these kernels, never
+
+
+@pytest.fixture
+def always_pair():
+    fb.check(fb.fl_set_tuning("pair_bias", PAIR))
+    yield
+    fb.fl_set_tuning("pair_bias", 0)
 
 
 @pytest.mark.parametrize("n_bias", [1, 2])
 @pytest.mark.parametrize("D,Sq,Sk,G,H", [(32, 1, 1, 2, 1), (32, 31, 33, 3, 2), (32, 64, 128, 9, 1), (32, 65, 129, 2, 2), (32, 257, 200, 3, 1), (32, 384, 300, 2, 2),
                                          (32, 385, 511, 2, 1), (32, 512, 40, 2, 1), (64, 33, 64, 5, 2), (64, 128, 65, 2, 2), (64, 129, 256, 3, 1), (64, 256, 257, 2, 1), (64, 300, 384, 2, 1)])
-def test_sizes(D, Sq, Sk, G, H, n_bias):
+def test_sizes(D, Sq, Sk, G, H, n_bias, always_pair):
     compare(C(D=D, n_bias=n_bias, S=Sq, Sk=Sk, G=G, B=2, H=H), "f32", label=f"D {D} {Sq} x {Sk} G {G} H {H} biases {n_bias}")
 
 
@@ -56,7 +64,7 @@ def test_same_as_general_kernels(D, form):
         w.biases = (pair[:1], key)
     dout = inputs.dout_for(w)
     dtype = "bf16" if form == "bf16" else "f32"
-    new, old = _grads(w, dout, 0, dtype), _grads(w, dout, 1, dtype)
+    new, old = _grads(w, dout, PAIR, dtype), _grads(w, dout, GENERAL, dtype)
     assert new.keys() == old.keys() and any(n.startswith("dbias") for n in new)
     for n in new:
         assert np.all(np.isfinite(new[n])), n
@@ -77,14 +85,14 @@ def test_hidden_keys(hide):
     if np.isinf(hide):
         key[0, 4] = hide
     w.biases = (w.biases[0], inputs.round_to_bf16(key))
-    g = _grads(w, inputs.dout_for(w), 0)
+    g = _grads(w, inputs.dout_for(w), PAIR)
     for n, x in g.items():
         assert np.all(np.isfinite(x)), n
     assert np.all(g["dk0"][0, 0, :, 100:] == 0) and np.all(g["dv0"][0, 0, :, 100:] == 0) and np.all(g["dk0"][0, 2, :, :70] == 0)
     assert np.any(g["dk0"][0, 0, :, :100] != 0) and np.any(g["dk0"][0, 2, :, 70:] != 0)
     if np.isinf(hide):
         assert all(np.all(g[n][0, 4] == 0) for n in ("dq0", "dk0", "dv0"))
-    old = _grads(w, inputs.dout_for(w), 1)
+    old = _grads(w, inputs.dout_for(w), GENERAL)
     for n in g:
         assert np.linalg.norm(g[n] - old[n]) <= 4e-3 * np.linalg.norm(old[n]), n
 
@@ -109,7 +117,7 @@ def _workload_with_hidden(D, value, by):
 LARGE = [-1e4, -1e9, -7.93e8, -3.1e9, -1e10, -1e20, -1e38, -1.69e38]
 
 
-@pytest.mark.parametrize("tune", [0, 1])           # these kernels, the general ones
+@pytest.mark.parametrize("tune", [PAIR, GENERAL])
 @pytest.mark.parametrize("by", ["key", "pair"])
 @pytest.mark.parametrize("value", LARGE)
 @pytest.mark.parametrize("D", [32, 64])
@@ -142,7 +150,7 @@ def test_exponents_are_those_of_the_general_kernels(D, n_bias, offset):
     if offset:                                     # (-1e4 and normal numbers have no sum in bf16: the last bias is the offset alone)
         w.biases = w.biases[:-1] + (inputs.round_to_bf16(np.full_like(w.biases[-1], offset)),)
     dout = inputs.dout_for(w)
-    new, old = _grads(w, dout, 0), _grads(w, dout, 1)
+    new, old = _grads(w, dout, PAIR), _grads(w, dout, GENERAL)
     for n in ("dq0", "dk0", "dv0", "dbias0"):
         rel = np.linalg.norm(new[n] - old[n]) / np.linalg.norm(old[n])
         print(f"D {D} biases {n_bias} offset {offset} {n}: {rel:.2e}", flush=True)
@@ -157,7 +165,7 @@ def test_nan_stays_where_it_is():
     v[0, 2, 1, 40, 3] = np.nan
     w.biases, w.v = (pair,), v
     dout = inputs.dout_for(w)
-    new, old = _grads(w, dout, 0), _grads(w, dout, 1)
+    new, old = _grads(w, dout, PAIR), _grads(w, dout, GENERAL)
     for n in new:
         assert np.array_equal(np.isnan(new[n]), np.isnan(old[n])), n
     assert np.isnan(new["dq0"][0, 0, 0, 5]).all() and not np.isnan(new["dq0"][0, 0, 0, 6]).any()
