@@ -1081,6 +1081,27 @@ PairLayout pair_layout(int64_t B, int64_t G, int64_t H, int64_t Sq, int64_t Sk, 
   return P;
 }
 
+// ... and where they are the faster ones.  Both routes' times over 21 launches (B * G * H 16 .. 2048, G 3 .. 256) x 8 row counts (72 .. 384) x
+// head dim x one or two biases, stationary over general:
+//   * the share of the launch that is work and not start-up or idle compute units, from G = 4 on: 0.45 or more with at least 192
+//     rows 0.48 - 0.98, 0.6 or more with more than 128 rows 0.55 - 1.01, 0.75 or more with more than 64 rows 0.60 - 1.02; below
+//     these up to 1.16 (B, G, H = 3, 7, 8, 384 rows, D = 64: 144 workgroups), 1.15 and 1.34;
+//   * launches that leave the general kernels short of workgroups, too: 0.66 - 1.05 up to 128 of them, from 192 rows and
+//     G = 4 on up to 256 of them 0.73 - 0.97 (G = 2 and 3: up to 1.11);
+//   * up to 64 rows: up to 1.71, and a narrow tensor (one row against 384 keys) up to 1.33.
+bool pair_pays(int64_t B, int64_t G, int64_t H, int64_t Sq, int64_t Sk, const PairLayout& P) {
+  const int64_t rows = std::min(Sq, Sk), general = B * G * H * ((std::max(Sq, Sk) + 127) / 128);
+  if (rows <= 64) return false;
+  if (general <= (rows >= 192 && G >= 4 ? 256 : 128)) return true;
+  // in problems of one workgroup: what the launch takes, and what it would with all compute units at work
+  auto share = [&](int64_t own, int64_t chunks) {
+    const int64_t base = B * H * ((own + 63) / 64);
+    return (double)(base * G) / (256 * ((base * chunks + 255) / 256) * ((G + chunks - 1) / chunks + 2));
+  };
+  const double least = std::min(share(Sq, P.chunks_q), share(Sk, P.chunks_k));
+  return G >= 4 && least >= (rows >= 192 ? 0.45 : rows > 128 ? 0.6 : 0.75);
+}
+
 // Workspace of fl_attn_bwd_ex (byte offsets; every region 256-byte aligned).
 struct ExLayout {
   int Dc, Dvc, ns, hsplit;          // head dims the kernels run at: (D, Dv) where such a kernel is compiled, else core_dim()
@@ -1147,7 +1168,7 @@ ExLayout ex_layout(int64_t B, int64_t G, int64_t H, int64_t Hkv, int64_t Sq, int
   if (L.pair) {
     const bool always = g_tuning.pair_bias == 2;
     L.pair_at = pair_layout(B, G, H, Sq, Sk, d->n_bias == 2, always ? SIZE_MAX : L.ds);
-    L.pair = L.pair_at.chunks_q > 0;
+    L.pair = L.pair_at.chunks_q > 0 && (always || pair_pays(B, G, H, Sq, Sk, L.pair_at));
     if (always) L.ds = std::max(L.ds, up256(L.pair_at.total));
   }
   L.off_ds = take(L.ds);

@@ -74,6 +74,19 @@ def test_same_as_general_kernels(D, form):
     assert not all(np.array_equal(new[n], old[n]) for n in new), "the switch chose the same kernels"
 
 
+# half of the compute units or a narrow tensor: the general kernels (two row problems, up to 64 rows, one query row, a last round of
+# workgroups that is nearly empty); enough row problems, and launches that are small for either
+@pytest.mark.parametrize("B,G,H,Sq,Sk,route", [(8, 2, 8, 200, 200, GENERAL), (1, 64, 4, 64, 64, GENERAL), (4, 16, 4, 1, 200, GENERAL), (4, 16, 4, 200, 1, GENERAL),
+                                               (10, 6, 8, 96, 96, GENERAL), (1, 128, 8, 96, 80, PAIR), (1, 128, 4, 200, 130, PAIR), (1, 6, 4, 100, 72, PAIR)])
+def test_route(B, G, H, Sq, Sk, route):
+    """Which kernels a call takes without the tuning switch: the general ones give the same bits with and without it."""
+    w = C(D=32, n_bias=1, S=Sq, Sk=Sk, G=G, B=B, H=H)
+    w.biases = (w.biases[0][:, :1],)
+    dout = inputs.dout_for(w)
+    got, general = _grads(w, dout, 0), _grads(w, dout, GENERAL)
+    assert all(np.array_equal(got[n], general[n]) for n in got) == (route == GENERAL)
+
+
 @pytest.mark.parametrize("hide", [-np.inf, -1e9])
 def test_hidden_keys(hide):
     """A key bias that hides keys: their gradients are zero, and so are those of a row problem without any visible key under
