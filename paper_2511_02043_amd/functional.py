@@ -206,7 +206,7 @@ def variant_attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, *, scal
             raise ValueError(f"biases[{n}] must be a 5-D bf16 tensor on {q.device}")
     variant = (float(q.shape[-1] ** -0.5 if scale is None else scale), _score_mod(softcap, alibi_slopes), float(softcap or 0.0),
                _mask_bits(causal, window, prefix, q_doc_ids), int(window or 0), int(prefix or 0), int(q_offset), bool(rmsnorm),
-               float(rms_eps), alibi_slopes, q_doc_ids, kv_doc_ids)
+               float(rms_eps) if rmsnorm else 0.0, alibi_slopes, q_doc_ids, kv_doc_ids)
     b0 = biases[0] if len(biases) > 0 else None
     b1 = biases[1] if len(biases) > 1 else None
     return _VariantAttention.apply(variant, q, k, v, q2, k2, lam, gate, b0, b1, rms_weight if rmsnorm else None)

@@ -107,3 +107,9 @@ def test_variant_ranks_agree(form):
         assert torch.equal(a, b if a.dim() == b.dim() else b[:, 0])
     with pytest.raises(ValueError, match="expected"):
         F.variant_attention(q, k[0], v, **kw)
+
+
+def test_eps_is_not_read_without_rmsnorm():
+    """rms_eps=None (a caller's "no normalisation") beside rmsnorm=False."""
+    q, k, v, gate = (normal(1, 2, 40, 64, seed=n) for n in range(4))
+    assert torch.equal(F.variant_attention(q, k, v, gate=gate, rms_eps=None), F.variant_attention(q, k, v, gate=gate))
