@@ -1015,9 +1015,9 @@ bwd_dkdv_kernel(const BwdParams p) {
   };
 
   // A whole tile's addresses: a uniform base and what this lane adds to it, the same for each of its load instructions (their rows
-  // are a multiple of 16 apart, which leaves the swizzle as it is).  Rows close enough for 32-bit offsets; not with bias values in
-  // registers, where there is no room for it.  (With the items as pairs: causal training step 4 x 16 x 4096, D = 64, 830 -> 818 us)
-  const bool near_rows = C::NBIAS == 0 && p.q.ss >= 0 && p.q.ss < (1 << 23) && p.dout.ss >= 0 && p.dout.ss < (1 << 23);   // 64 rows fit 32 bits
+  // are a multiple of 16 apart, which leaves the swizzle as it is).  64 rows fit 32 bits: the host refuses negative row strides and those of
+  // 2^23 elements and more.  Not with bias values in registers, where there is no room for it.  (With the items as pairs: causal
+  // training step 4 x 16 x 4096, D = 64, 830 -> 818 us)
   const uint32_t q_lane = tile_lane_offset<C::D>(wave, lane, (uint32_t)p.q.ss * 2), d_lane = tile_lane_offset<C::DV>(wave, lane, (uint32_t)p.dout.ss * 2);
   auto load_item = [&](Item it, int stage) __attribute__((always_inline)) {
     const int t = t_lo + it.r, h = h_first + it.h;
@@ -1026,7 +1026,7 @@ bwd_dkdv_kernel(const BwdParams p) {
     const unsigned char* qb = (const unsigned char*)((const uint16_t*)p.q.ptr + b * p.q.sb + g * p.q.sg + h * p.q.sh + (int64_t)(t * BN) * p.q.ss);
     const unsigned char* db = (const unsigned char*)((const uint16_t*)p.dout.ptr + b * p.dout.sb + g * p.dout.sg + h * p.dout.sh + (int64_t)(t * BN) * p.dout.ss);
     constexpr int NU = (C::TILE_INSTR > C::TILEV_INSTR ? C::TILE_INSTR : C::TILEV_INSTR) / C::NW;
-    if (nvalid == BN && near_rows) {
+    if (C::NBIAS == 0 && nvalid == BN) {
 #pragma unroll
       for (int u = 0; u < NU; ++u) {
         if (u < C::TILE_INSTR / C::NW)

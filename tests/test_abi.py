@@ -293,3 +293,22 @@ def test_bias_gradients_ask_for_no_more_than_the_staged_scores(sizes, D, n_bias)
     ds = B * G * H * ((Sk + 31) // 32 * 32) * (Sq if Sq <= 32 else (Sq + 31) // 32 * 32) * 2
     d = fb.variant_desc(scale=0.125, n_bias=n_bias)
     assert fb.fl_attn_bwd_ex_workspace_size(tensor(Sq), tensor(Sk), tensor(Sk), d) <= 2 * up(4 * rows) + up(ds)
+
+
+@pytest.mark.parametrize("stride", [-64, 1 << 23])
+def test_backward_refuses_row_strides_outside_32_bit_tiles(stride):
+    """The kernels form the addresses inside a tile of 64 rows with 32-bit offsets from a uniform base (nothing is launched here)."""
+    def tensor(ss=64, dtype=fb.FL_BF16, d=64):
+        t = fb.fl_tensor()
+        t.ptr, t.dtype = 4096, dtype
+        t.size[:] = (1, 1, 2, 70, d)
+        t.stride[:] = (70 * 128, 70 * 128, 64, ss, 1)
+        return t
+    good, bad = tensor(), tensor(stride)
+    lse = tensor(1, fb.FL_F32, 1)
+    aux = fb.aux_desc()
+    for desc, call in ((fb.variant_desc(scale=0.1), fb.fl_attn_bwd), (fb.variant_desc(scale=0.1, n_bias=1), fb.fl_attn_bwd_ex)):
+        for at in range(5):                        # q, k, v, out, dout
+            x = [bad if n == at else good for n in range(5)]
+            args = [*x, lse, desc, aux, good, good, good] + ([None] if call is fb.fl_attn_bwd_ex else [])
+            assert call(*args, None) == fb.FL_ERR_STRIDE, (call, at)
