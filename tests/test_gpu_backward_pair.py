@@ -182,3 +182,57 @@ def test_nan_stays_where_it_is():
     for n in new:
         assert np.array_equal(np.isnan(new[n]), np.isnan(old[n])), n
     assert np.isnan(new["dq0"][0, 0, 0, 5]).all() and not np.isnan(new["dq0"][0, 0, 0, 6]).any()
+
+
+def _call(x, biases, dbias, D):
+    """Gradients of q, k, v (dense) and of the biases (into `dbias`) from x = q, k, v, dout and biases in any layout.  The forward
+    pass, which wants biases with unit key stride, runs on dense copies."""
+    q, k, v, dout = x
+    desc = fb.variant_desc(scale=D ** -0.5, n_bias=len(biases))
+    out = torch.empty(q.shape, dtype=torch.bfloat16, device=q.device)
+    lse = torch.empty(q.shape[:-1] + (1,), device=q.device)
+    t = fb.tensor_desc
+    ws = torch.empty(fb.fl_attn_bwd_ex_workspace_size(t(q), t(k), t(v), desc), dtype=torch.uint8, device=q.device)
+    dense = [y.contiguous() for y in (q, k, v, *biases)]
+    fb.check(fb.fl_attn_fwd(*(t(y) for y in dense[:3]), desc, fb.aux_desc(biases=dense[3:]), t(out), t(lse), 0))
+    g = [torch.full(y.shape, float("nan"), device=q.device) for y in (q, k, v)]
+    fb.check(fb.fl_attn_bwd_ex(t(q), t(k), t(v), t(out), t(dout), t(lse), desc, fb.aux_desc(biases=biases, workspace=ws), *(t(y) for y in g),
+                               fb.bwd_extra(dbias=dbias), 0))
+    torch.cuda.synchronize()
+    return g
+
+
+@pytest.mark.parametrize("form", ["bias_by_columns", "bias_rows_apart", "strided_bias_gradients", "far_rows"])
+@pytest.mark.parametrize("D", [32, 64])
+def test_layouts(D, form, always_pair):
+    """The same numbers in other layouts give the same bits: a pair bias whose query axis is the contiguous one (no wide loads in either
+    kernel) or whose rows are an odd number of elements apart, bias gradients stored with gaps and transposed, rows of
+    q, k, v and dout 8 MB apart."""
+    B, G, H, Sq, Sk = 2, 5, 2, 70, 150
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    rand = lambda *s: torch.randn(*s, generator=gen, device="cuda:0").to(torch.bfloat16)
+    x = [rand(B, G, H, s, D) for s in (Sq, Sk, Sk, Sq)]
+    biases = [rand(B, 1, H, Sq, Sk), rand(B, G, 1, 1, Sk)]
+    dbias = [torch.full(b.shape, float("nan"), device=b.device) for b in biases]
+    want = _call(x, biases, dbias, D)
+    pair, key = biases
+    if form == "bias_by_columns":
+        biases = [pair.transpose(3, 4).contiguous().transpose(3, 4), key]
+    elif form == "bias_rows_apart":
+        wide = rand(B, 1, H, Sq, Sk + 7)
+        wide[..., 3:Sk + 3] = pair
+        biases = [wide[..., 3:Sk + 3], rand(B, G, 1, 1, 3 * Sk)[..., ::3].copy_(key)]
+    elif form == "far_rows":
+        far = []
+        for y in x:
+            store = torch.empty(y.shape[3], 1 << 22, dtype=torch.bfloat16, device="cuda:0")
+            view = store[:, :B * G * H * D].view(y.shape[3], B, G, H, D).permute(1, 2, 3, 0, 4)
+            far.append(view.copy_(y))
+        x = far
+    got_db = [torch.full(b.shape, float("nan"), device=b.device) for b in biases]
+    if form == "strided_bias_gradients":
+        got_db = [torch.full((B, 1, H, Sk, 2 * Sq), float("nan"), device="cuda:0")[..., ::2].transpose(3, 4),
+                  torch.full((B, G, 1, 1, 5 * Sk), float("nan"), device="cuda:0")[..., 1::5]]
+    got = _call(x, biases, got_db, D)
+    for a, b in zip(want + dbias, got + got_db):
+        assert torch.isfinite(b).all() and torch.equal(a, b)
