@@ -175,12 +175,12 @@ template <class C>
 struct Wave {
   static constexpr int D = C::D, DV = C::DV, NB = C::NB, KK = C::KK, DVB = C::DVB, NS = C::NS, RB = C::RB;
   static constexpr bool kPlain = (C::MOD == kModNone && C::NBIAS == 0);
-  // Soft-cap without biases: the score registers hold t = 1 / (exp(2 z) + 1), z the score over the cap, instead of the capped
-  // score cap * (1 - 2 t).  The row max is that of -t, and the step from t to the exponent's argument and the subtraction
-  // of the row's reference are one FMA.  A hidden score is t = +inf.  (The kernel is bound by its vector instructions:
-  // 8 x 16 heads x 1999 rows, D = 64: 247 -> 228 us with the error against fp64 unchanged.)
-  static constexpr bool kCapT = (C::MOD == kModSoftcap && C::NBIAS == 0);
-  static constexpr float kHidden = kCapT ? INFINITY : -INFINITY;   // what a hidden score's register holds
+  // Soft-cap without biases: the scores and their running max are kept less the cap, x - cap = -2 cap / (exp(2 z) + 1) with z the score
+  // over the cap.  The reciprocal gives that as it is, the sum and the factor under it being one FMA, so that a score takes no
+  // instruction more than its row's reference subtracted, which is exact for the row's largest (P = 1).  The kernel is bound by its
+  // vector instructions: 8 x 16 heads x 1999 rows, D = 64, 241 us with the cap added per score, 231 without, error against fp64
+  // no larger.
+  static constexpr bool kShifted = (C::MOD == kModSoftcap && C::NBIAS == 0);
   typedef f32x16 Scores[C::RB][C::NB];
   // Raw bias values of one tile for this lane: for bias n, row block rb, key block nb and
   // register group r4, the four bf16 values of keys jb + 8*r4 .. +3 (loaded ahead of their use).
@@ -208,7 +208,7 @@ struct Wave {
   int i[C::RB], ic[C::RB];      // this lane's query rows (unclamped / clamped), one per row block
   int qdoc[C::RB];
   float c_scale, slope_l2;
-  float cap_in, cap_l2;         // soft-cap, uniform: raw score -> exponent of exp(2 z); the cap in log2 units
+  float cap_in, cap_l2, cap_rcp;   // soft-cap, uniform: raw score -> exponent of exp(2 z); the cap in log2 units; -1 / (2 cap)
   float alibi_c[16];            // ALiBi, uniform: slope * key offset of score register r inside its 32-key block
   uint32_t ka[C::KK];           // per-lane byte offset of the K fragment of k-step kk (block 0)
   uint32_t va[C::DVB];          // per-lane byte offset of the V^T fragment of channel block d (key block 0)
@@ -315,15 +315,16 @@ struct Wave {
 
   // ---- variant transform (Eq. 4 score_mod, additive biases) of one score register.
   // Leaves the score in the domain exp_only() expects: raw for the plain variants (the scale is
-  // folded into the exponent's FMA), t for the soft-cap (kCapT), log2-scaled otherwise.  j0 is the tile's first key.
+  // folded into the exponent's FMA), log2-scaled otherwise (less the cap: kShifted).  j0 is the tile's first key.
   __device__ __forceinline__ float transform_one(float x, int j0, int rb, int nb, int r, const BiasRegs& br) const {
     if constexpr (kPlain) {
       return x;
     } else {
       const int j = j0 + 32 * nb + 4 * half + 8 * (r >> 2) + (r & 3);   // key of register r
       if constexpr (C::MOD == kModSoftcap) {
-        x = fast_rcp(fast_exp2(x * cap_in) + 1.f);
-        if constexpr (!kCapT) x = fmaf(x, -2.f * cap_l2, cap_l2);
+        const float e = fast_exp2(x * cap_in);
+        if constexpr (kShifted) x = fast_rcp(fmaf(e, cap_rcp, cap_rcp));
+        else x = fmaf(fast_rcp(e + 1.f), -2.f * cap_l2, cap_l2);
       } else if constexpr (C::MOD == kModAlibi) {
         // slope * |i - j| with j = (j0 + 32*nb + 4*half) + c, c the register's compile-time key
         // offset: one per-lane term per key block minus a uniform constant per register, then one FMA
@@ -454,7 +455,7 @@ struct Wave {
           for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              if (kd[nb][r >> 2][r & 3] != qdoc[rb]) sc[rb][nb][r] = kHidden;
+              if (kd[nb][r >> 2][r & 3] != qdoc[rb]) sc[rb][nb][r] = -INFINITY;
       }
       if (!pos) return;
     } else if constexpr (C::DOC) {
@@ -473,7 +474,7 @@ struct Wave {
           for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              if ((word >> (16 * nb + r)) & 1u) sc[rb][nb][r] = kHidden;
+              if ((word >> (16 * nb + r)) & 1u) sc[rb][nb][r] = -INFINITY;
         return;
       }
     }
@@ -500,21 +501,11 @@ struct Wave {
           if constexpr (C::DOC && !kSplit) hide = hide || kd[nb][r >> 2][r & 3] != qdoc[rb];
           if constexpr ((MASK & kMaskCustom) != 0)  // (valid indices only, as for the score_mod; a key past Sk is hidden already)
             hide = hide || fl_user_mask(b, g, h, ic[rb] + p.q_off, FL_USER_CLAMP && jl + c >= p.Sk ? p.Sk - 1 : jl + c, p);
-          if (hide) sc[rb][nb][r] = kHidden;
+          if (hide) sc[rb][nb][r] = -INFINITY;
         }
     }
   }
 
-  // A row's largest register value (kCapT: of -t) in log2 units
-  __device__ __forceinline__ float max_log2(float m) const {
-    if constexpr (kPlain) return m * c_scale;      // scale > 0 (checked on the host)
-    else if constexpr (kCapT) {
-      // rounded so that cap - reference, which the exponents use, is exact (one of the two subtractions always is): the
-      // saved lse then carries no error that the probabilities do not (5e-7 rms at cap 30; 9e-7 with the maximum itself)
-      return cap_l2 - (cap_l2 - fmaf(m, 2.f * cap_l2, cap_l2));
-    }
-    else return m;
-  }
   // ---- row max of the tile in log2 units, one per row block
   __device__ __forceinline__ void rowmax(const Scores& sc, float (&mx)[C::RB]) const {
 #pragma unroll
@@ -523,8 +514,10 @@ struct Wave {
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) m = fmaxf(m, kCapT ? -sc[rb][nb][r] : sc[rb][nb][r]);
-      mx[rb] = max_log2(half_swap_max(m));
+        for (int r = 0; r < 16; ++r) m = fmaxf(m, sc[rb][nb][r]);
+      m = half_swap_max(m);
+      if constexpr (kPlain) m *= c_scale;          // scale > 0 (checked on the host)
+      mx[rb] = m;
     }
   }
 
@@ -559,9 +552,6 @@ struct Wave {
     if constexpr (kPlain) {
       p0 = fast_exp2(fmaf(s0, c_scale, -m_safe));
       p1 = fast_exp2(fmaf(s1, c_scale, -m_safe));
-    } else if constexpr (kCapT) {                  // (m_safe is the reference minus the cap)
-      p0 = fast_exp2(fmaf(s0, -2.f * cap_l2, -m_safe));
-      p1 = fast_exp2(fmaf(s1, -2.f * cap_l2, -m_safe));
     } else {
       p0 = fast_exp2(s0 - m_safe);
       p1 = fast_exp2(s1 - m_safe);
@@ -632,7 +622,7 @@ struct Wave {
     const float x1 = transform_one(nxt[rb][nb][r + 1], j1, rb, nb, r + 1, br);
     nxt[rb][nb][r] = x0;
     nxt[rb][nb][r + 1] = x1;
-    ps.mx[rb] = fmaxf(fmaxf(ps.mx[rb], kCapT ? -x0 : x0), kCapT ? -x1 : x1);
+    ps.mx[rb] = fmaxf(fmaxf(ps.mx[rb], x0), x1);
   }
 
   // hook(f) runs after the work of fragment f: the caller's tile loads.
@@ -646,7 +636,6 @@ struct Wave {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       ps.m_safe[rb] = m_run[rb] == -INFINITY ? 0.f : m_run[rb];
-      if constexpr (kCapT) ps.m_safe[rb] -= cap_l2;
       ps.psum[rb] = 0.f;
       ps.mx[rb] = -INFINITY;
     }
@@ -726,7 +715,8 @@ struct Wave {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       l_run[rb] += ps.psum[rb];
-      const float mxs = max_log2(half_swap_max(ps.mx[rb]));
+      float mxs = half_swap_max(ps.mx[rb]);
+      if constexpr (kPlain) mxs *= c_scale;        // scale > 0 (checked on the host)
       const float m_old = m_run[rb];
       float m_new = (mxs - m_old > kLazyMaxLog2) ? mxs : m_old;   // false for NaN (-inf - -inf)
       m_new = advance ? m_new : m_old;
@@ -868,11 +858,15 @@ fwd_bf16_kernel(const FwdParams call) {
   }
   w.c_scale = p.scale * kLog2e;                    // raw score -> log2 domain
   w.slope_l2 = 0.f;
-  w.cap_in = w.cap_l2 = 0.f;
+  w.cap_in = w.cap_l2 = w.cap_rcp = 0.f;
   if constexpr (C::MOD == kModSoftcap) {
     // cap * tanh(z) with z = x * scale / cap, in the log2 domain; tanh(z) = 1 - 2 / (exp(2 z) + 1)
-    w.cap_in = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(2.f * w.c_scale / p.softcap)));
-    w.cap_l2 = p.softcap * kLog2e;
+    // (caps beyond these bounds leave every score 0 in fp32, as the bounds do; in between 1 / (2 cap) is a normal number)
+    const float cap = fminf(fmaxf(p.softcap, 0x1p-120f), 0x1p120f);
+    auto uniform = [](float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); };
+    w.cap_in = uniform(2.f * w.c_scale / cap);
+    w.cap_rcp = uniform(-0.5f / (cap * kLog2e));
+    w.cap_l2 = W::kShifted ? -fast_rcp(2.f * w.cap_rcp) : cap * kLog2e;   // (shifted: less this, a raw score of 0 is 0)
   }
   if constexpr (C::MOD == kModAlibi) {
     w.slope_l2 = p.alibi_slopes[h] * kLog2e;
@@ -1388,7 +1382,7 @@ fwd_bf16_kernel(const FwdParams call) {
 #pragma unroll
               for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) cur[rb][nb][r] = W::kHidden;
+                for (int r = 0; r < 16; ++r) cur[rb][nb][r] = -INFINITY;
           } else {
             w.template mask<C::ID_RING + slot_vc * C::ID_BYTES>(cur, t0 * BN, tbw[0], docs, pos);
             w.rowmax(cur, mx);
@@ -1480,7 +1474,12 @@ fwd_bf16_kernel(const FwdParams call) {
   for (int rb = 0; rb < RB; ++rb) {
     const float lt = half_swap_sum(w.l_run[rb]);
     const float inv = lt > 0.f ? 1.f / lt : 0.f;
-    const float lse_v = lt > 0.f ? w.m_run[rb] * kLn2 + __logf(lt) : -INFINITY;
+    float m_row = w.m_run[rb];
+    // (the shift is -1 / (2 cap_rcp), from which cap_l2 is off by the error of the reciprocal; past 2^24 a score is off by as much anyway,
+    // and one of 0 stays 0 without the correction)
+    if constexpr (W::kShifted)
+      m_row = (m_row + w.cap_l2) + (p.softcap < 0x1p24f ? fmaf(w.cap_l2, 2.f * w.cap_rcp, 1.f) * w.cap_l2 : 0.f);
+    const float lse_v = lt > 0.f ? m_row * kLn2 + __logf(lt) : -INFINITY;
 #pragma unroll
     for (int d = 0; d < DVB; ++d)
 #pragma unroll
