@@ -517,14 +517,15 @@ bwd_pair_kernel(const PairParams pp) {
 #pragma unroll
         for (int r2 = 0; r2 < 8; ++r2) {
           float pv[2], ds[2];
+          // (opaque: the compiler would unpack all of them in front of the loop over the problems and run out of registers.  The unpacking
+          // itself is left to it: it does not see what asm statements need behind matrix instructions)
+          if constexpr (!C::BIAS_F32) asm volatile("" : "+v"(blp[C::BIAS_F32 ? 0 : t][r2]));
 #pragma unroll
           for (int e = 0; e < 2; ++e) {
             const int r = 2 * r2 + e;
             float bl;
             if constexpr (C::BIAS_F32) bl = blf[C::BIAS_F32 ? t : 0][r];
-            // (by hand: the compiler would unpack all of them in front of the loop over the problems and run out of registers)
-            else if (e == 0) asm volatile("v_lshlrev_b32 %0, 16, %1" : "=v"(bl) : "v"(blp[C::BIAS_F32 ? 0 : t][r2]));
-            else asm volatile("v_and_b32 %0, 0xffff0000, %1" : "=v"(bl) : "v"(blp[C::BIAS_F32 ? 0 : t][r2]));
+            else bl = __uint_as_float(e ? (blp[C::BIAS_F32 ? 0 : t][r2] & 0xFFFF0000u) : (blp[C::BIAS_F32 ? 0 : t][r2] << 16));
             const float st_r = ROLE == 1 || C::KEYB ? __int_as_float(ql[r >> 2][r & 3]) : 0.f;
             if constexpr (C::KEYB) bl += ROLE == 0 ? st_r : st0;
             if constexpr (C::KEYB || !C::BIAS_F32) bl = bias_log2(bl);

@@ -32,3 +32,13 @@ def test_stationary_bias_kernels_are_built_without_scratch(tmp_path, scratch):
     r = subprocess.run(["make", "-f", os.path.join(CSRC, "Makefile"), "-C", str(tmp_path), "HDRS=", "_build/fl_inst_pairtest.o"], capture_output=True, text=True)
     assert (r.returncode != 0) == scratch, r.stdout + r.stderr
     assert (tmp_path / "_build" / "fl_inst_pairtest.o").exists() == (not scratch)
+
+
+def test_no_vector_instruction_is_written_by_hand():
+    """The wait states that a vector instruction needs behind a matrix instruction which reads or writes its destination are kept by the
+    compiler, and it does not look into asm statements."""
+    import glob
+    import re
+    for path in sorted(glob.glob(os.path.join(CSRC, "*.h*"))):
+        found = re.findall(r'\basm\b[^;]*?"[^"]*\bv_\w+[^"]*"', open(path).read())
+        assert not found, (path, found)
