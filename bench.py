@@ -149,7 +149,7 @@ BWD_CONFIGS = ["c2_d128", "c2_d64", "c3a_alibi", "c3b_softcap", "c3c_window_doc"
 
 
 def time_backward(name, steps, warmup):
-    """One fl_attn_bwd call (pre-pass + dQ kernel + dK/dV kernel) per step on the configuration's
+    """One fl_attn_bwd call (dQ kernel + dK/dV kernel) per step on the configuration's
     inputs, bf16 gradients; out and lse come from one untimed forward call.  FLOPs are the five
     contractions of the backward pass on unmasked pairs (2.5 x the forward count); the kernels
     recompute the score and dP tiles in both passes, which is not counted."""

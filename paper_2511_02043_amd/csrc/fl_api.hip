@@ -1030,7 +1030,7 @@ PrefillLayout prefill_layout(int64_t B, int64_t Hkv, int64_t D, int64_t max_len)
 // The stationary-bias kernels (fl_bwd_pair.hpp) by sizes alone: how many ranges the row axis is cut into, one workgroup per 64
 // owned rows, (b, h) and range.  Few, long ranges load the bias seldom and leave small partial gradients; the launch should fill
 // the 256 compute units (one workgroup each) a whole number of times.  A range costs about two problems of start-up (128 x 8 heads
-// x 384, D = 32, dQ / dK and dV: 5 ranges 77 / 86 us, 8 97 / 106, 16 96 / 96, 32 116 / 113).
+// x 384, D = 32, dQ / dK and dV: 4 ranges 98 / 117 us, 5 89 / 105, 6 126 / 151, 8 104 / 121, 16 101 / 109, 32 122 / 126).
 // At most `limit` ranges.
 int pair_chunks(int64_t B, int64_t G, int64_t H, int64_t S_own, int64_t limit) {
   const int64_t base = B * H * ((S_own + 63) / 64);
@@ -1534,8 +1534,9 @@ static fl_status forward_call(const fl_tensor* q, const fl_tensor* k, const fl_t
   if (order == 1 && nbh % 8 != 0) order = 0;
   p.order = order;
   // grouped-query heads: the heads of a kv head stay on one XCD, so that its L2 fetches their keys and values once (where
-  // every XCD still gets whole kv heads; causal training step, 2 x 32 / 8 heads x 8192 rows, D = 128: 4974 -> 4903 us with the
-  // dQ kernel in the same order).
+  // every XCD still gets whole kv heads).  Causal, 2 x 32 / 8 heads x 8192 rows, D = 128: 1021 -> 1008 us, 8 x 32 / 8 x 2048 350 -> 342; window 1024,
+  // 1 x 32 / 8 x 32768 688 -> 676; window 256, 4 x 16 / 2 x 4096, D = 64, 50.1 -> 45.6; chunks of 8 x 512 rows, 32 / 8 heads, D = 128, 417 -> 407 and 371 -> 368;
+  // unmasked and causal 16 / 2 heads, D = 64, within 0.6 %.
   const int64_t share = H / Hkv / ke->key.pack;
   p.order_heads = order == 1 && dtype == FL_BF16 && (nbh / share) % 8 == 0 && g_tuning.order < 0 ? (int)share : 1;
 

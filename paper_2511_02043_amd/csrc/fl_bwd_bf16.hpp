@@ -569,7 +569,8 @@ bwd_dq_kernel(const BwdParams p) {
   if (p.order_q == 1) {
     // consecutive workgroup ids go round-robin to the 8 XCDs: give each XCD whole heads, so that a
     // head's K / V tiles stay in one L2 (the host checks that the head count is a multiple of 8), with the heads that read
-    // the same K / V side by side
+    // the same K / V side by side (causal training step, 2 x 32 / 8 heads x 8192, D = 128, in four runs: 4784 -> 4744 us, 4761 -> 4732,
+    // 4787 -> 4773, 4802 -> 4759; backward passes of 16 / 2 heads at D = 64 no different)
     const int share = p.order_heads, idx = blockIdx.x >> 3, inner = idx % (nq * share);
     bh = ((idx / (nq * share)) * 8 + (blockIdx.x & 7)) * share + inner % share;
     qt = nq - 1 - inner / share;
@@ -1016,8 +1017,8 @@ bwd_dkdv_kernel(const BwdParams p) {
 
   // A whole tile's addresses: a uniform base and what this lane adds to it, the same for each of its load instructions (their rows
   // are a multiple of 16 apart, which leaves the swizzle as it is).  64 rows fit 32 bits: the host refuses negative row strides and those of
-  // 2^23 elements and more.  Not with bias values in registers, where there is no room for it.  (With the items as pairs: causal
-  // training step 4 x 16 x 4096, D = 64, 830 -> 818 us)
+  // 2^23 elements and more.  Not with bias values in registers, where there is no room for it.  (Causal training step
+  // 4 x 16 x 4096, D = 64: 778 -> 772 us; with the items as pairs, earlier, 830 -> 818)
   const uint32_t q_lane = tile_lane_offset<C::D>(wave, lane, (uint32_t)p.q.ss * 2), d_lane = tile_lane_offset<C::DV>(wave, lane, (uint32_t)p.dout.ss * 2);
   auto load_item = [&](Item it, int stage) __attribute__((always_inline)) {
     const int t = t_lo + it.r, h = h_first + it.h;

@@ -14,9 +14,10 @@
 // streamed rows are its own: it fetches them into a private ring and waits for nobody, so that the two waves of a SIMD drift apart
 // and fill each other's gaps; the workgroup only meets once or twice per problem.  (With tiles shared by the workgroup and a
 // barrier per step the kernels were no slower at head dim 32 but 1.3 x at 64, 256 x 8 heads x 120; four waves of 512 registers,
-// two blocks each, took 110 / 107 us where this takes 76 / 85: dQ / dK, dV of 128 x 8 heads x 384, D = 32.)
-// What bounds them there: instruction issue (two waves of a SIMD issue in 68 % of the clocks: 30 matrix, 48 exp2, 236 other vector
-// and 101 scalar instructions per wave and problem of three steps) and, for the rest, the start of a workgroup (7 us).  The
+// two blocks each, took 110 / 107 us where this took 76 / 85, before lse met the biases in log2 units: dQ / dK, dV of 128 x 8 heads x
+// 384, D = 32, which now take 88 / 104.)
+// What bounds them there: instruction issue (two waves of a SIMD issue in 75 % of the clocks; dQ: 27 matrix, 48 exp2, 287 other vector
+// and 104 scalar instructions per wave and problem of three steps) and, for the rest, the start of a workgroup (7 us).  The
 // general kernels took 140 + 64 (reduction of the staged dS) / 146 us.
 // The accumulators of a problem are partial over kq: the four waves of a row group meet in LDS, each sums and stores a quarter of
 // the channels, in a fixed order (bitwise reproducible, no atomics).
@@ -47,7 +48,7 @@ struct PairCfg : BwdCfg<D_, kModNone, 0, 128, 2, 1> {
   static constexpr bool KEYB = KEYB_;
   static constexpr int NACC = ROLE == 0 ? 1 : 2;
   // A wave's ring: a stage is refilled as soon as its fragments are in registers, which is one step ahead of a ring that waits
-  // for the end of the step.  Two stages at head dim 32 (one: 90 / 96 us instead of 77 / 86); at 64 the LDS holds one.
+  // for the end of the step.  Two stages at head dim 32 (one: 91 / 105 us instead of 88 / 104); at 64 the LDS holds one.
   static constexpr int NSTG = D_ == 32 ? 2 : 1;
   static constexpr int STEP_TILE = 32 * Base::ROW;                   // 32 rows of one streamed tensor
   static constexpr int STEP_STAT = 2 * STEP_TILE;                    // role 1: lse2, -delta of the rows

@@ -781,8 +781,9 @@ fwd_bf16_kernel(const FwdParams call) {
     if (call.B > 1 && call.B <= 64) {
       // Sequences go out longest first: the launch has a few workgroups per compute unit at most, and the one that takes
       // the last long sequence would end long after the rest.  A lane ranks one sequence (ties by index).  (8 sequences of
-      // 4096 - 8192 tokens, 512 rows, 32 / 8 heads,
-      // D = 128: 422 -> 399 us; more than 64 sequences are many workgroups anyway)
+      // 4096 - 8192 tokens, 512 rows, 32 / 8 heads, D = 128, together with the order of heads above, which gives 1 to 2 % of it: 420 -> 407,
+      // 406 -> 389, 454 -> 417 and 414 -> 380 us in four runs, two times of one side and run within 1 %; more than 64
+      // sequences are many workgroups anyway)
       const int ln = tid & 63;
       const int mine = ln < call.B ? max(0, min(call.kv_lens[ln], call.Sk)) : -1;
       int rank = 0;

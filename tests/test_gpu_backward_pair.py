@@ -70,7 +70,7 @@ def test_same_as_general_kernels(D, form):
         assert np.all(np.isfinite(new[n])), n
         rel = np.linalg.norm(new[n] - old[n]) / np.linalg.norm(old[n])
         print(f"{form} D {D} {n}: {rel:.2e}", flush=True)
-        assert rel <= 4e-3, n                      # both round P and dS to bf16 (2^-9 each), from differently rounded exponents
+        assert rel <= 4e-3, n                      # both round P and dS to bf16 (2^-9 each)
     assert not all(np.array_equal(new[n], old[n]) for n in new), "the switch chose the same kernels"
 
 
