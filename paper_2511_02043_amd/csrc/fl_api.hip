@@ -123,10 +123,11 @@ const fl::KernelEntry* find_entry(const fl_variant_desc* d, int dtype, int D, in
       if (packed != nullptr && k.key.nwaves != (packed->wide ? 8 : 4)) continue;
       if (dtype == FL_F32) {
         // The smallest head dim that fits; of its shapes the first (fewest key splits) that gives every CU a workgroup, two
-        // under a mask that leaves the query tiles unequal work, else the last.  Measured with 256- / 128- / 64- / 32-row
-        // workgroups: 2 x 8 heads of 1024 rows at D = 64 154 / 83 / 51 / 61 us (64, 128, 256, 512 workgroups), 4 x 16 heads
-        // 162 / 167 / 188 / 225; causal, 2 x 8 heads of 2048 rows 289 / 158 / 105 / 119.
-        if (D > k.key.D || Dv > k.key.DV) continue;
+        // under a mask that leaves the query tiles unequal work, else the last.  Measured with 512- / 256- / 128- / 64- / 32-row
+        // workgroups: 2 x 8 heads of 1024 rows at D = 64 170 / 92 / 56 / 37 / 46 us (256 workgroups of 64 rows), 8 x 16 heads of 2048
+        // 718 / 738 / 781 / 848 / 1031; causal, 2 x 8 heads of 2048 rows 315 / 170 / 97 / 73 / 87 (512 workgroups of 64 rows).
+        const bool plain = d->score_mod == FL_MOD_NONE && (mask & FL_MASK_DOC) == 0 && d->n_bias == 0 && d->combine == FL_SINGLE && d->epilogue == 0;
+        if (D > k.key.D || Dv > k.key.DV || (k.key.mod == 0) != plain) continue;
         const bool fills = best != nullptr && heads * ((Sq + best->bm - 1) / best->bm) >= (mask != 0 ? 512 : 256);
         if (best == nullptr || k.key.D < best->key.D || (k.key.D == best->key.D && (g_tuning.bm != 0 ? k.bm == g_tuning.bm : heads > 0 && !fills)))
           best = &k;

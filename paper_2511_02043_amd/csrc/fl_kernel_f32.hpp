@@ -1,27 +1,36 @@
-// fp32 attention-variant forward kernel: both contractions on the fp32 matrix instruction
-// (v_mfma_f32_32x32x2_f32), fp32 scores, softmax state and accumulators.
+// fp32 attention-variant forward kernel: fp32 storage, scores, softmax state and accumulators; both contractions over three bf16
+// parts of each operand (v_mfma_f32_32x32x16_bf16), or on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32).
 //
 // This is the fp32-storage specialisation of the fused pass; tanh, the logarithm and the gate use the
 // accurate math-library routines, and the result is meant to stay within 1e-5 of an fp64 evaluation.
-// Every variant feature is available here, as runtime switches.  It follows the same structure as the
-// bf16 kernel: a workgroup owns a tile of query rows, walks the visible key tiles (skipper), keeps
-// (m, l, O) in registers and never stores a score (Sec. 3.2 dimension demotion; Sec. 3.4 running max / sum
+// Every variant feature is available here, as runtime switches; calls without any (F32Cfg::PLAIN) have instances without the
+// switches.  It follows the same structure as the bf16 kernel: a workgroup owns a tile of query rows, walks the visible key tiles
+// (skipper), keeps (m, l, O) in registers and never stores a score (Sec. 3.2 dimension demotion; Sec. 3.4 running max / sum
 // with the exp(m_old - m_new) correction).
 //
 // Orientation as in the bf16 kernel: S^T = K Q^T with the query in the lane (lane % 32) and sixteen keys
-// n(r) = 8 (r / 4) + 4 (lane / 32) + r % 4 in the registers, so a softmax row is two lanes, and register r
-// of P is, as it stands, the B operand of the contraction step over the key pair n(r) of
-// O^T += V^T P^T.  Both operands of a step may take the channels (or keys) in any common order: a lane
-// reads K in 16-byte pieces (four steps per LDS read), and V^T row c of channel block d is channel
-// DVB c + d, so that one LDS read of 4 DVB bytes feeds the DVB steps of a key pair.
+// n(r) = 8 (r / 4) + 4 (lane / 32) + r % 4 in the registers, so a softmax row is two lanes, and the registers of P are, as they
+// stand, the B operand of O^T += V^T P^T (register r of the step over the key pair n(r); registers 8 s ... 8 s + 7, split, of the
+// s-th step of sixteen keys).  Both operands of a step may take the channels (or keys) in any common order: a lane
+// reads K in 16-byte pieces, and V^T row c of channel block d is channel DVB c + d, so that one LDS read of 4 DVB bytes feeds
+// DVB channel blocks.
 //
-// What bounds it: the fp32 matrix rate (157 TFLOP/s; a 32x32x2 step takes 64 cycles of a SIMD, in which it
-// issues sixteen other instructions).  It has to be kept supplied by every SIMD: a wave takes 32 query rows, and where the
-// call has fewer than two such waves per SIMD the key tiles of a row group are dealt to KS waves, which merge through LDS by
-// the rescale rule of Sec. 3.3.  K / V tiles of 32 keys go to LDS by direct loads.
-// Measured, 2 x 8 heads, 1024 rows and keys, D = 64: 48 us, 89 TFLOP/s; the same pass on plain VALU arithmetic (four lanes per
-// row, LDS broadcasts) took 508 us.  Large launches (8 x 16 heads, 2048 rows) run at 112 TFLOP/s: the softmax of the two
-// waves of a SIMD falls between the same two barriers.
+// Contractions on parts: x = h + m + l, each the bf16 rounding of what the ones before leave, holds 24 bits; six of the nine products
+// of two such sums (all above 2^-27 of the largest) cost 6 x 32 clocks for 16 channels where the fp32 instruction takes 8 x 64.  The error
+// against fp64 is lower than the fp32 instruction's (fewer roundings of the sum: 2 x 8 heads x 1024 rows, D = 64, relative 4.2e-7 before,
+// 2.9e-7).  Values below 2^-100 or beyond 2^100 may lose bits or round to infinity: Q is checked as it is split, and a lost bit of
+// K then is below 2^-134 2^100; V and overflows show in the accumulators (NaN, infinity, or below 2^-100).  A wave (where waves share
+// tiles: a workgroup) that finds such a value takes the pass again on the fp32 instruction, so that infinities, NaN and tiny values
+// give what they gave there.
+//
+// What bounds it: issue of vector instructions, 8.8 for each matrix instruction at D = 64 (eleven per pair of values split; four run beside
+// a matrix instruction).  So a wave takes two row blocks (K and V are split once for both) wherever registers allow, the split of
+// the next operands stands between the matrix instructions of the present ones (f32_stage), and where the call has fewer than two waves
+// per SIMD the key tiles of a row group are dealt to KS waves, which merge through LDS by the rescale rule of Sec. 3.3.  K / V tiles
+// of 32 keys go to LDS by direct loads.
+// Measured against the fp32 instruction in both contractions, one row block per wave: 2 x 8 heads, 1024 rows and keys, D = 32 / 64 / 128: 30 / 53 /
+// 107 -> 20 / 37 / 63 us, 8 x 16 heads x 2048 rows, D = 64: 1241 -> 718 us (191 TFLOP/s); the same pass on plain VALU arithmetic
+// took 508 us for the first at D = 64.
 #pragma once
 #include "fl_kernel_bf16.hpp"
 
@@ -29,12 +38,16 @@ namespace fl {
 
 constexpr int kF32Keys = 32;     // keys per LDS tile (= kSumBlock)
 
-template <int DMAX_, int RG_, int KS_>
+template <int DMAX_, int RB_, int RG_, int KS_, bool PLAIN_>
 struct F32Cfg {
+  static constexpr bool PLAIN = PLAIN_;            // no score_mod, bias, document mask, epilogue or second stream: nothing of those in the code
+  static constexpr bool PARTS = PLAIN_ || DMAX_ <= 64;   // contractions on bf16 parts (the switches of the variants leave no registers for them at 128)
   static constexpr int DMAX = DMAX_;               // head dims up to this one; smaller ones compute on channels that are zero in Q
-  static constexpr int RG = RG_, KS = KS_;         // row groups (32 query rows each) and key splits of the workgroup
+  static constexpr int RB = RB_;                   // 32-row blocks of a wave
+  static constexpr int RG = RG_, KS = KS_;         // row groups (32 RB query rows each) and key splits of the workgroup
   static constexpr int NT = RG * KS * 64;
-  static constexpr int BM = RG * 32;
+  static constexpr int WPE = RB * DMAX > 128 ? 1 : 2;    // waves per SIMD that the registers are cut for
+  static constexpr int WROWS = 32 * RB, BM = RG * WROWS;
   static constexpr int ROW = DMAX * 4;             // bytes of a tile row in LDS
   static constexpr int CH = DMAX / 4;              // 16-byte chunks of a tile row
   static constexpr int TILE = kF32Keys * ROW;
@@ -43,9 +56,18 @@ struct F32Cfg {
   static constexpr int RING = KS * NBUF * STAGE;   // [key split][buffer][K, V]
   static constexpr int DVB = DMAX / 32;            // 32-channel blocks of the output
   static constexpr int NINSTR = TILE / 1024;       // direct-load instructions per tile
-  static constexpr int OBYTES = DVB * 16 * 64 * 4; // one wave's accumulators
-  static constexpr int MERGE = RG * (KS - 1) * (OBYTES + 2 * 64 * 4);
-  static constexpr int LDS = RING > MERGE ? RING : MERGE;
+  static constexpr int OBYTES = RB * DVB * 16 * 64 * 4;   // one wave's accumulators
+  static constexpr int MLBYTES = RB * 2 * 64 * 4;  // ... running maxima and sums
+  // Every split of a row group hands its accumulators over, and each wave sums and stores its share of them.  An epilogue or a
+  // second stream needs whole rows: the other splits hand over to the first.
+  static constexpr bool SHARE = PLAIN_ && KS_ > 1;
+  static constexpr int MERGE = RG * (SHARE ? KS : KS - 1) * (OBYTES + MLBYTES);
+  // The third (and second) parts of Q's fragments wait in LDS where two waves per SIMD have no registers for them: [row group][step]
+  // [block][part], 1 KiB each.
+  static constexpr int QP = !PARTS ? 0 : DMAX == 128 && RG > 1 ? 1 : RB * DMAX >= 128 ? 2 : 0;   // parts in LDS: the third, the second
+  static constexpr int QBYTES = QP * RG * RB * (DMAX / 16) * 1024;
+  static constexpr int LDS = RING + QBYTES > MERGE ? RING + QBYTES : MERGE;
+  static constexpr int QBASE = RING;
   static_assert(DMAX == 32 || DMAX == 64 || DMAX == 128, "head dims of the fp32 kernel");
 };
 
@@ -97,12 +119,60 @@ __device__ __forceinline__ void f32_wait_lds() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// Three bf16 parts of eight fp32 values, each the rounded rest of the one before: 24 bits of the value, exact unless it is below
+// 2^-100 or rounds to infinity.  (A rest by v_dot2_f32_bf16 would take three instructions less per pair, but that runs on the matrix
+// unit: four of them beside a matrix instruction of 32 clocks make it 56, eight ordinary ones 43.)
+struct F32Split {
+  i32x4 h, m, l;
+};
+template <int E>   // values 2 E and 2 E + 1 of the eight
+__device__ __forceinline__ void f32_split(float a, float b, F32Split& out) {
+  auto rest = [&](uint32_t u) __attribute__((always_inline)) {
+    a -= __uint_as_float(u << 16);
+    b -= __uint_as_float(u & 0xffff0000u);
+  };
+  const uint32_t h = pack_bf16(a, b);
+  rest(h);
+  const uint32_t m = pack_bf16(a, b);
+  rest(m);
+  out.h[E] = (int)h;
+  out.m[E] = (int)m;
+  out.l[E] = (int)pack_bf16(a, b);
+}
+// The N-th of the six products of parts above 2^-27 of the largest, small ones first: acc += a b over one 16-element step
+template <int N>
+__device__ __forceinline__ f32x16 f32_mfma(const F32Split& a, const F32Split& b, f32x16 acc) {
+  const i32x4& x = N == 0 ? a.l : N == 2 || N == 3 ? a.m : a.h;
+  const i32x4& y = N == 1 ? b.l : N == 2 || N == 4 ? b.m : b.h;
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), acc, 0, 0, 0);
+}
+// N matrix instructions with W pieces of vector work spread between them, in this order: a wave issues in order, and the matrix unit
+// is free for its next instruction 32 clocks after the last
+template <int N, int W, class M, class J>
+__device__ __forceinline__ void f32_stage(M&& mfma, J&& job) {
+  static_for<0, N>([&](auto i) __attribute__((always_inline)) {
+    mfma(i);
+    static_for<i * W / N, (i + 1) * W / N>(job);
+    __builtin_amdgcn_sched_barrier(0);
+  });
+}
+// Whether all values taken are zero or of a magnitude in [2^-100, 2^100), for which the parts hold the value
+struct F32Range {
+  uint32_t least = 0xffffffffu, most = 0u;
+  __device__ __forceinline__ void take(float x) {
+    const uint32_t v = __float_as_uint(x) & 0x7fffffffu;
+    least = min(least, v - 1u);                    // (zero: the largest)
+    most = max(most, v);
+  }
+  __device__ __forceinline__ bool inside() const { return least >= 0x0d7fffffu && most < 0x71800000u; }
+};
+
 template <class C>
-__global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE)))
 fwd_f32_kernel(const FwdParams p) {
-  constexpr int DMAX = C::DMAX, RG = C::RG, KS = C::KS, DVB = C::DVB, ROW = C::ROW, NU = DMAX / 8;
-  const int MOD = p.mod, NBIAS = p.n_bias;
-  const uint32_t MASK = p.mask, EPI = p.epi;
+  constexpr int DMAX = C::DMAX, RB = C::RB, RG = C::RG, KS = C::KS, DVB = C::DVB, ROW = C::ROW, NU = DMAX / 8, NK = DMAX / 16;
+  const int MOD = C::PLAIN ? kModNone : p.mod, NBIAS = C::PLAIN ? 0 : p.n_bias;
+  const uint32_t MASK = C::PLAIN ? p.mask & ~kMaskDoc : p.mask, EPI = C::PLAIN ? 0 : p.epi;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
 
   const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
@@ -122,15 +192,13 @@ fwd_f32_kernel(const FwdParams p) {
   }
   const int h = bh % p.H, g = (bh / p.H) % p.G, b = bh / (p.H * p.G);
   const int hk = h / (p.H / p.Hkv);
-  const int i0 = qt * C::BM, iw = i0 + 32 * rg;    // first query row of the workgroup / of the wave
-  const int i = iw + col, ic = i < p.Sq ? i : p.Sq - 1;
-  const int ns = p.diff ? 2 : 1;                   // softmax streams, one after the other
+  const int i0 = qt * C::BM, iw = i0 + C::WROWS * rg;    // first query row of the workgroup / of the wave
+  const int ns = !C::PLAIN && p.diff ? 2 : 1;                   // softmax streams, one after the other
 
-  const int qdoc = (MASK & kMaskDoc) ? p.q_doc[(int64_t)b * p.Sq + ic] : 0;
   const float slope = MOD == kModAlibi ? p.alibi_slopes[h] : 0.f;
 
   // ---- visible key range of the workgroup (positional masks, rows by their positions); document summaries of its rows
-  const int i_max = min(i0 + C::BM, p.Sq) - 1, iw_max = min(iw + 32, p.Sq) - 1;
+  const int i_max = min(i0 + C::BM, p.Sq) - 1, iw_max = min(iw + C::WROWS, p.Sq) - 1;
   int k_lo, k_hi;
   key_range(MASK, i0 + p.q_off, i_max + p.q_off, p.Sk, p.window, p.prefix, k_lo, k_hi);
   const int t_lo = k_lo / kF32Keys, t_hi = (k_hi + kF32Keys - 1) / kF32Keys;
@@ -140,13 +208,17 @@ fwd_f32_kernel(const FwdParams p) {
   if ((MASK & kMaskDoc) != 0) {
     const int nqs = (p.Sq + kSumBlock - 1) / kSumBlock;
     const int2* s = p.q_sum + (int64_t)b * nqs;
-    qs_wg = s[min(i0 / kSumBlock, nqs - 1)];
-    for (int u = 1; u < RG; ++u) {
-      const int2 x = s[min(i0 / kSumBlock + u, nqs - 1)];
-      qs_wg.x = min(qs_wg.x, x.x);
-      qs_wg.y = max(qs_wg.y, x.y);
-    }
-    qs_w = s[min(iw / kSumBlock, nqs - 1)];
+    auto range = [&](int first, int n) __attribute__((always_inline)) -> int2 {
+      int2 r = s[min(first / kSumBlock, nqs - 1)];
+      for (int u = 1; u < n; ++u) {
+        const int2 x = s[min(first / kSumBlock + u, nqs - 1)];
+        r.x = min(r.x, x.x);
+        r.y = max(r.y, x.y);
+      }
+      return r;
+    };
+    qs_wg = range(i0, RG * RB);
+    qs_w = range(iw, RB);
   }
   auto tile_ids = [&](int t) __attribute__((always_inline)) -> int2 {   // document-id range of tile t's keys
     return (MASK & kMaskDoc) != 0 ? p.kv_sum[(int64_t)b * nks + t] : make_int2(0, 0);
@@ -163,23 +235,8 @@ fwd_f32_kernel(const FwdParams p) {
   for (int s = 0; s < ns; ++s) {
     const View& qv = s == 0 ? p.q : p.q2;
     const View& kv = s == 0 ? p.k : p.k2;
-    float4 qf[NU];                                 // B fragments of S^T = K Q^T; channels past D are zero
-    {
-      int ql = lane;                               // (opaque, as in the epilogue below)
-      asm volatile("" : "+v"(ql));
-      const float* qp = (const float*)qv.ptr + b * qv.sb + g * qv.sg + h * qv.sh + (int64_t)min(iw + (ql & 31), p.Sq - 1) * qv.ss;
-#pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        const int c = 8 * u + 4 * (ql >> 5);
-        qf[u] = c < p.D ? *(const float4*)(qp + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-    }
-    f32x16 o[DVB];
-#pragma unroll
-    for (int d = 0; d < DVB; ++d)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
-    float m = -INFINITY, l = 0.f;                  // log2-domain running max; this lane's part of the running sum
+    f32x16 o[RB][DVB];
+    float m[RB], l[RB];                            // log2-domain running max; this lane's part of the running sum
 
     const float* kp = (const float*)kv.ptr + b * kv.sb + g * kv.sg + hk * kv.sh;
     const float* vp = (const float*)p.v.ptr + b * p.v.sb + g * p.v.sg + hk * p.v.sh;
@@ -192,6 +249,21 @@ fwd_f32_kernel(const FwdParams p) {
       constexpr bool kKeys = decltype(is_k)::value;   // K rows are swizzled
       const int last = p.Sk - 1 - t * kF32Keys;    // last row of the tile that exists (uniform)
       const unsigned char* base = (const unsigned char*)(head + (int64_t)(t * kF32Keys) * ss);
+      if (last >= kF32Keys - 1 && dim == DMAX) {   // whole tile: a lane's offsets differ between the instructions in their chunk only
+        constexpr int RPI = 64 / C::CH;            // rows of an instruction; the swizzle of a row is that of its instruction's first ^ its own
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const int row = ln / C::CH, pos = ln % C::CH;
+        const uint32_t chunk = (uint32_t)(kKeys ? pos ^ swz_f32<C::CH>(row) : pos) << 4, first = (uint32_t)row * (uint32_t)ss * 4u;
+#pragma unroll
+        for (int u = 0; u < (C::NINSTR + RG - 1) / RG; ++u) {
+          const int inst = (rg + u * RG) % C::NINSTR;
+          const uint32_t off = (chunk ^ (kKeys ? (uint32_t)swz_f32<C::CH>(inst * RPI) << 4 : 0u)) + first;
+          __builtin_amdgcn_global_load_lds((global_cvoid*)(base + (int64_t)(inst * RPI) * ss * 4 + off),
+                                           (lds_void*)(lds_raw + lds_off + inst * 1024), 16, 0, 0);
+        }
+        return;
+      }
       auto issue = [&](auto zeros) __attribute__((always_inline)) {
         int ln = lane;
 #pragma unroll
@@ -234,225 +306,493 @@ fwd_f32_kernel(const FwdParams p) {
       return t < t_hi && classify(t, i0, i_max, qs_wg, tile_ids(t)) != kSkip;
     };
 
-    // one tile: scores, softmax update, P V.  before_softmax() runs when the K tile has been read, before_pv() before V is.
-    auto tile = [&](int t, int cls, uint32_t buf, auto&& before_softmax, auto&& before_pv) __attribute__((always_inline)) {
-      // S^T = K Q^T: one LDS read per four steps, four reads ahead
-      f32x16 sc;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+    // One pass over the keys.  EXACT = 0: both contractions on the bf16 matrix instruction, over the three parts of each operand;
+    // EXACT = 1: on the fp32 one.  Returns whether the parts may have lost something (EXACT = 0 only).
+    auto pass = [&](auto exact) __attribute__((always_inline)) -> bool {
+      constexpr bool EXACT = decltype(exact)::value;
+      float4 qf[EXACT ? RB : 1][EXACT ? NU : 1];   // B fragments of S^T = K Q^T; channels past D are zero
+      F32Split qp[EXACT ? 1 : RB][EXACT ? 1 : NK];
+      F32Range range;
       {
-        constexpr int G = 4 < NU ? 4 : NU, NG = NU / G;
-        F32Vec<4>::type kf[NU];
-        auto read = [&](auto uc) __attribute__((always_inline)) {
-          constexpr int u = decltype(uc)::value;
-          F32Vec<4>::template read<0>(kf[u], (ka ^ (uint32_t)(u << 5)) + buf);
-        };
-        static_for<0, G>(read);
-        static_for<0, NG>([&](auto gc) __attribute__((always_inline)) {
-          constexpr int gg = decltype(gc)::value;
-          if constexpr (gg + 1 < NG) static_for<(gg + 1) * G, (gg + 2) * G>(read);
-          f32_wait_lds<gg + 1 < NG ? G : 0>();
-          static_for<gg * G, (gg + 1) * G>([&](auto uc) __attribute__((always_inline)) {
-            constexpr int u = decltype(uc)::value;
-            sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[u][0], qf[u].x, sc, 0, 0, 0);
-            sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[u][1], qf[u].y, sc, 0, 0, 0);
-            sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[u][2], qf[u].z, sc, 0, 0, 0);
-            sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[u][3], qf[u].w, sc, 0, 0, 0);
-          });
-        });
-      }
-
-      before_softmax();
-      // variant transform (Eq. 3, Eq. 4, biases, masks); register r holds key jl + 8 (r / 4) + r % 4
-      const int jl = t * kF32Keys + 4 * half;
-      auto key = [&](int r) __attribute__((always_inline)) { return jl + 8 * (r >> 2) + (r & 3); };
-      const bool plain = MOD == kModNone && NBIAS == 0;   // then scale and log2(e) are one factor
-      const float f1 = plain ? p.scale * kLog2e : p.scale;
+        int ql = lane;                             // (opaque, as in the epilogue below)
+        asm volatile("" : "+v"(ql));
 #pragma unroll
-      for (int r = 0; r < 16; ++r) sc[r] *= f1;
-      if (MOD == kModSoftcap) {
+        for (int rb = 0; rb < RB; ++rb) {
+          const float* qrow = (const float*)qv.ptr + b * qv.sb + g * qv.sg + h * qv.sh + (int64_t)min(iw + 32 * rb + (ql & 31), p.Sq - 1) * qv.ss;
+          float4 x[NU];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sc[r] = p.softcap * tanhf(sc[r] / p.softcap);
-      }
-      if (MOD == kModAlibi) {
+          for (int u = 0; u < NU; ++u) {
+            const int c = 8 * u + 4 * (ql >> 5);
+            x[u] = c < p.D ? *(const float4*)(qrow + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+          }
+          if constexpr (EXACT) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sc[r] -= slope * fabsf((float)(i + p.q_off - key(r)));
-      }
-      for (int nb = 0; nb < NBIAS; ++nb) {
-        const BiasView& bv = p.bias[nb];
-        int bl = ic;
-        asm volatile("" : "+v"(bl));
-        const int64_t row = b * bv.sb + g * bv.sg + h * bv.sh + (int64_t)bl * bv.si;
+            for (int u = 0; u < NU; ++u) qf[rb][u] = x[u];
+          } else {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int64_t off = row + (int64_t)min(key(r), p.Sk - 1) * bv.sj;
-          sc[r] += bv.is_f32 ? ((const float*)bv.ptr)[off] : bf16_to_f32(((const uint16_t*)bv.ptr)[off]);
+            for (int kk = 0; kk < NK; ++kk) {
+              const float v[8] = {x[2 * kk].x, x[2 * kk].y, x[2 * kk].z, x[2 * kk].w,
+                                  x[2 * kk + 1].x, x[2 * kk + 1].y, x[2 * kk + 1].z, x[2 * kk + 1].w};
+#pragma unroll
+              for (int e = 0; e < 8; ++e) range.take(v[e]);
+              // (the waves of a row group hold the same rows: the ks-th stores every KS-th fragment)
+              if (C::QP < 2 || (kk * RB + rb) % KS == ks) {
+                static_for<0, 4>([&](auto e) __attribute__((always_inline)) { f32_split<e>(v[2 * e], v[2 * e + 1], qp[rb][kk]); });
+                if (C::QP > 0 && (kk * RB + rb) % KS == ks) {
+                  i32x4* dst = (i32x4*)(lds_raw + C::QBASE + ((rg * NK + kk) * RB + rb) * C::QP * 1024 + lane * 16);
+                  dst[0] = qp[rb][kk].l;
+                  if (C::QP > 1) dst[64] = qp[rb][kk].m;
+                }
+              } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) qp[rb][kk].h[e] = (int)pack_bf16(v[2 * e], v[2 * e + 1]);
+              }
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
         }
       }
-      if (cls == kPartial) {                       // the positional masks and the end of the keys as two bounds on the key
-        const int ip = i + p.q_off;
-        int last = p.Sk - 1, first = 0;
-        if ((MASK & kMaskPrefix) != 0) last = min(last, max(ip, p.prefix - 1));
-        else if ((MASK & (kMaskCausal | kMaskWindow)) != 0) last = min(last, ip);
-        if ((MASK & kMaskWindow) != 0) first = ip - p.window;
-        const int d_hi = last - jl, d_lo = first - jl;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int c = 8 * (r >> 2) + (r & 3);
-          sc[r] = (c > d_hi) | (c < d_lo) ? -INFINITY : sc[r];
-        }
-        if ((MASK & kMaskDoc) != 0) {
-          const int32_t* kdoc = p.kv_doc + (int64_t)b * p.Sk;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sc[r] = kdoc[min(key(r), p.Sk - 1)] != qdoc ? -INFINITY : sc[r];
-        }
+      asm volatile("" : "+v"(range.least), "+v"(range.most));   // (formed here: left to the compiler, behind the loop, and Q's values kept for it)
+      if (!EXACT && C::QP > 0) {
+        f32_wait_lds<0>();
+        if (KS > 1) __syncthreads();
       }
-
-      // online softmax update with the tile (Alg. 2), log2 domain
-      if (!plain) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sc[r] *= kLog2e;
-      }
-      float mx = m;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[r]);
-      mx = half_swap_max(mx);
-      const float ms = mx == -INFINITY ? 0.f : mx;
-      if (__builtin_amdgcn_ballot_w64(mx != m) != 0) {     // uniform: some row's maximum moved
-        const float alpha = fast_exp2(m - ms);
-        l *= alpha;
-        m = mx;
+      for (int rb = 0; rb < RB; ++rb) {
+        m[rb] = -INFINITY;
+        l[rb] = 0.f;
 #pragma unroll
         for (int d = 0; d < DVB; ++d)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
+          for (int r = 0; r < 16; ++r) o[rb][d][r] = 0.f;
       }
-      float psum = 0.f;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        sc[r] = fast_exp2(sc[r] - ms);             // (v_exp_f32: 1 ulp; results below 2^-126 are zero beside a row sum of at least 1)
-        psum += sc[r];
-      }
-      l += psum;
 
-      before_pv();
-      // O^T += V^T P^T: one LDS read per key pair, four ahead
-      {
+      const bool plain = MOD == kModNone && NBIAS == 0 && p.scale > 0.f;   // then scale and log2(e) are one factor under the exponent's FMA
+      const float fe = plain ? p.scale * kLog2e : 1.f;
+      // variant transform of a block's scores (Eq. 3, Eq. 4, biases, masks), log2 domain unless plain; register r holds key jl + 8 (r / 4) + r % 4
+      auto transform = [&](f32x16& x, int rb, int t, int cls) __attribute__((always_inline)) {
+        const int jl = t * kF32Keys + 4 * half;
+        const int i = iw + 32 * rb + col, ic = min(i, p.Sq - 1);
+        auto key = [&](int r) __attribute__((always_inline)) { return jl + 8 * (r >> 2) + (r & 3); };
+        if (!plain) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) x[r] *= p.scale;
+          if (MOD == kModSoftcap) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) x[r] = p.softcap * tanhf(x[r] / p.softcap);
+          }
+          if (MOD == kModAlibi) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) x[r] -= slope * fabsf((float)(i + p.q_off - key(r)));
+          }
+          for (int nb = 0; nb < NBIAS; ++nb) {
+            const BiasView& bv = p.bias[nb];
+            int bl = ic;
+            asm volatile("" : "+v"(bl));
+            const int64_t row = b * bv.sb + g * bv.sg + h * bv.sh + (int64_t)bl * bv.si;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const int64_t off = row + (int64_t)min(key(r), p.Sk - 1) * bv.sj;
+              x[r] += bv.is_f32 ? ((const float*)bv.ptr)[off] : bf16_to_f32(((const uint16_t*)bv.ptr)[off]);
+            }
+          }
+#pragma unroll
+          for (int r = 0; r < 16; ++r) x[r] *= kLog2e;
+        }
+        if (cls == kPartial) {                     // the positional masks and the end of the keys as two bounds on the key
+          const int ip = i + p.q_off;
+          int last = p.Sk - 1, first = 0;
+          if ((MASK & kMaskPrefix) != 0) last = min(last, max(ip, p.prefix - 1));
+          else if ((MASK & (kMaskCausal | kMaskWindow)) != 0) last = min(last, ip);
+          if ((MASK & kMaskWindow) != 0) first = ip - p.window;
+          const int d_hi = last - jl, d_lo = first - jl;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int c = 8 * (r >> 2) + (r & 3);
+            x[r] = (c > d_hi) | (c < d_lo) ? -INFINITY : x[r];
+          }
+          if ((MASK & kMaskDoc) != 0) {
+            const int32_t* kdoc = p.kv_doc + (int64_t)b * p.Sk;
+            const int qdoc = p.q_doc[(int64_t)b * p.Sq + ic];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) x[r] = kdoc[min(key(r), p.Sk - 1)] != qdoc ? -INFINITY : x[r];
+          }
+        }
+      };
+      // online softmax (Alg. 2): the running max moves to the block's, the sums follow; returns the exponent's reference
+      auto advance = [&](const f32x16& x, int rb) __attribute__((always_inline)) -> float {
+        float mx = x[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, x[r]);
+        mx = fmaxf(m[rb], half_swap_max(mx) * fe);
+        const float ms = mx == -INFINITY ? 0.f : mx;
+        if (__builtin_amdgcn_ballot_w64(mx != m[rb]) != 0) {       // uniform: some row's maximum moved
+          const float alpha = fast_exp2(m[rb] - ms);
+          l[rb] *= alpha;
+          m[rb] = mx;
+#pragma unroll
+          for (int d = 0; d < DVB; ++d)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[rb][d][r] *= alpha;
+        }
+        return ms;
+      };
+      // (v_exp_f32: 1 ulp; results below 2^-126 are zero beside a row sum of at least 1)
+      auto weight = [&](f32x16& x, int r, float ms, float& sum) __attribute__((always_inline)) {
+        x[r] = fast_exp2(fmaf(x[r], fe, -ms));
+        sum = r == 0 ? x[r] : sum + x[r];
+      };
+
+      // One tile.  k_free() runs when the K tile has been read, v_ready() before V is, v_free() when V has been read.
+      auto tile = [&](int t, int cls, uint32_t buf, auto&& k_free, auto&& v_ready, auto&& v_free) __attribute__((always_inline)) {
+        f32x16 sc[RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sc[rb][r] = 0.f;
         typename F32Vec<DVB>::type vf[16];
         const uint32_t a = va + buf;
-        auto read = [&](auto rc) __attribute__((always_inline)) {
+        auto read_v = [&](auto rc) __attribute__((always_inline)) {          // one key, DVB channels
           constexpr int r = decltype(rc)::value, OFF = (8 * (r >> 2) + (r & 3)) * ROW;
           F32Vec<DVB>::template read<OFF>(vf[r], a);
         };
-        static_for<0, 4>(read);
-        static_for<0, 4>([&](auto gc) __attribute__((always_inline)) {
-          constexpr int gg = decltype(gc)::value;
-          if constexpr (gg + 1 < 4) static_for<(gg + 1) * 4, (gg + 2) * 4>(read);
-          f32_wait_lds<gg + 1 < 4 ? 4 : 0>();
-          static_for<gg * 4, gg * 4 + 4>([&](auto rc) __attribute__((always_inline)) {
-            constexpr int r = decltype(rc)::value;
+        F32Vec<4>::type kf[NU];
+        auto read_k = [&](auto uc) __attribute__((always_inline)) {          // four channels
+          constexpr int u = decltype(uc)::value;
+          F32Vec<4>::template read<0>(kf[u], (ka ^ (uint32_t)(u << 5)) + buf);
+        };
+
+        if constexpr (EXACT) {
+          // S^T = K Q^T: one LDS read per four steps, four reads ahead
+          constexpr int G = 4 < NU ? 4 : NU, NG = NU / G;
+          static_for<0, G>(read_k);
+          static_for<0, NG>([&](auto gc) __attribute__((always_inline)) {
+            constexpr int gg = decltype(gc)::value;
+            if constexpr (gg + 1 < NG) static_for<(gg + 1) * G, (gg + 2) * G>(read_k);
+            f32_wait_lds<gg + 1 < NG ? G : 0>();
+            static_for<gg * G, (gg + 1) * G>([&](auto uc) __attribute__((always_inline)) {
+              constexpr int u = decltype(uc)::value;
 #pragma unroll
-            for (int d = 0; d < DVB; ++d) o[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(F32Vec<DVB>::at(vf[r], d), sc[r], o[d], 0, 0, 0);
+              for (int rb = 0; rb < RB; ++rb) {
+                sc[rb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[u][0], qf[rb][u].x, sc[rb], 0, 0, 0);
+                sc[rb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[u][1], qf[rb][u].y, sc[rb], 0, 0, 0);
+                sc[rb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[u][2], qf[rb][u].z, sc[rb], 0, 0, 0);
+                sc[rb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[u][3], qf[rb][u].w, sc[rb], 0, 0, 0);
+              }
+            });
           });
-        });
+          k_free();
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb) {
+            transform(sc[rb], rb, t, cls);
+            const float ms = advance(sc[rb], rb);
+            float sum;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) weight(sc[rb], r, ms, sum);
+            l[rb] += sum;
+          }
+          v_ready();
+          // O^T += V^T P^T: one LDS read per key pair, four ahead
+          static_for<0, 4>(read_v);
+          static_for<0, 4>([&](auto gc) __attribute__((always_inline)) {
+            constexpr int gg = decltype(gc)::value;
+            if constexpr (gg + 1 < 4) static_for<(gg + 1) * 4, (gg + 2) * 4>(read_v);
+            f32_wait_lds<gg + 1 < 4 ? 4 : 0>();
+            static_for<gg * 4, gg * 4 + 4>([&](auto rc) __attribute__((always_inline)) {
+              constexpr int r = decltype(rc)::value;
+#pragma unroll
+              for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int d = 0; d < DVB; ++d)
+                  o[rb][d] = __builtin_amdgcn_mfma_f32_32x32x2f32(F32Vec<DVB>::at(vf[r], d), sc[rb][r], o[rb][d], 0, 0, 0);
+            });
+          });
+          v_free();
+        } else {
+          // S^T = K Q^T, a step of sixteen channels per stage: its matrix instructions beside the split of the next step's K (of V's
+          // first piece in the last one); LDS reads one stage further ahead
+          constexpr int QP = C::QP;
+          F32Vec<4>::type qx[QP > 0 ? NK * RB * QP : 1];
+          uint32_t qa = (uint32_t)lane;
+          if (QP > 0) {
+            asm volatile("" : "+v"(qa));
+            qa = (uint32_t)(C::QBASE + rg * NK * RB * QP * 1024) + qa * 16u;
+          }
+          auto read_q = [&](auto kc) __attribute__((always_inline)) {
+            static_for<kc * RB * QP, (kc + 1) * RB * QP>([&](auto n) __attribute__((always_inline)) { F32Vec<4>::template read<n * 1024>(qx[n], qa); });
+          };
+          F32Split kp[2], vp[2], pp[2][RB];        // K and V: of this stage and the next; P: of either half of the keys
+          auto split_k = [&](auto kc, auto e) __attribute__((always_inline)) {
+            constexpr int kk = decltype(kc)::value, n = 2 * (e % 2);
+            f32_split<e>(kf[2 * kk + e / 2][n], kf[2 * kk + e / 2][n + 1], kp[kk % 2]);
+          };
+          auto split_v = [&](auto uc, auto e) __attribute__((always_inline)) {             // unit: half of the keys, channel block
+            constexpr int u = decltype(uc)::value, k0 = 8 * (u / DVB) + 2 * e, d = u % DVB;
+            f32_split<e>(F32Vec<DVB>::at(vf[k0], d), F32Vec<DVB>::at(vf[k0 + 1], d), vp[u % 2]);
+          };
+          read_k(std::integral_constant<int, 0>());
+          read_k(std::integral_constant<int, 1>());
+          read_q(std::integral_constant<int, 0>());
+          read_k(std::integral_constant<int, 2>());
+          read_k(std::integral_constant<int, 3>());
+          f32_wait_lds<2>();
+          static_for<0, 4>([&](auto e) __attribute__((always_inline)) { split_k(std::integral_constant<int, 0>(), e); });
+          static_for<0, NK>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int kk = decltype(kc)::value;
+            constexpr bool last = kk + 1 == NK;
+            if constexpr (!last) read_q(std::integral_constant<int, kk + 1>());
+            if constexpr (kk + 2 < NK) static_for<2 * kk + 4, 2 * kk + 6>(read_k);
+            if constexpr (last) {
+              k_free();
+              v_ready();
+              static_for<0, 8>(read_v);
+            }
+            f32_wait_lds<last ? 0 : QP * RB + (kk + 2 < NK ? 2 : 0)>();
+            f32_stage<6 * RB, 4>(
+                [&](auto i) __attribute__((always_inline)) {
+                  constexpr int rb = i % RB, n = i / RB;
+                  F32Split q = qp[rb][kk];
+                  if (QP > 0) q.l = __builtin_bit_cast(i32x4, qx[(kk * RB + rb) * QP]);
+                  if (QP > 1) q.m = __builtin_bit_cast(i32x4, qx[(kk * RB + rb) * QP + QP - 1]);
+                  sc[rb] = f32_mfma<n>(kp[kk % 2], q, sc[rb]);
+                },
+                [&](auto e) __attribute__((always_inline)) {
+                  if constexpr (last) split_v(std::integral_constant<int, 0>(), e);
+                  else split_k(std::integral_constant<int, kk + 1>(), e);
+                });
+          });
+
+          // the tile's maxima; the weights of the first half of its keys and their parts
+          float ms[RB], sum[RB];
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb) {
+            transform(sc[rb], rb, t, cls);
+            ms[rb] = advance(sc[rb], rb);
+          }
+          auto weights = [&](auto jc) __attribute__((always_inline)) {       // job 2 n: weights of the n-th pair, 2 n + 1: their parts
+            constexpr int hf = jc / (8 * RB), n = jc / 2 % (4 * RB), rb = n / 4, e = n % 4, r = 8 * hf + 2 * e;
+            if constexpr (jc % 2 == 0) {
+              weight(sc[rb], r, ms[rb], sum[rb]);
+              weight(sc[rb], r + 1, ms[rb], sum[rb]);
+              if (r + 2 == 16) l[rb] += sum[rb];
+            } else {
+              f32_split<e>(sc[rb][r], sc[rb][r + 1], pp[hf][rb]);
+            }
+          };
+          static_for<0, 8 * RB>(weights);
+          __builtin_amdgcn_sched_barrier(0);
+
+          // O^T += V^T P^T in units of (half of the keys, channel block): the matrix instructions of a unit beside the split of the next
+          // one's V, and beside the weights of the second half of the keys in the units of the first
+          static_for<0, 2 * DVB>([&](auto uc) __attribute__((always_inline)) {
+            constexpr int u = decltype(uc)::value, hf = u / DVB, d = u % DVB;
+            constexpr int NP = hf == 0 ? 8 * RB / DVB : 0, NV = u + 1 < 2 * DVB ? 4 : 0;
+            if constexpr (u + 1 == DVB) static_for<8, 16>(read_v);           // (the first half's values are split)
+            f32_stage<6 * RB, NP + NV>(
+                [&](auto i) __attribute__((always_inline)) {
+                  constexpr int rb = i % RB, n = i / RB;
+                  o[rb][d] = f32_mfma<n>(vp[u % 2], pp[hf][rb], o[rb][d]);
+                },
+                [&](auto j) __attribute__((always_inline)) {
+                  if constexpr (j < NP) {
+                    weights(std::integral_constant<int, 8 * RB + d * NP + j>());
+                  } else {
+                    if constexpr (j == NP && u + 1 == DVB) {
+                      f32_wait_lds<0>();
+                      v_free();
+                    }
+                    split_v(std::integral_constant<int, u + 1>(), std::integral_constant<int, j - NP>());
+                  }
+                });
+          });
+        }
+      };
+
+      if constexpr (RG == 1) {
+        // One wave per split: nobody shares its tiles, so it never meets another wave inside the loop.  One buffer is enough:
+        // K of the next tile is requested when the scores are formed, V when P V is, each has the other contraction's time
+        // to arrive, and vector memory completes in order, so that the wait for one leaves the other in flight.
+        auto next = [&](int t) __attribute__((always_inline)) {
+          while (t < t_hi && !wanted(t)) t += KS;
+          return t;
+        };
+        int t = next(t_lo + ks);
+        if (t < t_hi) {
+          load_k(t, 0);
+          load_v(t, 0);
+        }
+        while (t < t_hi) {
+          const int tn = next(t + KS);
+          f32_wait_mem<C::NINSTR>();
+          tile(t, classify(t, iw, iw_max, qs_w, tile_ids(t)), 0u,
+               [&]() __attribute__((always_inline)) { if (tn < t_hi) load_k(tn, 0); },
+               [&]() __attribute__((always_inline)) {
+                 if (tn < t_hi) f32_wait_mem<C::NINSTR>();
+                 else f32_wait_mem<0>();
+                 clear_v(t, 0);
+               },
+               [&]() __attribute__((always_inline)) { if (tn < t_hi) load_v(tn, 0); });
+          t = tn;
+        }
+      } else {
+        if (wanted(t_lo + ks)) {
+          load_k(t_lo + ks, 0);
+          load_v(t_lo + ks, 0);
+        }
+        for (int it = 0; it < n_iter; ++it) {
+          const int t = t_lo + it * KS + ks;
+          f32_wait_mem<0>();                       // this wave's loads of tile t have landed ...
+          clear_k(t, it & 1);
+          clear_v(t, it & 1);
+          f32_wait_lds<0>();
+          __syncthreads();                         // ... and everyone's; the other buffer is free
+          if (it + 1 < n_iter && wanted(t + KS)) {
+            load_k(t + KS, (it + 1) & 1);
+            load_v(t + KS, (it + 1) & 1);
+          }
+          if (t >= t_hi) continue;
+          const int cls = iw < p.Sq ? classify(t, iw, iw_max, qs_w, tile_ids(t)) : kSkip;
+          if (cls == kSkip) continue;              // (uniform over the wave)
+          tile(t, cls, (uint32_t)((it & 1) * C::STAGE), []() __attribute__((always_inline)) {}, []() __attribute__((always_inline)) {},
+               []() __attribute__((always_inline)) {});
+        }
       }
+      if constexpr (!EXACT) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+          for (int d = 0; d < DVB; ++d)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) range.take(o[rb][d][r]);
+      }
+      return !EXACT && __builtin_amdgcn_ballot_w64(!range.inside()) != 0;
     };
 
     if (s > 0) __syncthreads();                    // LDS is reused by the second stream
-    if constexpr (RG == 1) {
-      // One wave per split: nobody shares its tiles, so it never meets another wave inside the loop.  One buffer is enough:
-      // K of the next tile is requested when the scores are formed, V when P V is, each has the other contraction's time
-      // to arrive, and vector memory completes in order, so that the wait for one leaves the other in flight.
-      auto next = [&](int t) __attribute__((always_inline)) {
-        while (t < t_hi && !wanted(t)) t += KS;
-        return t;
-      };
-      int t = next(t_lo + ks);
-      if (t < t_hi) {
-        load_k(t, 0);
-        load_v(t, 0);
-      }
-      while (t < t_hi) {
-        const int tn = next(t + KS);
-        f32_wait_mem<C::NINSTR>();
-        tile(t, classify(t, iw, iw_max, qs_w, tile_ids(t)), 0u,
-             [&]() __attribute__((always_inline)) { if (tn < t_hi) load_k(tn, 0); },
-             [&]() __attribute__((always_inline)) {
-               if (tn < t_hi) f32_wait_mem<C::NINSTR>();
-               else f32_wait_mem<0>();
-               clear_v(t, 0);
-             });
-        if (tn < t_hi) load_v(tn, 0);
-        t = tn;
-      }
-    } else {
-      if (wanted(t_lo + ks)) {
-        load_k(t_lo + ks, 0);
-        load_v(t_lo + ks, 0);
-      }
-      for (int it = 0; it < n_iter; ++it) {
-        const int t = t_lo + it * KS + ks;
-        f32_wait_mem<0>();                         // this wave's loads of tile t have landed ...
-        clear_k(t, it & 1);
-        clear_v(t, it & 1);
-        f32_wait_lds<0>();
-        __syncthreads();                           // ... and everyone's; the other buffer is free
-        if (it + 1 < n_iter && wanted(t + KS)) {
-          load_k(t + KS, (it + 1) & 1);
-          load_v(t + KS, (it + 1) & 1);
-        }
-        if (t >= t_hi) continue;
-        const int cls = iw < p.Sq ? classify(t, iw, iw_max, qs_w, tile_ids(t)) : kSkip;
-        if (cls == kSkip) continue;                // (uniform over the wave)
-        tile(t, cls, (uint32_t)((it & 1) * C::STAGE), []() __attribute__((always_inline)) {}, []() __attribute__((always_inline)) {});
-      }
+    bool again = true;
+    if constexpr (C::PARTS) again = pass(std::integral_constant<bool, false>());
+    if constexpr (C::PARTS && RG > 1) {                        // waves that share tiles take the second pass together
+      int* flags = (int*)lds_raw;
+      __syncthreads();
+      if (lane == 0) flags[wave] = again ? 1 : 0;
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < RG * KS; ++w) again = again || flags[w] != 0;
+      again = __builtin_amdgcn_readfirstlane(again ? 1 : 0) != 0;
+      __syncthreads();
     }
+    if (again) pass(std::integral_constant<bool, true>());
 
     // ---- the splits of a row group merge in split 0 (rescale rule of Sec. 3.3), in the order of the splits
-    l = half_swap_sum(l);
-    if constexpr (KS > 1) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) l[rb] = half_swap_sum(l[rb]);
+    if constexpr (C::SHARE) {
+      __syncthreads();                             // the tile ring is free
+      float* mo = (float*)(lds_raw + rg * KS * C::OBYTES) + lane * 4;               // [split][block][register group][channel block]
+      float* ml = (float*)(lds_raw + RG * KS * C::OBYTES + rg * KS * C::MLBYTES) + lane;
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+#pragma unroll
+          for (int d = 0; d < DVB; ++d)
+            *(float4*)(mo + ks * (C::OBYTES / 4) + ((rb * 4 + r4) * DVB + d) * 256) =
+                make_float4(o[rb][d][4 * r4], o[rb][d][4 * r4 + 1], o[rb][d][4 * r4 + 2], o[rb][d][4 * r4 + 3]);
+        ml[(ks * RB + rb) * 128] = m[rb];
+        ml[(ks * RB + rb) * 128 + 64] = l[rb];
+      }
+      __syncthreads();
+      int el = lane;                               // (opaque, as in the epilogue below)
+      asm volatile("" : "+v"(el));
+      const int eh = el >> 5;
+      for (int n = ks; n < 4 * RB; n += KS) {      // block n / 4, register group n % 4
+        const int rb = n / 4, r4 = n % 4, er = iw + 32 * rb + (el & 31);
+        float f[KS], mall = -INFINITY, lt = 0.f;
+#pragma unroll
+        for (int u = 0; u < KS; ++u) mall = fmaxf(mall, ml[(u * RB + rb) * 128]);
+        const float ms = mall == -INFINITY ? 0.f : mall;
+#pragma unroll
+        for (int u = 0; u < KS; ++u) {
+          f[u] = fast_exp2(ml[(u * RB + rb) * 128] - ms);
+          lt += ml[(u * RB + rb) * 128 + 64] * f[u];
+        }
+        float x[DVB][4] = {};
+#pragma unroll
+        for (int u = 0; u < KS; ++u)
+#pragma unroll
+          for (int d = 0; d < DVB; ++d) {
+            const float4 y = *(const float4*)(mo + u * (C::OBYTES / 4) + (n * DVB + d) * 256);
+            x[d][0] += y.x * f[u];
+            x[d][1] += y.y * f[u];
+            x[d][2] += y.z * f[u];
+            x[d][3] += y.w * f[u];
+          }
+        if (er < p.Sq) {
+          const float inv = lt > 0.f ? 1.f / lt : 0.f;
+          float* op = (float*)p.out.ptr + b * p.out.sb + g * p.out.sg + h * p.out.sh + (int64_t)er * p.out.ss;
+          if (p.lse != nullptr && eh == 0 && r4 == 0)
+            p.lse[b * p.lse_sb + (int64_t)g * p.lse_sg + h * p.lse_sh + er] = lt > 0.f ? mall * kLn2 + logf(lt) : -INFINITY;
+#pragma unroll
+          for (int e4 = 0; e4 < DVB; ++e4) {       // (channel DVB i + d is element i of channel block d)
+            const int c = DVB * (8 * r4 + 4 * eh) + 4 * e4;
+            auto at = [&](int e) __attribute__((always_inline)) { return x[(4 * e4 + e) % DVB][(4 * e4 + e) / DVB] * inv; };
+            if (c < p.Dv) *(float4*)(op + c) = make_float4(at(0), at(1), at(2), at(3));
+          }
+        }
+      }
+      return;
+    } else if constexpr (KS > 1) {
       __syncthreads();                             // the tile ring is free
       float* mo = (float*)(lds_raw + (rg * (KS - 1) + ks - 1) * C::OBYTES) + lane * 4;
-      float* ml = (float*)(lds_raw + RG * (KS - 1) * C::OBYTES) + (rg * (KS - 1) + ks - 1) * 128 + lane;
+      float* ml = (float*)(lds_raw + RG * (KS - 1) * C::OBYTES) + (rg * (KS - 1) + ks - 1) * (128 * RB) + lane;
       if (ks > 0) {
 #pragma unroll
-        for (int d = 0; d < DVB; ++d)
+        for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4)
-            *(float4*)(mo + (d * 4 + r4) * 256) = make_float4(o[d][4 * r4], o[d][4 * r4 + 1], o[d][4 * r4 + 2], o[d][4 * r4 + 3]);
-        ml[0] = m;
-        ml[64] = l;
+          for (int d = 0; d < DVB; ++d)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4)
+              *(float4*)(mo + ((rb * DVB + d) * 4 + r4) * 256) =
+                  make_float4(o[rb][d][4 * r4], o[rb][d][4 * r4 + 1], o[rb][d][4 * r4 + 2], o[rb][d][4 * r4 + 3]);
+          ml[rb * 128] = m[rb];
+          ml[rb * 128 + 64] = l[rb];
+        }
       }
       __syncthreads();
       if (ks == 0) {
-        float f[KS], mall = m;
 #pragma unroll
-        for (int u = 1; u < KS; ++u) mall = fmaxf(mall, ml[u * 128]);
-        const float ms = mall == -INFINITY ? 0.f : mall;
-        f[0] = fast_exp2(m - ms);
-        float lt = l * f[0];
+        for (int rb = 0; rb < RB; ++rb) {
+          const float* mr = ml + rb * 128;
+          float f[KS], mall = m[rb];
 #pragma unroll
-        for (int u = 1; u < KS; ++u) {
-          f[u] = fast_exp2(ml[u * 128] - ms);
-          lt += ml[u * 128 + 64] * f[u];
-        }
-        m = mall;
-        l = lt;
+          for (int u = 1; u < KS; ++u) mall = fmaxf(mall, mr[u * 128 * RB]);
+          const float ms = mall == -INFINITY ? 0.f : mall;
+          f[0] = fast_exp2(m[rb] - ms);
+          float lt = l[rb] * f[0];
 #pragma unroll
-        for (int d = 0; d < DVB; ++d)
-#pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[d][4 * r4 + e] *= f[0];
-#pragma unroll
-            for (int u = 1; u < KS; ++u) {
-              const float4 x = *(const float4*)(mo + u * (C::OBYTES / 4) + (d * 4 + r4) * 256);
-              o[d][4 * r4] += x.x * f[u];
-              o[d][4 * r4 + 1] += x.y * f[u];
-              o[d][4 * r4 + 2] += x.z * f[u];
-              o[d][4 * r4 + 3] += x.w * f[u];
-            }
+          for (int u = 1; u < KS; ++u) {
+            f[u] = fast_exp2(mr[u * 128 * RB] - ms);
+            lt += mr[u * 128 * RB + 64] * f[u];
           }
+          m[rb] = mall;
+          l[rb] = lt;
+#pragma unroll
+          for (int d = 0; d < DVB; ++d)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+              f32x16& a = o[rb][d];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) a[4 * r4 + e] *= f[0];
+#pragma unroll
+              for (int u = 1; u < KS; ++u) {
+                const float4 x = *(const float4*)(mo + u * (C::OBYTES / 4) + ((rb * DVB + d) * 4 + r4) * 256);
+                a[4 * r4] += x.x * f[u];
+                a[4 * r4 + 1] += x.y * f[u];
+                a[4 * r4 + 2] += x.z * f[u];
+                a[4 * r4 + 3] += x.w * f[u];
+              }
+            }
+        }
       }
     }
 
@@ -462,22 +802,26 @@ fwd_f32_kernel(const FwdParams p) {
     // and hold registers through it.)
     int el = lane;
     asm volatile("" : "+v"(el));
-    const int er = iw + (el & 31), eh = el >> 5;
-    if (ks == 0 && er < p.Sq) {
-      const float inv = l > 0.f ? 1.f / l : 0.f;
+    const int eh = el >> 5;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const int er = iw + 32 * rb + (el & 31);
+      if (ks != 0 || er >= p.Sq) continue;
+      f32x16 (&x)[DVB] = o[rb];
+      const float inv = l[rb] > 0.f ? 1.f / l[rb] : 0.f;
       float* op = (float*)p.out.ptr + b * p.out.sb + g * p.out.sg + h * p.out.sh + (int64_t)er * p.out.ss;
       if (p.lse != nullptr && eh == 0)
-        p.lse[b * p.lse_sb + (int64_t)(ns * g + s) * p.lse_sg + h * p.lse_sh + er] = l > 0.f ? m * kLn2 + logf(l) : -INFINITY;
+        p.lse[b * p.lse_sb + (int64_t)(ns * g + s) * p.lse_sg + h * p.lse_sh + er] = l[rb] > 0.f ? m[rb] * kLn2 + logf(l[rb]) : -INFINITY;
       const float lam = s == 1 ? p.lambda[h] : 0.f;
       const bool last = s + 1 == ns;
       float ssq = 0.f;
       // register group r4 holds 4 DVB consecutive channels, in DVB pieces of four; element e of piece e4 sits in ...
       auto chan = [&](int r4, int e4) __attribute__((always_inline)) { return DVB * (8 * r4 + 4 * eh) + 4 * e4; };
-      auto at = [&](int r4, int e4, int e) __attribute__((always_inline)) -> float { return o[(4 * e4 + e) % DVB][4 * r4 + (4 * e4 + e) / DVB]; };
+      auto at = [&](int r4, int e4, int e) __attribute__((always_inline)) -> float { return x[(4 * e4 + e) % DVB][4 * r4 + (4 * e4 + e) / DVB]; };
 #pragma unroll
       for (int d = 0; d < DVB; ++d)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[d][r] *= inv;
+        for (int r = 0; r < 16; ++r) x[d][r] *= inv;
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4)
 #pragma unroll
@@ -490,7 +834,7 @@ fwd_f32_kernel(const FwdParams p) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const int d = (4 * e4 + e) % DVB, r = 4 * r4 + (4 * e4 + e) / DVB;
-              o[d][r] = f4[e] - lam * o[d][r];
+              x[d][r] = f4[e] - lam * x[d][r];
             }
           }
 #pragma unroll
