@@ -289,14 +289,16 @@ decode_kernel(const DecodeParams p) {
   }
 
   // ---- merge the waves (Sec. 3.3 / 3.4 rescale rule), one column block at a time: everyone parks
-  // (m, l, O) in its own ring region, wave 0 folds them and writes the split's partial result
+  // (m, l, O) in its own ring region, then folds and writes its share of the channels of the split's partial result
+  // (one wave folding everything held the whole workgroup's LDS for as long: 128 sequences of 64 - 128 tokens, 32 / 8 heads, D = 64, 19.7 -> 15.6
+  // us; 64 of 256 - 512, D = 128, 29.2 -> 26.9; one of 1500 - 2000, D = 64, 9.3 -> 8.8)
   static_assert((DB * 4 + 1) * 64 * 16 <= C::WAVE_LDS, "parking area");
   W::template wait_lds<0>();
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
     const float l_wave = half_swap_sum(l_run[cb]);
     float4* park = (float4*)(lds_raw + wave * C::WAVE_LDS) + lane;     // [quad][lane] float4, then (m, l)
-    if (cb > 0) __syncthreads();                   // wave 0 has read the previous block's parked values
+    if (cb > 0) __syncthreads();                   // everyone has read the previous block's parked values
 #pragma unroll
     for (int d = 0; d < DB; ++d)
 #pragma unroll
@@ -304,116 +306,106 @@ decode_kernel(const DecodeParams p) {
         park[(d * 4 + r4) * 64] = make_float4(oacc[cb][d][4 * r4], oacc[cb][d][4 * r4 + 1], oacc[cb][d][4 * r4 + 2], oacc[cb][d][4 * r4 + 3]);
     park[DB * 4 * 64] = make_float4(m_run[cb], l_wave, 0.f, 0.f);
     __syncthreads();
-    if (wave != 0) continue;
-    float m_all = m_run[cb];
+    float wgt[C::NWV], m_all = -INFINITY, l_all = 0.f;
 #pragma unroll
-    for (int u = 1; u < C::NWV; ++u) {
-      const float4* other = (const float4*)(lds_raw + u * C::WAVE_LDS) + lane;
-      m_all = fmaxf(m_all, other[DB * 4 * 64].x);
-    }
+    for (int u = 0; u < C::NWV; ++u) m_all = fmaxf(m_all, ((const float4*)(lds_raw + u * C::WAVE_LDS) + lane)[DB * 4 * 64].x);
     const float m_safe = m_all == -INFINITY ? 0.f : m_all;
-    float l_all = 0.f;
-    f32x16 o[DB];
-#pragma unroll
-    for (int d = 0; d < DB; ++d) o[d] = W::zero16();
 #pragma unroll
     for (int u = 0; u < C::NWV; ++u) {
-      const float4* other = (const float4*)(lds_raw + u * C::WAVE_LDS) + lane;
-      const float4 ml = other[DB * 4 * 64];
-      const float wgt = fast_exp2(ml.x - m_safe);                 // 0 for a wave that saw no key
-      l_all = fmaf(ml.y, wgt, l_all);
-#pragma unroll
-      for (int d = 0; d < DB; ++d)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const float4 q4 = other[(d * 4 + r4) * 64];
-          o[d][4 * r4] = fmaf(q4.x, wgt, o[d][4 * r4]);
-          o[d][4 * r4 + 1] = fmaf(q4.y, wgt, o[d][4 * r4 + 1]);
-          o[d][4 * r4 + 2] = fmaf(q4.z, wgt, o[d][4 * r4 + 2]);
-          o[d][4 * r4 + 3] = fmaf(q4.w, wgt, o[d][4 * r4 + 3]);
-        }
+      const float4 ml = ((const float4*)(lds_raw + u * C::WAVE_LDS) + lane)[DB * 4 * 64];
+      wgt[u] = fast_exp2(ml.x - m_safe);           // 0 for a wave that saw no key
+      l_all = fmaf(ml.y, wgt[u], l_all);
     }
-    if (live[cb] && p.nsplit == 1) {
-      // the only split of its sequence: this is the result, no partials and no merge kernel
-      const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
-      const int64_t ob = b * p.o_sb + hq[cb] * p.o_sh + row[cb] * p.o_st;
+    const bool result = p.nsplit == 1;             // the only split of its sequence: no partials and no merge kernel
+    const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
+    const int64_t slot = (((int64_t)b * p.T + row[cb]) * p.H + hq[cb]) * p.nsplit + split;
+    const int64_t ob = b * p.o_sb + hq[cb] * p.o_sh + row[cb] * p.o_st;
+    for (int q = wave; q < DB * 4; q += C::NWV) {  // quads of channels 8 q + 4 half
+      float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-      for (int d = 0; d < DB; ++d)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const int ch = 32 * d + 8 * r4 + 4 * w.half;
-          const float x0 = o[d][4 * r4] * inv, x1 = o[d][4 * r4 + 1] * inv, x2 = o[d][4 * r4 + 2] * inv, x3 = o[d][4 * r4 + 3] * inv;
-          if (p.out_f32) *(float4*)((float*)p.out + ob + ch) = make_float4(x0, x1, x2, x3);
-          else *(uint2*)((uint16_t*)p.out + ob + ch) = make_uint2(pack_bf16(x0, x1), pack_bf16(x2, x3));
-        }
-      if (w.half == 0 && p.lse != nullptr)
+      for (int u = 0; u < C::NWV; ++u) {
+        const float4 q4 = ((const float4*)(lds_raw + u * C::WAVE_LDS) + lane)[q * 64];
+        x.x = fmaf(q4.x, wgt[u], x.x);
+        x.y = fmaf(q4.y, wgt[u], x.y);
+        x.z = fmaf(q4.z, wgt[u], x.z);
+        x.w = fmaf(q4.w, wgt[u], x.w);
+      }
+      const int ch = 8 * q + 4 * w.half;
+      if (!live[cb]) continue;
+      if (!result) *(float4*)(p.part_o + slot * D + ch) = x;
+      else if (p.out_f32) *(float4*)((float*)p.out + ob + ch) = make_float4(x.x * inv, x.y * inv, x.z * inv, x.w * inv);
+      else *(uint2*)((uint16_t*)p.out + ob + ch) = make_uint2(pack_bf16(x.x * inv, x.y * inv), pack_bf16(x.z * inv, x.w * inv));
+    }
+    if (wave == 0 && w.half == 0 && live[cb]) {
+      if (!result) *(float2*)(p.part_ml + slot * 2) = make_float2(m_all, l_all);
+      else if (p.lse != nullptr)
         p.lse[b * p.lse_sb + hq[cb] * p.lse_sh + row[cb] * p.lse_st] = l_all > 0.f ? (m_all + __log2f(l_all)) * kLn2 : -INFINITY;
-    } else if (live[cb]) {
-      const int64_t slot = (((int64_t)b * p.T + row[cb]) * p.H + hq[cb]) * p.nsplit + split;
-      float* po = p.part_o + slot * D;
-#pragma unroll
-      for (int d = 0; d < DB; ++d)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4)
-          *(float4*)(po + 32 * d + 8 * r4 + 4 * w.half) = make_float4(o[d][4 * r4], o[d][4 * r4 + 1], o[d][4 * r4 + 2], o[d][4 * r4 + 3]);
-      if (w.half == 0) *(float2*)(p.part_ml + slot * 2) = make_float2(m_all, l_all);
     }
   }
 }
 
 // Merge of the splits of one (sequence, head): out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M).
-// One wave per (sequence, query row, head).  The statistics are read one split per lane (maximum and sum by
-// wave reductions); the partial outputs are then accumulated with each lane on its D / 64 channels,
-// the weight of split s taken from lane s, several loads in flight (a loop that waited for every
-// split's load in turn cost more than the attention itself on a long single sequence).
+// One wave per (sequence, query row, head).  What bounds it is the chain of memory round trips, so everything about the first 32
+// splits (all there are, unless more are asked for) is requested at once: the statistics one split per lane, the partial
+// outputs 16 bytes per lane, 64 / (D / 4) splits per load.  The weight of a split comes from the lane that holds its statistics.
+// (one sequence of 1500 - 2000 tokens, 32 / 8 heads, D = 64, 15 splits: the step 10.0 -> 9.3 us, D = 128 11.6 -> 11.1; before, the statistics were
+// read twice, then the outputs eight at a time)
 template <int D>
 __global__ void __launch_bounds__(64) decode_combine_kernel(const DecodeParams p) {
   const int bh = blockIdx.x;                       // (b * T + row) * H + h, the order of the partial results
-  const int h = bh % p.H, row = (bh / p.H) % p.T, b = bh / p.H / p.T;
-  const int lane = threadIdx.x;
-  constexpr int CPT = D / 64;
-  const float* ml = p.part_ml + (int64_t)bh * p.nsplit * 2;
-  float m_all = -INFINITY;
-  for (int s = lane; s < p.nsplit; s += 64) m_all = fmaxf(m_all, ml[2 * s]);
+  const int lane = threadIdx.x, ns = p.nsplit;
+  constexpr int LPR = D / 4, SPL = 64 / LPR, NL = 32 / SPL;   // lanes per row, splits per load, loads for 32 splits
+  const float2* ml = (const float2*)p.part_ml + (int64_t)bh * ns;
+  const float* po = p.part_o + (int64_t)bh * ns * D + lane % LPR * 4;
+  float4 x[NL];
+  auto load = [&](int c) __attribute__((always_inline)) {      // splits c .. c + 31; past the last one: the last again, weight 0
+#pragma unroll
+    for (int k = 0; k < NL; ++k)
+      if (c + k * SPL < ns) x[k] = *(const float4*)(po + (int64_t)min(c + k * SPL + lane / LPR, ns - 1) * D);
+  };
+  const float2 first = ml[min(lane, ns - 1)];
+  load(0);
+  float m_all = first.x;
+  for (int s = lane + 64; s < ns; s += 64) m_all = fmaxf(m_all, ml[s].x);
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) m_all = fmaxf(m_all, __shfl_xor(m_all, o));
   const float m_safe = m_all == -INFINITY ? 0.f : m_all;
-  float l_all = 0.f, acc[CPT];
-#pragma unroll
-  for (int e = 0; e < CPT; ++e) acc[e] = 0.f;
-  for (int c = 0; c < p.nsplit; c += 64) {         // 64 splits per round, one per lane
+  float l_all = 0.f;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int c = 0; c < ns; c += 64) {               // 64 splits per round, one per lane
     const int s = c + lane;
-    float wgt = 0.f;
-    if (s < p.nsplit) {
-      wgt = fast_exp2(ml[2 * s] - m_safe);
-      l_all = fmaf(ml[2 * s + 1], wgt, l_all);
-    }
-    const int n = min(64, p.nsplit - c);           // uniform
-    const float* po = p.part_o + ((int64_t)bh * p.nsplit + c) * D + lane * CPT;
-    for (int u0 = 0; u0 < n; u0 += 8) {            // eight loads in flight; past n: the last split again, weight 0
-      float x[8][CPT];
+    const float2 st = c == 0 ? first : ml[min(s, ns - 1)];
+    const float wgt = s < ns ? fast_exp2(st.x - m_safe) : 0.f;
+    l_all = fmaf(st.y, wgt, l_all);
+    for (int half = 0; half < 64 && c + half < ns; half += 32) {
+      if (c + half > 0) load(c + half);
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int u = min(u0 + k, n - 1);
-#pragma unroll
-        for (int e = 0; e < CPT; ++e) x[k][e] = po[(int64_t)u * D + e];
-      }
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const float wu = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(wgt), u0 + k));
-#pragma unroll
-        for (int e = 0; e < CPT; ++e) acc[e] = fmaf(x[k][e], wu, acc[e]);
+      for (int k = 0; k < NL; ++k) {
+        if (c + half + k * SPL >= ns) break;
+        const float wu = __shfl(wgt, half + k * SPL + lane / LPR);
+        acc.x = fmaf(x[k].x, wu, acc.x);
+        acc.y = fmaf(x[k].y, wu, acc.y);
+        acc.z = fmaf(x[k].z, wu, acc.z);
+        acc.w = fmaf(x[k].w, wu, acc.w);
       }
     }
   }
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) l_all += __shfl_xor(l_all, o);
+  for (int o = 32; o >= 1; o >>= 1) {
+    l_all += __shfl_xor(l_all, o);
+    if (o >= LPR) {
+      acc.x += __shfl_xor(acc.x, o);
+      acc.y += __shfl_xor(acc.y, o);
+      acc.z += __shfl_xor(acc.z, o);
+      acc.w += __shfl_xor(acc.w, o);
+    }
+  }
+  const int h = bh % p.H, row = (bh / p.H) % p.T, b = bh / p.H / p.T;
   const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
-  const int64_t o = b * p.o_sb + h * p.o_sh + row * p.o_st + lane * CPT;
-#pragma unroll
-  for (int e = 0; e < CPT; ++e) {
-    if (p.out_f32) ((float*)p.out)[o + e] = acc[e] * inv;
-    else ((uint16_t*)p.out)[o + e] = (uint16_t)(pack_bf16(acc[e] * inv, 0.f) & 0xFFFFu);
+  const int64_t o = b * p.o_sb + h * p.o_sh + row * p.o_st + lane * 4;
+  if (lane < LPR) {
+    if (p.out_f32) *(float4*)((float*)p.out + o) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+    else *(uint2*)((uint16_t*)p.out + o) = make_uint2(pack_bf16(acc.x * inv, acc.y * inv), pack_bf16(acc.z * inv, acc.w * inv));
   }
   if (lane == 0 && p.lse != nullptr)
     p.lse[b * p.lse_sb + h * p.lse_sh + row * p.lse_st] = l_all > 0.f ? (m_all + __log2f(l_all)) * kLn2 : -INFINITY;
