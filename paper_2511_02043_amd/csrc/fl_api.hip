@@ -357,12 +357,27 @@ BwdWorkspace bwd_workspace(int64_t B, int64_t G, int64_t H, int64_t Hkv, int64_t
   return w;
 }
 
-const fl::DecodeEntry* find_decode_entry(int D, int mod, int cb) {
+const fl::DecodeEntry* find_decode_entry(int D, int mod, int cb, int waves) {
   int n = 0;
   const fl::DecodeEntry* tab = fl::entries_decode(&n);
-  for (int e = 0; e < n; ++e)
-    if (tab[e].D == D && tab[e].mod == mod && tab[e].cb == cb) return &tab[e];
+  for (int i = 0; i < n; ++i)
+    if (tab[i].D == D && tab[i].mod == mod && tab[i].cb == cb && tab[i].waves == waves) return &tab[i];
   return nullptr;
+}
+
+// Waves of a decode workgroup.  A wave's ring takes 32 KiB of LDS at D = 128, 16 at 64, and the full number of them all of a CU's: a CU
+// with more than one workgroup to do then takes them one after the other, each with its start-up (length, pages, first tiles) and
+// its merge.  Fewer waves per workgroup let several share the CU, and leave none without a tile where sequences are short; with
+// a workgroup per CU at most, or long ranges, the full number reads faster.
+// Measured (us, 32 / 8 heads, 8 workgroups per sequence and split; full / middle / fewest waves), D = 64: 128 sequences of up to 64, 256, 1024, 2048 tokens
+// 15.6 / 9.7 / 6.2, 20.9 / 15.8 / 14.0, 42.9 / 41.5 / 40.4, 97.8 / 93.3 / 96.8; 64 sequences 8.5 / 5.8 / 6.0, 10.7 / 8.0 / 11.2, 24.8 / 23.3 / 32.2, 44.2 / 42.8 /
+// 45.3; 32 sequences of up to 512, 8192 7.7 / 9.6 / 15.4, 87.1 / 93.4.  D = 128: 128 sequences of up to 64, 256, 512, 1024 tokens 21.0 / 13.6 / 9.8, 33.7 / 29.4 / 25.1, 47.9 / 49.9 /
+// 43.0, 89 / 94 / 91; 64 sequences 11.3 / 7.7 / 9.3, 18.3 / 15.9 / 22.6, 27.5 / 26.3 / 40.4, 43 / 48 / 75; 32 sequences of up to 256 8.7 / 12.9 / 22.4.
+int decode_waves(int64_t D, int cb, int64_t workgroups, int64_t tiles) {   // tiles: of the longest workgroup
+  const int full = fl::decode_full_waves((int)D, cb);
+  if (cb != 1 || workgroups <= 256) return full;
+  if (tiles > 16) return D == 128 || tiles > 48 ? full : 4;
+  return (D == 128 ? 1 : 2) * (workgroups > 512 ? 1 : 2);
 }
 
 // The decode kernels hold the (query row, head) pairs of a kv head as MFMA columns: at most two blocks of 32.
@@ -2149,7 +2164,8 @@ fl_status fl_attn_decode(const fl_tensor* q, const fl_tensor* k_cache, const fl_
     if (pages < B) return fail(FL_ERR_SHAPE, "without a block table the cache needs a page per sequence");
     if (kv->max_seq_len > page_size) return fail(FL_ERR_SHAPE, "max_seq_len exceeds the page size");
   }
-  const fl::DecodeEntry* de = find_decode_entry((int)D, (int)desc->score_mod, H > 0 && (H / Hkv) * T > 32 ? 2 : 1);
+  const int ns = decode_splits(B, Hkv, D, kv->max_seq_len), cb = H > 0 && (H / Hkv) * T > 32 ? 2 : 1;
+  const fl::DecodeEntry* de = find_decode_entry((int)D, (int)desc->score_mod, cb, decode_waves(D, cb, B * Hkv * ns, ((int64_t)kv->max_seq_len + 32 * ns - 1) / (32 * ns)));
   if (de == nullptr || v_cache->size[4] != D)
     return fail(FL_ERR_UNSUPPORTED, "no decode specialisation for D=%lld Dv=%lld score_mod=%u", (long long)D,
                 (long long)v_cache->size[4], desc->score_mod);
@@ -2176,7 +2192,6 @@ fl_status fl_attn_decode(const fl_tensor* q, const fl_tensor* k_cache, const fl_
   if (empty) return FL_OK;
   if (aux == nullptr) return fail(FL_ERR_AUX_MISSING, "the decode step needs aux (workspace)");
   if (desc->score_mod == FL_MOD_ALIBI && aux->alibi_slopes == nullptr) return fail(FL_ERR_AUX_MISSING, "alibi_slopes");
-  const int ns = decode_splits(B, Hkv, D, kv->max_seq_len);
   const size_t ws_need = (size_t)(B * T * H * ns) * (size_t)(D + 2) * sizeof(float);
   if (aux->workspace == nullptr || aux->workspace_bytes < ws_need)
     return fail(FL_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", ws_need, aux->workspace ? aux->workspace_bytes : (size_t)0);

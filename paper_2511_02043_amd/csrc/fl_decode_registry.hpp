@@ -8,7 +8,7 @@ namespace fl {
 typedef hipError_t (*DecodeLaunchFn)(const DecodeParams& p, int nblocks, hipStream_t stream);
 
 struct DecodeEntry {
-  int D, mod, cb;                 // cb: blocks of 32 (query row, head) columns per kv head
+  int D, mod, cb, waves;          // cb: blocks of 32 (query row, head) columns per kv head; waves of a workgroup
   DecodeLaunchFn main, combine;   // main: B * Hkv * nsplit workgroups; combine: B * T * H workgroups
 };
 
@@ -26,9 +26,9 @@ hipError_t launch_decode_combine(const DecodeParams& p, int nblocks, hipStream_t
   return hipGetLastError();
 }
 
-template <int D, int MOD, int CB = 1>
+template <int D, int MOD, int CB = 1, int WAVES = decode_full_waves(D, CB)>
 constexpr DecodeEntry decode_entry() {
-  return DecodeEntry{D, MOD, CB, &launch_decode<DecodeCfg<D, MOD, CB>>, &launch_decode_combine<D>};
+  return DecodeEntry{D, MOD, CB, WAVES, &launch_decode<DecodeCfg<D, MOD, CB, WAVES>>, &launch_decode_combine<D>};
 }
 
 const DecodeEntry* entries_decode(int* n);
