@@ -180,7 +180,8 @@ struct Wave {
   // follow (settle_sums).  That is half a vector instruction less per score and no max between the two contractions: causal,
   // 2 x 32 / 8 heads x 8192 rows, D = 128: 1015 -> 983 us; soft-cap, 8 x 16 x 1999, D = 64: 223 -> 213; chunks of 8 x 512 rows, 32 / 8 heads: 410 -> 398.
   // What overflows on the way (a row that gains a factor of 2^100 in a tile, or values near the end of the range) is found at the end of
-  // the q-tile, which then runs again with the max of every tile (kCareful), for about twice the time.  So not with ALiBi and
+  // the q-tile, which then runs again with the max of every tile (kCareful), for about twice the time (causal, 2 x 16 x 4096, D = 128, scores
+  // of standard deviation 1 / 4 / 16 / 40: 170 / 165 / 157 / 148 -> 169 / 159 / 155 / 291 us).  So not with ALiBi and
   // biases, whose scores do rise that steeply (a mask given as a large negative bias), nor for expressions; and not under a window
   // or document mask: rows of few tiles, whose max a partly visible tile needs in any case (training step, window 512: 281 us either way).
   static constexpr bool kTrust = C::NBIAS == 0 && (C::MOD == kModNone || C::MOD == kModSoftcap) && (C::MASK & (kMaskWindow | kMaskDoc | kMaskCustom)) == 0;
@@ -224,8 +225,9 @@ struct Wave {
   bf16x8 qf[C::RB][C::KK];      // Q fragments of the wave's rows (of its own stream, differential variant)
   f32x16 oacc[C::RB][C::DVB];
   float m_run[C::RB], l_run[C::RB];                // log2-domain running max; per-lane partial sum
-  int trust;                                       // kTrust (uniform): kFresh, kGrown once a tile's sum has passed 2^8, or kCareful
+  int trust;                                       // kTrust (uniform): kFresh, kGrown once a tile's sum has passed kFollow, or kCareful
   static constexpr int kFresh = 0, kGrown = 1, kCareful = 2;
+  static constexpr float kFollow = NB * 16 * 0x1p8f;   // a lane's sum of a tile, at most, where a running max lets 2^8 per score through
 
   __device__ __forceinline__ Wave(const FwdParams& p_) : p(p_) {}
 
@@ -680,7 +682,7 @@ struct Wave {
     }
   }
 
-  // kTrust: adds the tile's row sums.  Where one has passed 2^8 the reference moves up by a power of two that holds it; where a
+  // kTrust: adds the tile's row sums.  Where one has passed kFollow the reference moves up by a power of two that holds it; where a
   // row has no reference yet (nothing of it was visible), and in careful runs, it is the running max of the next tile's scores
   // (`advance`: they are final).
   __device__ __forceinline__ void settle_sums(const Pipe& ps, const Scores& nxt, bool advance) {
@@ -688,7 +690,7 @@ struct Wave {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       l_run[rb] += ps.psum[rb];
-      any = any || ps.psum[rb] > 0x1p8f || m_run[rb] == -INFINITY;
+      any = any || ps.psum[rb] > kFollow || m_run[rb] == -INFINITY;
     }
     if (__builtin_amdgcn_ballot_w64(any) != 0 || trust >= kCareful) {   // rare and wave-uniform
       trust = trust | kGrown;
@@ -696,7 +698,7 @@ struct Wave {
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
         const float top = half_swap_max(ps.psum[rb]), m_old = m_run[rb];
-        const bool up = top > 0x1p8f;
+        const bool up = top > kFollow;
         m_run[rb] = up ? m_old + (float)__builtin_amdgcn_frexp_expf(top) : m_old;
         const float alpha = up ? fast_exp2(m_old - m_run[rb]) : 1.f;
         l_run[rb] = top > 0x1p100f ? INFINITY : l_run[rb] * alpha;   // (too far for a factor that fp32 holds: settled by the careful run)
@@ -713,8 +715,7 @@ struct Wave {
       }
     }
   }
-  // Did a sum or an accumulator of this wave overflow?  (While no sum passes 2^8, neither does a probability: no more than a running
-  // max lets through.)
+  // Did a sum or an accumulator of this wave overflow?  (While no sum passes kFollow, a tile adds no more than it may under a running max.)
   __device__ __forceinline__ bool overflowed() const {
     if (trust != kGrown) return false;
     float t = 0.f;
