@@ -584,7 +584,7 @@ struct Wave {
   //             of the next tile's first key block, which is complete by then;
   //   phase B:  PV MFMAs of the current tile  +  exponentials of its second half during the
   //             MFMAs that consume the first, then the transform / row max of the next tile's
-  //             last key block and the running-max update (Alg. 2 / Sec. 3.4).
+  //             last key block and the running-max update (Alg. 2 / Sec. 3.4); with kTrust no max, and settle_sums.
   // The sum / bf16 conversion of a pair follows one pair after its exponentials (a
   // transcendental result cannot be consumed by the very next instruction without an idle
   // cycle).  Scheduling barriers pin the order; the empty asm statement keeps the sum and the
