@@ -84,6 +84,14 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
 }
 __device__ __forceinline__ float bf16_to_f32(uint16_t u) { return __uint_as_float((uint32_t)u << 16); }
 
+// lse of a row with reference m (log2 domain) and sum l: the product is rounded, then the sum, in kernels of every shape (left to
+// the compiler, some had an FMA; the backward pass forms P from this value, so that its gradients follow the last bit of it)
+__device__ __forceinline__ float row_lse(float m, float l) {
+#pragma clang fp contract(off)
+  const float ref = m * kLn2, sum = __logf(l);
+  return ref + sum;
+}
+
 // 16-byte chunk swizzles of the LDS tiles (row r, chunk c of a row of ROW_ELEMS bf16); both are
 // XORs, hence their own inverses, and both depend on r only through bits that are the same for
 // every row a given lane ever touches.  K is read one 16-byte chunk per lane with 32 consecutive
@@ -1563,7 +1571,7 @@ fwd_bf16_kernel(const FwdParams call) {
     // and one of 0 stays 0 without the correction)
     if constexpr (W::kShifted)
       m_row = (m_row + w.cap_l2) + (p.softcap < 0x1p24f ? fmaf(w.cap_l2, 2.f * w.cap_rcp, 1.f) * w.cap_l2 : 0.f);
-    const float lse_v = lt > 0.f ? fmaf(m_row, kLn2, __logf(lt)) : -INFINITY;
+    const float lse_v = lt > 0.f ? row_lse(m_row, lt) : -INFINITY;
 #pragma unroll
     for (int d = 0; d < DVB; ++d)
 #pragma unroll
