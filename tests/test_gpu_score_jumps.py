@@ -82,6 +82,22 @@ def test_large_values(D, causal):
     compare(w, unit=2.0 ** 60)
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("part", [dict(D=64), dict(D=128), dict(D=64, score_mod="softcap", cap=4000.0, qscale=1.0), dict(D=64, Dv=128, diff=True)], ids=str)
+@pytest.mark.parametrize("masked", [0, 24])
+def test_one_score_beside_large_values(part, causal, masked):
+    """One key 12 log2 units above its row's reference: the sum of its tile stays within the bound up to which the reference is kept, but
+    2^12 times values of 2^116 is past the range.  And a key of the last tile, which is masked, from which on both seem small."""
+    w = inputs.combination_bf16(B=1, H=4, S=300, Sk=300, pos_mask="causal" if causal else "none", **part)
+    rise = np.log(2.0) * (np.where(np.arange(300) == 200, 12.0, 0.0) + np.where(np.arange(300) == 260, masked, 0.0))
+    raise_scores(w.q, w.k, w.scale, rise)
+    if w.q2 is not None:
+        raise_scores(w.q2, w.k2, w.scale, rise)
+    # (one key's value is most of a row's result: its weight and the result rounded to bf16, 2 x 2^-9 of at most 2, is within the 1e-2)
+    w.v = np.clip(w.v, -2, 2) * np.float32(2.0 ** 116)
+    compare(w, unit=2.0 ** 116)
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_infinite_scores(D):
     """A score of -inf hides its key; one of +inf makes its row NaN; the other rows of the workgroup stay as they are."""
