@@ -249,7 +249,10 @@ fwd_f32_kernel(const FwdParams p) {
       constexpr bool kKeys = decltype(is_k)::value;   // K rows are swizzled
       const int last = p.Sk - 1 - t * kF32Keys;    // last row of the tile that exists (uniform)
       const unsigned char* base = (const unsigned char*)(head + (int64_t)(t * kF32Keys) * ss);
-      if (last >= kF32Keys - 1 && dim == DMAX) {   // whole tile: a lane's offsets differ between the instructions in their chunk only
+      // Whole tile: a lane's offsets differ between the instructions in their chunk only.  (Not in kernels with document masks whose waves share
+      // tiles: beside the general loads the compiler keeps an offset in a register that it also loads tile summaries into, and
+      // waits there for the loads just issued.  8 x 16 heads x 512 rows, ALiBi, D = 64 / 128: 83 / 178 us with it, 80 / 173 without.)
+      if ((C::PLAIN || RG == 1) && last >= kF32Keys - 1 && dim == DMAX) {
         constexpr int RPI = 64 / C::CH;            // rows of an instruction; the swizzle of a row is that of its instruction's first ^ its own
         int ln = lane;
         asm volatile("" : "+v"(ln));
