@@ -114,6 +114,7 @@ const fl::KernelEntry* find_entry(const fl_variant_desc* d, int dtype, int D, in
   const fl::KernelEntry* short_loop = nullptr;    // the variant's 32-key-tile shape at three or four waves per SIMD, if listed
   const fl::KernelEntry* four_waves = nullptr;    // a 4-wave, one-row-block shape of the variant (128 query rows per workgroup)
   const fl::KernelEntry* deep_ring = nullptr;     // the default shape with four-slot K / V rings (a barrier per two tiles)
+  bool settled = false;                           // fp32: the present shape of the head dim stays
   for (int t = 0; t < 5; ++t)
     for (int e = 0; e < r.n[t]; ++e) {
       const fl::KernelEntry& k = r.tab[t][e];
@@ -127,10 +128,25 @@ const fl::KernelEntry* find_entry(const fl_variant_desc* d, int dtype, int D, in
         // workgroups: 2 x 8 heads of 1024 rows at D = 64 170 / 92 / 56 / 37 / 46 us (256 workgroups of 64 rows), 8 x 16 heads of 2048
         // 718 / 738 / 781 / 848 / 1031; causal, 2 x 8 heads of 2048 rows 315 / 170 / 97 / 73 / 87 (512 workgroups of 64 rows).
         const bool plain = d->score_mod == FL_MOD_NONE && (mask & FL_MASK_DOC) == 0 && d->n_bias == 0 && d->combine == FL_SINGLE && d->epilogue == 0;
+        // And of two shapes of two row blocks per wave, the smaller one where its tiles have a quarter less rows to pad, unless its key splits
+        // would have no tiles: of few rows, the one wave that has any is alone on its CU.  64 x 8 heads, 512- / 256- / 128- / 64- / 32-row
+        // workgroups, D = 64: 64 rows and keys 27 / 28 / 23 / 24 / 28 us, 100 42 / 41 / 34 / 51 / 61, 200 64 / 61 / 82 / 119 / 133, 300 (causal) 100 /
+        // 133 / 126 / 145 / 172, 513 398 / 322 / 331 / 374 / 450; 64 rows, 1024 keys 208 / 178 / 107 / 76 / 87; D = 32: 64 rows and keys 19 / 19 / 16 / 15 / 13.
+        // (One row block per wave, D = 128: waves without rows cost nothing; 64 rows and keys 33 / 37 / 40 / 44 us from 256 rows on.)
         if (D > k.key.D || Dv > k.key.DV || (k.key.mod == 0) != plain) continue;
-        const bool fills = best != nullptr && heads * ((Sq + best->bm - 1) / best->bm) >= (mask != 0 ? 512 : 256);
-        if (best == nullptr || k.key.D < best->key.D || (k.key.D == best->key.D && (g_tuning.bm != 0 ? k.bm == g_tuning.bm : heads > 0 && !fills)))
+        if (best == nullptr || k.key.D < best->key.D) {
           best = &k;
+          settled = false;
+        } else if (k.key.D == best->key.D && g_tuning.bm != 0) {
+          if (k.bm == g_tuning.bm) best = &k;
+        } else if (k.key.D == best->key.D && heads > 0 && !settled) {
+          auto tiles = [&](int rows) { return (Sq + rows - 1) / rows; };
+          const bool fills = heads * tiles(best->bm) >= (mask != 0 ? 512 : 256);
+          const bool narrower = plain && k.key.D <= 64 && 4 * tiles(k.bm) * k.bm <= 3 * tiles(best->bm) * best->bm &&
+                                (Sq <= 32 || k.key.rb * k.key.D <= 128 * ((Sk + 31) / 32));
+          if (!fills || narrower) best = &k;
+          else settled = true;
+        }
         continue;
       }
       if (k.key.diff != (int)d->combine) continue;

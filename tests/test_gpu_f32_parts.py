@@ -39,6 +39,13 @@ def test_shapes(B, H, S, Sk, D):
     compare(inputs.plain_f32(B=B, H=H, S=S, Sk=Sk, D=D))
 
 
+@pytest.mark.parametrize("B,H,S,Sk,D", [(64, 8, 64, 64, 64), (64, 8, 32, 32, 64), (64, 8, 33, 100, 64), (64, 8, 100, 129, 60), (64, 8, 64, 33, 32),
+                                        (64, 8, 1, 300, 64), (64, 8, 17, 256, 32), (32, 8, 513, 65, 64), (32, 8, 257, 97, 20)])
+def test_many_problems_of_few_rows(B, H, S, Sk, D):
+    """Workgroups of fewer rows although the launch fills the chip without; one tile of keys and up to ten, ends of the row and key tiles."""
+    compare(inputs.plain_f32(B=B, H=H, S=S, Sk=Sk, D=D))
+
+
 @pytest.mark.parametrize("B,H,S,D", [(2, 8, 300, 32), (2, 8, 300, 64), (2, 8, 300, 128), (4, 32, 257, 64), (4, 32, 257, 128)])
 @pytest.mark.parametrize("q,k,v", [(1, 1, 2.0 ** -118), (2.0 ** -112, 2.0 ** 112, 1), (2.0 ** 112, 2.0 ** -112, 1), (1, 1, 2.0 ** 122), (1, 1, 0)])
 def test_magnitudes(B, H, S, D, q, k, v):
