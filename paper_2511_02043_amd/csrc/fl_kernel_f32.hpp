@@ -18,10 +18,12 @@
 // Contractions on parts: x = h + m + l, each the bf16 rounding of what the ones before leave, holds 24 bits; six of the nine products
 // of two such sums (all above 2^-27 of the largest) cost 6 x 32 clocks for 16 channels where the fp32 instruction takes 8 x 64.  The error
 // against fp64 is lower than the fp32 instruction's (fewer roundings of the sum: 2 x 8 heads x 1024 rows, D = 64, relative 4.2e-7 before,
-// 2.9e-7).  Values below 2^-100 or beyond 2^100 may lose bits or round to infinity: Q is checked as it is split, and a lost bit of
-// K then is below 2^-134 2^100; V and overflows show in the accumulators (NaN, infinity, or below 2^-100).  A wave (where waves share
-// tiles: a workgroup) that finds such a value takes the pass again on the fp32 instruction, so that infinities, NaN and tiny values
-// give what they gave there.
+// 2.9e-7).  A bf16 part holds nothing below 2^-134, so that a value below 2^-110 loses bits, and a value may round to infinity.  What is lost
+// of K comes to 2^-27 of a score at most while |Q| < 2^100 / max(scale, 1); of Q nothing from 2^-100 on: both are checked as Q is split (sums of
+// products below 2^-126 meet a scale of 2^64 at most).  What is lost of P and V shows in the accumulators beside the largest value
+// (f32_most), overflows as infinity or NaN there.  A wave (where waves share tiles: a workgroup) that finds such a value takes the pass again
+// on the fp32 instruction, so that infinities, NaN and tiny values give what they gave there; but beside ordinary values, a channel
+// whose values are all below 2^-134 gives zero.
 //
 // What bounds it: issue of vector instructions, 8.8 for each matrix instruction at D = 64 (eleven per pair of values split; four run beside
 // a matrix instruction).  So a wave takes two row blocks (K and V are split once for both) wherever registers allow, the split of
@@ -156,7 +158,7 @@ __device__ __forceinline__ void f32_stage(M&& mfma, J&& job) {
     __builtin_amdgcn_sched_barrier(0);
   });
 }
-// Whether all values taken are zero or of a magnitude in [2^-100, 2^100), for which the parts hold the value
+// Magnitudes of the values taken: the least other than zero, and the largest
 struct F32Range {
   uint32_t least = 0xffffffffu, most = 0u;
   __device__ __forceinline__ void take(float x) {
@@ -164,8 +166,13 @@ struct F32Range {
     least = min(least, v - 1u);                    // (zero: the largest)
     most = max(most, v);
   }
-  __device__ __forceinline__ bool inside() const { return least >= 0x0d7fffffu && most < 0x71800000u; }
+  // all zero or in [lo, hi), lo > 0; a NaN is not
+  __device__ __forceinline__ bool inside(float lo, float hi) const { return least >= __float_as_uint(lo) - 1u && most < __float_as_uint(hi); }
 };
+// most = max(most, |a|, |b|), a NaN left out (one instruction: written in C, each value is made canonical first)
+__device__ __forceinline__ void f32_most(float& most, float a, float b) {
+  asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(a), "v"(b));
+}
 
 template <class C>
 __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE)))
@@ -316,6 +323,7 @@ fwd_f32_kernel(const FwdParams p) {
       float4 qf[EXACT ? RB : 1][EXACT ? NU : 1];   // B fragments of S^T = K Q^T; channels past D are zero
       F32Split qp[EXACT ? 1 : RB][EXACT ? 1 : NK];
       F32Range range;
+      float vmost = 0.f;                           // largest magnitude of this lane's values
       {
         int ql = lane;                             // (opaque, as in the epilogue below)
         asm volatile("" : "+v"(ql));
@@ -531,6 +539,7 @@ fwd_f32_kernel(const FwdParams p) {
           };
           auto split_v = [&](auto uc, auto e) __attribute__((always_inline)) {             // unit: half of the keys, channel block
             constexpr int u = decltype(uc)::value, k0 = 8 * (u / DVB) + 2 * e, d = u % DVB;
+            f32_most(vmost, F32Vec<DVB>::at(vf[k0], d), F32Vec<DVB>::at(vf[k0 + 1], d));
             f32_split<e>(F32Vec<DVB>::at(vf[k0], d), F32Vec<DVB>::at(vf[k0 + 1], d), vp[u % 2]);
           };
           read_k(std::integral_constant<int, 0>());
@@ -660,20 +669,34 @@ fwd_f32_kernel(const FwdParams p) {
                []() __attribute__((always_inline)) {});
         }
       }
-      if constexpr (!EXACT) {
+      if constexpr (EXACT) {
+        return false;
+      } else {
+        const bool q_inside = range.inside(0x1p-100f, 0x1p100f / fmaxf(fabsf(p.scale), 1.f));
+        // A weight below 2^-110 loses up to 2^-134 of itself: an accumulator from 2^-98 of the largest value on holds 2^-24 of its own
+        // beside up to 2^12 of them.  Where no value reaches 2^-88, zero in an accumulator may be what bf16 made of them.
+        float lo = 0x1p-88f;
+        if (__builtin_amdgcn_ballot_w64(vmost > 0x1p10f) != 0) {
+#pragma unroll
+          for (int x = 32; x >= 1; x >>= 1) vmost = fmaxf(vmost, __shfl_xor(vmost, x));
+          lo = vmost * 0x1p-98f;
+        }
+        const bool tiny = __builtin_amdgcn_ballot_w64(vmost >= 0x1p-88f) == 0 && __builtin_amdgcn_ballot_w64(vmost > 0.f) != 0;
+        F32Range sums;
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
           for (int d = 0; d < DVB; ++d)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) range.take(o[rb][d][r]);
+            for (int r = 0; r < 16; ++r) sums.take(o[rb][d][r]);
+        return tiny || __builtin_amdgcn_ballot_w64(!(q_inside && sums.inside(lo, INFINITY))) != 0;
       }
-      return !EXACT && __builtin_amdgcn_ballot_w64(!range.inside()) != 0;
     };
 
     if (s > 0) __syncthreads();                    // LDS is reused by the second stream
     bool again = true;
-    if constexpr (C::PARTS) again = pass(std::integral_constant<bool, false>());
+    if constexpr (C::PARTS)
+      if (fabsf(p.scale) <= 0x1p64f) again = pass(std::integral_constant<bool, false>());
     if constexpr (C::PARTS && RG > 1) {                        // waves that share tiles take the second pass together
       int* flags = (int*)lds_raw;
       __syncthreads();
