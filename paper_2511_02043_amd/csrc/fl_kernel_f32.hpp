@@ -363,10 +363,28 @@ fwd_f32_kernel(const FwdParams p) {
           }
         }
       }
-      asm volatile("" : "+v"(range.least), "+v"(range.most));   // (formed here: left to the compiler, behind the loop, and Q's values kept for it)
-      if (!EXACT && C::QP > 0) {
-        f32_wait_lds<0>();
-        if (KS > 1) __syncthreads();
+      if (RG > 1 && wanted(t_lo + ks)) {           // the loop's first tile
+        load_k(t_lo + ks, 0);
+        load_v(t_lo + ks, 0);
+      }
+      if constexpr (!EXACT) {                      // a row that the parts do not hold: none of the keys is looked at
+        bool outside = __builtin_amdgcn_ballot_w64(!range.inside(0x1p-100f, 0x1p100f / fmaxf(fabsf(p.scale), 1.f))) != 0;
+        if (RG > 1) {                              // (in the first split's second buffer, which is free until the loop's first barrier)
+          int* flags = (int*)(lds_raw + C::STAGE);
+          if (lane == 0) flags[wave] = outside ? 1 : 0;
+          f32_wait_lds<0>();
+          __syncthreads();
+#pragma unroll
+          for (int w = 0; w < RG * KS; ++w) outside = outside || flags[w] != 0;
+          outside = __builtin_amdgcn_readfirstlane(outside ? 1 : 0) != 0;
+        } else if (C::QP > 0) {
+          f32_wait_lds<0>();
+          if (KS > 1) __syncthreads();
+        }
+        if (outside) {
+          if (RG > 1) f32_wait_mem<0>();
+          return true;
+        }
       }
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
@@ -647,10 +665,6 @@ fwd_f32_kernel(const FwdParams p) {
           t = tn;
         }
       } else {
-        if (wanted(t_lo + ks)) {
-          load_k(t_lo + ks, 0);
-          load_v(t_lo + ks, 0);
-        }
         for (int it = 0; it < n_iter; ++it) {
           const int t = t_lo + it * KS + ks;
           f32_wait_mem<0>();                       // this wave's loads of tile t have landed ...
@@ -672,7 +686,6 @@ fwd_f32_kernel(const FwdParams p) {
       if constexpr (EXACT) {
         return false;
       } else {
-        const bool q_inside = range.inside(0x1p-100f, 0x1p100f / fmaxf(fabsf(p.scale), 1.f));
         // A weight below 2^-110 loses up to 2^-134 of itself: an accumulator from 2^-98 of the largest value on holds 2^-24 of its own
         // beside up to 2^12 of them.  Where no value reaches 2^-88, zero in an accumulator may be what bf16 made of them.
         float lo = 0x1p-88f;
@@ -689,7 +702,7 @@ fwd_f32_kernel(const FwdParams p) {
           for (int d = 0; d < DVB; ++d)
 #pragma unroll
             for (int r = 0; r < 16; ++r) sums.take(o[rb][d][r]);
-        return tiny || __builtin_amdgcn_ballot_w64(!(q_inside && sums.inside(lo, INFINITY))) != 0;
+        return tiny || __builtin_amdgcn_ballot_w64(!sums.inside(lo, INFINITY)) != 0;
       }
     };
 
