@@ -188,8 +188,11 @@ struct Wave {
   // follow (settle_sums).  That is half a vector instruction less per score and no max between the two contractions: causal,
   // 2 x 32 / 8 heads x 8192 rows, D = 128: 1015 -> 983 us; soft-cap, 8 x 16 x 1999, D = 64: 223 -> 213; chunks of 8 x 512 rows, 32 / 8 heads: 410 -> 398.
   // What overflows on the way (a row that gains a factor of 2^100 in a tile, or values near the end of the range) is found at the end of
-  // the q-tile, which then runs again with the max of every tile (kCareful), for about twice the time (causal, 2 x 16 x 4096, D = 128, scores
-  // of standard deviation 1 / 4 / 16 / 40: 170 / 165 / 157 / 148 -> 169 / 159 / 155 / 291 us).  So not with ALiBi and
+  // the q-tile, which then runs again with the max of every tile (kCareful), for about twice the time; scores so far apart that this would
+  // be the rule show in the first tile, and have the max of every tile taken at once (kSteep), behind the tile and not beside its matrix
+  // instructions.  Causal, scores of standard deviation 1 / 4 / 8 / 16 / 40, with the max in the loop, without and rerun, as it is:
+  // 2 x 16 x 4096, D = 128 137 / 142 / 144 / 145 / 138, 134 / 137 / 143 / 146 / 273, 135 / 138 / 146 / 150 / 146 us; 4 x 16 x 2048, D = 64 56 / 58 / 59 /
+  // 59 / 59, 54 / 56 / 60 / 61 / 128, 54 / 57 / 63 / 67 / 68.  (Two copies of the loop, with and without the max, have no registers.)  So not with ALiBi and
   // biases, whose scores do rise that steeply (a mask given as a large negative bias), nor for expressions; and not under a window
   // or document mask: rows of few tiles, whose max a partly visible tile needs in any case (training step, window 512: 281 us either way).
   static constexpr bool kTrust = C::NBIAS == 0 && (C::MOD == kModNone || C::MOD == kModSoftcap) && (C::MASK & (kMaskWindow | kMaskDoc | kMaskCustom)) == 0;
@@ -233,8 +236,10 @@ struct Wave {
   bf16x8 qf[C::RB][C::KK];      // Q fragments of the wave's rows (of its own stream, differential variant)
   f32x16 oacc[C::RB][C::DVB];
   float m_run[C::RB], l_run[C::RB];                // log2-domain running max; per-lane partial sum
-  int trust;                                       // kTrust (uniform): kFresh, kGrown once accumulators may have overflowed, or kCareful
-  static constexpr int kFresh = 0, kGrown = 1, kCareful = 2;
+  // kTrust (uniform), bits: kGrown once accumulators may have overflowed; the max of each tile is taken with kCareful, when the q-tile runs
+  // again, and kSteep, where its scores are seen to be far apart (settle_sums); kFirst until the first tile's sums are known
+  int trust;
+  static constexpr int kGrown = 1, kCareful = 2, kSteep = 4, kFirst = 8;
   static constexpr float kFollow = NB * 16 * 0x1p8f;   // a lane's sum of a tile, at most, where a running max lets 2^8 per score through
   static constexpr float kFar = 0x1p8f;            // while a row sum is no more than this, no score has gone further than under a running max
 
@@ -701,8 +706,11 @@ struct Wave {
   }
 
   // kTrust: adds the tile's row sums.  Where one has passed kFollow the reference moves up by a power of two that holds it; where a
-  // row has no reference yet (nothing of it was visible), and in careful runs, it is the running max of the next tile's scores
-  // (`advance`: they are final).
+  // row has no reference yet (nothing of it was visible), and while the max of every tile is taken, it is the running max of the next
+  // tile's scores (`advance`: they are final).
+  // The max of every tile is taken where the first tile shows scores so far apart that a later one would pass the reference by 2^100, and the
+  // q-tile run twice: one half of its keys has a sum below 2^-32 of its max in the other, in some row of the wave.  (Of normal scores, 1 % of
+  // waves at a standard deviation of 8, 80 % at 16, all at 25, where 40 % of the q-tiles ran twice; with 2^-40, a third still did in some shapes.)
   __device__ __forceinline__ void settle_sums(const Pipe& ps, const Scores& nxt, bool advance) {
     bool any = false;
 #pragma unroll
@@ -710,23 +718,34 @@ struct Wave {
       l_run[rb] += ps.psum[rb];
       any = any || ps.psum[rb] > kFollow || m_run[rb] == -INFINITY;
     }
-    if (__builtin_amdgcn_ballot_w64(any) != 0 || trust >= kCareful) {   // rare and wave-uniform
-      trust = trust | kGrown;
-      bool hidden = trust >= kCareful;
+    const bool moves = __builtin_amdgcn_ballot_w64(any) != 0;
+    if (moves || trust >= kCareful) {              // rare and wave-uniform
+      if (trust == kFirst) {
+        bool apart = false;                        // (a sum of zero: the lane's keys are hidden)
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const float top = half_swap_max(ps.psum[rb]), m_old = m_run[rb];
-        const bool up = top > kFollow;
-        m_run[rb] = up ? m_old + (float)__builtin_amdgcn_frexp_expf(top) : m_old;
-        const float alpha = up ? fast_exp2(m_old - m_run[rb]) : 1.f;
-        l_run[rb] = top > 0x1p100f ? INFINITY : l_run[rb] * alpha;   // (too far for a factor that fp32 holds: settled by the careful run)
-#pragma unroll
-        for (int d = 0; d < DVB; ++d)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) oacc[rb][d][r] *= alpha;
-        hidden = hidden || m_run[rb] == -INFINITY;
+        for (int rb = 0; rb < RB; ++rb) apart = apart || (ps.psum[rb] > 0.f && ps.psum[rb] < 0x1p-32f);
+        trust = __builtin_amdgcn_ballot_w64(apart) != 0 ? kSteep : 0;
       }
-      if (advance && __builtin_amdgcn_ballot_w64(hidden) != 0) {
+      bool follow = trust >= kCareful;
+      if (moves) {
+        trust = trust | kGrown;
+        bool hidden = false;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+          const float top = half_swap_max(ps.psum[rb]), m_old = m_run[rb];
+          const bool up = top > kFollow;
+          m_run[rb] = up ? m_old + (float)__builtin_amdgcn_frexp_expf(top) : m_old;
+          const float alpha = up ? fast_exp2(m_old - m_run[rb]) : 1.f;
+          l_run[rb] = top > 0x1p100f ? INFINITY : l_run[rb] * alpha;   // (too far for a factor that fp32 holds: settled by the careful run)
+#pragma unroll
+          for (int d = 0; d < DVB; ++d)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[rb][d][r] *= alpha;
+          hidden = hidden || m_run[rb] == -INFINITY;
+        }
+        follow = follow || __builtin_amdgcn_ballot_w64(hidden) != 0;
+      }
+      if (advance && follow) {
         float mx[RB];
         rowmax(nxt, mx);
         advance_max(mx);
@@ -737,8 +756,8 @@ struct Wave {
   // row's reference, beside values near the end of the range.  It shows in the row sum: while that is at most kFar, nothing has to be
   // looked at (rows of few keys; the look took 0.16 us of a call on [1, 8, 128, 64]).
   __device__ __forceinline__ bool overflowed() const {
-    if (trust >= kCareful) return false;
-    bool far = trust == kGrown;
+    if ((trust & kCareful) != 0) return false;
+    bool far = (trust & kGrown) != 0;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) far = far || l_run[rb] > kFar;
     if (__builtin_amdgcn_ballot_w64(far) == 0) return false;
@@ -892,7 +911,7 @@ fwd_bf16_kernel(const FwdParams call) {
     p.q_off = len - call.Sq;
   }
   W w(p);
-  w.trust = W::kFresh;
+  w.trust = W::kFirst;
 #pragma nounroll
   for (int pass = 0; pass < 2; ++pass) {
   const int qt = pass == 0 ? nq - 1 - pi : pi;
@@ -1567,7 +1586,7 @@ fwd_bf16_kernel(const FwdParams call) {
         __syncthreads();
         const bool again = __builtin_amdgcn_ballot_w64(flag[ln % C::NWAVES] != 0) != 0;
         if (C::DIFF || again) __syncthreads();     // (LDS is written again)
-        w.trust = __builtin_amdgcn_readfirstlane(again ? W::kCareful : W::kFresh);
+        w.trust = __builtin_amdgcn_readfirstlane(again ? W::kCareful : W::kFirst);
         if (again) {
           --pass;
           continue;
