@@ -389,6 +389,8 @@ const fl::DecodeEntry* find_decode_entry(int D, int mod, int cb, int waves) {
 // 15.6 / 9.7 / 6.2, 20.9 / 15.8 / 14.0, 42.9 / 41.5 / 40.4, 97.8 / 93.3 / 96.8; 64 sequences 8.5 / 5.8 / 6.0, 10.7 / 8.0 / 11.2, 24.8 / 23.3 / 32.2, 44.2 / 42.8 /
 // 45.3; 32 sequences of up to 512, 8192 7.7 / 9.6 / 15.4, 87.1 / 93.4.  D = 128: 128 sequences of up to 64, 256, 512, 1024 tokens 21.0 / 13.6 / 9.8, 33.7 / 29.4 / 25.1, 47.9 / 49.9 /
 // 43.0, 89 / 94 / 91; 64 sequences 11.3 / 7.7 / 9.3, 18.3 / 15.9 / 22.6, 27.5 / 26.3 / 40.4, 43 / 48 / 75; 32 sequences of up to 256 8.7 / 12.9 / 22.4.
+// Under a window a workgroup has the window's tiles only: 64 sequences of 8192 tokens with windows of 64 / 256 / 1024 / 2048, full number of waves and by the
+// window's tiles, D = 64 24.8 / 26.2 / 39.2 / 59.9 and 12.8 / 16.6 / 34.3 / 53.5, D = 128 42.7 / 45.0 / 72.6 / 126 and 17.4 / 27.2 / 59.6 / 125.
 int decode_waves(int64_t D, int cb, int64_t workgroups, int64_t tiles) {   // tiles: of the longest workgroup
   const int full = fl::decode_full_waves((int)D, cb);
   if (cb != 1 || workgroups <= 256) return full;
@@ -2181,7 +2183,9 @@ fl_status fl_attn_decode(const fl_tensor* q, const fl_tensor* k_cache, const fl_
     if (kv->max_seq_len > page_size) return fail(FL_ERR_SHAPE, "max_seq_len exceeds the page size");
   }
   const int ns = decode_splits(B, Hkv, D, kv->max_seq_len), cb = H > 0 && (H / Hkv) * T > 32 ? 2 : 1;
-  const fl::DecodeEntry* de = find_decode_entry((int)D, (int)desc->score_mod, cb, decode_waves(D, cb, B * Hkv * ns, ((int64_t)kv->max_seq_len + 32 * ns - 1) / (32 * ns)));
+  // a window's keys, from the oldest query row's first one, begin anywhere in a tile
+  const int64_t reach = (mask & FL_MASK_WINDOW) != 0 && desc->window >= 0 ? std::min<int64_t>(kv->max_seq_len, desc->window + T + 31) : kv->max_seq_len;
+  const fl::DecodeEntry* de = find_decode_entry((int)D, (int)desc->score_mod, cb, decode_waves(D, cb, B * Hkv * ns, (reach + 32 * ns - 1) / (32 * ns)));
   if (de == nullptr || v_cache->size[4] != D)
     return fail(FL_ERR_UNSUPPORTED, "no decode specialisation for D=%lld Dv=%lld score_mod=%u", (long long)D,
                 (long long)v_cache->size[4], desc->score_mod);

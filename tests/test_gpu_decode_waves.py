@@ -38,3 +38,13 @@ def test_decode_waves_variants(B, D, variant):
         w.alibi = inputs.alibi_slopes(16)
         w.window = 70
     compare(w, variant, out_dtype="bf16" if variant == "bf16" else "f32")
+
+
+@pytest.mark.parametrize("B,D,window", [(33, 64, 40), (65, 64, 255), (33, 128, 40), (65, 128, 255), (33, 128, 600)])
+def test_decode_waves_window(B, D, window):
+    """Long sequences of which a workgroup sees a window's tiles only: fewer waves, as for short ones."""
+    lens = np.random.default_rng(B).integers(1, 1301, size=B)
+    lens[:8] = [0, 1, 31, window, window + 1, window + 33, 1299, 1300]
+    w = inputs.decode_bf16(H=16, Hkv=8, D=D, page_size=16, seq_lens=lens, salt=9)
+    w.window = window
+    compare(w, f"window {window}")
