@@ -363,10 +363,13 @@ fwd_f32_kernel(const FwdParams p) {
           }
         }
       }
-      if (RG > 1 && wanted(t_lo + ks)) {           // the loop's first tile
-        load_k(t_lo + ks, 0);
-        load_v(t_lo + ks, 0);
-      }
+      auto load_first = [&]() __attribute__((always_inline)) {
+        if (wanted(t_lo + ks)) {
+          load_k(t_lo + ks, 0);
+          load_v(t_lo + ks, 0);
+        }
+      };
+      if (RG > 1 && C::PLAIN) load_first();
       if constexpr (!EXACT) {                      // a row that the parts do not hold: none of the keys is looked at
         bool outside = __builtin_amdgcn_ballot_w64(!range.inside(0x1p-100f, 0x1p100f / fmaxf(fabsf(p.scale), 1.f))) != 0;
         if (RG > 1) {                              // (in the first split's second buffer, which is free until the loop's first barrier)
@@ -382,7 +385,7 @@ fwd_f32_kernel(const FwdParams p) {
           if (KS > 1) __syncthreads();
         }
         if (outside) {
-          if (RG > 1) f32_wait_mem<0>();
+          if (RG > 1 && C::PLAIN) f32_wait_mem<0>();
           return true;
         }
       }
@@ -665,6 +668,7 @@ fwd_f32_kernel(const FwdParams p) {
           t = tn;
         }
       } else {
+        if (!C::PLAIN) load_first();
         for (int it = 0; it < n_iter; ++it) {
           const int t = t_lo + it * KS + ks;
           f32_wait_mem<0>();                       // this wave's loads of tile t have landed ...
@@ -708,8 +712,13 @@ fwd_f32_kernel(const FwdParams p) {
 
     if (s > 0) __syncthreads();                    // LDS is reused by the second stream
     bool again = true;
+    // The variants take the parts where there are tiles enough to earn what they cost beside the tiles (the split of Q, the check and the
+    // agreement of the waves).  16 x 16 heads x 32 / 64 / 96 / 128 / 160 rows and keys, on parts and not: ALiBi, D = 32 8.5 / 10.5 / 12.7 / 15.2 / 20.1 and
+    // 7.8 / 9.8 / 12.2 / 14.7 / 21.0 us, gate, D = 64 12.9 / 16.0 / 18.9 / 22.3 / 32.0 and 11.9 / 15.5 / 18.8 / 22.5 / 36.2; the second stream, 4 x 16 x 256,
+    // D = 32 / 64 (two tiles for each of four splits) 22.7 / 34.4 and 21.4 / 35.0.  With one wave per split parts are as fast from the first tile on.
+    const int least = RG == 1 ? 0 : KS > 1 ? (DMAX == 32 ? 2 : 0) : DMAX == 32 ? 4 : 3;
     if constexpr (C::PARTS)
-      if (fabsf(p.scale) <= 0x1p64f) again = pass(std::integral_constant<bool, false>());
+      if (fabsf(p.scale) <= 0x1p64f && (C::PLAIN || n_iter > least)) again = pass(std::integral_constant<bool, false>());
     if constexpr (C::PARTS && RG > 1) {                        // waves that share tiles take the second pass together
       int* flags = (int*)lds_raw;
       __syncthreads();
