@@ -91,13 +91,16 @@ def _score_mod(softcap, alibi_slopes):
     return fb.FL_MOD_SOFTCAP if softcap is not None else (fb.FL_MOD_ALIBI if alibi_slopes is not None else fb.FL_MOD_NONE)
 
 
-_transforms_active, _tracing_state, _grad_enabled = torch._C._are_functorch_transforms_active, torch._C._get_tracing_state, torch.is_grad_enabled
+# private names of torch: where one is missing, its state counts as there and every call gets its node
+_transforms_active = getattr(torch._C, "_are_functorch_transforms_active", lambda: True)
+_tracing_state = getattr(torch._C, "_get_tracing_state", lambda: True)
+_grad_enabled = torch.is_grad_enabled
 
 
 def _without_node(tensors) -> bool:
     """Whether a call takes no part in a derivative, a transform or a trace, so that it needs no autograd node: building one takes
     3.7 us, of 8.8 us for a call on [1, 8, 128, 64] whose kernel runs 8 us (training calls are unchanged)."""
-    if _transforms_active() or forward_ad._current_level >= 0 or _tracing_state() is not None or torch.compiler.is_compiling():
+    if _transforms_active() or getattr(forward_ad, "_current_level", 0) >= 0 or _tracing_state() is not None or torch.compiler.is_compiling():
         return False
     if _grad_enabled():
         for t in tensors:

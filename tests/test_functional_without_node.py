@@ -1,4 +1,7 @@
 """When the PyTorch entry points may run without an autograd node (CPU): never inside a derivative, a transform or a trace."""
+import importlib.util
+
+import pytest
 import torch
 from torch.autograd import forward_ad
 
@@ -30,3 +33,13 @@ def test_only_without_derivatives_transforms_and_traces():
     with torch.no_grad():
         torch.jit.trace(call, (x,), check_trace=False)
     assert not any(seen) and len(seen) == 6, seen
+
+
+@pytest.mark.parametrize("owner,name", [(torch._C, "_are_functorch_transforms_active"), (torch._C, "_get_tracing_state"), (forward_ad, "_current_level")])
+def test_with_a_torch_that_has_not_the_name(owner, name, monkeypatch):
+    """A state that cannot be asked for is one that may be there: the module is imported, and every call gets its node."""
+    monkeypatch.delattr(owner, name)
+    spec = importlib.util.spec_from_file_location(fn.__name__ + "_again", fn.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+    assert not again._without_node((torch.zeros(2),))
