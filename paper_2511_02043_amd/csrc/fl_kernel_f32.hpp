@@ -171,7 +171,7 @@ struct F32Range {
 };
 // most = max(most, |a|, |b|), a NaN left out (one instruction: written in C, each value is made canonical first)
 __device__ __forceinline__ void f32_most(float& most, float a, float b) {
-  asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(a), "v"(b));
+  most = __builtin_elementwise_maximum(__builtin_elementwise_maximum(__builtin_fabsf(a), __builtin_fabsf(b)), most);
 }
 
 template <class C>
