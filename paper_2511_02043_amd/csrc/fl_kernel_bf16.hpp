@@ -41,6 +41,9 @@
 // more than 2^8 (the exponent of P stays bounded by 8), which makes the O rescale a rare,
 // wave-uniform branch; l and the final normalisation use the same reference, so the result is
 // unchanged in real arithmetic.
+// Plain and soft-cap kernels without biases, window, document or custom mask (Wave::kTrust) take no
+// row max on fully visible tiles unless the scores are seen to be far apart: their P may be as large as fp32 holds within a
+// tile, and a tile whose row sum has passed 2^8 per score moves the reference afterwards (settle_sums).
 #pragma once
 #include "fl_params.hpp"
 

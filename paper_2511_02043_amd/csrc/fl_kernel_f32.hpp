@@ -1,5 +1,6 @@
 // fp32 attention-variant forward kernel: fp32 storage, scores, softmax state and accumulators; both contractions over three bf16
-// parts of each operand (v_mfma_f32_32x32x16_bf16), or on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32).
+// parts of each operand (v_mfma_f32_32x32x16_bf16), or on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32): variants above head dim
+// 64 and with few key tiles, and values that the parts do not hold.
 //
 // This is the fp32-storage specialisation of the fused pass; tanh, the logarithm and the gate use the
 // accurate math-library routines, and the result is meant to stay within 1e-5 of an fp64 evaluation.
@@ -25,14 +26,15 @@
 // on the fp32 instruction, so that infinities, NaN and tiny values give what they gave there; but beside ordinary values, a channel
 // whose values are all below 2^-134 gives zero.
 //
-// What bounds it: issue of vector instructions, 8.8 for each matrix instruction at D = 64 (eleven per pair of values split; four run beside
-// a matrix instruction).  So a wave takes two row blocks (K and V are split once for both) wherever registers allow, the split of
+// What bounds it: issue of vector instructions, 10.8 for each matrix instruction of a call at D = 64, about nine of them in the key loop (eleven per
+// pair of values split, one per pair of V for its magnitude; four run beside a matrix instruction).  So a wave takes two row blocks (K and V are split once for both) wherever registers allow, the split of
 // the next operands stands between the matrix instructions of the present ones (f32_stage), and where the call has fewer than two waves
 // per SIMD the key tiles of a row group are dealt to KS waves, which merge through LDS by the rescale rule of Sec. 3.3.  K / V tiles
 // of 32 keys go to LDS by direct loads.
 // Measured against the fp32 instruction in both contractions, one row block per wave: 2 x 8 heads, 1024 rows and keys, D = 32 / 64 / 128: 30 / 53 /
-// 107 -> 20 / 37 / 63 us, 8 x 16 heads x 2048 rows, D = 64: 1241 -> 718 us (191 TFLOP/s); the same pass on plain VALU arithmetic
-// took 508 us for the first at D = 64.
+// 107 -> 21 / 33 / 65 us, 8 x 16 heads x 2048 rows, D = 64: 1260 -> 732 us (188 TFLOP/s); the same pass on plain VALU arithmetic
+// took 508 us for the first at D = 64.  Variants (PARTS) 2 x 8 x 1024, ALiBi / bias / gate / differential, D = 32: 31 / 60 / 31 / 55 -> 28 / 55 / 29 / 51,
+// D = 64: 48 / 75 / 50 / 89 -> 42 / 65 / 43 / 76; at D = 128 they run on the fp32 instruction: 107 / 138 / 121 / 212 and 105 / 135 / 116 / 205.
 #pragma once
 #include "fl_kernel_bf16.hpp"
 
@@ -169,7 +171,7 @@ struct F32Range {
   // all zero or in [lo, hi), lo > 0; a NaN is not
   __device__ __forceinline__ bool inside(float lo, float hi) const { return least >= __float_as_uint(lo) - 1u && most < __float_as_uint(hi); }
 };
-// most = max(most, |a|, |b|), a NaN left out (one instruction: written in C, each value is made canonical first)
+// most = max(most, |a|, |b|), one instruction (fmaxf would make each value canonical first); a NaN stays one, and shows in the accumulators, too
 __device__ __forceinline__ void f32_most(float& most, float a, float b) {
   most = __builtin_elementwise_maximum(__builtin_elementwise_maximum(__builtin_fabsf(a), __builtin_fabsf(b)), most);
 }
