@@ -190,12 +190,12 @@ struct Wave {
   // a little less), without the row max of the tile; its row sum, which there is anyway, tells afterwards whether the reference has to
   // follow (settle_sums).  That is half a vector instruction less per score and no max between the two contractions: causal,
   // 2 x 32 / 8 heads x 8192 rows, D = 128: 1015 -> 983 us; soft-cap, 8 x 16 x 1999, D = 64: 223 -> 213; chunks of 8 x 512 rows, 32 / 8 heads: 410 -> 398.
-  // What overflows on the way (a row that gains a factor of 2^100 in a tile, or values near the end of the range) is found at the end of
+  // What overflows on the way (a row that gains a factor of 2^117 in a tile, or values near the end of the range) is found at the end of
   // the q-tile, which then runs again with the max of every tile (kCareful), for about twice the time; scores so far apart that this would
   // be the rule show in the first tile, and have the max of every tile taken at once (kSteep), behind the tile and not beside its matrix
-  // instructions.  Causal, scores of standard deviation 1 / 4 / 8 / 16 / 40, with the max in the loop, without and rerun, as it is:
-  // 2 x 16 x 4096, D = 128 137 / 142 / 144 / 145 / 138, 134 / 137 / 143 / 146 / 273, 135 / 138 / 146 / 150 / 146 us; 4 x 16 x 2048, D = 64 56 / 58 / 59 /
-  // 59 / 59, 54 / 56 / 60 / 61 / 128, 54 / 57 / 63 / 67 / 68.  (Two copies of the loop, with and without the max, have no registers.)  So not with ALiBi and
+  // instructions.  Causal, scores of standard deviation 1 / 4 / 8 / 16 / 40, with the max in the loop and as it is: 2 x 16 x 4096, D = 128
+  // 141 / 148 / 150 / 150 / 145 and 138 / 141 / 146 / 152 / 149 us; 4 x 16 x 2048, D = 64 57 / 59 / 60 / 61 / 60 and 55 / 57 / 61 / 67 / 69; with every
+  // q-tile that overflows run again instead, 273 and 128 at 40.  (Two copies of the loop, with and without the max, have no registers.)  So not with ALiBi and
   // biases, whose scores do rise that steeply (a mask given as a large negative bias), nor for expressions; and not under a window
   // or document mask: rows of few tiles, whose max a partly visible tile needs in any case (training step, window 512: 281 us either way).
   static constexpr bool kTrust = C::NBIAS == 0 && (C::MOD == kModNone || C::MOD == kModSoftcap) && (C::MASK & (kMaskWindow | kMaskDoc | kMaskCustom)) == 0;
@@ -708,12 +708,14 @@ struct Wave {
     }
   }
 
-  // kTrust: adds the tile's row sums.  Where one has passed kFollow the reference moves up by a power of two that holds it; where a
+  // kTrust: adds the tile's row sums.  Where one has passed kFollow the reference moves up by a power of two, 2^8 past what holds it, and that of
+  // the wave's rows on their way there, so that this stays rare (standard deviation 8, D = 64 as above: 62.6 -> 60.6 us); where a
   // row has no reference yet (nothing of it was visible), and while the max of every tile is taken, it is the running max of the next
   // tile's scores (`advance`: they are final).
-  // The max of every tile is taken where the first tile shows scores so far apart that a later one would pass the reference by 2^100, and the
-  // q-tile run twice: one half of its keys has a sum below 2^-32 of its max in the other, in some row of the wave.  (Of normal scores, 1 % of
-  // waves at a standard deviation of 8, 80 % at 16, all at 25, where 40 % of the q-tiles ran twice; with 2^-40, a third still did in some shapes.)
+  // The max of every tile is taken where the first tile shows scores so far apart that a later one would pass the reference by 2^117, and the
+  // q-tile run twice: one half of its keys has a sum below 2^-40 of its max in the other, in some row of the wave.  (Of normal scores, 6 % of
+  // waves at a standard deviation of 12, 45 % at 16, 97 % at 25; with 2^-32, 21 % at 12, where the loop without is faster; with 2^-48, 20 -
+  // 40 % more time at 25 at D = 64, for q-tiles run twice.)
   __device__ __forceinline__ void settle_sums(const Pipe& ps, const Scores& nxt, bool advance) {
     bool any = false;
 #pragma unroll
@@ -726,7 +728,7 @@ struct Wave {
       if (trust == kFirst) {
         bool apart = false;                        // (a sum of zero: the lane's keys are hidden)
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) apart = apart || (ps.psum[rb] > 0.f && ps.psum[rb] < 0x1p-32f);
+        for (int rb = 0; rb < RB; ++rb) apart = apart || (ps.psum[rb] > 0.f && ps.psum[rb] < 0x1p-40f);
         trust = __builtin_amdgcn_ballot_w64(apart) != 0 ? kSteep : 0;
       }
       bool follow = trust >= kCareful;
@@ -736,10 +738,10 @@ struct Wave {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
           const float top = half_swap_max(ps.psum[rb]), m_old = m_run[rb];
-          const bool up = top > kFollow;
-          m_run[rb] = up ? m_old + (float)__builtin_amdgcn_frexp_expf(top) : m_old;
+          const bool up = top > NB * 16;           // (1 per score)
+          m_run[rb] = up ? m_old + (float)(__builtin_amdgcn_frexp_expf(top) + 8) : m_old;
           const float alpha = up ? fast_exp2(m_old - m_run[rb]) : 1.f;
-          l_run[rb] = top > 0x1p100f ? INFINITY : l_run[rb] * alpha;   // (too far for a factor that fp32 holds: settled by the careful run)
+          l_run[rb] = top > 0x1p117f ? INFINITY : l_run[rb] * alpha;   // (too far for a factor that fp32 holds: settled by the careful run)
 #pragma unroll
           for (int d = 0; d < DVB; ++d)
 #pragma unroll

@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 LEVELS = {
     "ramp": lambda x, n: 70.0 * x,                                   # the reference follows, tile by tile
     "step": lambda x, n: np.where(x < 0.5, 0.0, 60.0),               # ... once, by 2^86
-    "jump": lambda x, n: np.where(x < 0.5, 0.0, 120.0),              # past 2^100: the q-tile runs again
+    "far": lambda x, n: np.where(x < 0.5, 0.0, 76.0),                # ... by 2^110
+    "jump": lambda x, n: np.where(x < 0.5, 0.0, 120.0),              # past 2^117: the q-tile runs again
     "jumps": lambda x, n: 100.0 * np.floor(4 * x),
     "last": lambda x, n: np.where(np.arange(n) == n - 1, 300.0, 0.0),
     "down": lambda x, n: np.where(x < 0.4, 200.0, 0.0),
