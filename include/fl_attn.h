@@ -445,7 +445,8 @@ const char* fl_last_error_detail(void);
  * query heads into subsets; both change the workspace size the matching *_workspace_size reports),
  * "prefill_gather" (fl_attn_prefill_paged: 1 = always copy the pages first, 2 = always read them in place with the
  * forward kernel; either also keeps chunks of a few rows away from the decode kernels), "prefill_pack" (1 = never
- * pack the query heads of a kv head into one workgroup of the in-place kernel), "pair_bias" (fl_attn_bwd_ex with a bias shared
+ * pack the query heads of a kv head into one workgroup of the in-place kernel), "bwd_keys" (the dK / dV kernel with 64 keys per wave:
+ * 1 = never, 2 = always where the variant has one), "pair_bias" (fl_attn_bwd_ex with a bias shared
  * along G: 1 = never the kernels that keep it in registers, 2 = always where they can, which may enlarge the workspace
  * that the query reports).
  * Value 0 restores the built-in choice.  Returns FL_OK or FL_ERR_UNSUPPORTED.  The requests are kept

@@ -45,6 +45,7 @@ struct Tuning {
   int prefill_gather = 0;          // fl_attn_prefill_paged: 1 always copies the pages into dense tensors first, 2 never
                                    // (where the pages allow it); 0: by chunk length
   int bwd_wg_target = 0;           // 0: the default of choose_hsplit
+  int bwd_keys = 0;                // dK/dV: 1 never takes the kernel with 64 keys per wave, 2 always where the variant has one
   int pair_bias = 0;               // fl_attn_bwd_ex: 1 never takes the stationary-bias kernels, 2 always where they can
 };
 thread_local Tuning g_tuning;
@@ -326,8 +327,33 @@ const fl::BwdEntry* find_bwd_entry(const fl_variant_desc* d, int D, int nbias = 
 hipError_t run_bwd_dq(const fl::BwdEntry* be, const fl::BwdParams& p, int nblocks, hipStream_t stream) {
   return be->jit != nullptr ? fl::jit_backward_launch(*be, 0, p, nblocks, stream) : be->dq(p, nblocks, stream);
 }
-hipError_t run_bwd_dkdv(const fl::BwdEntry* be, const fl::BwdParams& p, int nblocks, hipStream_t stream) {
-  return be->jit != nullptr ? fl::jit_backward_launch(*be, 1, p, nblocks, stream) : be->dkdv(p, nblocks, stream);
+// The dK/dV kernel with 64 keys per wave where the variant has one, the call suits it and its workgroups of 256 keys keep the 256 compute
+// units as busy as those of 128 keys do.  With the same share of them at work it is the faster one (us, partial sums added, 128 / 256 keys, D = 128: causal
+// 8 x 16 heads x 1024 153 / 119, 16 x 16 x 512 113 / 97, 2 x 32/8 x 2048 258 / 208, 64 x 8 x 256 80.5 / 79.5; without a mask 2 x 16 x 2048 160 / 133,
+// 1 x 16/2 x 4096 308 / 261, 64 x 8 x 256 79 / 73); with half of it the slower one (causal 4 x 16 x 512 27 / 47, 1 x 16/2 x 4096 186 / 246,
+// without a mask 1 x 8 x 4096 148 / 212, 64 x 16 x 128 67 / 95).
+const fl::WideEntry* wide_dkdv(const fl::BwdEntry* be, const fl::BwdParams& p) {
+  if (be->jit != nullptr || g_tuning.bwd_keys == 1) return nullptr;
+  const fl::WideEntry* w = fl::find_wide(be->key);
+  // it forms a row's offset in a tile with 24-bit products
+  if (w == nullptr || p.q.ss >= (1 << 23) || p.dout.ss >= (1 << 23)) return nullptr;
+  if (g_tuning.bwd_keys == 2) return w;
+  const int64_t problems = (int64_t)p.B * p.G * p.Hkv * p.hsplit;
+  // A launch's time in keys of one workgroup after the other on a compute unit.  Under a positional mask a workgroup has half of the longest
+  // one's rows on average, and the longest start first.
+  auto keys = [&](int bm) {
+    const int64_t wgs = problems * ((p.Sk + bm - 1) / bm);
+    return bm * (be->key.mask != 0 ? std::max<int64_t>(1, (wgs + 511) / 512) : (wgs + 255) / 256);
+  };
+  return 10 * keys(w->bm) <= 11 * keys(be->bm) ? w : nullptr;
+}
+hipError_t run_bwd_dkdv(const fl::BwdEntry* be, const fl::WideEntry* wide, const fl::BwdParams& p, int64_t problems, hipStream_t stream) {
+  fl::BwdParams pk = p;
+  const int bm = wide != nullptr ? wide->bm : be->bm;
+  pk.n_ktiles = (p.Sk + bm - 1) / bm;
+  const int nblocks = (int)(problems * pk.n_ktiles);
+  if (wide != nullptr) return wide->dkdv(pk, nblocks, stream);
+  return be->jit != nullptr ? fl::jit_backward_launch(*be, 1, pk, nblocks, stream) : be->dkdv(pk, nblocks, stream);
 }
 
 bool bwd_desc_ok(const fl_variant_desc* d) { return d->n_bias == 0 && d->combine == FL_SINGLE && d->epilogue == 0; }
@@ -1324,6 +1350,7 @@ fl_status fl_set_tuning(const char* key, int value) {
   else if (!strcmp(key, "prefill_pack")) g_tuning.prefill_pack = value;
   else if (!strcmp(key, "prefill_gather")) g_tuning.prefill_gather = value;
   else if (!strcmp(key, "bwd_wg_target")) g_tuning.bwd_wg_target = value;
+  else if (!strcmp(key, "bwd_keys")) g_tuning.bwd_keys = value;
   else if (!strcmp(key, "pair_bias")) g_tuning.pair_bias = value;
   else return fail(FL_ERR_UNSUPPORTED, "unknown tuning key '%s'", key);
   return FL_OK;
@@ -1797,7 +1824,7 @@ fl_status fl::backward_call(const fl_tensor* q, const fl_tensor* k, const fl_ten
   }
   if (!no_keys) {
     // Sq == 0: the query loop is empty and dk, dv come out as zeros
-    if ((e = run_bwd_dkdv(be, p, (int)nb_k, stream)) != hipSuccess) return fail(FL_ERR_LAUNCH, "dk/dv launch: %s", hipGetErrorString(e));
+    if ((e = run_bwd_dkdv(be, wide_dkdv(be, p), p, B * G * Hkv * p.hsplit, stream)) != hipSuccess) return fail(FL_ERR_LAUNCH, "dk/dv launch: %s", hipGetErrorString(e));
     if (p.hsplit > 1) {
       const int64_t chunks = B * G * Hkv * Sk * (D / 4);
       if ((e = be->reduce(p, (int)((chunks + 255) / 256), stream)) != hipSuccess)
@@ -2113,7 +2140,7 @@ fl_status fl_attn_bwd_ex(const fl_tensor* q, const fl_tensor* k, const fl_tensor
         else if (few) hipLaunchKernelGGL((reduce_dbias_kernel<false, true>), grid, dim3(256), 0, stream, dp);
         else hipLaunchKernelGGL((reduce_dbias_kernel<false, false>), grid, dim3(256), 0, stream, dp);
       }
-    if ((e = run_bwd_dkdv(be, p, (int)nb_k, stream)) != hipSuccess) return fail(FL_ERR_LAUNCH, "dk/dv launch: %s", hipGetErrorString(e));
+    if ((e = run_bwd_dkdv(be, wide_dkdv(be, p), p, B * G * Hkv * p.hsplit, stream)) != hipSuccess) return fail(FL_ERR_LAUNCH, "dk/dv launch: %s", hipGetErrorString(e));
     if (p.hsplit > 1) {
       const int64_t chunks = rows_k * ((Dc > Dvc ? Dc : Dvc) / 4);
       if ((e = be->reduce(p, (int)((chunks + 255) / 256), stream)) != hipSuccess)

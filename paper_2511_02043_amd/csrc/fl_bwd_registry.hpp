@@ -25,6 +25,14 @@ struct BwdEntry {
   void* jit;        // entries instantiated at run time: their dq / dkdv are null and launched through jit_backward_launch
 };
 
+// A dK/dV kernel with 64 keys per wave (fl_bwd_wide.hpp) of a compiled specialisation; null: none is compiled.
+struct WideEntry {
+  BwdKey key;
+  int bm;           // keys per workgroup
+  BwdLaunchFn dkdv;
+};
+const WideEntry* find_wide(const BwdKey& key);
+
 // A backward specialisation outside the compiled table, instantiated from the same kernel templates with hipRTC
 // on first use and kept for the life of the process (null if it does not compile).  reduce: the compiled
 // partial-sum kernel of that head dim, which does not depend on the variant.

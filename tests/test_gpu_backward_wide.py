@@ -1,0 +1,87 @@
+"""The dK/dV kernel with 64 keys per wave against the fp64 oracle where its tiles end: 32-row blocks, 64-row tiles (rings of three), 64 keys
+of a wave, 256 of a workgroup; every variant that has one, grouped heads in one piece and cut.  The tuning switch selects it for calls of any
+size.  Tolerance: fl_attn_bwd's (P and dS in bf16, fp32 sums; relative L2 <= 5e-3)."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import attention_backward_oracle as bo
+from paper_2511_02043_amd import binding as fb
+from paper_2511_02043_amd import inputs, runner
+import test_gpu_backward as simple
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def always():
+    fb.check(fb.fl_set_tuning("bwd_keys", 2))
+    yield
+    fb.fl_set_tuning("bwd_keys", 0)
+
+
+SIZES = [(1, 1), (31, 63), (65, 64), (200, 255), (129, 257), (320, 256), (333, 600)]
+VARIANTS = {
+    "plain": lambda **k: inputs.causal_bf16(causal=False, **k),
+    "causal": lambda **k: inputs.causal_bf16(**k),
+    "alibi": lambda **k: dataclasses.replace(inputs.causal_bf16(causal=False, **k), alibi=np.array([0.25, 0.01], np.float32)),
+    "softcap": lambda **k: dataclasses.replace(inputs.causal_bf16(causal=False, **k), softcap=2.0),
+    "prefix": lambda **k: dataclasses.replace(inputs.causal_bf16(causal=False, **k), prefix=70),
+}
+
+
+@pytest.mark.parametrize("Sq,Sk", SIZES)
+@pytest.mark.parametrize("variant", list(VARIANTS))
+def test_sizes(variant, Sq, Sk, always):
+    simple.compare(VARIANTS[variant](B=1, H=2, S=Sq, Sk=Sk, D=128), label=f"{variant} {Sq} x {Sk}")
+
+
+@pytest.mark.parametrize("wgs", [0, 4096])
+def test_grouped_heads(wgs, always):
+    fb.check(fb.fl_set_tuning("bwd_wg_target", wgs))
+    try:
+        simple.compare(inputs.causal_bf16(B=2, H=8, Hkv=2, S=391, D=128), "bf16", label="grouped")
+    finally:
+        fb.fl_set_tuning("bwd_wg_target", 0)
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("S", [33, 65, 257, 400])
+def test_differential(S, causal, always):
+    """What the kernel makes of the two streams: dK, dK2 and dV, which the second stream's pass adds to the first one's."""
+    w = inputs.differential_bf16(B=1, H=2, S=S, D=64, Dv=128, causal=causal, rmsnorm=False)
+    dout = inputs.dout_for(w)
+    db = runner.upload_backward_ex(w, dout, grad_dtype="f32")
+    db.fwd.run_checked()
+    db.run_checked()
+    torch.cuda.synchronize()
+    ref = bo.variant_backward(w, dout)
+    for name in ("dk", "dk2", "dv"):
+        diff = db.grads[name].cpu().numpy() - ref[name]
+        assert np.sqrt(np.sum(diff * diff) / np.sum(ref[name] ** 2)) <= simple.REL_L2, name
+
+
+def test_same_as_128_keys_and_reproducible():
+    """The sums of a key run over the rows in the same order: up to dS's last bit before its rounding, the results are the same."""
+    w = inputs.causal_bf16(B=64, H=8, S=255, D=128)          # taken by the host's rule
+    dout = inputs.dout_for(w)
+    db = runner.upload_backward(w, dout, grad_dtype="f32")
+    db.fwd.run_checked()
+    got = []
+    for keys in (0, 0, 2, 1):
+        fb.check(fb.fl_set_tuning("bwd_keys", keys))
+        try:
+            for t in (db.dk, db.dv):
+                t.fill_(float("nan"))
+            db.run_checked()
+            torch.cuda.synchronize()
+        finally:
+            fb.fl_set_tuning("bwd_keys", 0)
+        got.append([t.cpu().numpy() for t in (db.dk, db.dv)])
+    for n in range(2):
+        assert np.array_equal(got[0][n], got[1][n]) and np.array_equal(got[0][n], got[2][n])
+        diff = got[0][n] - got[3][n]
+        assert np.sqrt(np.sum(diff * diff) / np.sum(got[3][n] ** 2)) < 1e-3
+    assert not np.array_equal(got[0][0], got[3][0])          # two kernels, not one
