@@ -324,14 +324,24 @@ const fl::BwdEntry* find_bwd_entry(const fl_variant_desc* d, int D, int nbias = 
   return nullptr;
 }
 
-hipError_t run_bwd_dq(const fl::BwdEntry* be, const fl::BwdParams& p, int nblocks, hipStream_t stream) {
+// Do the longest tiles of all problems go out first, instead of one problem after the other?  Where a mask makes them unequal; at D = 128 many problems of few
+// tiles each are better off with their keys and values in an L2 (us, problem by problem / tile by tile: causal 20 x 16 heads x 600 forward 72 / 77, dQ 92 / 100, windows 64 x 8 x 300
+// dK / dV 93 / 100; the other way 30 x 8 x 500 dQ 62 / 55, 16 x 8 x 999 101 / 75), without a mask all are (D = 64, 64 x 8 x 300 dK / dV 52 / 57).
+bool longest_first(int64_t mask, int64_t D, int64_t Dv, int64_t problems, int64_t tiles) {
+  return mask != 0 && (std::max(D, Dv) < 128 || tiles >= 8 || problems * tiles <= 1024);
+}
+
+hipError_t run_bwd_dq(const fl::BwdEntry* be, const fl::BwdParams& p_in, int nblocks, hipStream_t stream) {
+  fl::BwdParams p = p_in;
+  const int problems = nblocks / std::max(p.n_qtiles, 1);
+  p.step_q = longest_first(be->key.mask, be->key.D, be->key.Dv, problems, p.n_qtiles) ? (p.order_q ? problems / 8 : problems) : 0;
   return be->jit != nullptr ? fl::jit_backward_launch(*be, 0, p, nblocks, stream) : be->dq(p, nblocks, stream);
 }
-// The dK/dV kernel with 64 keys per wave where the variant has one, the call suits it and its workgroups of 256 keys keep the 256 compute
-// units as busy as those of 128 keys do.  With the same share of them at work it is the faster one (us, partial sums added, 128 / 256 keys, D = 128: causal
-// 8 x 16 heads x 1024 153 / 119, 16 x 16 x 512 113 / 97, 2 x 32/8 x 2048 258 / 208, 64 x 8 x 256 80.5 / 79.5; without a mask 2 x 16 x 2048 160 / 133,
-// 1 x 16/2 x 4096 308 / 261, 64 x 8 x 256 79 / 73); with half of it the slower one (causal 4 x 16 x 512 27 / 47, 1 x 16/2 x 4096 186 / 246,
-// without a mask 1 x 8 x 4096 148 / 212, 64 x 16 x 128 67 / 95).
+// The dK/dV kernel with 64 keys per wave where the variant has one, the call suits it and its workgroups of 256 keys leave the 256 compute
+// units little more idle than those of 128 keys do.  Alike at work it is 1.2 - 1.35 times as fast (us, partial sums added, 128 / 256 keys, D = 128: causal
+// 8 x 16 heads x 1024 125 / 105, 16 x 16 x 512 92 / 84, 2 x 32/8 x 2048 202 / 170, 64 x 8 x 256 74 / 71; no mask 2 x 16 x 2048 152 / 119,
+// 1 x 16/2 x 4096 293 / 230, 64 x 8 x 256 81 / 67), with a third more idle about as fast (causal 5 x 16 x 1777 180 / 163, 3 x 16 x 2048 139 / 122, no mask 3 x 16 x 2048
+// 229 / 218), with half of them idle slower (causal 4 x 16 x 1024 63.0 / 69.6, 1 x 16/2 x 4096 166 / 203, 1 x 8 x 1024 39.5 / 59.7).
 const fl::WideEntry* wide_dkdv(const fl::BwdEntry* be, const fl::BwdParams& p) {
   if (be->jit != nullptr || g_tuning.bwd_keys == 1) return nullptr;
   const fl::WideEntry* w = fl::find_wide(be->key);
@@ -343,15 +353,17 @@ const fl::WideEntry* wide_dkdv(const fl::BwdEntry* be, const fl::BwdParams& p) {
   // one's rows on average, and the longest start first.
   auto keys = [&](int bm) {
     const int64_t wgs = problems * ((p.Sk + bm - 1) / bm);
-    return bm * (be->key.mask != 0 ? std::max<int64_t>(1, (wgs + 511) / 512) : (wgs + 255) / 256);
+    return bm * (be->key.mask != 0 ? std::max(1.0, wgs / 512.0) : (double)((wgs + 255) / 256));
   };
-  return 10 * keys(w->bm) <= 11 * keys(be->bm) ? w : nullptr;
+  return keys(w->bm) <= 1.34 * keys(be->bm) ? w : nullptr;
 }
 hipError_t run_bwd_dkdv(const fl::BwdEntry* be, const fl::WideEntry* wide, const fl::BwdParams& p, int64_t problems, hipStream_t stream) {
   fl::BwdParams pk = p;
   const int bm = wide != nullptr ? wide->bm : be->bm;
   pk.n_ktiles = (p.Sk + bm - 1) / bm;
   const int nblocks = (int)(problems * pk.n_ktiles);
+  const bool by_tile = wide != nullptr || longest_first(be->key.mask, be->key.D, be->key.Dv, problems, pk.n_ktiles);
+  pk.step_k = by_tile ? (int)(p.order_k ? problems / 8 : problems) : 0;
   if (wide != nullptr) return wide->dkdv(pk, nblocks, stream);
   return be->jit != nullptr ? fl::jit_backward_launch(*be, 1, pk, nblocks, stream) : be->dkdv(pk, nblocks, stream);
 }
@@ -1582,11 +1594,18 @@ static fl_status forward_call(const fl_tensor* q, const fl_tensor* k, const fl_t
     p.lds_bytes = (int)(kv + (staged ? stage : 0));
   }
   const int64_t nbh = B * G * H / ke->key.pack;    // (packed heads: a workgroup takes key.pack heads of one kv head)
-  // bf16 kernels under a causal / prefix mask without a window: the work of a q-tile grows with
-  // its index, so a workgroup takes a long and a short one -- when that still leaves every CU
-  // several workgroups
+  // bf16 kernels under a causal / prefix mask without a window: the work of a q-tile grows with its index.  Either the tiles of all heads go out
+  // longest first, or a workgroup takes a long and a short one, which makes all alike and keeps a head's tiles together, but leaves compute units idle
+  // where the pairs don't come out as whole rounds (two waves per SIMD).  Pairs where they fill 80 % of their rounds (a middle tile without a partner is
+  // half a pair); at D = 64 they cost short lists more than they give, unless the
+  // launch has three rounds of them.  Measured (us, pairs / single tiles): D = 128 16 x 16 x 1024 112 / 125, 16 x 8 x 999 53 / 56,
+  // 2 x 16 x 4096 146 / 152, 1 x 16 x 8192 270 / 281, with 55 and 75 % 5 x 16 x 1777 105 / 87, 32 x 16 x 700 176 / 156; D = 64 1 x 16 x 8192 168 / 177, 2 x 16 x 4096 92 / 95,
+  // 32 x 16 x 700 70 / 73, 8 x 16 x 1024 38 / 33, 4 x 16 x 2048 59 / 52, 8 x 16 x 2048 98 / 93, 5 x 16 x 1777 63 / 51, 16 x 8 x 999 37 / 32.
   const bool tri = (mask & (FL_MASK_CAUSAL | FL_MASK_PREFIX)) != 0 && (mask & (FL_MASK_WINDOW | FL_MASK_DOC)) == 0;
-  p.pair = g_tuning.pair >= 0 ? g_tuning.pair : (dtype == FL_BF16 && tri && nbh * ((p.n_qtiles + 1) / 2) >= 512);
+  const int64_t pairs = nbh * ((p.n_qtiles + 1) / 2), round = 256 * 8 / (ke->key.nwaves > 0 ? ke->key.nwaves : 4);
+  const bool filled = 10 * nbh * p.n_qtiles >= 16 * round * ((pairs + round - 1) / round);
+  p.pair = g_tuning.pair >= 0 ? g_tuning.pair
+                              : (dtype == FL_BF16 && tri && pairs >= 512 && (kv_lens != nullptr || (filled && (D >= 128 || p.n_qtiles >= 32 || pairs >= 3 * round))));
   if (dtype != FL_BF16) p.pair = 0;
   const int64_t nblocks = nbh * (p.pair ? (p.n_qtiles + 1) / 2 : p.n_qtiles);
   if (nblocks > 0x7fffffffLL || nbh * Sq > 0x7fffffff00LL) return fail(FL_ERR_SHAPE, "too many workgroups");
@@ -1599,6 +1618,12 @@ static fl_status forward_call(const fl_tensor* q, const fl_tensor* k, const fl_t
   // 1 x 32 / 8 x 32768 688 -> 676; window 256, 4 x 16 / 2 x 4096, D = 64, 50.1 -> 45.6; chunks of 8 x 512 rows, 32 / 8 heads, D = 128, 417 -> 407 and 371 -> 368;
   // unmasked and causal 16 / 2 heads, D = 64, within 0.6 %.
   const int64_t share = H / Hkv / ke->key.pack;
+  // Single tiles of unequal length: longest first over all heads (us, heads one after the other and tiles first: causal 2 x 16 x 2048, D = 64 43 / 33, D = 128 59 / 50;
+  // windows and documents 8 x 16 x 1500 64 / 56 and 98 / 83; documents 4 x 16 x 4096 123 / 116 and 184 / 171; windows, whose tiles are nearly alike,
+  // 32 x 8 x 500 30 / 24 and 45.7 / 44.9, 4 x 16 x 4096 67 / 65 and 112.5 / 115.3: not at D = 128).  Chunks of sequences go out by their keys.
+  const bool windows = D >= 128 && (mask & FL_MASK_WINDOW) && !(mask & FL_MASK_DOC);
+  const bool by_tile = dtype == FL_BF16 && !p.pair && kv_lens == nullptr && !windows && longest_first(mask, D, Dv, nbh, p.n_qtiles);
+  p.tile_step = by_tile ? (int)(order == 1 ? nbh / 8 : nbh) : 0;
   p.order_heads = order == 1 && dtype == FL_BF16 && (nbh / share) % 8 == 0 && g_tuning.order < 0 ? (int)share : 1;
 
   hipStream_t stream = (hipStream_t)stream_v;

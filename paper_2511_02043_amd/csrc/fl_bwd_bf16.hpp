@@ -53,6 +53,7 @@ struct BwdParams {
   int32_t dq_f32, dk_f32, dv_f32;  // 1: that output is float, 0: bf16
   int32_t n_qtiles, n_ktiles;      // workgroups per (b, g, h) of the dQ kernel / per (b, g, hkv) of the dK/dV kernel
   int32_t order_q, order_k;        // 1: XCD-aware workgroup order (whole (b, g, h) problems per XCD) in that kernel
+  int32_t step_q, step_k;          // > 0: the longest tiles of so many problems (all, or an XCD's) come first, 0: one problem after the other
   int32_t order_heads;             // dQ kernel, order_q 1: heads with the same keys that an XCD takes one after the other (FwdParams)
   int32_t hsplit;                  // dK/dV kernel: the query heads of a group are cut into hsplit subsets, one workgroup each
   float* part_dk;                  // hsplit > 1: fp32 partial sums [hsplit][B, G, Hkv, Sk, D | DV], summed by bwd_reduce_kv_kernel
@@ -75,6 +76,17 @@ struct BwdParams {
 // A call of fewer than 32 query rows keeps only the lanes of rows that exist: a block is [2][2 halves][rows][8].
 __host__ __device__ inline int ds_rows(int64_t Sq) { return Sq < 32 ? (int)Sq : 32; }
 __host__ __device__ inline int ds_block(int64_t Sq) { return 32 * ds_rows(Sq); }
+
+// Item `idx`, `tiles` of them for every problem: the tiles of one problem after the other, or tile by tile through all problems.
+// Under a mask the tiles of a problem are unequal, the first ones the longest.  With few of them per compute unit the last problem's long ones, begun when
+// the rest was half done, were the launch's end (us, problem by problem / tile by tile: dQ causal 16 x 8 heads x 999, D = 64 55 / 42, 8 x 16 x 2048 154 / 126, D = 128
+// 8 x 16 x 1024 98 / 80, 4 x 16 x 4096 552 / 487, windows and documents 8 x 16 x 2048, D = 64 82 / 73; dK / dV there 77 / 59, 217 / 185, 123 / 108).
+// step > 0: so many problems, tile by tile; 0: problem by problem.
+__device__ __forceinline__ void tile_of(int step, unsigned idx, unsigned tiles, int& problem, int& tile) {
+  const unsigned per = step > 0 ? step : tiles, a = idx / per, b = idx - a * per;
+  problem = (int)(step > 0 ? b : a);
+  tile = (int)(step > 0 ? a : b);
+}
 
 // chunk swizzle of a tile row (see the header comment): an XOR on the 16-byte chunk index that
 // depends on row % 16 only.
@@ -563,21 +575,23 @@ bwd_dq_kernel(const BwdParams p) {
   w.init(tid & 63);
   const int lane = w.lane;
 
-  // grid decode: longest q-tiles (under a causal mask) first
+  // grid decode: longest q-tiles (under a causal mask) first, of one head after the other or of all heads
   const int nq = p.n_qtiles;
   int qt, bh;
   if (p.order_q == 1) {
     // consecutive workgroup ids go round-robin to the 8 XCDs: give each XCD whole heads, so that a
     // head's K / V tiles stay in one L2 (the host checks that the head count is a multiple of 8), with the heads that read
-    // the same K / V side by side (causal training step, 2 x 32 / 8 heads x 8192, D = 128, in four runs: 4784 -> 4744 us, 4761 -> 4732,
-    // 4787 -> 4773, 4802 -> 4759; backward passes of 16 / 2 heads at D = 64 no different)
-    const int share = p.order_heads, idx = blockIdx.x >> 3, inner = idx % (nq * share);
-    bh = ((idx / (nq * share)) * 8 + (blockIdx.x & 7)) * share + inner % share;
-    qt = nq - 1 - inner / share;
+    // the same K / V side by side
+    const int share = p.order_heads;
+    int n;                                         // which of the XCD's heads
+    tile_of(p.step_q, blockIdx.x >> 3, nq * share, n, qt);
+    if (p.step_q == 0) n = n * share + qt % share;
+    bh = share == 1 ? n * 8 + (blockIdx.x & 7) : (n / share * 8 + (blockIdx.x & 7)) * share + n % share;
+    if (p.step_q == 0) qt /= share;
   } else {
-    qt = nq - 1 - (int)(blockIdx.x % nq);
-    bh = blockIdx.x / nq;
+    tile_of(p.step_q, blockIdx.x, nq, bh, qt);
   }
+  qt = nq - 1 - qt;
   const int h = bh % p.H, g = (bh / p.H) % p.G, b = bh / (p.H * p.G);
   const int hk = h / (p.H / p.Hkv);
   const FwdParams uctx = user_context(p);          // what a compiled variant's expressions read (unused otherwise)
@@ -914,15 +928,12 @@ bwd_dkdv_kernel(const BwdParams p) {
   const int lane = w.lane;
 
   // grid decode: key tiles in increasing order (under a causal mask the first ones see the most rows)
-  const int nk = p.n_ktiles;
   int kt, bh;
   if (p.order_k == 1) {                            // whole key/value heads per XCD: their Q / dO tiles stay in one L2
-    const int idx = blockIdx.x >> 3;
-    bh = (idx / nk) * 8 + (blockIdx.x & 7);
-    kt = idx % nk;
+    tile_of(p.step_k, blockIdx.x >> 3, p.n_ktiles, bh, kt);
+    bh = bh * 8 + (blockIdx.x & 7);
   } else {
-    kt = blockIdx.x % nk;
-    bh = blockIdx.x / nk;
+    tile_of(p.step_k, blockIdx.x, p.n_ktiles, bh, kt);
   }
   // bh counts (b, g, kv head, subset of the group's query heads)
   const int split = bh % p.hsplit, bhk = bh / p.hsplit;
@@ -1313,15 +1324,12 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
   w.init(tid & 63);
   const int lane = w.lane;
 
-  const int nk = p.n_ktiles;
   int kt, bh;
   if (p.order_k == 1) {                            // whole key/value heads per XCD: their Q / dO tiles stay in one L2
-    const int idx = blockIdx.x >> 3;
-    bh = (idx / nk) * 8 + (blockIdx.x & 7);
-    kt = idx % nk;
+    tile_of(p.step_k, blockIdx.x >> 3, p.n_ktiles, bh, kt);
+    bh = bh * 8 + (blockIdx.x & 7);
   } else {
-    kt = blockIdx.x % nk;
-    bh = blockIdx.x / nk;
+    tile_of(p.step_k, blockIdx.x, p.n_ktiles, bh, kt);
   }
   // bh counts (b, g, kv head, subset of the group's query heads)
   const int split = bh % p.hsplit, bhk = bh / p.hsplit;

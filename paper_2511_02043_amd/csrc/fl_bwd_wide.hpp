@@ -54,16 +54,15 @@ bwd_dkdv_wide_kernel(const BwdParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, half = lane >> 5, col = lane & 31;
 
-  const int nk = p.n_ktiles;
+  // tile by tile through all problems, the longest (under a causal mask) first: with one workgroup per compute unit the launch is a few rounds
   int kt, bh;
-  const int nbh = gridDim.x / nk;
   if (p.order_k == 1) {                            // whole key/value heads per XCD: their Q / dO tiles stay in one L2
     const int idx = blockIdx.x >> 3;
-    bh = (idx % (nbh >> 3)) * 8 + (blockIdx.x & 7);
-    kt = idx / (nbh >> 3);
+    kt = idx / p.step_k;
+    bh = (idx % p.step_k) * 8 + (blockIdx.x & 7);
   } else {
-    bh = blockIdx.x % nbh;
-    kt = blockIdx.x / nbh;
+    kt = blockIdx.x / p.step_k;
+    bh = blockIdx.x % p.step_k;
   }
   const int split = bh % p.hsplit, bhk = bh / p.hsplit;
   const int hk = bhk % p.Hkv, g = (bhk / p.Hkv) % p.G, b = bhk / (p.Hkv * p.G);

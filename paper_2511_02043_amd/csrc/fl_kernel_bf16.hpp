@@ -876,9 +876,19 @@ fwd_bf16_kernel(const FwdParams call) {
     // that read the same K/V one after the other (grouped-query heads; 1 where that leaves XCDs without work).
     constexpr bool user = C::MOD == kModCustom || (C::MASK & kMaskCustom) != 0;   // (the host sets 1: no divisions by it)
     const int xcd = bid & 7, share = user ? 1 : call.order_heads;
-    const int idx = bid >> 3, inner = idx % (npairs * share);
-    bh = ((idx / (npairs * share)) * 8 + xcd) * share + inner % share;
-    pi = inner / share;
+    const int idx = bid >> 3;
+    if (call.tile_step > 0) {
+      const int n = idx % call.tile_step;
+      pi = idx / call.tile_step;
+      bh = share == 1 ? n * 8 + xcd : (n / share * 8 + xcd) * share + n % share;
+    } else {
+      const int inner = idx % (npairs * share);
+      bh = ((idx / (npairs * share)) * 8 + xcd) * share + inner % share;
+      pi = inner / share;
+    }
+  } else if (call.tile_step > 0) {
+    bh = bid % call.tile_step;
+    pi = bid / call.tile_step;
   } else {
     pi = bid % npairs;
     bh = bid / npairs;

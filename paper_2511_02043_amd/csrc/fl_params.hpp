@@ -82,6 +82,7 @@ struct FwdParams {
   int32_t mod, mask, n_bias, epi, diff;   // runtime copy of the descriptor (fp32 kernel reads these)
   int32_t n_qtiles;      // ceil(Sq / rows per workgroup)
   int32_t order;         // workgroup ordering scheme
+  int32_t tile_step;     // > 0: q-tiles go out longest first over all problems, or an XCD's (so many problems); 0: one problem after the other
   int32_t order_heads;   // order 1: problems with the same keys that an XCD takes one after the other (1 or the heads per kv head)
   int32_t lds_bytes;     // bf16 kernels: dynamic LDS size of this launch (K/V rings, then bias staging)
   int32_t bias_lds_base; // byte offset of the per-wave bias staging buffers in LDS
