@@ -186,6 +186,10 @@ template <class C>
 struct Wave {
   static constexpr int D = C::D, DV = C::DV, NB = C::NB, KK = C::KK, DVB = C::DVB, NS = C::NS, RB = C::RB;
   static constexpr bool kPlain = (C::MOD == kModNone && C::NBIAS == 0);
+  // Scores in the units that the FMA of the exponent's argument takes: raw ones of the plain variants, an expression's results.  The others
+  // are in log2 units.
+  static constexpr bool kScaled = kPlain || (C::MOD == kModCustom && C::NBIAS == 0);
+  __device__ __forceinline__ float score_scale() const { return kPlain ? c_scale : kLog2e; }
   // The exponentials of a fully visible tile are taken against the reference that the row has (its maximum over the first tiles, or
   // a little less), without the row max of the tile; its row sum, which there is anyway, tells afterwards whether the reference has to
   // follow (settle_sums).  That is half a vector instruction less per score and no max between the two contractions: causal,
@@ -344,9 +348,11 @@ struct Wave {
   }
 
   // ---- variant transform (Eq. 4 score_mod, additive biases) of one score register.
-  // Leaves the score in the domain exp_only() expects: raw for the plain variants (the scale is
-  // folded into the exponent's FMA), log2-scaled otherwise (less the cap: kShifted).  j0 is the tile's first key.
-  __device__ __forceinline__ float transform_one(float x, int j0, int rb, int nb, int r, const BiasRegs& br) const {
+  // Leaves the score in the domain exp_only() expects: raw for the plain variants and as the expression gives it (the scale is
+  // folded into the exponent's FMA: kScaled), log2-scaled otherwise (less the cap: kShifted).  j0 is the tile's first key.
+  // INNER: the tile ends at or before the last key.
+  template <bool INNER = false>
+  __device__ __forceinline__ float transform_one(float x, int j0, int rb, int nb, int r, const BiasRegs& br, int row = 0) const {
     if constexpr (kPlain) {
       return x;
     } else {
@@ -367,7 +373,7 @@ struct Wave {
         // indexes a captured array by i or j must not be handed an index outside the call's sizes)
         // (FL_USER_CLAMP 0: the expressions capture no array, so any index is as good as another and the minimum per
         // score is saved)
-        x = fl_user_score_mod(x * p.scale, b, g, h, ic[rb] + p.q_off, FL_USER_CLAMP && j >= p.Sk ? p.Sk - 1 : j, p) * kLog2e;
+        x = fl_user_score_mod(x * p.scale, b, g, h, (INNER ? row : ic[rb] + p.q_off), FL_USER_CLAMP && !INNER && j >= p.Sk ? p.Sk - 1 : j, p) * (kScaled ? 1.f : kLog2e);
       } else {
         x *= c_scale;
       }
@@ -381,14 +387,18 @@ struct Wave {
       return x;
     }
   }
+  template <bool INNER = false>
   __device__ __forceinline__ void transform(Scores& sc, int j0, const BiasRegs& br) const {
     if constexpr (!kPlain) {
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
+      for (int rb = 0; rb < RB; ++rb) {
+        int row = ic[rb] + p.q_off;
+        if constexpr (INNER) asm volatile("" : "+v"(row));   // (row - key of every score would be kept in registers over the loop)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) sc[rb][nb][r] = transform_one(sc[rb][nb][r], j0, rb, nb, r, br);
+          for (int r = 0; r < 16; ++r) sc[rb][nb][r] = transform_one<INNER>(sc[rb][nb][r], j0, rb, nb, r, br, row);
+      }
     }
   }
 
@@ -546,7 +556,7 @@ struct Wave {
 #pragma unroll
         for (int r = 0; r < 16; ++r) m = fmaxf(m, sc[rb][nb][r]);
       m = half_swap_max(m);
-      if constexpr (kPlain) m *= c_scale;          // scale > 0 (checked on the host)
+      if constexpr (kScaled) m *= score_scale();   // > 0 (checked on the host)
       mx[rb] = m;
     }
   }
@@ -588,9 +598,9 @@ struct Wave {
 
   // ---- one probability pair: p = exp2(s - m); then running row sum and bf16 pair (and remainder)
   __device__ __forceinline__ void exp_only(float s0, float s1, float m_safe, float& p0, float& p1) const {
-    if constexpr (kPlain) {
-      p0 = fast_exp2(fmaf(s0, c_scale, -m_safe));
-      p1 = fast_exp2(fmaf(s1, c_scale, -m_safe));
+    if constexpr (kScaled) {
+      p0 = fast_exp2(fmaf(s0, score_scale(), -m_safe));
+      p1 = fast_exp2(fmaf(s1, score_scale(), -m_safe));
     } else {
       p0 = fast_exp2(s0 - m_safe);
       p1 = fast_exp2(s1 - m_safe);
@@ -675,6 +685,8 @@ struct Wave {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       ps.m_safe[rb] = m_run[rb] == -INFINITY ? 0.f : m_run[rb];
+      // (an expression's score past the range in log2 units makes its row NaN, as an infinite one does)
+      if constexpr (C::MOD == kModCustom) ps.m_safe[rb] = fmaf(ps.m_safe[rb], 0.f, ps.m_safe[rb]);
       ps.psum[rb] = 0.f;
       ps.mx[rb] = -INFINITY;
     }
@@ -780,9 +792,10 @@ struct Wave {
 
   // `advance` (uniform) is false when the next tile still needs its mask: then the running-max
   // update is left to the start of the next step.  The O rescale is a rare branch at the end.
+  // `none` (uniform, kLate): nothing of the next tile is visible to the wave, or there is no such tile; its scores are left as they are.
   template <int VOFF>
   __device__ __forceinline__ void phase_b(Pipe& ps, const Scores& cur, Scores& nxt, int j1, const BiasRegs& br,
-                                          bool advance) {
+                                          bool advance, bool none) {
     constexpr int NF = NB * 2 * DVB, HALF = NF / 2;
     constexpr int SE = HALF * RB, SM = NF * RB - SE, PA = NPAIR / 2;
     static_assert(NF % 2 == 0, "chunking");
@@ -812,13 +825,17 @@ struct Wave {
       }
     });
     if constexpr (kLate) {
-      transform(nxt, j1, br);
+      // uniform branches: the minimum with the last key per score only where the tile reaches past it
+      if (!none) {
+        if (j1 + C::BN <= p.Sk) transform<true>(nxt, j1, br);
+        else transform(nxt, j1, br);
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+          for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-          for (int r = 0; r < 16; r += 2) ps.mx[rb] = fmaxf(fmaxf(ps.mx[rb], nxt[rb][nb][r]), nxt[rb][nb][r + 1]);
+            for (int r = 0; r < 16; r += 2) ps.mx[rb] = fmaxf(fmaxf(ps.mx[rb], nxt[rb][nb][r]), nxt[rb][nb][r + 1]);
+      }
     }
     if constexpr (kTrust) {
       settle_sums(ps, nxt, advance);
@@ -831,7 +848,7 @@ struct Wave {
     for (int rb = 0; rb < RB; ++rb) {
       l_run[rb] += ps.psum[rb];
       float mxs = half_swap_max(ps.mx[rb]);
-      if constexpr (kPlain) mxs *= c_scale;        // scale > 0 (checked on the host)
+      if constexpr (kScaled) mxs *= score_scale(); // > 0 (checked on the host)
       const float m_old = m_run[rb];
       float m_new = (mxs - m_old > kLazyMaxLog2) ? mxs : m_old;   // false for NaN (-inf - -inf)
       m_new = advance ? m_new : m_old;
@@ -1229,6 +1246,12 @@ fwd_bf16_kernel(const FwdParams call) {
     if constexpr ((MASK & kMaskDoc) != 0) return wave_class(t, ks) == kTileFull;
     else return t >= tf_lo && t < tf_hi;
   };
+  // is it known that nothing of tile t is visible to the wave?  (document masks: settled where the tile is masked)
+  auto wave_none = [&](int t, int2 ks) __attribute__((always_inline)) -> bool {
+    if (W::kLate && t >= t_hi) return true;
+    if constexpr (kMapped) return ((my_classes(ks) >> (8 * (wave % C::NROWG))) & 0xffull) == 0;
+    return kWaveSkip && (t < tv_lo || t >= tv_hi);
+  };
 
   // ---- direct global -> LDS loads of one K or V tile (a2): every wave instruction moves
   // 64 x 16 B into 1 KiB of consecutive LDS; the swizzle is applied by choosing which global
@@ -1495,7 +1518,7 @@ fwd_bf16_kernel(const FwdParams call) {
         const int tn = t1;
         const bool fulln = wave_full(t1, tks[1]);
         if (!full0) {                              // fully visible tiles were settled in phase B
-          bool none = kWaveSkip && (t0 < tv_lo || t0 >= tv_hi), docs = true, pos = true;
+          bool none = wave_none(t0, tks[0]), docs = true, pos = true;
           if constexpr (C::DOC && (MASK & kMaskCustom) == 0) {
             none = wave_class(t0, tks[0]) == kTileSkip;
             docs = !(qs_wave.x == qs_wave.y && tks[0].x == tks[0].y && qs_wave.x == tks[0].x);
@@ -1555,7 +1578,7 @@ fwd_bf16_kernel(const FwdParams call) {
                   issue_v(u, C::PAGED ? vbp[u] : vb, C::V_RING + slot_vl * C::V_BYTES);
               });
             });
-        w.template phase_b<slot_vc * C::V_BYTES>(ps, cur, nxt, tn * BN, br, fulln);
+        w.template phase_b<slot_vc * C::V_BYTES>(ps, cur, nxt, tn * BN, br, fulln, W::kLate && wave_none(tn, tks[1]));
         if constexpr (N % SPB == SPB - 1) wait_loads_and_sync();
         if constexpr (C::PAGED) {                  // this step's K tile is the next step's V tile
 #pragma unroll
@@ -1728,7 +1751,6 @@ __global__ void __launch_bounds__(256) block_map_kernel(const FwdParams p, unsig
   // -> key 32 nb + 8 (r / 4) + r % 4 + 4 (lane / 32) of the tile; bit 16 nb + r of the lane's word = hidden
   const int i = qb * 32 + (lane & 31);
   const int jl = kt * BN + 4 * (lane >> 5);
-  bool some_visible = false, some_hidden = false;
   uint32_t word = 0;
   // The expression is only ever handed (row, key) pairs that the base mask leaves visible -- it may index an array by i - j
   // under a causal one.  So that its loads need no branch of their own, and all 16 or 32 of a lane are in flight together, a
@@ -1736,10 +1758,19 @@ __global__ void __launch_bounds__(256) block_map_kernel(const FwdParams p, unsig
   // (12 documents in 4 x 4096 rows: 31.8 us with a branch per score, 22.2 us this way.)
   constexpr uint32_t POS = MASK & (kMaskCausal | kMaskWindow | kMaskPrefix);
   const int q_lo = qb * 32 + p.q_off;
-  const bool hidden_block = qb * 32 >= p.Sq || classify_block(POS, q_lo, q_lo + 31, kt * BN, kt * BN + BN - 1, p.Sk, p.window, p.prefix,
-                                                              make_int2(0, 0), make_int2(0, 0)) == kSkip;
+  const int cls = qb * 32 >= p.Sq ? kSkip : classify_block(POS, q_lo, q_lo + 31, kt * BN, kt * BN + BN - 1, p.Sk, p.window, p.prefix,
+                                                           make_int2(0, 0), make_int2(0, 0));
   const int jv = min(i + p.q_off, p.Sk - 1);
-  if (!hidden_block && i < p.Sq && !is_masked(POS, i + p.q_off, jv, p.window, p.prefix, 0, 0)) {
+  constexpr uint32_t kAll = BN == 64 ? ~0u : (1u << (BN / 2)) - 1;   // the bits of a lane's BN / 2 scores
+  if (cls == kFull && (qb + 1) * 32 <= p.Sq) {     // uniform
+    // Every score of the tile is visible under the base mask: the expression as it is, on consecutive keys, whose loads from
+    // an array that it indexes by the key the compiler makes four at a time.
+#pragma unroll
+    for (int nb = 0; nb < BN / 32; ++nb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        word |= fl_user_mask(b, g, h, i + p.q_off, jl + (32 * nb + 8 * (r >> 2) + (r & 3)), p) ? (1u << (16 * nb + r)) : 0u;
+  } else if (cls != kSkip && i < p.Sq && !is_masked(POS, i + p.q_off, jv, p.window, p.prefix, 0, 0)) {
 #pragma unroll
     for (int nb = 0; nb < BN / 32; ++nb)
 #pragma unroll
@@ -1747,19 +1778,16 @@ __global__ void __launch_bounds__(256) block_map_kernel(const FwdParams p, unsig
         const int j = jl + 32 * nb + 8 * (r >> 2) + (r & 3);
         bool hide = (j >= p.Sk) | is_masked(POS, i + p.q_off, j, p.window, p.prefix, 0, 0);
         const bool user = fl_user_mask(b, g, h, i + p.q_off, hide ? jv : j, p);
-        hide = hide | user;
-        some_visible = some_visible || !hide;
-        some_hidden = some_hidden || hide;
-        word |= hide ? (1u << (16 * nb + r)) : 0u;
+        word |= (hide || user) ? (1u << (16 * nb + r)) : 0u;
       }
   } else {
     word = ~0u;
-    some_hidden = i < p.Sq;
   }
-  const bool vis = __builtin_amdgcn_ballot_w64(some_visible) != 0, hid = __builtin_amdgcn_ballot_w64(some_hidden) != 0;
+  // (rows past Sq have every bit set and count as neither)
+  const bool vis = __builtin_amdgcn_ballot_w64((word & kAll) != kAll) != 0, hid = __builtin_amdgcn_ballot_w64(i < p.Sq && word != 0) != 0;
   const int64_t block = ((int64_t)prob * p.map_nkt + kt) * p.map_nqb8 + qb;
   if (lane == 0) map[block] = (unsigned char)(vis ? (hid ? 1 : 2) : 0);
-  if (bits != nullptr) bits[block * 64 + lane] = word;
+  if (bits != nullptr && vis && hid) bits[block * 64 + lane] = word;   // (read for partly visible tiles only)
 }
 
 }  // namespace fl

@@ -61,6 +61,19 @@ bool mentions(const char* e, const char* name) {
   return false;
 }
 
+// Does every mention of `name` in the expression index it at once, `name[`?
+bool only_indexed(const char* e, const char* name) {
+  const size_t n = strlen(name);
+  auto word = [](char c) { return (c >= 'a' && c <= 'z') || (c >= 'A' && c <= 'Z') || (c >= '0' && c <= '9') || c == '_'; };
+  for (const char* c = e; *c; ++c) {
+    if (strncmp(c, name, n) != 0 || (c != e && word(c[-1])) || word(c[n])) continue;
+    const char* after = c + n;
+    while (*after == ' ') ++after;
+    if (*after != '[') return false;
+  }
+  return true;
+}
+
 // Is the time of a score_mod that of its loads from captured arrays?  It reads at least one, and every function it calls is a
 // few instructions without a branch; anything else keeps its arithmetic between the matrix instructions (Wave::kLate has
 // the times of both).
@@ -326,27 +339,45 @@ fl_status fl_compile_variant_aux(const char* score_mod_expr, const char* mask_ex
 
 // The three device functions that wrap a variant's expressions (what an expression sees besides its arguments: the
 // call's sizes and the captured arrays aux0 .. aux3; bf16 arrays read as float through a one-field wrapper).
+// An array that an expression only indexes comes as fl_array: where the compiler can tell that the index of a bf16 element is not
+// negative, twice the index fits 32 bits, and the load takes that beside the array's address in scalar registers, instead of a 64-bit sum
+// in a pair of vector registers per score (the arguments are never negative, which the compiler is told).  A learned bias by head and
+// clipped distance: 600 -> 402 instructions per tile of 32 x 64 scores, together with the clamp and the factor log2(e) per score that
+// the transform of a whole tile does without.
 static std::string hook_source(const fl_custom_variant* v, bool with_grad) {
-  std::string scope = "  const int B = fl_p.B, G = fl_p.G, H = fl_p.H, Sq = fl_p.Sq, Sk = fl_p.Sk; (void)B; (void)G; (void)H; (void)Sq; (void)Sk;\n";
-  for (int n = 0; n < 4; ++n) {
-    if (v->aux_dtype[n] == 0) continue;
-    const char* ty = v->aux_dtype[n] == FL_I32 ? "int" : (v->aux_dtype[n] == FL_F32 ? "float" : "fl_bf16_elem");
-    char line[160];
-    snprintf(line, sizeof(line), "  const %s* aux%d = (const %s*)fl_p.user_aux[%d]; (void)aux%d;\n", ty, n, ty, n, n);
-    scope += line;
-  }
-  std::string src = "struct fl_bf16_elem { unsigned short u; __device__ operator float() const { return __uint_as_float((unsigned)u << 16); } };\n";
-  src += "__device__ float fl_user_score_mod(float s, int b, int g, int h, int i, int j, const fl::FwdParams& fl_p) {\n" + scope + "  return (";
-  src += v->has_mod ? v->mod_expr : std::string("s");
-  src += "); }\n";
+  auto scope = [&](const std::string& expr) {
+    std::string text = "  __builtin_assume(b >= 0); __builtin_assume(g >= 0); __builtin_assume(h >= 0); __builtin_assume(i >= 0); __builtin_assume(j >= 0);\n"
+                       "  const int B = fl_p.B, G = fl_p.G, H = fl_p.H, Sq = fl_p.Sq, Sk = fl_p.Sk; (void)B; (void)G; (void)H; (void)Sq; (void)Sk;\n";
+    for (int n = 0; n < 4; ++n) {
+      if (v->aux_dtype[n] == 0) continue;
+      const char* ty = v->aux_dtype[n] == FL_I32 ? "int" : (v->aux_dtype[n] == FL_F32 ? "float" : "fl_bf16_elem");
+      const std::string name = "aux" + std::to_string(n);
+      char line[200];
+      if (only_indexed(expr.c_str(), name.c_str()))
+        snprintf(line, sizeof(line), "  const fl_array<%s> aux%d = {(const %s*)fl_p.user_aux[%d]}; (void)aux%d;\n", ty, n, ty, n, n);
+      else
+        snprintf(line, sizeof(line), "  const %s* aux%d = (const %s*)fl_p.user_aux[%d]; (void)aux%d;\n", ty, n, ty, n, n);
+      text += line;
+    }
+    return text + "  return (" + expr + "); }\n";
+  };
+  std::string src = "struct fl_bf16_elem { unsigned short u; __device__ operator float() const { return __uint_as_float((unsigned)u << 16); } };\n"
+                    "template <class T> struct fl_array {\n"
+                    "  const T* p;\n"
+                    "  template <class I> __device__ __forceinline__ const T& operator[](I n) const { return p[n]; }\n"
+                    "  __device__ __forceinline__ const T& operator[](int n) const {\n"
+                    "    if (sizeof(T) == 2 && __builtin_constant_p(n >= 0) && n >= 0) return *(const T*)((const char*)p + 2u * (unsigned)n);\n"
+                    "    return p[n];\n"
+                    "  }\n"
+                    "};\n";
+  src += "__device__ float fl_user_score_mod(float s, int b, int g, int h, int i, int j, const fl::FwdParams& fl_p) {\n";
+  src += scope(v->has_mod ? v->mod_expr : std::string("s"));
   if (with_grad) {
-    src += "__device__ float fl_user_score_mod_grad(float s, int b, int g, int h, int i, int j, const fl::FwdParams& fl_p) {\n" + scope + "  return (";
-    src += v->grad_expr.empty() ? std::string("1.0f") : v->grad_expr;
-    src += "); }\n";
+    src += "__device__ float fl_user_score_mod_grad(float s, int b, int g, int h, int i, int j, const fl::FwdParams& fl_p) {\n";
+    src += scope(v->grad_expr.empty() ? std::string("1.0f") : v->grad_expr);
   }
-  src += "__device__ bool fl_user_mask(int b, int g, int h, int i, int j, const fl::FwdParams& fl_p) {\n" + scope + "  return (";
-  src += v->has_mask_expr ? v->mask_expr : std::string("false");
-  src += "); }\n";
+  src += "__device__ bool fl_user_mask(int b, int g, int h, int i, int j, const fl::FwdParams& fl_p) {\n";
+  src += scope(v->has_mask_expr ? v->mask_expr : std::string("false"));
   return src;
 }
 
@@ -572,12 +603,15 @@ static fl_status custom_forward(fl_custom_variant* v, const fl_tensor* q, const 
   const int64_t nbh = B * G * H;
   p.order = nbh % 8 == 0 ? 1 : 0;
   p.order_heads = 1;
-  // under a causal / prefix base mask without a window a workgroup takes a long and a short q-tile
+  // under a causal / prefix base mask without a window a workgroup takes a long and a short q-tile; under a mask expression with a map, which
+  // may leave anything of them, the q-tiles of all problems go out by themselves, the last ones first
   const bool tri = (v->mask & (FL_MASK_CAUSAL | FL_MASK_PREFIX)) != 0 && (v->mask & FL_MASK_WINDOW) == 0;
-  p.pair = tri && nbh * ((p.n_qtiles + 1) / 2) >= 512;
+  const bool mapped = skip && v->has_mask_expr;
+  p.pair = tri && !mapped && nbh * ((p.n_qtiles + 1) / 2) >= 512;
+  p.tile_step = mapped ? (int)(p.order == 1 ? nbh / 8 : nbh) : 0;
   const int64_t nblocks = nbh * (p.pair ? (p.n_qtiles + 1) / 2 : p.n_qtiles);
   if (nblocks > 0x7fffffffLL) return fl::host::fail(FL_ERR_SHAPE, "too many workgroups");
-  if (skip && v->has_mask_expr) {
+  if (mapped) {
     // the pre-pass: the mask once per score, one class byte per (32-row block, 64-key tile); the kernel then passes over
     // tiles with nothing visible and skips the per-score mask on tiles where everything is
     const MapLayout ML = map_layout(v, B, G, H, Sq, Sk);

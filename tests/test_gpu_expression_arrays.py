@@ -1,0 +1,54 @@
+"""GPU tests: captured arrays of run-time compiled variants, however an expression reads them; tiles at the end of the keys and tiles of
+which a wave sees nothing, whose transform the kernel leaves out."""
+import numpy as np
+import pytest
+
+from oracle import attention_oracle as ao
+from paper_2511_02043_amd import binding as fb
+from paper_2511_02043_amd import inputs, runner
+
+pytestmark = pytest.mark.gpu
+
+FORMS = {
+    "indexed": "aux2[h * 64 + min(abs(i - j), 63)]",
+    "pointer": "*(aux2 + h * 64 + min(abs(i - j), 63))",
+    "long_index": "aux2[(long)h * 64 + min(abs(i - j), 63)]",
+    "unsigned_index": "aux2[(unsigned)(h * 64 + min(abs(i - j), 63))]",
+    "negative_index": "aux3[h * 64 + min(abs(i - j), 63) - 100]",
+}
+
+
+@pytest.mark.parametrize("Sq,Sk", [(333, 333), (100, 64), (64, 65), (500, 320)])
+def test_array_forms(Sq, Sk):
+    """The same bias read in every form gives the same bits, with and without the pre-pass over the tiles, within the tolerance of the oracle."""
+    import torch
+    dev = "cuda:0"
+    B, H, D = 2, 4, 64
+    w = inputs.causal_bf16(B=B, H=H, Hkv=2, S=Sq, Sk=Sk, D=D, causal=False, salt=21)
+    ids_q, ids_k = (inputs.doc_ids(B, n, seed=78, lo=20, hi=90) for n in (Sq, Sk))
+    ids_k[:, 0] = 0                                                            # no row of a document without keys
+    ids_q = np.minimum(ids_q, ids_k.max(axis=1)[:, None])
+    table = inputs.normal((H, 64), inputs.tensor_seed(9, 8), "bf16")
+    flat = torch.from_numpy(table.astype(np.float32)).to(dev, torch.bfloat16).reshape(-1)
+    arrays = [torch.from_numpy(ids_q).to(dev), torch.from_numpy(ids_k).to(dev), flat, flat[100:]]
+    dw = runner.upload(w, out_dtype="f32")
+    ref, ref_lse = ao.attention_custom(w.q, w.k, w.v, scale=w.scale,
+                                       score_mod=lambda s, b, g, h, i, j: s + table.astype(np.float64)[h][np.minimum(np.abs(i - j), 63)],
+                                       mask=lambda b, g, h, i, j: ids_q[b][:, None] != ids_k[b][None, :])
+    first = None
+    for name, form in FORMS.items():
+        var = fb.CustomVariant(f"s + {form}", "aux0[b * Sq + i] != aux1[b * Sk + j]", D, aux=arrays)
+        need = var.skip_workspace_size(dw.tq, dw.tk)
+        for ws in (None, torch.empty(need, dtype=torch.uint8, device=dev)):
+            dw.out.fill_(float("nan"))
+            dw.lse.fill_(float("nan"))
+            fb.check(var.forward(dw.tq, dw.tk, dw.tv, float(w.scale), dw.tout, dw.tlse, workspace=ws))
+            torch.cuda.synchronize()
+            got = dw.out.cpu().numpy().copy(), dw.lse.cpu().numpy()[..., 0].copy()
+            if first is None:
+                first = got
+                dead = np.isneginf(ref_lse)
+                assert np.array_equal(np.isneginf(got[1]), dead)
+                assert float(np.max(np.abs(got[0] - ref))) <= 1e-2 and float(np.max(np.abs(got[1][~dead] - ref_lse[~dead]))) <= 1e-3
+            assert np.array_equal(got[0], first[0]) and np.array_equal(got[1], first[1]), (name, ws is None)
+        var.release()
