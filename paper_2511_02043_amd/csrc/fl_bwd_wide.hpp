@@ -32,12 +32,14 @@ struct WideCfg {
 constexpr uint32_t kHiddenBits = 0xff7ffffdu;     // -3.4e38
 
 // acc += a b on accumulation registers.  The accumulators live there for the whole kernel and only these instructions touch them;
-// left to the compiler, every MFMA result of a kernel with more than 256 registers goes there and is copied back.
-// FRESH: the vector ALU may have written b just before (two wait states).
+// left to the compiler, every MFMA result of a kernel with more than 256 registers goes there and is copied back (or, told to leave results in
+// vector registers, it moves the accumulators through them: 178 registers in scratch).  The compiler keeps no wait states for an instruction that it cannot see, so
+// they are part of the statement: two where the vector ALU may have written b just before (FRESH), else one.  Nothing else can be needed: a has
+// come from LDS behind a wait, the results go to registers that no other instruction reads or writes before the loop has ended, and an
+// accumulator's next product comes several MFMAs later, which the hardware would hold back anyway.
 template <bool FRESH>
 __device__ __forceinline__ void mfma_acc(f32x16& acc, bf16x8 a, bf16x8 b) {
-  if constexpr (FRESH) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+  asm volatile("s_nop %3\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b), "n"(FRESH ? 1 : 0));
 }
 
 template <class C>
