@@ -5,6 +5,8 @@
 // The same in Python (ctypes structures filled field by field) cost 20 us of a 31 us causal call on [1, 8, 128, 64] and of
 // a 31 us decode step of one sequence, whose kernels take 8 and 10 us; a training step with a bias and a gate on
 // [1, 16, 4, 64, 32] took 252 us that way and takes 117 this way, most of it in the autograd engine.
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/extension.h>
 
 #include <optional>
@@ -101,11 +103,7 @@ std::tuple<int, Tensor, Tensor> attention_fwd(const Tensor& q, const Tensor& k, 
   const size_t need = fl_attn_fwd_workspace_size(&tq, &tk, &d);
   if (need != 0) ws = bytes(need, q);
   const fl_aux a = aux_of(slopes, q_ids, kv_ids, ws);
-  int status;
-  {
-    py::gil_scoped_release nogil;
-    status = fl_attn_fwd(&tq, &tk, &tv, &d, &a, &tout, &tlse, (void*)stream);
-  }
+  const int status = fl_attn_fwd(&tq, &tk, &tv, &d, &a, &tout, &tlse, (void*)stream);
   return {status, out, lse};
 }
 
@@ -121,11 +119,7 @@ std::tuple<int, Tensor, Tensor, Tensor> attention_bwd(const Tensor& q, const Ten
   fl_tensor tdq = desc(dq), tdk = desc(dk), tdv = desc(dv);
   const Tensor ws = bytes(std::max<size_t>(fl_attn_bwd_workspace_size(&tq, &tk, &d), 16), q);
   const fl_aux a = aux_of(slopes, q_ids, kv_ids, ws);
-  int status;
-  {
-    py::gil_scoped_release nogil;
-    status = fl_attn_bwd(&tq, &tk, &tv, &tout, &tdo, &tlse, &d, &a, &tdq, &tdk, &tdv, (void*)stream);
-  }
+  const int status = fl_attn_bwd(&tq, &tk, &tv, &tout, &tdo, &tlse, &d, &a, &tdq, &tdk, &tdv, (void*)stream);
   return {status, dq, dk, dv};
 }
 
@@ -171,11 +165,7 @@ std::tuple<int, Tensor, Tensor> variant_fwd(const Tensor& q, const Tensor& k, co
   const size_t need = fl_attn_fwd_workspace_size(&tq, &tk, &d);
   if (need != 0) ws = bytes(need, q);
   const fl_aux a = x.fill(aux_of(slopes, q_ids, kv_ids, ws));
-  int status;
-  {
-    py::gil_scoped_release nogil;
-    status = fl_attn_fwd(&tq, &tk, &tv, &d, &a, &tout, &tlse, (void*)stream);
-  }
+  const int status = fl_attn_fwd(&tq, &tk, &tv, &d, &a, &tout, &tlse, (void*)stream);
   return {status, out, lse};
 }
 
@@ -210,11 +200,7 @@ std::tuple<int, std::vector<OptTensor>> variant_bwd(const Tensor& q, const Tenso
   fl_tensor tdq = desc(dq), tdk = desc(dk), tdv = desc(dv);
   const Tensor ws = bytes(std::max<size_t>(fl_attn_bwd_ex_workspace_size(&tq, &tk, &tv, &d), 16), q);
   const fl_aux a = x.fill(aux_of(slopes, q_ids, kv_ids, ws));
-  int status;
-  {
-    py::gil_scoped_release nogil;
-    status = fl_attn_bwd_ex(&tq, &tk, &tv, &tout, &tdo, &tlse, &d, &a, &tdq, &tdk, &tdv, &e, (void*)stream);
-  }
+  const int status = fl_attn_bwd_ex(&tq, &tk, &tv, &tout, &tdo, &tlse, &d, &a, &tdq, &tdk, &tdv, &e, (void*)stream);
   if (status == 0) {
     if (dbias0.has_value()) dbias0 = dbias0->to(bias0->scalar_type());
     if (dbias1.has_value()) dbias1 = dbias1->to(bias1->scalar_type());
@@ -253,21 +239,129 @@ std::tuple<int, int64_t, Tensor, OptTensor> paged(bool decode, const Tensor& q, 
   const Tensor ws = workspace.has_value() ? *workspace : bytes(need, q);
   const fl_variant_desc d = variant(scale, mod, softcap, mask, window, 0, 0);
   const fl_aux a = aux_of(slopes, std::nullopt, std::nullopt, ws);
-  int status;
-  {
-    py::gil_scoped_release nogil;
-    status = (decode ? fl_attn_decode : fl_attn_prefill_paged)(&tq, &tk, &tv, &kv, &d, &a, &tout, want_lse ? &tlse : nullptr,
-                                                              (void*)stream);
-  }
+  const int status = (decode ? fl_attn_decode : fl_attn_prefill_paged)(&tq, &tk, &tv, &kv, &d, &a, &tout, want_lse ? &tlse : nullptr,
+                                                                      (void*)stream);
   return {status, (int64_t)need, out, lse};
+}
+
+// ---- the autograd nodes of training calls.  A node written in Python is entered by the engine's thread under the interpreter's lock, which the
+// calling thread has just given up.  A causal forward and backward call on [1, 8, 110, 128] took 45 or 89 us with one, by where the process runs, and
+// takes 38 or 72 with these; documents and windows 3 x 32/8 x 182 61 or 97, and 49 or 84.  Calls under a transform, a trace, forward-mode derivatives or torch.compile keep the Python node (functional.py).
+
+PyObject* g_check = nullptr;                       // binding.check: raises for a status
+
+// The exception that binding.check raises for `status`, thrown on a thread without the interpreter's lock; the engine carries it to the caller.
+[[noreturn]] void throw_status(int status) {
+  py::gil_scoped_acquire gil;
+  PyObject* r = PyObject_CallFunction(g_check, "i", status);
+  if (r != nullptr) {                              // (not reached: it raises for every status but 0)
+    Py_DECREF(r);
+    PyErr_SetString(PyExc_RuntimeError, "backward pass failed");
+  }
+  python_error e;
+  e.persist();
+  throw e;
+}
+
+int64_t current_stream(const Tensor& t) { return (int64_t)c10::hip::getCurrentHIPStream(t.device().index()).stream(); }
+
+// The outputs of a forward pass, taken through Function::apply unseen, and what its backward pass needs beside tensors that autograd saves.
+struct Done {
+  const Tensor &out, &lse;
+  const std::vector<double>& scalars;
+  const OptTensor &slopes, &q_ids, &kv_ids;
+
+  void keep(torch::autograd::AutogradContext* ctx) const {
+    ctx->saved_data["scalars"] = scalars;
+    if (slopes.has_value()) ctx->saved_data["slopes"] = *slopes;
+    if (q_ids.has_value()) ctx->saved_data["q_ids"] = *q_ids;
+    if (kv_ids.has_value()) ctx->saved_data["kv_ids"] = *kv_ids;
+  }
+};
+OptTensor kept(torch::autograd::AutogradContext* ctx, const char* name) {
+  const auto it = ctx->saved_data.find(name);
+  return it == ctx->saved_data.end() ? OptTensor() : OptTensor(it->second.toTensor());
+}
+// (slopes are an input without a gradient: a call that only they would need a derivative of has a node all the same)
+struct AttentionNode : torch::autograd::Function<AttentionNode> {
+  static Tensor forward(torch::autograd::AutogradContext* ctx, const Tensor& q, const Tensor& k, const Tensor& v, const OptTensor&, const Done& done) {
+    ctx->save_for_backward({q, k, v, done.out, done.lse});
+    done.keep(ctx);
+    return done.out;
+  }
+  static torch::autograd::variable_list backward(torch::autograd::AutogradContext* ctx, const torch::autograd::variable_list& grads) {
+    const auto t = ctx->get_saved_variables();
+    const auto s = ctx->saved_data["scalars"].toDoubleVector();
+    auto [status, dq, dk, dv] = attention_bwd(t[0], t[1], t[2], t[3], t[4], grads[0], s[0], (int)s[1], s[2], (int)s[3], (int)s[4], (int)s[5],
+                                              (int)s[6], kept(ctx, "slopes"), kept(ctx, "q_ids"), kept(ctx, "kv_ids"), current_stream(t[0]));
+    if (status != 0) throw_status(status);
+    return {dq, dk, dv, Tensor(), Tensor()};
+  }
+};
+
+// attention_fwd with a node: the status and out
+std::tuple<int, Tensor> attention_node(const Tensor& q, const Tensor& k, const Tensor& v, double scale, int mod, double softcap, int mask,
+                                       int window, int prefix, int q_offset, const OptTensor& slopes, const OptTensor& q_ids,
+                                       const OptTensor& kv_ids, int64_t stream) {
+  auto [status, out, lse] = attention_fwd(q, k, v, scale, mod, softcap, mask, window, prefix, q_offset, slopes, q_ids, kv_ids, stream);
+  if (status != 0) return {status, out};
+  const std::vector<double> scalars = {scale, (double)mod, softcap, (double)mask, (double)window, (double)prefix, (double)q_offset};
+  return {0, AttentionNode::apply(q, k, v, slopes, Done{out, lse, scalars, slopes, q_ids, kv_ids})};
+}
+
+struct VariantNode : torch::autograd::Function<VariantNode> {
+  static Tensor forward(torch::autograd::AutogradContext* ctx, const Tensor& q, const Tensor& k, const Tensor& v, const OptTensor& q2,
+                        const OptTensor& k2, const OptTensor& lam, const OptTensor& gate, const OptTensor& bias0, const OptTensor& bias1,
+                        const OptTensor& rms_weight, const Done& done) {
+    torch::autograd::variable_list saved = {q, k, v};
+    for (const OptTensor* x : {&q2, &k2, &lam, &gate, &bias0, &bias1, &rms_weight}) saved.push_back(x->has_value() ? **x : Tensor());
+    saved.push_back(done.out);
+    saved.push_back(done.lse);
+    ctx->save_for_backward(std::move(saved));
+    done.keep(ctx);
+    return done.out;
+  }
+  static torch::autograd::variable_list backward(torch::autograd::AutogradContext* ctx, const torch::autograd::variable_list& grads) {
+    const auto t = ctx->get_saved_variables();
+    const auto s = ctx->saved_data["scalars"].toDoubleVector();
+    auto opt = [](const Tensor& x) { return x.defined() ? OptTensor(x) : OptTensor(); };
+    auto [status, g] = variant_bwd(t[0], t[1], t[2], opt(t[3]), opt(t[4]), opt(t[5]), opt(t[6]), opt(t[7]), opt(t[8]), opt(t[9]), t[10], t[11],
+                                   grads[0], s[0], (int)s[1], s[2], (int)s[3], (int)s[4], (int)s[5], (int)s[6], s[7] != 0, s[8], kept(ctx, "slopes"),
+                                   kept(ctx, "q_ids"), kept(ctx, "kv_ids"), current_stream(t[0]));
+    if (status != 0) throw_status(status);
+    torch::autograd::variable_list out;
+    for (const OptTensor& x : g) out.push_back(x.has_value() ? *x : Tensor());
+    out.emplace_back();                            // the forward pass's results
+    return out;
+  }
+};
+
+// variant_fwd with a node: the status and out
+std::tuple<int, Tensor> variant_node(const Tensor& q, const Tensor& k, const Tensor& v, const OptTensor& q2, const OptTensor& k2, const OptTensor& lam,
+                                     const OptTensor& gate, const OptTensor& bias0, const OptTensor& bias1, const OptTensor& rms_weight,
+                                     double scale, int mod, double softcap, int mask, int window, int prefix, int q_offset, bool rmsnorm,
+                                     double rms_eps, const OptTensor& slopes, const OptTensor& q_ids, const OptTensor& kv_ids, int64_t stream) {
+  auto [status, out, lse] = variant_fwd(q, k, v, q2, k2, lam, gate, bias0, bias1, rms_weight, scale, mod, softcap, mask, window, prefix, q_offset,
+                                        rmsnorm, rms_eps, slopes, q_ids, kv_ids, stream);
+  if (status != 0) return {status, out};
+  const std::vector<double> scalars = {scale,          (double)mod,      softcap, (double)mask, (double)window,
+                                       (double)prefix, (double)q_offset, rmsnorm ? 1.0 : 0.0, rms_eps};
+  return {0, VariantNode::apply(q, k, v, q2, k2, lam, gate, bias0, bias1, rms_weight, Done{out, lse, scalars, slopes, q_ids, kv_ids})};
 }
 
 }  // namespace
 
 PYBIND11_MODULE(_fltorch, m) {
-  m.def("attention_fwd", &attention_fwd);
-  m.def("attention_bwd", &attention_bwd);
-  m.def("variant_fwd", &variant_fwd);
-  m.def("variant_bwd", &variant_bwd);
-  m.def("paged", &paged);
+  typedef py::call_guard<py::gil_scoped_release> nogil;
+  m.def("attention_fwd", &attention_fwd, nogil());
+  m.def("attention_bwd", &attention_bwd, nogil());
+  m.def("attention_node", &attention_node, nogil());
+  m.def("variant_fwd", &variant_fwd, nogil());
+  m.def("variant_bwd", &variant_bwd, nogil());
+  m.def("variant_node", &variant_node, nogil());
+  m.def("paged", &paged, nogil());
+  m.def("set_check", [](py::object check) {
+    Py_XDECREF(g_check);
+    g_check = check.release().ptr();
+  });
 }

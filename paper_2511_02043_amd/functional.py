@@ -33,6 +33,7 @@ def _host():
         except ImportError as e:
             raise ImportError("_fltorch.so is missing or was built for another interpreter or torch: run "
                               "make -C paper_2511_02043_amd/csrc PYTHON=<this interpreter>") from e
+        _fltorch.set_check(fb.check)
         _host_module = _fltorch
     return _host_module
 
@@ -97,16 +98,24 @@ _tracing_state = getattr(torch._C, "_get_tracing_state", lambda: True)
 _grad_enabled = torch.is_grad_enabled
 
 
-def _without_node(tensors) -> bool:
-    """Whether a call takes no part in a derivative, a transform or a trace, so that it needs no autograd node: building one takes
-    3.7 us, of 8.8 us for a call on [1, 8, 128, 64] whose kernel runs 8 us (training calls are unchanged)."""
+_NO_NODE, _NATIVE_NODE, _PYTHON_NODE = range(3)
+
+
+def _node_for(tensors) -> int:
+    """The autograd node that a call needs.  None where it takes no part in a derivative, a transform or a trace: building one takes 3.7 us, of
+    8.8 us for a call on [1, 8, 128, 64] whose kernel runs 8 us.  The compiled one for ordinary derivatives; the Python one, which
+    transforms, traces and torch.compile look into, for the rest."""
     if _transforms_active() or getattr(forward_ad, "_current_level", 0) >= 0 or _tracing_state() is not None or torch.compiler.is_compiling():
-        return False
+        return _PYTHON_NODE
     if _grad_enabled():
         for t in tensors:
             if t is not None and t.requires_grad:
-                return False
-    return True
+                return _NATIVE_NODE
+    return _NO_NODE
+
+
+def _without_node(tensors) -> bool:
+    return _node_for(tensors) == _NO_NODE
 
 
 def _forward(q, k, v, variant):
@@ -165,8 +174,14 @@ def attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, *, scale: Optio
         raise ValueError("q_offset must be >= 0")
     variant = (float(scale), _score_mod(softcap, alibi_slopes), float(softcap or 0.0), _mask_bits(causal, window, prefix, q_doc_ids),
                int(window or 0), int(prefix or 0), int(q_offset), alibi_slopes, q_doc_ids, kv_doc_ids)
-    if _without_node((q, k, v, alibi_slopes)):
+    node = _node_for((q, k, v, alibi_slopes))
+    if node == _NO_NODE:
         return _forward(q, k, v, variant)[0]
+    if node == _NATIVE_NODE:
+        status, out = _host().attention_node(q, k, v, *variant, _stream(q))
+        if status:
+            fb.check(status)
+        return out
     return _Attention.apply(q, k, v, alibi_slopes, q_doc_ids, kv_doc_ids, variant)
 
 
@@ -242,8 +257,14 @@ def variant_attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, *, scal
     b0 = biases[0] if len(biases) > 0 else None
     b1 = biases[1] if len(biases) > 1 else None
     tensors = (q, k, v, q2, k2, lam, gate, b0, b1, rms_weight if rmsnorm else None)
-    if _without_node(tensors):
+    node = _node_for(tensors)
+    if node == _NO_NODE:
         return _variant_forward(tensors, variant)[0]
+    if node == _NATIVE_NODE:
+        status, out = _host().variant_node(*tensors, *variant, _stream(q))
+        if status:
+            fb.check(status)
+        return out
     return _VariantAttention.apply(variant, *tensors)
 
 
