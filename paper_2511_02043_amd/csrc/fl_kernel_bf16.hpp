@@ -186,10 +186,6 @@ template <class C>
 struct Wave {
   static constexpr int D = C::D, DV = C::DV, NB = C::NB, KK = C::KK, DVB = C::DVB, NS = C::NS, RB = C::RB;
   static constexpr bool kPlain = (C::MOD == kModNone && C::NBIAS == 0);
-  // Scores in the units that the FMA of the exponent's argument takes: raw ones of the plain variants, an expression's results.  The others
-  // are in log2 units.
-  static constexpr bool kScaled = kPlain || (C::MOD == kModCustom && C::NBIAS == 0);
-  __device__ __forceinline__ float score_scale() const { return kPlain ? c_scale : kLog2e; }
   // The exponentials of a fully visible tile are taken against the reference that the row has (its maximum over the first tiles, or
   // a little less), without the row max of the tile; its row sum, which there is anyway, tells afterwards whether the reference has to
   // follow (settle_sums).  That is half a vector instruction less per score and no max between the two contractions: causal,
@@ -348,8 +344,8 @@ struct Wave {
   }
 
   // ---- variant transform (Eq. 4 score_mod, additive biases) of one score register.
-  // Leaves the score in the domain exp_only() expects: raw for the plain variants and as the expression gives it (the scale is
-  // folded into the exponent's FMA: kScaled), log2-scaled otherwise (less the cap: kShifted).  j0 is the tile's first key.
+  // Leaves the score in the domain exp_only() expects: raw for the plain variants (the scale is
+  // folded into the exponent's FMA), log2-scaled otherwise (less the cap: kShifted).  j0 is the tile's first key.
   // INNER: the tile ends at or before the last key.
   template <bool INNER = false>
   __device__ __forceinline__ float transform_one(float x, int j0, int rb, int nb, int r, const BiasRegs& br, int row = 0) const {
@@ -373,7 +369,7 @@ struct Wave {
         // indexes a captured array by i or j must not be handed an index outside the call's sizes)
         // (FL_USER_CLAMP 0: the expressions capture no array, so any index is as good as another and the minimum per
         // score is saved)
-        x = fl_user_score_mod(x * p.scale, b, g, h, (INNER ? row : ic[rb] + p.q_off), FL_USER_CLAMP && !INNER && j >= p.Sk ? p.Sk - 1 : j, p) * (kScaled ? 1.f : kLog2e);
+        x = fl_user_score_mod(x * p.scale, b, g, h, (INNER ? row : ic[rb] + p.q_off), FL_USER_CLAMP && !INNER && j >= p.Sk ? p.Sk - 1 : j, p) * kLog2e;
       } else {
         x *= c_scale;
       }
@@ -556,7 +552,7 @@ struct Wave {
 #pragma unroll
         for (int r = 0; r < 16; ++r) m = fmaxf(m, sc[rb][nb][r]);
       m = half_swap_max(m);
-      if constexpr (kScaled) m *= score_scale();   // > 0 (checked on the host)
+      if constexpr (kPlain) m *= c_scale;          // scale > 0 (checked on the host)
       mx[rb] = m;
     }
   }
@@ -598,9 +594,11 @@ struct Wave {
 
   // ---- one probability pair: p = exp2(s - m); then running row sum and bf16 pair (and remainder)
   __device__ __forceinline__ void exp_only(float s0, float s1, float m_safe, float& p0, float& p1) const {
-    if constexpr (kScaled) {
-      p0 = fast_exp2(fmaf(s0, score_scale(), -m_safe));
-      p1 = fast_exp2(fmaf(s1, score_scale(), -m_safe));
+    // (an expression's or a bias's log2(e) is not folded in: where every score of a row is near a finite -1e30, the rounding of
+    // the reference would be all that is left, and is large)
+    if constexpr (kPlain) {
+      p0 = fast_exp2(fmaf(s0, c_scale, -m_safe));
+      p1 = fast_exp2(fmaf(s1, c_scale, -m_safe));
     } else {
       p0 = fast_exp2(s0 - m_safe);
       p1 = fast_exp2(s1 - m_safe);
@@ -685,8 +683,6 @@ struct Wave {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       ps.m_safe[rb] = m_run[rb] == -INFINITY ? 0.f : m_run[rb];
-      // (an expression's score past the range in log2 units makes its row NaN, as an infinite one does)
-      if constexpr (C::MOD == kModCustom) ps.m_safe[rb] = fmaf(ps.m_safe[rb], 0.f, ps.m_safe[rb]);
       ps.psum[rb] = 0.f;
       ps.mx[rb] = -INFINITY;
     }
@@ -848,7 +844,7 @@ struct Wave {
     for (int rb = 0; rb < RB; ++rb) {
       l_run[rb] += ps.psum[rb];
       float mxs = half_swap_max(ps.mx[rb]);
-      if constexpr (kScaled) mxs *= score_scale(); // > 0 (checked on the host)
+      if constexpr (kPlain) mxs *= c_scale;        // scale > 0 (checked on the host)
       const float m_old = m_run[rb];
       float m_new = (mxs - m_old > kLazyMaxLog2) ? mxs : m_old;   // false for NaN (-inf - -inf)
       m_new = advance ? m_new : m_old;

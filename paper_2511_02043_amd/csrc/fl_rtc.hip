@@ -342,8 +342,8 @@ fl_status fl_compile_variant_aux(const char* score_mod_expr, const char* mask_ex
 // An array that an expression only indexes comes as fl_array: where the compiler can tell that the index of a bf16 element is not
 // negative, twice the index fits 32 bits, and the load takes that beside the array's address in scalar registers, instead of a 64-bit sum
 // in a pair of vector registers per score (the arguments are never negative, which the compiler is told).  A learned bias by head and
-// clipped distance: 600 -> 402 instructions per tile of 32 x 64 scores, together with the clamp and the factor log2(e) per score that
-// the transform of a whole tile does without.
+// clipped distance: 600 -> 450 instructions per tile of 32 x 64 scores, together with the clamp per score that the transform of an
+// inner tile does without.
 static std::string hook_source(const fl_custom_variant* v, bool with_grad) {
   auto scope = [&](const std::string& expr) {
     std::string text = "  __builtin_assume(b >= 0); __builtin_assume(g >= 0); __builtin_assume(h >= 0); __builtin_assume(i >= 0); __builtin_assume(j >= 0);\n"

@@ -52,3 +52,24 @@ def test_array_forms(Sq, Sk):
                 assert float(np.max(np.abs(got[0] - ref))) <= 1e-2 and float(np.max(np.abs(got[1][~dead] - ref_lse[~dead]))) <= 1e-3
             assert np.array_equal(got[0], first[0]) and np.array_equal(got[1], first[1]), (name, ws is None)
         var.release()
+
+
+@pytest.mark.parametrize("far", [-1e4, -1e9, -1e30, -2.2e38])
+def test_rows_hidden_by_a_finite_score(far):
+    """Rows whose scores are all far below zero by the same amount, and rows with one key that is not: the average of the values, and that key's."""
+    import torch
+    B, H, S, D = 1, 2, 160, 64
+    w = inputs.causal_bf16(B=B, H=H, Hkv=H, S=S, D=D, causal=False, salt=22)
+    hidden = np.ones((S, S), np.float32)
+    hidden[:100, 3] = 0.0
+    hidden[100:120, 130:] = 0.0
+    table = torch.from_numpy(hidden).to("cuda:0", torch.bfloat16)
+    dw = runner.upload(w, out_dtype="f32")
+    var = fb.CustomVariant(f"0.0f * s + {far:.9e}f * (float)aux2[i * Sk + j]", None, D, aux=[None, None, table])
+    fb.check(var.forward(dw.tq, dw.tk, dw.tv, float(w.scale), dw.tout, dw.tlse))
+    torch.cuda.synchronize()
+    ref, ref_lse = ao.attention_custom(w.q, w.k, w.v, scale=w.scale, score_mod=lambda s, b, g, h, i, j: np.float64(np.float32(far)) * hidden, mask=None)
+    assert float(np.max(np.abs(dw.out.cpu().numpy() - ref))) <= 1e-2
+    # lse: the product far * log2(e) and its way back are rounded to fp32
+    assert float(np.max(np.abs(dw.lse.cpu().numpy()[..., 0] - ref_lse) / (1e-3 + 2.0 ** -22 * np.abs(ref_lse)))) <= 1.0
+    var.release()
