@@ -335,6 +335,12 @@ hipError_t run_bwd_dq(const fl::BwdEntry* be, const fl::BwdParams& p_in, int nbl
   fl::BwdParams p = p_in;
   const int problems = nblocks / std::max(p.n_qtiles, 1);
   p.step_q = longest_first(be->key.mask, be->key.D, be->key.Dv, problems, p.n_qtiles) ? (p.order_q ? problems / 8 : problems) : 0;
+  const int64_t share = p.order_q ? p.order_heads : 1;
+  p.q_tiles = fl::Divisor::of(p.step_q > 0 ? p.step_q : p.n_qtiles * share);
+  p.q_share = fl::Divisor::of(share);
+  p.q_heads = fl::Divisor::of(p.H);
+  p.q_group = fl::Divisor::of(p.H / std::max(p.Hkv, 1));
+  p.by_g = fl::Divisor::of(p.G);
   return be->jit != nullptr ? fl::jit_backward_launch(*be, 0, p, nblocks, stream) : be->dq(p, nblocks, stream);
 }
 // The dK/dV kernel with 64 keys per wave where the variant has one, the call suits it and its workgroups of 256 keys leave the 256 compute
@@ -364,6 +370,12 @@ hipError_t run_bwd_dkdv(const fl::BwdEntry* be, const fl::WideEntry* wide, const
   const int nblocks = (int)(problems * pk.n_ktiles);
   const bool by_tile = wide != nullptr || longest_first(be->key.mask, be->key.D, be->key.Dv, problems, pk.n_ktiles);
   pk.step_k = by_tile ? (int)(p.order_k ? problems / 8 : problems) : 0;
+  pk.heads_kv = p.H / std::max(p.Hkv, 1);
+  pk.heads_wg = pk.heads_kv / std::max(p.hsplit, 1);
+  pk.k_tiles = fl::Divisor::of(pk.step_k > 0 ? pk.step_k : pk.n_ktiles);
+  pk.k_split = fl::Divisor::of(p.hsplit);
+  pk.k_heads = fl::Divisor::of(p.Hkv);
+  pk.by_g = fl::Divisor::of(p.G);
   if (wide != nullptr) return wide->dkdv(pk, nblocks, stream);
   return be->jit != nullptr ? fl::jit_backward_launch(*be, 1, pk, nblocks, stream) : be->dkdv(pk, nblocks, stream);
 }
@@ -623,10 +635,19 @@ __global__ void __launch_bounds__(256) epi_bwd_rows_kernel(const EpiBwdParams e)
   const int64_t row = live ? row_raw : rows - 1;
   const int c0 = sub * 8;
   const bool ok = live && c0 < e.Dv;               // Dv is a multiple of 8: a lane's channels are all inside or all outside
-  const int i = (int)(row % e.Sq);
-  const int h = (int)((row / e.Sq) % e.H);
-  const int g = (int)((row / ((int64_t)e.Sq * e.H)) % e.G);
-  const int b = (int)(row / ((int64_t)e.Sq * e.H * e.G));
+  int i, h, g, b;
+  if (rows <= 0x7fffffffLL) {                      // uniform.  64-bit divisions, five of them, were half of the kernel's instructions
+    const uint32_t r = (uint32_t)row, rh = r / (uint32_t)e.Sq, rg = rh / (uint32_t)e.H;
+    i = (int)(r - rh * (uint32_t)e.Sq);
+    h = (int)(rh - rg * (uint32_t)e.H);
+    b = (int)(rg / (uint32_t)e.G);
+    g = (int)(rg - (uint32_t)b * (uint32_t)e.G);
+  } else {
+    i = (int)(row % e.Sq);
+    h = (int)((row / e.Sq) % e.H);
+    g = (int)((row / ((int64_t)e.Sq * e.H)) % e.G);
+    b = (int)(row / ((int64_t)e.Sq * e.H * e.G));
+  }
   auto off = [&](const fl::View& v) { return b * v.sb + g * v.sg + h * v.sh + (int64_t)i * v.ss + c0; };
   auto gsum = [](float x) {                        // over the lanes of a row
 #pragma unroll

@@ -56,6 +56,9 @@ struct BwdParams {
   int32_t step_q, step_k;          // > 0: the longest tiles of so many problems (all, or an XCD's) come first, 0: one problem after the other
   int32_t order_heads;             // dQ kernel, order_q 1: heads with the same keys that an XCD takes one after the other (FwdParams)
   int32_t hsplit;                  // dK/dV kernel: the query heads of a group are cut into hsplit subsets, one workgroup each
+  int32_t heads_kv, heads_wg;      // query heads per kv head; of those, what a workgroup of the dK/dV kernel sums over
+  // what a workgroup's index is divided by: dQ kernel, dK/dV kernel, both (set where they are launched)
+  Divisor q_tiles, q_share, q_heads, q_group, k_tiles, k_split, k_heads, by_g;
   float* part_dk;                  // hsplit > 1: fp32 partial sums [hsplit][B, G, Hkv, Sk, D | DV], summed by bwd_reduce_kv_kernel
   float* part_dv;
   const float* dv_add;             // added to dV before it is written, dense fp32 [B, G, Hkv, Sk, DV]: the first softmax
@@ -81,11 +84,25 @@ __host__ __device__ inline int ds_block(int64_t Sq) { return 32 * ds_rows(Sq); }
 // Under a mask the tiles of a problem are unequal, the first ones the longest.  With few of them per compute unit the last problem's long ones, begun when
 // the rest was half done, were the launch's end (us, problem by problem / tile by tile: dQ causal 16 x 8 heads x 999, D = 64 55 / 42, 8 x 16 x 2048 154 / 126, D = 128
 // 8 x 16 x 1024 98 / 80, 4 x 16 x 4096 552 / 487, windows and documents 8 x 16 x 2048, D = 64 82 / 73; dK / dV there 77 / 59, 217 / 185, 123 / 108).
-// step > 0: so many problems, tile by tile; 0: problem by problem.
-__device__ __forceinline__ void tile_of(int step, unsigned idx, unsigned tiles, int& problem, int& tile) {
-  const unsigned per = step > 0 ? step : tiles, a = idx / per, b = idx - a * per;
-  problem = (int)(step > 0 ? b : a);
-  tile = (int)(step > 0 ? a : b);
+// step > 0: so many problems, tile by tile; 0: problem by problem.  per: divides by step, or by the tiles of a problem.
+__device__ __forceinline__ void tile_of(int step, int idx, const Divisor& per, int& problem, int& tile) {
+  int a, b;
+  per.split(idx, a, b);
+  problem = step > 0 ? b : a;
+  tile = step > 0 ? a : b;
+}
+// Problem bh of the dK/dV kernels, (b, g, kv head, subset of the group's query heads)
+struct KeyProblem {
+  int split, hk, g, b, h_first;
+};
+__device__ __forceinline__ KeyProblem key_problem(const BwdParams& p, int bh) {
+  KeyProblem r;
+  int bhk, bg;
+  p.k_split.split(bh, bhk, r.split);
+  p.k_heads.split(bhk, bg, r.hk);
+  p.by_g.split(bg, r.b, r.g);
+  r.h_first = r.hk * p.heads_kv + r.split * p.heads_wg;
+  return r;
 }
 
 // chunk swizzle of a tile row (see the header comment): an XOR on the 16-byte chunk index that
@@ -582,18 +599,23 @@ bwd_dq_kernel(const BwdParams p) {
     // consecutive workgroup ids go round-robin to the 8 XCDs: give each XCD whole heads, so that a
     // head's K / V tiles stay in one L2 (the host checks that the head count is a multiple of 8), with the heads that read
     // the same K / V side by side
-    const int share = p.order_heads;
-    int n;                                         // which of the XCD's heads
-    tile_of(p.step_q, blockIdx.x >> 3, nq * share, n, qt);
-    if (p.step_q == 0) n = n * share + qt % share;
-    bh = share == 1 ? n * 8 + (blockIdx.x & 7) : (n / share * 8 + (blockIdx.x & 7)) * share + n % share;
-    if (p.step_q == 0) qt /= share;
+    int n, inner, r;                               // which of the XCD's heads, or sets of heads
+    tile_of(p.step_q, blockIdx.x >> 3, p.q_tiles, n, inner);
+    if (p.step_q == 0) {
+      p.q_share.split(inner, qt, r);
+    } else {
+      qt = inner;
+      p.q_share.split(n, n, r);
+    }
+    bh = (n * 8 + (int)(blockIdx.x & 7)) * (int)p.q_share.d + r;
   } else {
-    tile_of(p.step_q, blockIdx.x, nq, bh, qt);
+    tile_of(p.step_q, blockIdx.x, p.q_tiles, bh, qt);
   }
   qt = nq - 1 - qt;
-  const int h = bh % p.H, g = (bh / p.H) % p.G, b = bh / (p.H * p.G);
-  const int hk = h / (p.H / p.Hkv);
+  int bg, h, b, g;
+  p.q_heads.split(bh, bg, h);
+  p.by_g.split(bg, b, g);
+  const int hk = p.q_group.div(h);
   const FwdParams uctx = user_context(p);          // what a compiled variant's expressions read (unused otherwise)
   const int i0 = qt * C::BM, iw = i0 + 32 * wave;
   const int i = iw + w.col, ic = i < p.Sq ? i : p.Sq - 1;
@@ -930,16 +952,14 @@ bwd_dkdv_kernel(const BwdParams p) {
   // grid decode: key tiles in increasing order (under a causal mask the first ones see the most rows)
   int kt, bh;
   if (p.order_k == 1) {                            // whole key/value heads per XCD: their Q / dO tiles stay in one L2
-    tile_of(p.step_k, blockIdx.x >> 3, p.n_ktiles, bh, kt);
+    tile_of(p.step_k, blockIdx.x >> 3, p.k_tiles, bh, kt);
     bh = bh * 8 + (blockIdx.x & 7);
   } else {
-    tile_of(p.step_k, blockIdx.x, p.n_ktiles, bh, kt);
+    tile_of(p.step_k, blockIdx.x, p.k_tiles, bh, kt);
   }
-  // bh counts (b, g, kv head, subset of the group's query heads)
-  const int split = bh % p.hsplit, bhk = bh / p.hsplit;
-  const int hk = bhk % p.Hkv, g = (bhk / p.Hkv) % p.G, b = bhk / (p.Hkv * p.G);
-  const int group = p.H / p.Hkv / p.hsplit;        // query heads this workgroup sums over
-  const int h_first = hk * (p.H / p.Hkv) + split * group;
+  const KeyProblem kp = key_problem(p, bh);
+  const int split = kp.split, hk = kp.hk, g = kp.g, b = kp.b, h_first = kp.h_first;
+  const int group = p.heads_wg;                    // query heads this workgroup sums over
   const int j0 = kt * C::BM, jw = j0 + 32 * wave;
   const int j = jw + w.col, jc = j < p.Sk ? j : p.Sk - 1;
   const Span span = C::NBIAS > 0 ? Span{0, 0u} : seeing_rows(MASK, j, p.Sq, p.Sk, p.q_off, p.window, p.prefix);
@@ -1326,16 +1346,14 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
 
   int kt, bh;
   if (p.order_k == 1) {                            // whole key/value heads per XCD: their Q / dO tiles stay in one L2
-    tile_of(p.step_k, blockIdx.x >> 3, p.n_ktiles, bh, kt);
+    tile_of(p.step_k, blockIdx.x >> 3, p.k_tiles, bh, kt);
     bh = bh * 8 + (blockIdx.x & 7);
   } else {
-    tile_of(p.step_k, blockIdx.x, p.n_ktiles, bh, kt);
+    tile_of(p.step_k, blockIdx.x, p.k_tiles, bh, kt);
   }
-  // bh counts (b, g, kv head, subset of the group's query heads)
-  const int split = bh % p.hsplit, bhk = bh / p.hsplit;
-  const int hk = bhk % p.Hkv, g = (bhk / p.Hkv) % p.G, b = bhk / (p.Hkv * p.G);
-  const int group = p.H / p.Hkv / p.hsplit;        // query heads this workgroup sums over
-  const int h_first = hk * (p.H / p.Hkv) + split * group;
+  const KeyProblem kp = key_problem(p, bh);
+  const int split = kp.split, hk = kp.hk, g = kp.g, b = kp.b, h_first = kp.h_first;
+  const int group = p.heads_wg;                    // query heads this workgroup sums over
   const int j0 = kt * C::BM, jw = j0 + 32 * kg;
   const int j = jw + w.col, jc = j < p.Sk ? j : p.Sk - 1;
   const Span span = seeing_rows(MASK, j, p.Sq, p.Sk, p.q_off, p.window, p.prefix);

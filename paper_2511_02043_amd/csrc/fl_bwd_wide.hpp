@@ -59,17 +59,14 @@ bwd_dkdv_wide_kernel(const BwdParams p) {
   // tile by tile through all problems, the longest (under a causal mask) first: with one workgroup per compute unit the launch is a few rounds
   int kt, bh;
   if (p.order_k == 1) {                            // whole key/value heads per XCD: their Q / dO tiles stay in one L2
-    const int idx = blockIdx.x >> 3;
-    kt = idx / p.step_k;
-    bh = (idx % p.step_k) * 8 + (blockIdx.x & 7);
+    p.k_tiles.split(blockIdx.x >> 3, kt, bh);
+    bh = bh * 8 + (blockIdx.x & 7);
   } else {
-    kt = blockIdx.x / p.step_k;
-    bh = blockIdx.x % p.step_k;
+    p.k_tiles.split(blockIdx.x, kt, bh);
   }
-  const int split = bh % p.hsplit, bhk = bh / p.hsplit;
-  const int hk = bhk % p.Hkv, g = (bhk / p.Hkv) % p.G, b = bhk / (p.Hkv * p.G);
-  const int group = p.H / p.Hkv / p.hsplit;        // query heads this workgroup sums over
-  const int h_first = hk * (p.H / p.Hkv) + split * group;
+  const KeyProblem kp = key_problem(p, bh);
+  const int split = kp.split, hk = kp.hk, g = kp.g, b = kp.b, h_first = kp.h_first;
+  const int group = p.heads_wg;                    // query heads this workgroup sums over
   const int j0 = kt * X::BM, jw = j0 + X::KEYS * wave;
   const float c_scale = p.scale * kLog2e;
 

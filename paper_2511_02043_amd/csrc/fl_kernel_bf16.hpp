@@ -880,42 +880,39 @@ fwd_bf16_kernel(const FwdParams call) {
   // With p.pair a workgroup takes q-tile nq - 1 - pi and then q-tile pi: under a causal mask the
   // two together see the same number of key tiles for every pi, so all workgroups carry the same
   // load and the launch has no tail of long stragglers.  Without it, q-tiles go out longest first.
-  const int nq = call.n_qtiles, npairs = call.pair ? (nq + 1) / 2 : nq;
+  const int nq = call.n_qtiles;
   int bid = blockIdx.x;
   int pi, bh;
   if (call.order == 1) {
     // XCD-aware: consecutive workgroup ids go round-robin to the 8 XCDs; give each XCD whole
     // (b, g, h) problems so that a head's K/V stay in one L2 (host checks (B*G*H) % 8 == 0), and all order_heads problems
     // that read the same K/V one after the other (grouped-query heads; 1 where that leaves XCDs without work).
-    constexpr bool user = C::MOD == kModCustom || (C::MASK & kMaskCustom) != 0;   // (the host sets 1: no divisions by it)
-    const int xcd = bid & 7, share = user ? 1 : call.order_heads;
-    const int idx = bid >> 3;
+    const int xcd = bid & 7;
+    int n, rest, q, r;
+    call.by_tiles.split(bid >> 3, n, rest);
     if (call.tile_step > 0) {
-      const int n = idx % call.tile_step;
-      pi = idx / call.tile_step;
-      bh = share == 1 ? n * 8 + xcd : (n / share * 8 + xcd) * share + n % share;
+      pi = n;
+      call.by_share.split(rest, q, r);
+      bh = (q * 8 + xcd) * (int)call.by_share.d + r;
     } else {
-      const int inner = idx % (npairs * share);
-      bh = ((idx / (npairs * share)) * 8 + xcd) * share + inner % share;
-      pi = inner / share;
+      call.by_share.split(rest, pi, r);
+      bh = (n * 8 + xcd) * (int)call.by_share.d + r;
     }
   } else if (call.tile_step > 0) {
-    bh = bid % call.tile_step;
-    pi = bid / call.tile_step;
+    call.by_tiles.split(bid, pi, bh);
   } else {
-    pi = bid % npairs;
-    bh = bid / npairs;
+    call.by_tiles.split(bid, bh, pi);
   }
   // The problem as this workgroup sees it.  With per-sequence key counts (a chunk of new query rows against each
   // sequence's cached keys, Sec. 4.1 serving) sequence b has kv_lens[b] keys, cut to [0, Sk], and its query rows are the
   // last Sq positions of those: row i sits at position kv_lens[b] - Sq + i (rows at negative positions see nothing).
   // (packed heads: bh counts groups of PACK heads)
-  const int heads_wg = call.H / C::PACK;
+  const int heads_wg = (int)call.by_heads.d;       // H / PACK
   FwdParams p = call;
   constexpr bool kv_counts = (C::MASK & (kMaskDoc | kMaskCustom)) == 0 && C::MOD != kModCustom;   // the host passes none with these
   if (kv_counts && call.kv_lens != nullptr) {
     const int seq_wgs = heads_wg * call.G;
-    int b = bh / seq_wgs, len;
+    int b = call.by_g.div(call.by_heads.div(bh)), len;
     if (call.B > 1 && call.B <= 64) {
       // Sequences go out longest first: the launch has a few workgroups per compute unit at most, and the one that takes
       // the last long sequence would end long after the rest.  A lane ranks one sequence (ties by index).  (8 sequences of
@@ -954,10 +951,11 @@ fwd_bf16_kernel(const FwdParams call) {
   w.half = lane >> 5;
   w.col = lane & 31;
   const int wrow = (wave % C::NROWG) * C::WROWS;   // the wave's first row among the workgroup's BM
-  const int h = (bh % heads_wg) * C::PACK + wrow / C::HEAD_ROWS;   // (one head per workgroup unless heads are packed)
-  const int g = (bh / heads_wg) % p.G;
-  const int b = bh / (heads_wg * p.G);
-  const int hk = h / (p.H / p.Hkv);                // the same for all heads of a pack (the host checks)
+  int bg, h_wg, b, g;
+  call.by_heads.split(bh, bg, h_wg);
+  call.by_g.split(bg, b, g);
+  const int h = h_wg * C::PACK + wrow / C::HEAD_ROWS;   // (one head per workgroup unless heads are packed)
+  const int hk = call.by_group.div(h);             // the same for all heads of a pack (the host checks)
   const int stream = C::DIFF ? wave / C::NROWG : 0;   // softmax stream of this wave (uniform)
   const int i0 = qt * C::HEAD_ROWS;                // first query row of the workgroup
   const int iw = i0 + wrow % C::HEAD_ROWS;         // first query row of the wave

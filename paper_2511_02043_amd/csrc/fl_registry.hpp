@@ -52,7 +52,9 @@ hipError_t jit_forward_launch(const KernelEntry& e, const FwdParams& p, int nblo
 constexpr int kMaxLdsBytes = 160 * 1024;           // LDS of a gfx950 compute unit
 
 template <class C>
-hipError_t launch_bf16(const FwdParams& p, int nblocks, hipStream_t stream) {
+hipError_t launch_bf16(const FwdParams& call, int nblocks, hipStream_t stream) {
+  FwdParams p = call;
+  set_divisors(p, C::PACK);
   // Raising the dynamic-LDS limit is per device and sticky; cheap enough to repeat per device.
   static std::atomic<bool> done[64];              // zero-initialised; a repeated call from a second thread is harmless
   int dev = 0;

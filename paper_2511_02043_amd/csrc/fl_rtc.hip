@@ -248,6 +248,7 @@ hipError_t jit_forward_launch(const KernelEntry& e, const FwdParams& p, int nblo
   hipError_t err = j->k.get(&f);
   if (err != hipSuccess) return err;
   FwdParams copy = p;
+  set_divisors(copy, e.key.pack);
   void* args[] = {&copy};
   return hipModuleLaunchKernel(f, (unsigned)nblocks, 1, 1, (unsigned)j->nthreads, 1, 1, (unsigned)p.lds_bytes, stream, args, nullptr);
 }
@@ -631,6 +632,7 @@ static fl_status custom_forward(fl_custom_variant* v, const fl_tensor* q, const 
     e = hipModuleLaunchKernel(v->map_func[dev], (unsigned)mblocks, 1, 1, 256, 1, 1, 0, (hipStream_t)stream_v, margs, nullptr);
     if (e != hipSuccess) return fl::host::fail(FL_ERR_LAUNCH, "tile-class pre-pass launch: %s", hipGetErrorString(e));
   }
+  fl::set_divisors(p, 1);
   void* args[] = {&p};
   e = hipModuleLaunchKernel(v->func[dev], (unsigned)nblocks, 1, 1, (unsigned)v->waves * 64, 1, 1, (unsigned)p.lds_bytes, (hipStream_t)stream_v, args, nullptr);
   if (e != hipSuccess) return fl::host::fail(FL_ERR_LAUNCH, "custom variant launch: %s", hipGetErrorString(e));
