@@ -1219,17 +1219,16 @@ fwd_bf16_kernel(const FwdParams call) {
   constexpr bool kWaveSkip = (MASK & (kMaskCausal | kMaskWindow | kMaskPrefix)) != 0 &&
                              (MASK & (kMaskDoc | kMaskCustom)) == 0;
   int tv_lo = 0, tv_hi = 0;
-  if constexpr (kWaveSkip) {
+  if constexpr (kWaveSkip || C::DOC) {
     int lo, hi;
     key_range(MASK, posw, posw + C::WROWS - 1, p.Sk, p.window, p.prefix, lo, hi);
     tv_lo = __builtin_amdgcn_readfirstlane(lo / BN);
     tv_hi = __builtin_amdgcn_readfirstlane((hi + BN - 1) / BN);
   }
   auto wave_class = [&](int t, int2 ks) __attribute__((always_inline)) -> int {   // uniform over the wave; ks: the tile's id range
-    if (t >= t_hi) return kTileSkip;
-    const int c = classify_block(MASK, posw, posw + C::WROWS - 1, t * BN, t * BN + BN - 1, p.Sk, p.window, p.prefix,
-                                 qs_wave, ks);
-    return __builtin_amdgcn_readfirstlane(c);
+    // classify_block() of the wave's rows, its positional part by the two ranges of tiles above
+    if (t >= t_hi || t < tv_lo || t >= tv_hi || qs_wave.y < ks.x || ks.y < qs_wave.x) return kTileSkip;
+    return t >= tf_lo && t < tf_hi && qs_wave.x == qs_wave.y && ks.x == ks.y && qs_wave.x == ks.x ? kTileFull : kTilePartial;
   };
 
   auto wave_full = [&](int t, int2 ks) __attribute__((always_inline)) -> bool {   // is tile t fully visible to the wave?
@@ -1468,6 +1467,7 @@ fwd_bf16_kernel(const FwdParams call) {
       w.transform(sa, tl[0] * BN, br);
       float mx[RB];
       bool full0 = wave_full(tl[0], tks[0]);
+      int cls0 = C::DOC ? wave_class(tl[0], tks[0]) : 0;   // (document masks)
       if (full0) {
         w.rowmax(sa, mx);
         w.advance_max(mx);
@@ -1510,14 +1510,14 @@ fwd_bf16_kernel(const FwdParams call) {
         constexpr int slot_kl = (N + SPB + 1) % RING, slot_vl = (N + SPB) % RING;   // written by this step's loads
         const int t0 = tl[0], t1 = tl[1];
         const int tn = t1;
-        const bool fulln = wave_full(t1, tks[1]);
+        const int clsn = C::DOC ? wave_class(t1, tks[1]) : 0;
+        const bool fulln = C::DOC ? clsn == kTileFull : wave_full(t1, tks[1]);
         if (!full0) {                              // fully visible tiles were settled in phase B
           bool none = wave_none(t0, tks[0]), docs = true, pos = true;
           if constexpr (C::DOC && (MASK & kMaskCustom) == 0) {
-            none = wave_class(t0, tks[0]) == kTileSkip;
+            none = cls0 == kTileSkip;
             docs = !(qs_wave.x == qs_wave.y && tks[0].x == tks[0].y && qs_wave.x == tks[0].x);
-            pos = classify_block(MASK & ~kMaskDoc, posw, posw + C::WROWS - 1, t0 * BN, t0 * BN + BN - 1, p.Sk, p.window, p.prefix,
-                                 make_int2(0, 0), make_int2(0, 0)) != kFull;
+            pos = t0 < tf_lo || t0 >= tf_hi;
           }
           if (none) {
             // nothing of the tile is visible to this wave's rows: all -inf, the running max stays
@@ -1587,6 +1587,7 @@ fwd_bf16_kernel(const FwdParams call) {
         }
         tl[NTL - 1] = after(tl[NTL - 1], tks[NTL - 1], tbw[NTL - 1], std::integral_constant<bool, false>());
         full0 = fulln;
+        cls0 = clsn;
         if (!gaps) {                               // consecutive tiles: advance the bases until the list ends
           if (tl[SPB] < t_hi) vb += vstep;
 #pragma unroll
