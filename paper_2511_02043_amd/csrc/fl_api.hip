@@ -368,7 +368,9 @@ hipError_t run_bwd_dkdv(const fl::BwdEntry* be, const fl::WideEntry* wide, const
   const int bm = wide != nullptr ? wide->bm : be->bm;
   pk.n_ktiles = (p.Sk + bm - 1) / bm;
   const int nblocks = (int)(problems * pk.n_ktiles);
-  const bool by_tile = wide != nullptr || longest_first(be->key.mask, be->key.D, be->key.Dv, problems, pk.n_ktiles);
+  // (Documents alone do not make the first key tiles the longest ones, and a problem's tiles in a row share the rows of their document; us, problem by problem / tile by tile, three
+  // sets of 12 documents: 2 x 16/2 x 11147, D = 128 931 / 1052, D = 64 462 / 493, 2 x 32/8 x 8525, D = 128 1112 / 1233, 4 x 16 x 4096 351 / 356, 1 x 16 x 16000 799 / 812.)
+  const bool by_tile = wide != nullptr || (be->key.mask != (int)fl::kMaskDoc && longest_first(be->key.mask, be->key.D, be->key.Dv, problems, pk.n_ktiles));
   pk.step_k = by_tile ? (int)(p.order_k ? problems / 8 : problems) : 0;
   pk.heads_kv = p.H / std::max(p.Hkv, 1);
   pk.heads_wg = pk.heads_kv / std::max(p.hsplit, 1);
