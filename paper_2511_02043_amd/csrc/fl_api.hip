@@ -334,8 +334,10 @@ bool longest_first(int64_t mask, int64_t D, int64_t Dv, int64_t problems, int64_
 hipError_t run_bwd_dq(const fl::BwdEntry* be, const fl::BwdParams& p_in, int nblocks, hipStream_t stream) {
   fl::BwdParams p = p_in;
   const int problems = nblocks / std::max(p.n_qtiles, 1);
-  p.step_q = longest_first(be->key.mask, be->key.D, be->key.Dv, problems, p.n_qtiles) ? (p.order_q ? problems / 8 : problems) : 0;
   const int64_t share = p.order_q ? p.order_heads : 1;
+  // (documents alone, D = 128, heads that read the same keys: their tiles stay side by side; 2 x 16/2 x 11147 578 us, 600 tile by tile, 2 x 32/8 x 8525 651 and 648)
+  const bool shared_documents = be->key.mask == (int)fl::kMaskDoc && share > 1 && std::max(be->key.D, be->key.Dv) >= 128;
+  p.step_q = !shared_documents && longest_first(be->key.mask, be->key.D, be->key.Dv, problems, p.n_qtiles) ? (p.order_q ? problems / 8 : problems) : 0;
   p.q_tiles = fl::Divisor::of(p.step_q > 0 ? p.step_q : p.n_qtiles * share);
   p.q_share = fl::Divisor::of(share);
   p.q_heads = fl::Divisor::of(p.H);

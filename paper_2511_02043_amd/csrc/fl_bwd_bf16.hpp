@@ -1176,7 +1176,7 @@ bwd_dkdv_kernel(const BwdParams p) {
     const int t = t_lo + it.r, h = h_first + it.h;
     const int ib = t * BN + 32 * QB;
     const float slope2 = C::MOD == kModAlibi ? p.alibi_slopes[h] * kLog2e : 0.f;
-    const bool need_mask = doc_mask || (MASK & kMaskCustom) != 0 || ib + 31 >= p.Sq || !bounds.whole(ib + p.q_off, ib + 31 + p.q_off);
+    const bool need_mask = doc_mask || (MASK & kMaskCustom) != 0 || ib + 31 >= p.Sq || (POS == 0 ? jw + 31 >= p.Sk : !bounds.whole(ib + p.q_off, ib + 31 + p.q_off));
     // lane addresses: row reads of the next block (Q fragments, then dO), transposing reads of the current one (dO, then Q)
     uint32_t ra_n[KK + KV], ta_c[DBV + DB][2];
 #pragma unroll
@@ -1535,7 +1535,7 @@ bwd_dkdv_ws_kernel(const BwdParams p) {
       const int t = t_lo + it % nt, h = h_first + it / nt;
       const int ib = t * BN + 32 * QB;
       const float slope2 = C::MOD == kModAlibi ? p.alibi_slopes[h] * kLog2e : 0.f;
-      const bool need_mask = dm0 || ib + 31 >= p.Sq || !bounds.whole(ib + p.q_off, ib + 31 + p.q_off);
+      const bool need_mask = dm0 || ib + 31 >= p.Sq || (POS == 0 ? jw + 31 >= p.Sk : !bounds.whole(ib + p.q_off, ib + 31 + p.q_off));
       uint32_t ra_n[KK];
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) ra_n[kk] = w.ra[kk] + base_n;
