@@ -1324,6 +1324,9 @@ hipError_t run_pair_bwd(const fl::BwdParams& call, const PairLayout& P, int D, i
     p.n_own = (own + 63) / 64;
     const int64_t units = (int64_t)B * H * chunks;
     p.xcd = units % 8 == 0;
+    p.by_own = fl::Divisor::of(p.n_own);
+    p.by_chunks = fl::Divisor::of(chunks);
+    p.by_h = fl::Divisor::of(H);
     return (D == 32 ? fl::launch_pair32 : fl::launch_pair64)((streamed + 127) / 128, role, keyb >= 0, p, (int)(units * p.n_own), stream);
   };
   p.bias_part = dbias[pair].ptr != nullptr ? (float*)(ws + P.off_part) : nullptr;
@@ -2341,6 +2344,11 @@ fl_status fl_attn_decode(const fl_tensor* q, const fl_tensor* k_cache, const fl_
   p.part_ml = p.part_o + B * T * H * ns * D;
   p.alibi_slopes = aux->alibi_slopes;
   p.B = (int)B; p.H = (int)H; p.Hkv = (int)Hkv; p.nsplit = ns; p.T = (int)T;
+  p.by_split = fl::Divisor::of(ns);
+  p.by_hkv = fl::Divisor::of(Hkv);
+  p.by_group = fl::Divisor::of(H / Hkv);
+  p.by_h = fl::Divisor::of(H);
+  p.by_t = fl::Divisor::of(T);
   p.max_len = kv->max_seq_len;
   p.num_pages = (int)pages;
   p.window = (mask & FL_MASK_WINDOW) ? clamp_window(desc->window, kv->max_seq_len, kv->max_seq_len) : -1;

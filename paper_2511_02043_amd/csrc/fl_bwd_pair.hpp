@@ -37,6 +37,7 @@ struct PairParams {
   int32_t chunks;                  // the problems g of a (b, h) are cut into this many ranges, one workgroup each
   int32_t n_own;                   // ceil(rows of the owned axis / 64)
   int32_t xcd;                     // 1: the tiles of a (b, h, chunk) run on one XCD (chunks * B * H % 8 == 0)
+  Divisor by_own, by_chunks, by_h; // n_own, chunks, H
 };
 
 // ROLE 0: dQ and the pair bias gradient (streams K, V); 1: dK, dV and the key bias gradient (streams Q, dO).
@@ -108,15 +109,19 @@ bwd_pair_kernel(const PairParams pp) {
   // 8 XCDs; the host checks that the number of units is a multiple of 8).
   int unit, ot;
   if (pp.xcd == 1) {
-    const int idx = blockIdx.x >> 3;
-    unit = (idx / pp.n_own) * 8 + (blockIdx.x & 7);
-    ot = idx % pp.n_own;
+    pp.by_own.split(blockIdx.x >> 3, unit, ot);
+    unit = unit * 8 + (int)(blockIdx.x & 7);
   } else {
-    unit = blockIdx.x / pp.n_own;
-    ot = blockIdx.x % pp.n_own;
+    pp.by_own.split(blockIdx.x, unit, ot);
   }
-  const int chunk = unit % pp.chunks, bh = unit / pp.chunks, h = bh % p.H, b = bh / p.H;
-  const int g_lo = (int)((int64_t)p.G * chunk / pp.chunks), g_hi = (int)((int64_t)p.G * (chunk + 1) / pp.chunks);
+  int bh, chunk, h, b;
+  pp.by_chunks.split(unit, bh, chunk);
+  pp.by_h.split(bh, b, h);
+  auto first_problem = [&](int c) __attribute__((always_inline)) -> int {
+    const int64_t n = (int64_t)p.G * c;
+    return n <= 0x7fffffff ? pp.by_chunks.div((int)n) : (int)(n / pp.chunks);
+  };
+  const int g_lo = first_problem(chunk), g_hi = first_problem(chunk + 1);
   const int n_prob = g_hi - g_lo;                  // (at least one: chunks <= G)
   const int S_own = ROLE == 0 ? p.Sq : p.Sk, S_str = ROLE == 0 ? p.Sk : p.Sq;
   const int o0 = ot * 64;                          // first owned row of the workgroup

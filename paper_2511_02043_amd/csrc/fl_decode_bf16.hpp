@@ -46,6 +46,7 @@ struct DecodeParams {
   int32_t max_len;                 // the host-side bound of seq_lens that sized the launch, the table and the workspace
   int32_t window;                  // < 0: no window
   float scale, softcap;
+  Divisor by_split, by_hkv, by_group, by_h, by_t;   // nsplit, Hkv, H / Hkv, H, T: the lengths, the pages and the tiles are loads one after the other behind them
 };
 
 // Waves per workgroup where the launch has a workgroup per CU at most, or a workgroup enough tiles for them (decode_waves() chooses)
@@ -90,10 +91,10 @@ decode_kernel(const DecodeParams p) {
   w.init(tid & 63);
   const int lane = w.lane;
 
-  const int split = blockIdx.x % p.nsplit;
-  const int bhk = blockIdx.x / p.nsplit;
-  const int hk = bhk % p.Hkv, b = bhk / p.Hkv;
-  const int group = p.H / p.Hkv;                   // query heads per kv head
+  int split, bhk, hk, b;
+  p.by_split.split(blockIdx.x, bhk, split);
+  p.by_hkv.split(bhk, b, hk);
+  const int group = (int)p.by_group.d;             // query heads per kv head
   const int ncol = p.T * group;                    // (row, head) pairs of this kv head (<= 32 * CB)
   // a length outside [0, max_len] would walk past the block table: such a sequence is cut to the bound
   const int len = min(max(p.seq_lens[b], 0), p.max_len);
@@ -105,8 +106,9 @@ decode_kernel(const DecodeParams p) {
     const int c = 32 * cb + w.col;
     live[cb] = c < ncol;
     const int cc = live[cb] ? c : ncol - 1;
-    row[cb] = cc / group;
-    hq[cb] = hk * group + cc % group;
+    int head;
+    p.by_group.split(cc, row[cb], head);
+    hq[cb] = hk * group + head;
     pos[cb] = len - p.T + row[cb];                 // negative: a row before the sequence's first token sees no key
   }
 
@@ -115,7 +117,7 @@ decode_kernel(const DecodeParams p) {
   // tiles that start before the newest row's first key, or end after the oldest row's position, hide scores
   const int first_full = p.window >= 0 ? max(0, len - 1 - p.window) : 0;
   const int t_lo = first_key / BN, t_hi = (len + BN - 1) / BN;
-  const int per_split = (t_hi - t_lo + p.nsplit - 1) / p.nsplit;
+  const int per_split = p.by_split.div(t_hi - t_lo + p.nsplit - 1);   // (a sequence without tiles: t_lo <= t_hi all the same)
   const int t_begin = t_lo + split * per_split, t_end = min(t_hi, t_begin + per_split);
 
   bf16x8 qf[CB][KK];
@@ -404,7 +406,9 @@ __global__ void __launch_bounds__(64) decode_combine_kernel(const DecodeParams p
       acc.w += __shfl_xor(acc.w, o);
     }
   }
-  const int h = bh % p.H, row = (bh / p.H) % p.T, b = bh / p.H / p.T;
+  int h, row, b, bt;
+  p.by_h.split(bh, bt, h);
+  p.by_t.split(bt, b, row);
   const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
   const int64_t o = b * p.o_sb + h * p.o_sh + row * p.o_st + lane * 4;
   if (lane < LPR) {

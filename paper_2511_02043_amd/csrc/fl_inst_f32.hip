@@ -4,7 +4,11 @@
 #include "fl_kernel_f32.hpp"
 namespace fl {
 template <class C>
-static hipError_t launch_f32(const FwdParams& p, int nblocks, hipStream_t stream) {
+static hipError_t launch_f32(const FwdParams& call, int nblocks, hipStream_t stream) {
+  FwdParams p = call;
+  p.order_heads = 1;                               // (its tiles go out one problem after the other)
+  p.tile_step = 0;
+  set_divisors(p, 1);
   static std::atomic<bool> done[64];               // the dynamic-LDS limit is per device and sticky, as in launch_bf16
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);

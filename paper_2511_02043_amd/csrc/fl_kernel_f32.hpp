@@ -192,15 +192,16 @@ fwd_f32_kernel(const FwdParams p) {
   const int nq = p.n_qtiles;
   int qt, bh;
   if (p.order == 1) {
-    const int idx = blockIdx.x >> 3;
-    bh = (idx / nq) * 8 + (blockIdx.x & 7);
-    qt = nq - 1 - idx % nq;
+    p.by_tiles.split(blockIdx.x >> 3, bh, qt);
+    bh = bh * 8 + (int)(blockIdx.x & 7);
   } else {
-    bh = blockIdx.x / nq;
-    qt = nq - 1 - (int)(blockIdx.x % nq);
+    p.by_tiles.split(blockIdx.x, bh, qt);
   }
-  const int h = bh % p.H, g = (bh / p.H) % p.G, b = bh / (p.H * p.G);
-  const int hk = h / (p.H / p.Hkv);
+  qt = nq - 1 - qt;
+  int bg, h, b, g;
+  p.by_heads.split(bh, bg, h);
+  p.by_g.split(bg, b, g);
+  const int hk = p.by_group.div(h);
   const int i0 = qt * C::BM, iw = i0 + C::WROWS * rg;    // first query row of the workgroup / of the wave
   const int ns = !C::PLAIN && p.diff ? 2 : 1;                   // softmax streams, one after the other
 
