@@ -114,9 +114,15 @@ __device__ __forceinline__ int swz_u(int r) {
   else return (r >> 2) & 3;                        // 64-byte rows: four of them are one line of all banks
 }
 
+// a + b for a, b >= 0, not past the largest number (a key and a window may each have 31 bits)
+__host__ __device__ __forceinline__ int capped_sum(int a, int b) {
+  const uint32_t sum = (uint32_t)a + (uint32_t)b;
+  return sum > 0x7fffffffu ? 0x7fffffff : (int)sum;
+}
+
 // Query rows [lo, hi) that can see any key in [j_lo, j_hi] under the positional masks.
-__device__ __forceinline__ void query_range(const uint32_t MASK, int j_lo, int j_hi, int Sq, int window, int prefix,
-                                            int& lo, int& hi) {
+__host__ __device__ __forceinline__ void query_range(const uint32_t MASK, int j_lo, int j_hi, int Sq, int window, int prefix,
+                                                     int& lo, int& hi) {
   lo = 0;
   hi = Sq;
   if ((MASK & kMaskPrefix) != 0) {
@@ -124,7 +130,7 @@ __device__ __forceinline__ void query_range(const uint32_t MASK, int j_lo, int j
   } else if ((MASK & (kMaskCausal | kMaskWindow)) != 0) {
     lo = j_lo;
   }
-  if ((MASK & kMaskWindow) != 0) hi = min(Sq, j_hi + window + 1);
+  if ((MASK & kMaskWindow) != 0) hi = min(Sq, capped_sum(j_hi, window + 1));
   lo = min(lo, hi);
 }
 
@@ -133,10 +139,10 @@ __device__ __forceinline__ void query_range(const uint32_t MASK, int j_lo, int j
 constexpr int kFarBelow = -0x7fffffff - 1, kFarAbove = 0x7fffffff;
 struct KeyBounds {                                 // of rows at the positions [q_lo, q_hi]
   int end, first, whole_last, whole_first;
-  __device__ __forceinline__ bool hidden(int k_lo, int k_hi) const { return k_lo >= end || k_hi < first; }
-  __device__ __forceinline__ bool whole(int k_lo, int k_hi) const { return k_hi <= whole_last && k_lo >= whole_first; }
+  __host__ __device__ __forceinline__ bool hidden(int k_lo, int k_hi) const { return k_lo >= end || k_hi < first; }
+  __host__ __device__ __forceinline__ bool whole(int k_lo, int k_hi) const { return k_hi <= whole_last && k_lo >= whole_first; }
 };
-__device__ __forceinline__ KeyBounds key_bounds(const uint32_t MASK, int q_lo, int q_hi, int Sk, int window, int prefix) {
+__host__ __device__ __forceinline__ KeyBounds key_bounds(const uint32_t MASK, int q_lo, int q_hi, int Sk, int window, int prefix) {
   KeyBounds b = {Sk, kFarBelow, Sk - 1, kFarBelow};
   if ((MASK & kMaskPrefix) != 0) {
     b.end = min(Sk, max(q_hi + 1, prefix));
@@ -153,10 +159,10 @@ __device__ __forceinline__ KeyBounds key_bounds(const uint32_t MASK, int q_lo, i
 }
 struct RowBounds {                                 // of the keys [k_lo, k_hi]; rows as positions
   int first, last, whole_first, whole_last;
-  __device__ __forceinline__ bool hidden(int q_lo, int q_hi) const { return q_hi < first || q_lo > last; }
-  __device__ __forceinline__ bool whole(int q_lo, int q_hi) const { return q_lo >= whole_first && q_hi <= whole_last; }
+  __host__ __device__ __forceinline__ bool hidden(int q_lo, int q_hi) const { return q_hi < first || q_lo > last; }
+  __host__ __device__ __forceinline__ bool whole(int q_lo, int q_hi) const { return q_lo >= whole_first && q_hi <= whole_last; }
 };
-__device__ __forceinline__ RowBounds row_bounds(const uint32_t MASK, int k_lo, int k_hi, int Sk, int window, int prefix) {
+__host__ __device__ __forceinline__ RowBounds row_bounds(const uint32_t MASK, int k_lo, int k_hi, int Sk, int window, int prefix) {
   RowBounds b = {kFarBelow, kFarAbove, kFarBelow, kFarAbove};
   if ((MASK & kMaskPrefix) != 0) {
     if (k_lo >= prefix) b.first = k_lo;
@@ -166,8 +172,8 @@ __device__ __forceinline__ RowBounds row_bounds(const uint32_t MASK, int k_lo, i
     b.whole_first = k_hi;
   }
   if ((MASK & kMaskWindow) != 0) {
-    b.last = min(k_hi, Sk - 1) + window;
-    b.whole_last = k_lo + window;
+    b.last = capped_sum(min(k_hi, Sk - 1), window);
+    b.whole_last = capped_sum(k_lo, window);
   }
   if (k_lo >= Sk) b.last = kFarBelow;
   if (k_hi >= Sk) b.whole_first = kFarAbove;

@@ -172,7 +172,7 @@ __device__ __forceinline__ bool is_masked(const uint32_t MASK, int i, int j, int
 
 // Key range [lo, hi) that can be visible to any query row in [i_min, i_max] under the
 // positional masks (document masks are handled per tile through the summaries).
-__device__ __forceinline__ void key_range(const uint32_t MASK, int i_min, int i_max, int Sk,
+__host__ __device__ __forceinline__ void key_range(const uint32_t MASK, int i_min, int i_max, int Sk,
                                           int window, int prefix, int& lo, int& hi) {
   lo = 0;
   hi = Sk;
@@ -189,7 +189,7 @@ enum BlockClass : int { kSkip = 0, kFull = 1, kPartial = 2 };
 
 // Classify the block of query rows [q_lo, q_hi] x keys [k_lo, k_hi] (all inclusive, k_hi may
 // exceed Sk - 1 for a ragged tail): kSkip = every score masked, kFull = none masked.
-__device__ __forceinline__ int classify_block(const uint32_t MASK, int q_lo, int q_hi, int k_lo,
+__host__ __device__ __forceinline__ int classify_block(const uint32_t MASK, int q_lo, int q_hi, int k_lo,
                                               int k_hi, int Sk, int window, int prefix, int2 qs,
                                               int2 ks) {
   if (k_lo >= Sk) return kSkip;
@@ -216,7 +216,7 @@ __device__ __forceinline__ int classify_block(const uint32_t MASK, int q_lo, int
 // Tiles of BN keys that are fully visible (classify_block == kFull) to the query rows
 // [q_lo, q_hi] under the positional masks form one range [lo, hi); this is that range in closed
 // form (document masks need the per-tile summaries instead).
-__device__ __forceinline__ void full_tile_range(const uint32_t MASK, int q_lo, int q_hi, int Sk, int window,
+__host__ __device__ __forceinline__ void full_tile_range(const uint32_t MASK, int q_lo, int q_hi, int Sk, int window,
                                                 int prefix, int BN, int& lo, int& hi) {
   lo = 0;
   hi = Sk / BN;                                    // tiles that end inside the key range
