@@ -36,7 +36,8 @@ constexpr uint32_t kHiddenBits = 0xff7ffffdu;     // -3.4e38
 // vector registers, it moves the accumulators through them: 178 registers in scratch).  The compiler keeps no wait states for an instruction that it cannot see, so
 // they are part of the statement: two where the vector ALU may have written b just before (FRESH), else one.  Nothing else can be needed: a has
 // come from LDS behind a wait, the results go to registers that no other instruction reads or writes before the loop has ended, and an
-// accumulator's next product comes several MFMAs later, which the hardware would hold back anyway.
+// accumulator's next product comes several MFMAs later, which the hardware would hold back anyway.  A copy of a or b that the compiler put in front
+// would need two as well (two everywhere: 1 % of the kernel); there is none, and the build looks for one in the assembly (check_wide.py).
 template <bool FRESH>
 __device__ __forceinline__ void mfma_acc(f32x16& acc, bf16x8 a, bf16x8 b) {
   asm volatile("s_nop %3\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b), "n"(FRESH ? 1 : 0));
@@ -156,7 +157,9 @@ bwd_dkdv_wide_kernel(const BwdParams p) {
 #pragma unroll
   for (int d = 0; d < DBV; ++d) dv[d][0] = dv[d][1] = W::zero16();
   f32x16 s[2], dp[2];                              // scores, then P; delta - dP
-  i32x4 fr[X::PD];                                 // fragments in flight
+  // fragments in flight: by rows, transposed (two reads each, put together behind their wait: until then the compiler has no use of either)
+  i32x4 fr[X::PD];
+  i32x2 lo[X::PD], hi[X::PD];
   i32x4 lse[4], del[4];
   uint32_t pw[2][8], dw[2][8];                     // bf16 pairs of P and of -dS
 
@@ -166,24 +169,20 @@ bwd_dkdv_wide_kernel(const BwdParams p) {
     constexpr bool NEXT = F >= X::NS;
     constexpr int f = NEXT ? F - X::NS : F, QB = NEXT ? decltype(qn_c)::value : decltype(qb_c)::value, QN = decltype(qn_c)::value;
     const uint32_t base = NEXT ? nxt : cur;
-    i32x4& dst = fr[F % X::PD];
+    constexpr int slot = F % X::PD;
     if constexpr (f < X::N1) {
-      W::template read_b128<C::TILE + QB * 32 * ROWV>(dst, (rv0 + base) ^ (f * 32));
+      W::template read_b128<C::TILE + QB * 32 * ROWV>(fr[slot], (rv0 + base) ^ (f * 32));
     } else if constexpr (f < X::N1 + X::N2) {
       constexpr int d = (f - X::N1) % DBV, ks = (f - X::N1) / DBV, off = C::TILE + (QB * 32 + ks * 16) * ROWV;
-      i32x2 lo, hi;
-      W::template read_tr<off>(lo, (tv0 + base) ^ (d * 64));
-      W::template read_tr<off + 8 * ROWV>(hi, (tv0 + base) ^ (d * 64 + 32));
-      dst = (i32x4){lo[0], lo[1], hi[0], hi[1]};
+      W::template read_tr<off>(lo[slot], (tv0 + base) ^ (d * 64));
+      W::template read_tr<off + 8 * ROWV>(hi[slot], (tv0 + base) ^ (d * 64 + 32));
     } else if constexpr (f < X::N1 + X::N2 + X::N3) {
       constexpr int d = (f - X::N1 - X::N2) % DB, ks = (f - X::N1 - X::N2) / DB, off = (QB * 32 + ks * 16) * ROW;
-      i32x2 lo, hi;
-      W::template read_tr<off>(lo, (tq0 + base) ^ (d * 64));
-      W::template read_tr<off + 8 * ROW>(hi, (tq0 + base) ^ (d * 64 + 32));
-      dst = (i32x4){lo[0], lo[1], hi[0], hi[1]};
+      W::template read_tr<off>(lo[slot], (tq0 + base) ^ (d * 64));
+      W::template read_tr<off + 8 * ROW>(hi[slot], (tq0 + base) ^ (d * 64 + 32));
     } else {
       constexpr int kk = f - X::N1 - X::N2 - X::N3;
-      W::template read_b128<QN * 32 * ROW>(dst, (rq0 + nxt) ^ (kk * 32));
+      W::template read_b128<QN * 32 * ROW>(fr[slot], (rq0 + nxt) ^ (kk * 32));
     }
   };
   // LDS instructions of fragment F
@@ -292,7 +291,9 @@ bwd_dkdv_wide_kernel(const BwdParams p) {
       static_assert(behind(f) <= 15, "lgkmcnt is a 4-bit counter");
       constexpr int extra = f >= STAT0 && f < STAT0 + 8 ? 1 : 0;
       W::template wait_lds<behind(f) + extra>();
-      const bf16x8 a = __builtin_bit_cast(bf16x8, fr[f % X::PD]);
+      constexpr int slot = f % X::PD;
+      constexpr bool tr = f >= X::N1 && f < X::N1 + X::N2 + X::N3;
+      const bf16x8 a = __builtin_bit_cast(bf16x8, tr ? (i32x4){lo[slot][0], lo[slot][1], hi[slot][0], hi[slot][1]} : fr[slot]);
       static_for<0, 2>([&](auto khc) __attribute__((always_inline)) {
         constexpr int kh = decltype(khc)::value;
         if constexpr (f < X::N1) {
