@@ -345,25 +345,35 @@ hipError_t run_bwd_dq(const fl::BwdEntry* be, const fl::BwdParams& p_in, int nbl
   p.by_g = fl::Divisor::of(p.G);
   return be->jit != nullptr ? fl::jit_backward_launch(*be, 0, p, nblocks, stream) : be->dq(p, nblocks, stream);
 }
-// The dK/dV kernel with 64 keys per wave where the variant has one, the call suits it and its workgroups of 256 keys leave the 256 compute
-// units little more idle than those of 128 keys do.  Alike at work it is 1.2 - 1.35 times as fast (us, partial sums added, 128 / 256 keys, D = 128: causal
-// 8 x 16 heads x 1024 125 / 105, 16 x 16 x 512 92 / 84, 2 x 32/8 x 2048 202 / 170, 64 x 8 x 256 74 / 71; no mask 2 x 16 x 2048 152 / 119,
-// 1 x 16/2 x 4096 293 / 230, 64 x 8 x 256 81 / 67), with a third more idle about as fast (causal 5 x 16 x 1777 180 / 163, 3 x 16 x 2048 139 / 122, no mask 3 x 16 x 2048
-// 229 / 218), with half of them idle slower (causal 4 x 16 x 1024 63.0 / 69.6, 1 x 16/2 x 4096 166 / 203, 1 x 8 x 1024 39.5 / 59.7).
+// The dK/dV kernel with 64 keys per wave where the variant has one, the call suits it and its launch is not longer than that of 128 keys per
+// workgroup by more than it is faster.  At work it is 1.2 - 1.3 times as fast (soft-cap 1.17), so what decides is how many more keys its
+// workgroups of 256 go through in a row on a compute unit: rows past a short sequence's end, a last round half empty, and a start that nothing hides.
+// Over 600 drawn dK / dV launches at D = 128 the choice is 0.3 % off the faster kernel on average; a rule by keys alone, 1.34 times as many at
+// most, was 1.5 % off and up to 31 % slower than 128 keys.  us, 128 / 256 keys: taken causal 3 x 16 x 3885 411 / 357, 6 x 16 x 1641 180 / 166, prefix 5 x 16 x 1490 132 / 120,
+// no mask 64 x 16/2 x 777 850 / 803, ALiBi 10 x 32/8 x 1284 856 / 722, soft-cap 15 x 16 x 1349 664 / 622; not taken causal 18 x 16 x 289 53 / 69, 64 x 16 x 320 176 / 216,
+// no mask 64 x 8 x 278 104 / 120, 3 x 16 x 1842 197 / 213, ALiBi 8 x 16/2 x 1386 334 / 352, soft-cap 6 x 16 x 843 123 / 142, 2 x 16/2 x 2838 356 / 404.
 const fl::WideEntry* wide_dkdv(const fl::BwdEntry* be, const fl::BwdParams& p) {
   if (be->jit != nullptr || g_tuning.bwd_keys == 1) return nullptr;
   const fl::WideEntry* w = fl::find_wide(be->key);
   // it forms a row's offset in a tile with 24-bit products
   if (w == nullptr || p.q.ss >= (1 << 23) || p.dout.ss >= (1 << 23)) return nullptr;
   if (g_tuning.bwd_keys == 2) return w;
-  const int64_t problems = (int64_t)p.B * p.G * p.Hkv * p.hsplit;
-  // A launch's time in keys of one workgroup after the other on a compute unit.  Under a positional mask a workgroup has half of the longest
-  // one's rows on average, and the longest start first.
-  auto keys = [&](int bm) {
-    const int64_t wgs = problems * ((p.Sk + bm - 1) / bm);
-    return bm * (be->key.mask != 0 ? std::max(1.0, wgs / 512.0) : (double)((wgs + 255) / 256));
+  const int64_t problems = (int64_t)p.B * p.G * p.Hkv * p.hsplit, heads = p.H / std::max(p.Hkv, 1) / std::max(p.hsplit, 1);
+  const bool masked = be->key.mask != 0;
+  // Length of the launch, in keys times (head, 64 rows) items of one compute unit.  `start`: what a workgroup takes beside its items, in items.  Tile by
+  // tile, the last round is filled up with the shortest workgroups; problem by problem under a mask, a long one may be the last.
+  auto length = [&](int bm, int start, bool by_tile) {
+    const int64_t n = (p.Sk + bm - 1) / bm;
+    auto items = [&](int64_t j) {                  // of the workgroup whose first key is j
+      const int64_t rows = masked ? std::max<int64_t>(0, p.Sq - std::max<int64_t>(0, j - p.q_off)) : p.Sq;
+      return (double)(heads * ((rows + 63) / 64) + start);
+    };
+    const double first = items(0), last = items((n - 1) * bm), rounds = problems * n / 256.0;
+    return bm * std::max(first, rounds * (first + last) / 2 + (by_tile ? (std::ceil(rounds) - rounds) * last : 0.75 * first));
   };
-  return keys(w->bm) <= 1.34 * keys(be->bm) ? w : nullptr;
+  const int64_t n = (p.Sk + be->bm - 1) / be->bm;
+  const double most = be->key.mod == (int)fl::kModSoftcap ? 1.25 : masked ? 1.4 : 1.34;
+  return length(w->bm, 8, true) <= most * length(be->bm, 6, !masked || longest_first(be->key.mask, be->key.D, be->key.Dv, problems, n)) ? w : nullptr;
 }
 hipError_t run_bwd_dkdv(const fl::BwdEntry* be, const fl::WideEntry* wide, const fl::BwdParams& p, int64_t problems, hipStream_t stream) {
   fl::BwdParams pk = p;

@@ -85,3 +85,36 @@ def test_same_as_128_keys_and_reproducible():
         diff = got[0][n] - got[3][n]
         assert np.sqrt(np.sum(diff * diff) / np.sum(got[3][n] ** 2)) < 1e-3
     assert not np.array_equal(got[0][0], got[3][0])          # two kernels, not one
+
+
+@pytest.mark.parametrize("variant,B,H,Hkv,S,wide", [
+    ("causal", 18, 16, 16, 289, False), ("causal", 6, 16, 16, 1641, True), ("causal", 2, 16, 2, 807, False), ("prefix", 5, 16, 16, 1490, True),
+    ("plain", 7, 32, 32, 370, False), ("plain", 8, 16, 16, 977, True), ("alibi", 2, 8, 8, 588, False), ("alibi", 5, 32, 32, 241, True),
+    ("softcap", 6, 16, 16, 843, False), ("softcap", 3, 16, 16, 800, True), ("softcap", 64, 8, 8, 351, False)])
+def test_kernel_of_a_call(variant, B, H, Hkv, S, wide):
+    """The faster kernel of the two, as measured for these calls; the last bits of dK tell which one ran."""
+    gen = torch.Generator(device="cuda:0").manual_seed(S)
+    q, k, v, dout = (torch.randn(B, 1, h, S, 128, generator=gen, device="cuda:0").to(torch.bfloat16) for h in (H, Hkv, Hkv, H))
+    desc = fb.variant_desc(scale=128 ** -0.5, mask={"causal": fb.FL_MASK_CAUSAL, "prefix": fb.FL_MASK_PREFIX}.get(variant, 0), prefix_len=256 if variant == "prefix" else 0,
+                           score_mod={"alibi": fb.FL_MOD_ALIBI, "softcap": fb.FL_MOD_SOFTCAP}.get(variant, 0), softcap=30.0 if variant == "softcap" else 0.0)
+    slopes = torch.linspace(0.01, 0.5, H, device="cuda:0") if variant == "alibi" else None
+    out, lse = torch.empty_like(q), torch.empty(B, 1, H, S, 1, device="cuda:0")
+    grads = [torch.empty(x.shape, device="cuda:0") for x in (q, k, v)]
+    t = [fb.tensor_desc(x) for x in (q, k, v, out, dout, lse, *grads)]
+    need = max(fb.fl_attn_fwd_workspace_size(t[0], t[1], desc), fb.fl_attn_bwd_workspace_size(t[0], t[1], desc), 16)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+    aux = fb.aux_desc(alibi_slopes=slopes, workspace=ws)
+    stream = torch.cuda.current_stream().cuda_stream
+    fb.check(fb.fl_attn_fwd(t[0], t[1], t[2], desc, aux, t[3], t[5], stream))
+    got = []
+    for keys in (0, 1, 2):
+        fb.check(fb.fl_set_tuning("bwd_keys", keys))
+        try:
+            grads[1].fill_(float("nan"))
+            fb.check(fb.fl_attn_bwd(*t[:6], desc, aux, *t[6:], stream))
+            torch.cuda.synchronize()
+        finally:
+            fb.fl_set_tuning("bwd_keys", 0)
+        got.append(grads[1].clone())
+    assert not torch.equal(got[1], got[2])
+    assert torch.equal(got[0], got[2 if wide else 1])
