@@ -604,12 +604,19 @@ static fl_status custom_forward(fl_custom_variant* v, const fl_tensor* q, const 
   const int64_t nbh = B * G * H;
   p.order = nbh % 8 == 0 ? 1 : 0;
   p.order_heads = 1;
-  // under a causal / prefix base mask without a window a workgroup takes a long and a short q-tile; under a mask expression with a map, which
-  // may leave anything of them, the q-tiles of all problems go out by themselves, the last ones first
+  // Under a causal / prefix base mask without a window a workgroup takes a long and a short q-tile.  A mask expression with a map may leave anything of
+  // them, equal halves of a launch or a few long tiles: its q-tiles go out by themselves, the last ones of all problems first, but for few tiles per
+  // problem whose pairs come out as whole rounds of the compute units (as in forward_call): there pairs are ahead whatever is hidden.  us, pairs / tiles, one
+  // key in 64 hidden and 12 documents: D = 128 16 x 16 heads x 1024 135 / 143 and 126 / 129, 32 x 8 x 1024 136 / 142 and 133 / 140, 16 x 16 x 1500 253 / 264 and 203 / 208,
+  // 64 x 8 x 300 82 / 84 and 89 / 91, D = 64 64 x 16 x 256 52 / 54 and 65 / 65; beyond, the documents decide: D = 128 16 x 16 x 2048 415 / 427 and 308 / 288,
+  // 4 x 16 x 4096 347 / 357 and 201 / 188, D = 64 64 x 16 x 500 120 / 123 and 140 / 131, 1 x 16 x 8192 255 / 267 and 153 / 101.
   const bool tri = (v->mask & (FL_MASK_CAUSAL | FL_MASK_PREFIX)) != 0 && (v->mask & FL_MASK_WINDOW) == 0;
+  const int64_t pairs = nbh * ((p.n_qtiles + 1) / 2), round = 256 * 8 / v->waves;
+  const bool filled = 10 * nbh * p.n_qtiles >= 16 * round * ((pairs + round - 1) / round);
+  const bool few = p.n_qtiles % 2 == 0 && p.n_qtiles <= (D == 128 ? 6 : 2);
   const bool mapped = skip && v->has_mask_expr;
-  p.pair = tri && !mapped && nbh * ((p.n_qtiles + 1) / 2) >= 512;
-  p.tile_step = mapped ? (int)(p.order == 1 ? nbh / 8 : nbh) : 0;
+  p.pair = tri && pairs >= 512 && (!mapped || (filled && few));
+  p.tile_step = mapped && !p.pair ? (int)(p.order == 1 ? nbh / 8 : nbh) : 0;
   const int64_t nblocks = nbh * (p.pair ? (p.n_qtiles + 1) / 2 : p.n_qtiles);
   if (nblocks > 0x7fffffffLL) return fl::host::fail(FL_ERR_SHAPE, "too many workgroups");
   if (mapped) {

@@ -73,3 +73,31 @@ def test_rows_hidden_by_a_finite_score(far):
     # lse: the product far * log2(e) and its way back are rounded to fp32
     assert float(np.max(np.abs(dw.lse.cpu().numpy()[..., 0] - ref_lse) / (1e-3 + 2.0 ** -22 * np.abs(ref_lse)))) <= 1.0
     var.release()
+
+
+@pytest.mark.parametrize("B,H,S,D", [(64, 8, 300, 128), (64, 8, 500, 128), (33, 16, 770, 128), (64, 8, 250, 64), (72, 8, 129, 64)])
+@pytest.mark.parametrize("hidden", ["documents", "columns"])
+def test_pairs_of_tiles_with_a_map(hidden, B, H, S, D):
+    """Launches whose workgroups take a long and a short q-tile, with the classes of the pre-pass: the bits of the call without them, and fp32 torch."""
+    import torch
+    dev = "cuda:0"
+    gen = torch.Generator(device=dev).manual_seed(S)
+    q, k, v = (torch.randn(B, 1, H, S, D, generator=gen, device=dev).to(torch.bfloat16) for _ in range(3))
+    ids = torch.from_numpy(inputs.doc_ids(B, S, seed=5, lo=20, hi=90)).to(dev)
+    mask, aux = ("aux0[b * Sq + i] != aux0[b * Sk + j]", [ids]) if hidden == "documents" else ("(j % 64) == 5", [])
+    var = fb.CustomVariant(None, mask, D, aux=aux, base_mask=fb.FL_MASK_CAUSAL)
+    t = [fb.tensor_desc(x) for x in (q, k, v)]
+    got = []
+    for ws in (None, torch.empty(var.skip_workspace_size(t[0], t[1]), dtype=torch.uint8, device=dev)):
+        out, lse = torch.full_like(q, float("nan")), torch.full((B, 1, H, S, 1), float("nan"), device=dev)
+        fb.check(var.forward(*t, D ** -0.5, fb.tensor_desc(out), fb.tensor_desc(lse), workspace=ws))
+        torch.cuda.synchronize()
+        got.append((out, lse))
+    var.release()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    i = torch.arange(S, device=dev)
+    for b in range(0, B, 9):
+        off = (i[None, :] > i[:, None]) | ((ids[b][:, None] != ids[b][None, :]) if hidden == "documents" else (i[None, :] % 64 == 5))
+        s = (torch.matmul(q[b, 0].float(), k[b, 0].float().transpose(-1, -2).contiguous()) * D ** -0.5).masked_fill(off, float("-inf"))
+        ref = torch.matmul(torch.softmax(s, -1), v[b, 0].float())
+        assert float((got[1][0][b, 0].float() - ref).abs().max()) <= 2e-2    # the output's own rounding to bf16, values up to 4
