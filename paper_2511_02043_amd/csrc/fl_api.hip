@@ -324,11 +324,31 @@ const fl::BwdEntry* find_bwd_entry(const fl_variant_desc* d, int D, int nbias = 
   return nullptr;
 }
 
+// `mask` where it hides anything: not a prefix over all keys, nor a causal mask whose rows all come behind them
+int64_t hiding_mask(int64_t mask, int64_t Sk, int64_t q_off, int64_t prefix) {
+  const bool nothing = (mask == FL_MASK_PREFIX && prefix >= Sk) || (mask == FL_MASK_CAUSAL && q_off >= Sk - 1);
+  return nothing ? 0 : mask;
+}
+
 // Do the longest tiles of all problems go out first, instead of one problem after the other?  Where a mask makes them unequal; at D = 128 many problems of few
 // tiles each are better off with their keys and values in an L2 (us, problem by problem / tile by tile: causal 20 x 16 heads x 600 forward 72 / 77, dQ 92 / 100, windows 64 x 8 x 300
-// dK / dV 93 / 100; the other way 30 x 8 x 500 dQ 62 / 55, 16 x 8 x 999 101 / 75), without a mask all are (D = 64, 64 x 8 x 300 dK / dV 52 / 57).
-bool longest_first(int64_t mask, int64_t D, int64_t Dv, int64_t problems, int64_t tiles) {
-  return mask != 0 && (std::max(D, Dv) < 128 || tiles >= 8 || problems * tiles <= 1024);
+// dK / dV 93 / 100; the other way 30 x 8 x 500 dQ 62 / 55, 16 x 8 x 999 101 / 75).  Below, over 90 drawn calls of more than 1024 tiles, all masks, 2 - 9 tiles a problem: the
+// forward pass and dQ are within 2 % either way on average (worst 11 and 4 % of the backward pass lost, best 13 and 5 % gained), dK / dV gains up to a quarter of the
+// backward pass (40 x 32/8 x 416 301 / 225).  Where nothing is hidden all are better off problem by problem (D = 64: 64 x 8 x 300 dK / dV 52 / 57, a prefix over all of 64 x 16 x 256
+// rows and 1024 keys forward 102 / 111, dQ and its backward pass 367 / 388).
+bool longest_first(int64_t hiding, int64_t D, int64_t Dv, int64_t problems, int64_t tiles) {
+  return hiding != 0 && (std::max(D, Dv) < 128 || tiles >= 8 || problems * tiles <= 1024);
+}
+
+// longest_first() for q-tiles of `rows` rows.  Where those of many problems see nearly the same keys, as a chunk's behind many cached ones does, they are better off side by side,
+// unless other heads read the same keys, too (D = 64, causal, the last rows of the keys, us problem by problem / tile by tile, forward and backward pass: 64 x 16 x 130 of 2000
+// 171 / 215 and 616 / 652, 128 x 8 x 256 of 1500 139 / 172 and 504 / 544, 64 x 16 x 256 of 1024 99 / 99 and 348 / 373; less alike 64 x 16 x 256 of 512 51 / 53 and 186 / 183,
+// 64 x 8 x 300 of 900 58 / 60 and 199 / 192; heads that share keys 64 x 16/2 x 256 of 1024 82 / 80 and 257 / 253).
+bool rows_longest_first(int64_t mask, int64_t D, int64_t Dv, int64_t Sq, int64_t Sk, int64_t q_off, int64_t prefix, int64_t rows, int64_t share, int64_t problems, int64_t tiles) {
+  auto seen = [&](int64_t i) { return std::min(Sk, std::max(i + q_off + 1, mask == FL_MASK_PREFIX ? prefix : 0)); };   // keys of row i
+  const bool alike = (mask == FL_MASK_CAUSAL || mask == FL_MASK_PREFIX) && 100 * seen(std::min(rows, Sq) - 1) >= 83 * seen(Sq - 1);
+  if (alike && share == 1 && tiles < 8 && problems * tiles > 1024) return false;
+  return longest_first(hiding_mask(mask, Sk, q_off, prefix), D, Dv, problems, tiles);
 }
 
 hipError_t run_bwd_dq(const fl::BwdEntry* be, const fl::BwdParams& p_in, int nblocks, hipStream_t stream) {
@@ -337,7 +357,8 @@ hipError_t run_bwd_dq(const fl::BwdEntry* be, const fl::BwdParams& p_in, int nbl
   const int64_t share = p.order_q ? p.order_heads : 1;
   // (documents alone, D = 128, heads that read the same keys: their tiles stay side by side; 2 x 16/2 x 11147 578 us, 600 tile by tile, 2 x 32/8 x 8525 651 and 648)
   const bool shared_documents = be->key.mask == (int)fl::kMaskDoc && share > 1 && std::max(be->key.D, be->key.Dv) >= 128;
-  p.step_q = !shared_documents && longest_first(be->key.mask, be->key.D, be->key.Dv, problems, p.n_qtiles) ? (p.order_q ? problems / 8 : problems) : 0;
+  p.step_q = !shared_documents && rows_longest_first(be->key.mask, be->key.D, be->key.Dv, p.Sq, p.Sk, p.q_off, p.prefix, be->bm, p.H / std::max(p.Hkv, 1), problems, p.n_qtiles)
+                 ? (p.order_q ? problems / 8 : problems) : 0;
   p.q_tiles = fl::Divisor::of(p.step_q > 0 ? p.step_q : p.n_qtiles * share);
   p.q_share = fl::Divisor::of(share);
   p.q_heads = fl::Divisor::of(p.H);
@@ -359,7 +380,8 @@ const fl::WideEntry* wide_dkdv(const fl::BwdEntry* be, const fl::BwdParams& p) {
   if (w == nullptr || p.q.ss >= (1 << 23) || p.dout.ss >= (1 << 23)) return nullptr;
   if (g_tuning.bwd_keys == 2) return w;
   const int64_t problems = (int64_t)p.B * p.G * p.Hkv * p.hsplit, heads = p.H / std::max(p.Hkv, 1) / std::max(p.hsplit, 1);
-  const bool masked = be->key.mask != 0;
+  const int64_t hiding = hiding_mask(be->key.mask, p.Sk, p.q_off, p.prefix);
+  const bool masked = hiding != 0;
   // Length of the launch, in keys times (head, 64 rows) items of one compute unit.  `start`: what a workgroup takes beside its items, in items.  Tile by
   // tile, the last round is filled up with the shortest workgroups; problem by problem under a mask, a long one may be the last.
   auto length = [&](int bm, int start, bool by_tile) {
@@ -373,7 +395,7 @@ const fl::WideEntry* wide_dkdv(const fl::BwdEntry* be, const fl::BwdParams& p) {
   };
   const int64_t n = (p.Sk + be->bm - 1) / be->bm;
   const double most = be->key.mod == (int)fl::kModSoftcap ? 1.25 : masked ? 1.4 : 1.34;
-  return length(w->bm, 8, true) <= most * length(be->bm, 6, !masked || longest_first(be->key.mask, be->key.D, be->key.Dv, problems, n)) ? w : nullptr;
+  return length(w->bm, 8, true) <= most * length(be->bm, 6, !masked || longest_first(hiding, be->key.D, be->key.Dv, problems, n)) ? w : nullptr;
 }
 hipError_t run_bwd_dkdv(const fl::BwdEntry* be, const fl::WideEntry* wide, const fl::BwdParams& p, int64_t problems, hipStream_t stream) {
   fl::BwdParams pk = p;
@@ -382,7 +404,8 @@ hipError_t run_bwd_dkdv(const fl::BwdEntry* be, const fl::WideEntry* wide, const
   const int nblocks = (int)(problems * pk.n_ktiles);
   // (Documents alone do not make the first key tiles the longest ones, and a problem's tiles in a row share the rows of their document; us, problem by problem / tile by tile, three
   // sets of 12 documents: 2 x 16/2 x 11147, D = 128 931 / 1052, D = 64 462 / 493, 2 x 32/8 x 8525, D = 128 1112 / 1233, 4 x 16 x 4096 351 / 356, 1 x 16 x 16000 799 / 812.)
-  const bool by_tile = wide != nullptr || (be->key.mask != (int)fl::kMaskDoc && longest_first(be->key.mask, be->key.D, be->key.Dv, problems, pk.n_ktiles));
+  const bool by_tile = wide != nullptr || (be->key.mask != (int)fl::kMaskDoc &&
+                                           longest_first(hiding_mask(be->key.mask, p.Sk, p.q_off, p.prefix), be->key.D, be->key.Dv, problems, pk.n_ktiles));
   pk.step_k = by_tile ? (int)(p.order_k ? problems / 8 : problems) : 0;
   pk.heads_kv = p.H / std::max(p.Hkv, 1);
   pk.heads_wg = pk.heads_kv / std::max(p.hsplit, 1);
@@ -1673,7 +1696,8 @@ static fl_status forward_call(const fl_tensor* q, const fl_tensor* k, const fl_t
   // windows and documents 8 x 16 x 1500 64 / 56 and 98 / 83; documents 4 x 16 x 4096 123 / 116 and 184 / 171; windows, whose tiles are nearly alike,
   // 32 x 8 x 500 30 / 24 and 45.7 / 44.9, 4 x 16 x 4096 67 / 65 and 112.5 / 115.3: not at D = 128).  Chunks of sequences go out by their keys.
   const bool windows = D >= 128 && (mask & FL_MASK_WINDOW) && !(mask & FL_MASK_DOC);
-  const bool by_tile = dtype == FL_BF16 && !p.pair && kv_lens == nullptr && !windows && longest_first(mask, D, Dv, nbh, p.n_qtiles);
+  const bool by_tile = dtype == FL_BF16 && !p.pair && kv_lens == nullptr && !windows &&
+                       rows_longest_first(mask, D, Dv, Sq, Sk, p.q_off, p.prefix, ke->bm, H / Hkv, nbh, p.n_qtiles);
   p.tile_step = by_tile ? (int)(order == 1 ? nbh / 8 : nbh) : 0;
   p.order_heads = order == 1 && dtype == FL_BF16 && (nbh / share) % 8 == 0 && g_tuning.order < 0 ? (int)share : 1;
 

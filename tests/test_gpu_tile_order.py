@@ -41,3 +41,34 @@ def test_every_problem(B, H, Hkv, S, D, mask):
     for name, a, r in zip(("out", "dq", "dk", "dv"), (x.detach() for x in got), _reference(q, k, v, dout, mask != "none", window)):
         err = (a.float() - r.detach()).flatten(2).norm(dim=-1) / r.detach().flatten(2).norm(dim=-1)
         assert float(err.max()) <= 5e-3, (name, int(err.argmax()), float(err.max()))
+
+
+@pytest.mark.parametrize("mask", ["prefix", "causal"])
+@pytest.mark.parametrize("B,H,Hkv,Sq,Sk,D", [(64, 16, 16, 150, 150, 64), (3, 8, 2, 300, 391, 64), (40, 8, 8, 260, 130, 64), (7, 3, 3, 140, 333, 128), (24, 16, 4, 200, 300, 128)])
+def test_masks_that_hide_nothing(B, H, Hkv, Sq, Sk, D, mask):
+    """A prefix over all keys and rows behind all keys under a causal mask: the order of calls without a mask, and their results."""
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(Sq)
+    q, k, v, dout = (torch.randn(B, h, s, D, generator=gen, device="cuda:0").to(torch.bfloat16) for h, s in ((H, Sq), (Hkv, Sk), (Hkv, Sk), (H, Sq)))
+    x = [t.clone().requires_grad_(True) for t in (q, k, v)]
+    out = fn.attention(*x, **({"prefix": Sk} if mask == "prefix" else {"causal": True, "q_offset": Sk - 1}))
+    got = (out,) + torch.autograd.grad(out, x, dout)
+    for name, a, r in zip(("out", "dq", "dk", "dv"), (x.detach() for x in got), _reference(q, k, v, dout, False, None)):
+        err = (a.float() - r.detach()).flatten(2).norm(dim=-1) / r.detach().flatten(2).norm(dim=-1)
+        assert float(err.max()) <= 5e-3, (name, int(err.argmax()), float(err.max()))
+
+
+@pytest.mark.parametrize("B,H,Hkv,Sq,Sk,D", [(64, 16, 16, 150, 700, 64), (43, 11, 11, 270, 1300, 64), (64, 16, 4, 150, 300, 64)])
+def test_chunks_of_rows_behind_many_keys(B, H, Hkv, Sq, Sk, D):
+    """Many problems of few tiles that see nearly the same keys: side by side, and with heads that share them tile by tile."""
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(Sq)
+    q, k, v, dout = (torch.randn(B, h, s, D, generator=gen, device="cuda:0").to(torch.bfloat16) for h, s in ((H, Sq), (Hkv, Sk), (Hkv, Sk), (H, Sq)))
+    x = [t.clone().requires_grad_(True) for t in (q, k, v)]
+    out = fn.attention(*x, causal=True, q_offset=Sk - Sq)
+    got = (out,) + torch.autograd.grad(out, x, dout)
+    full = torch.zeros(B, H, Sk - Sq, D, device="cuda:0", dtype=torch.bfloat16)
+    want = _reference(torch.cat([full, q], 2), k, v, torch.cat([full, dout], 2), True, None)
+    for name, a, r in zip(("out", "dq", "dk", "dv"), (x.detach() for x in got), (r.detach()[:, :, -a.shape[2]:] for r, a in zip(want, got))):
+        err = (a.float() - r).flatten(2).norm(dim=-1) / r.flatten(2).norm(dim=-1)
+        assert float(err.max()) <= 5e-3, (name, int(err.argmax()), float(err.max()))
