@@ -98,23 +98,77 @@ def test_kernel_of_a_call(variant, B, H, Hkv, S, wide):
     desc = fb.variant_desc(scale=128 ** -0.5, mask={"causal": fb.FL_MASK_CAUSAL, "prefix": fb.FL_MASK_PREFIX}.get(variant, 0), prefix_len=256 if variant == "prefix" else 0,
                            score_mod={"alibi": fb.FL_MOD_ALIBI, "softcap": fb.FL_MOD_SOFTCAP}.get(variant, 0), softcap=30.0 if variant == "softcap" else 0.0)
     slopes = torch.linspace(0.01, 0.5, H, device="cuda:0") if variant == "alibi" else None
-    out, lse = torch.empty_like(q), torch.empty(B, 1, H, S, 1, device="cuda:0")
-    grads = [torch.empty(x.shape, device="cuda:0") for x in (q, k, v)]
-    t = [fb.tensor_desc(x) for x in (q, k, v, out, dout, lse, *grads)]
-    need = max(fb.fl_attn_fwd_workspace_size(t[0], t[1], desc), fb.fl_attn_bwd_workspace_size(t[0], t[1], desc), 16)
-    ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
-    aux = fb.aux_desc(alibi_slopes=slopes, workspace=ws)
-    stream = torch.cuda.current_stream().cuda_stream
-    fb.check(fb.fl_attn_fwd(t[0], t[1], t[2], desc, aux, t[3], t[5], stream))
-    got = []
-    for keys in (0, 1, 2):
-        fb.check(fb.fl_set_tuning("bwd_keys", keys))
-        try:
-            grads[1].fill_(float("nan"))
-            fb.check(fb.fl_attn_bwd(*t[:6], desc, aux, *t[6:], stream))
-            torch.cuda.synchronize()
-        finally:
-            fb.fl_set_tuning("bwd_keys", 0)
-        got.append(grads[1].clone())
+    got = [gradients(keys, q, k, v, dout, desc, slopes)[0] for keys in (0, 1, 2)]
     assert not torch.equal(got[1], got[2])
     assert torch.equal(got[0], got[2 if wide else 1])
+
+
+@pytest.mark.parametrize("Sq,Sk,off", [(130, 700, 570), (130, 700, 150), (333, 600, 1), (64, 257, 193), (1, 300, 299)])
+@pytest.mark.parametrize("variant", ["causal", "prefix", "alibi"])
+def test_rows_at_an_offset(variant, Sq, Sk, off, always):
+    """A chunk of rows against more keys; keys behind the chunk, which no row sees, get exactly zero."""
+    w = VARIANTS[variant](B=1, H=2, S=Sq, Sk=Sk, D=128)
+    w.q_offset = off
+    simple.compare(w, label=f"{variant} {Sq} of {Sk} at {off}")
+    if variant != "alibi":
+        _, (_, dk, dv) = simple.run_backward(w)
+        unseen = max(off + Sq, 70 if variant == "prefix" else 0)
+        assert np.all(dk[..., unseen:, :] == 0) and np.all(dv[..., unseen:, :] == 0)
+
+
+def gradients(keys, q, k, v, dout, desc, slopes=None, spoil=None):
+    """dK and dV of tensors with any strides on the kernel that `keys` asks for; spoil(lse): what is done to the forward pass's lse."""
+    out, lse = torch.empty_like(q), torch.empty(*q.shape[:4], 1, device="cuda:0")
+    grads = [torch.full(x.shape, float("nan"), device="cuda:0") for x in (q, k, v)]
+    t = [fb.tensor_desc(x) for x in (q, k, v, out, dout, lse, *grads)]
+    need = max(fb.fl_attn_fwd_workspace_size(t[0], t[1], desc), fb.fl_attn_bwd_workspace_size(t[0], t[1], desc), 16)
+    aux = fb.aux_desc(alibi_slopes=slopes, workspace=torch.empty(need, dtype=torch.uint8, device="cuda:0"))
+    stream = torch.cuda.current_stream().cuda_stream
+    fb.check(fb.fl_attn_fwd(t[0], t[1], t[2], desc, aux, t[3], t[5], stream))
+    if spoil is not None:
+        spoil(lse)
+    fb.check(fb.fl_set_tuning("bwd_keys", keys))
+    try:
+        fb.check(fb.fl_attn_bwd(*t[:6], desc, aux, *t[6:], stream))
+        torch.cuda.synchronize()
+    finally:
+        fb.fl_set_tuning("bwd_keys", 0)
+    return grads[1:]
+
+
+def normal(*shape, seed=0):
+    return torch.randn(shape, generator=torch.Generator(device="cuda:0").manual_seed(seed), device="cuda:0").to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("B,G,H,Hkv,Sq,Sk", [(2, 1, 4, 2, 333, 300), (1, 3, 2, 2, 130, 257), (2, 2, 4, 4, 65, 600)])
+def test_strides_and_row_axes(B, G, H, Hkv, Sq, Sk, causal):
+    """Heads side by side in storage, rows of a wider buffer, several problems along G: the bits of dense tensors."""
+    desc = fb.variant_desc(scale=128 ** -0.5, mask=fb.FL_MASK_CAUSAL if causal else 0)
+    view = lambda h, s, wide, seed: normal(B, G, s, h, wide, seed=seed)[..., wide - 128:].transpose(2, 3)     # [B, G, h, s, 128]
+    q, k, v, dout = view(H, Sq, 256, 1), view(Hkv, Sk, 128, 2), view(Hkv, Sk, 192, 3), view(H, Sq, 136, 4)
+    assert not q.is_contiguous() and dout.stride(3) == H * 136
+    strided = gradients(2, q, k, v, dout, desc)
+    dense = gradients(2, *(x.contiguous() for x in (q, k, v, dout)), desc)
+    other = gradients(1, q, k, v, dout, desc)
+    for a, b, c in zip(strided, dense, other):
+        assert torch.equal(a, b) and float((a - c).norm() / c.norm()) < 1e-3
+
+
+@pytest.mark.parametrize("variant", ["plain", "causal", "softcap"])
+@pytest.mark.parametrize("row", [5, 100, 198])
+def test_a_row_whose_lse_is_nan(variant, row):
+    """Its keys get NaN and no others do, with 64 and 32 keys per wave: rows inside a tile and the last one, which stands in for rows past the end."""
+    Sq, Sk, off = 199, 400, 30
+    q, k, v, dout = normal(1, 1, 2, Sq, 128, seed=5), normal(1, 1, 2, Sk, 128, seed=6), normal(1, 1, 2, Sk, 128, seed=7), normal(1, 1, 2, Sq, 128, seed=8)
+    desc = fb.variant_desc(scale=128 ** -0.5, mask=fb.FL_MASK_CAUSAL if variant == "causal" else 0, q_offset=off if variant == "causal" else 0,
+                           score_mod=fb.FL_MOD_SOFTCAP if variant == "softcap" else 0, softcap=30.0 if variant == "softcap" else 0.0)
+
+    def spoil(lse):
+        lse[0, 0, 0, row] = float("nan")
+    wide, narrow = (gradients(keys, q, k, v, dout, desc, spoil=spoil) for keys in (2, 1))
+    seen = row + off + 1 if variant == "causal" else Sk
+    for a, b in zip(wide, narrow):
+        assert a[0, 0, 0, :seen].isnan().all() and not a[0, 0, 0, seen:].isnan().any() and not a[0, 0, 1].isnan().any()
+        assert torch.equal(a.isnan(), b.isnan())
+        assert float((a - b)[~a.isnan()].norm() / b[~b.isnan()].norm()) < 1e-3

@@ -72,3 +72,30 @@ def test_chunks_of_rows_behind_many_keys(B, H, Hkv, Sq, Sk, D):
     for name, a, r in zip(("out", "dq", "dk", "dv"), (x.detach() for x in got), (r.detach()[:, :, -a.shape[2]:] for r, a in zip(want, got))):
         err = (a.float() - r).flatten(2).norm(dim=-1) / r.flatten(2).norm(dim=-1)
         assert float(err.max()) <= 5e-3, (name, int(err.argmax()), float(err.max()))
+
+
+@pytest.mark.parametrize("B,H,Hkv,S,D,mask", [
+    (16, 16, 16, 1024, 128, "causal"), (17, 16, 8, 1000, 128, "prefix"), (32, 16, 16, 700, 64, "causal"), (2, 16, 16, 4096, 64, "causal"),     # pairs of tiles
+    (2, 8, 2, 600, 128, "documents"), (3, 16, 2, 500, 128, "documents"), (16, 8, 8, 600, 64, "documents"), (3, 5, 5, 391, 128, "documents"),
+    (5, 8, 4, 391, 64, "prefix"), (24, 16, 16, 400, 128, "prefix")])
+def test_pairs_prefixes_and_documents(B, H, Hkv, S, D, mask):
+    """Launches whose workgroups take a long and a short tile; prefix masks; documents alone, whose dK / dV and, at D = 128 with shared keys, dQ go
+    problem by problem."""
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(S)
+    q, k, v, dout = (torch.randn(B, h, S, D, generator=gen, device="cuda:0").to(torch.bfloat16) for h in (H, Hkv, Hkv, H))
+    ids = torch.cumsum(torch.rand(B, S, generator=gen, device="cuda:0") < 0.01, 1).int()
+    i = torch.arange(S, device="cuda:0")
+    hidden = {"causal": i[None, :] > i[:, None], "prefix": (i[None, :] > i[:, None]) & (i[None, :] >= S // 3)}.get(mask)
+    x = [t.clone().requires_grad_(True) for t in (q, k, v)]
+    out = fn.attention(*x, **{"causal": {"causal": True}, "prefix": {"prefix": S // 3}, "documents": {"q_doc_ids": ids}}[mask])
+    got = (out.detach(),) + torch.autograd.grad(out, x, dout)
+    for b in range(0, B, 5):                         # problem after problem: the reference's scores are large
+        y = [t[b:b + 1].detach().float().requires_grad_(True) for t in (q, k, v)]
+        kk, vv = (t.repeat_interleave(H // Hkv, 1) for t in y[1:])
+        s = torch.matmul(y[0], kk.transpose(-1, -2).contiguous()) * D ** -0.5
+        s = s.masked_fill(hidden if hidden is not None else ids[b][None, :] != ids[b][:, None], float("-inf"))
+        ref = torch.matmul(torch.softmax(s, -1), vv)
+        for name, a, r in zip(("out", "dq", "dk", "dv"), got, (ref.detach(),) + torch.autograd.grad(ref, y, dout[b:b + 1].float())):
+            err = (a[b:b + 1].float() - r).flatten(2).norm(dim=-1) / r.flatten(2).norm(dim=-1)
+            assert float(err.max()) <= 5e-3, (name, b, int(err.argmax()), float(err.max()))
