@@ -330,21 +330,26 @@ int64_t hiding_mask(int64_t mask, int64_t Sk, int64_t q_off, int64_t prefix) {
   return nothing ? 0 : mask;
 }
 
-// Do the longest tiles of all problems go out first, instead of one problem after the other?  Where a mask makes them unequal; at D = 128 many problems of few
-// tiles each are better off with their keys and values in an L2 (us, problem by problem / tile by tile: causal 20 x 16 heads x 600 forward 72 / 77, dQ 92 / 100, windows 64 x 8 x 300
-// dK / dV 93 / 100; the other way 30 x 8 x 500 dQ 62 / 55, 16 x 8 x 999 101 / 75).  Below, over 90 drawn calls of more than 1024 tiles, all masks, 2 - 9 tiles a problem: the
-// forward pass and dQ are within 2 % either way on average (worst 11 and 4 % of the backward pass lost, best 13 and 5 % gained), dK / dV gains up to a quarter of the
-// backward pass (40 x 32/8 x 416 301 / 225).  Where nothing is hidden all are better off problem by problem (D = 64: 64 x 8 x 300 dK / dV 52 / 57, a prefix over all of 64 x 16 x 256
-// rows and 1024 keys forward 102 / 111, dQ and its backward pass 367 / 388).
+// Do the longest tiles of all problems go out first, instead of one problem after the other?  Where a mask makes them unequal; at
+// D = 128 only if the problems are few or have many tiles, otherwise their keys and values are better off in an L2.
+// Measured, us, problem by problem / tile by tile.  D = 128: causal 20 x 16 heads x 600 forward 72 / 77, dQ 92 / 100, windows
+// 64 x 8 x 300 dK / dV 93 / 100; the other way dQ 30 x 8 x 500 62 / 55, 16 x 8 x 999 101 / 75.  Below D = 128, more than 1024 tiles
+// of 2 - 9 per problem, 90 drawn calls under all masks: forward and dQ within 2 % either way on average (forward 11 % lost to 13 %
+// gained, dQ 4 to 5 % of the backward pass), dK / dV up to a quarter of the backward pass gained (40 x 32/8 x 416 301 / 225).
+// Nothing hidden, D = 64: 64 x 8 x 300 dK / dV 52 / 57; a prefix over all of 64 x 16 heads x 256 rows, 1024 keys: forward 102 / 111,
+// backward pass, dQ's order 367 / 388.
 bool longest_first(int64_t hiding, int64_t D, int64_t Dv, int64_t problems, int64_t tiles) {
   return hiding != 0 && (std::max(D, Dv) < 128 || tiles >= 8 || problems * tiles <= 1024);
 }
 
-// longest_first() for q-tiles of `rows` rows.  Where those of many problems see nearly the same keys, as a chunk's behind many cached ones does, they are better off side by side,
-// unless other heads read the same keys, too (D = 64, causal, the last rows of the keys, us problem by problem / tile by tile, forward and backward pass: 64 x 16 x 130 of 2000
-// 171 / 215 and 616 / 652, 128 x 8 x 256 of 1500 139 / 172 and 504 / 544, 64 x 16 x 256 of 1024 99 / 99 and 348 / 373; less alike 64 x 16 x 256 of 512 51 / 53 and 186 / 183,
-// 64 x 8 x 300 of 900 58 / 60 and 199 / 192; heads that share keys 64 x 16/2 x 256 of 1024 82 / 80 and 257 / 253).
-bool rows_longest_first(int64_t mask, int64_t D, int64_t Dv, int64_t Sq, int64_t Sk, int64_t q_off, int64_t prefix, int64_t rows, int64_t share, int64_t problems, int64_t tiles) {
+// longest_first() for q-tiles of `rows` rows.  Where those of many problems see nearly the same keys, as a chunk's behind many cached
+// ones does, they are better off side by side, unless other heads read the same keys, too.
+// Measured, us, problem by problem / tile by tile, forward and backward pass at D = 64, causal, the last rows of the keys: 64 x 16 heads
+// x 130 of 2000 171 / 215 and 616 / 652, 128 x 8 x 256 of 1500 139 / 172 and 504 / 544, 64 x 16 x 256 of 1024 99 / 99 and 348 / 373;
+// less alike 64 x 16 x 256 of 512 51 / 53 and 186 / 183, 64 x 8 x 300 of 900 58 / 60 and 199 / 192; heads that share keys
+// 64 x 16/2 x 256 of 1024 82 / 80 and 257 / 253.
+bool rows_longest_first(int64_t mask, int64_t D, int64_t Dv, int64_t Sq, int64_t Sk, int64_t q_off, int64_t prefix, int64_t rows,
+                        int64_t share, int64_t problems, int64_t tiles) {
   auto seen = [&](int64_t i) { return std::min(Sk, std::max(i + q_off + 1, mask == FL_MASK_PREFIX ? prefix : 0)); };   // keys of row i
   const bool alike = (mask == FL_MASK_CAUSAL || mask == FL_MASK_PREFIX) && 100 * seen(std::min(rows, Sq) - 1) >= 83 * seen(Sq - 1);
   if (alike && share == 1 && tiles < 8 && problems * tiles > 1024) return false;
@@ -355,10 +360,12 @@ hipError_t run_bwd_dq(const fl::BwdEntry* be, const fl::BwdParams& p_in, int nbl
   fl::BwdParams p = p_in;
   const int problems = nblocks / std::max(p.n_qtiles, 1);
   const int64_t share = p.order_q ? p.order_heads : 1;
-  // (documents alone, D = 128, heads that read the same keys: their tiles stay side by side; 2 x 16/2 x 11147 578 us, 600 tile by tile, 2 x 32/8 x 8525 651 and 648)
+  // Documents alone at D = 128: tiles of heads that read the same keys stay side by side (us, side by side / tile by tile: 2 x 16/2 x
+  // 11147 578 / 600, 2 x 32/8 x 8525 651 / 648).
   const bool shared_documents = be->key.mask == (int)fl::kMaskDoc && share > 1 && std::max(be->key.D, be->key.Dv) >= 128;
-  p.step_q = !shared_documents && rows_longest_first(be->key.mask, be->key.D, be->key.Dv, p.Sq, p.Sk, p.q_off, p.prefix, be->bm, p.H / std::max(p.Hkv, 1), problems, p.n_qtiles)
-                 ? (p.order_q ? problems / 8 : problems) : 0;
+  const bool by_tile = !shared_documents && rows_longest_first(be->key.mask, be->key.D, be->key.Dv, p.Sq, p.Sk, p.q_off, p.prefix, be->bm,
+                                                               p.H / std::max(p.Hkv, 1), problems, p.n_qtiles);
+  p.step_q = by_tile ? (p.order_q ? problems / 8 : problems) : 0;
   p.q_tiles = fl::Divisor::of(p.step_q > 0 ? p.step_q : p.n_qtiles * share);
   p.q_share = fl::Divisor::of(share);
   p.q_heads = fl::Divisor::of(p.H);
@@ -366,13 +373,15 @@ hipError_t run_bwd_dq(const fl::BwdEntry* be, const fl::BwdParams& p_in, int nbl
   p.by_g = fl::Divisor::of(p.G);
   return be->jit != nullptr ? fl::jit_backward_launch(*be, 0, p, nblocks, stream) : be->dq(p, nblocks, stream);
 }
-// The dK/dV kernel with 64 keys per wave where the variant has one, the call suits it and its launch is not longer than that of 128 keys per
-// workgroup by more than it is faster.  At work it is 1.2 - 1.3 times as fast (soft-cap 1.17), so what decides is how many more keys its
-// workgroups of 256 go through in a row on a compute unit: rows past a short sequence's end, a last round half empty, and a start that nothing hides.
-// Over 600 drawn dK / dV launches at D = 128 the choice is 0.3 % off the faster kernel on average; a rule by keys alone, 1.34 times as many at
-// most, was 1.5 % off and up to 31 % slower than 128 keys.  us, 128 / 256 keys: taken causal 3 x 16 x 3885 411 / 357, 6 x 16 x 1641 180 / 166, prefix 5 x 16 x 1490 132 / 120,
-// no mask 64 x 16/2 x 777 850 / 803, ALiBi 10 x 32/8 x 1284 856 / 722, soft-cap 15 x 16 x 1349 664 / 622; not taken causal 18 x 16 x 289 53 / 69, 64 x 16 x 320 176 / 216,
-// no mask 64 x 8 x 278 104 / 120, 3 x 16 x 1842 197 / 213, ALiBi 8 x 16/2 x 1386 334 / 352, soft-cap 6 x 16 x 843 123 / 142, 2 x 16/2 x 2838 356 / 404.
+// The dK/dV kernel with 64 keys per wave where the variant has one, the call suits it and its launch is not longer than that of 128 keys
+// per workgroup by more than it is faster.  At work it is 1.2 - 1.3 times as fast (soft-cap 1.17), so what decides is how many more keys
+// its workgroups of 256 go through in a row on a compute unit: rows past a short sequence's end, a last round half empty, and a start
+// that nothing hides.  Over 600 drawn dK / dV launches at D = 128 the choice is 0.3 % off the faster kernel on average; a rule by keys
+// alone, 1.34 times as many at most, was 1.5 % off and up to 31 % slower than 128 keys.
+// Measured, us, 128 / 256 keys.  Taken: causal 3 x 16 x 3885 411 / 357, 6 x 16 x 1641 180 / 166, prefix 5 x 16 x 1490 132 / 120, no mask
+// 64 x 16/2 x 777 850 / 803, ALiBi 10 x 32/8 x 1284 856 / 722, soft-cap 15 x 16 x 1349 664 / 622.  Not taken: causal 18 x 16 x 289 53 / 69,
+// 64 x 16 x 320 176 / 216, no mask 64 x 8 x 278 104 / 120, 3 x 16 x 1842 197 / 213, ALiBi 8 x 16/2 x 1386 334 / 352, soft-cap 6 x 16 x 843
+// 123 / 142, 2 x 16/2 x 2838 356 / 404.
 const fl::WideEntry* wide_dkdv(const fl::BwdEntry* be, const fl::BwdParams& p) {
   if (be->jit != nullptr || g_tuning.bwd_keys == 1) return nullptr;
   const fl::WideEntry* w = fl::find_wide(be->key);
@@ -402,8 +411,9 @@ hipError_t run_bwd_dkdv(const fl::BwdEntry* be, const fl::WideEntry* wide, const
   const int bm = wide != nullptr ? wide->bm : be->bm;
   pk.n_ktiles = (p.Sk + bm - 1) / bm;
   const int nblocks = (int)(problems * pk.n_ktiles);
-  // (Documents alone do not make the first key tiles the longest ones, and a problem's tiles in a row share the rows of their document; us, problem by problem / tile by tile, three
-  // sets of 12 documents: 2 x 16/2 x 11147, D = 128 931 / 1052, D = 64 462 / 493, 2 x 32/8 x 8525, D = 128 1112 / 1233, 4 x 16 x 4096 351 / 356, 1 x 16 x 16000 799 / 812.)
+  // Documents alone do not make the first key tiles the longest ones, and a problem's tiles in a row share the rows of their document.
+  // Measured, us, problem by problem / tile by tile, three sets of 12 documents: 2 x 16/2 x 11147, D = 128 931 / 1052, D = 64 462 / 493,
+  // 2 x 32/8 x 8525, D = 128 1112 / 1233, 4 x 16 x 4096 351 / 356, 1 x 16 x 16000 799 / 812.
   const bool by_tile = wide != nullptr || (be->key.mask != (int)fl::kMaskDoc &&
                                            longest_first(hiding_mask(be->key.mask, p.Sk, p.q_off, p.prefix), be->key.D, be->key.Dv, problems, pk.n_ktiles));
   pk.step_k = by_tile ? (int)(p.order_k ? problems / 8 : problems) : 0;
@@ -432,11 +442,13 @@ constexpr int kBwdKeysPerWg = 128;                 // keys per workgroup of the 
 // sums a small kernel adds up afterwards.  Cutting pays while a workgroup keeps enough (head, 64-row
 // query tile) items to amortise its partial sums: up to 1024 workgroups if at least 24 items remain
 // each, up to 2048 if at least 256 remain (fitted to a sweep over the paper's grouped-head shapes).
-// Fewer items are worth cutting where the launch leaves compute units idle.  In items, a launch takes the workgroups that a compute unit has one after
-// the other (two side by side at D <= 64; under a mask, where a workgroup has half of the longest one's rows on average, 0.6 of those past the first),
-// each 1.5 longer than its items, and the partial sums 0.01 per workgroup and 64 channels: over 270 drawn backward calls of 16/2 and 32/8 heads, 64 - 8192 rows, within
-// 1 % of the best cut on average, where the rule above alone was 19 % off (us, then and now: causal 2 x 16/2 x 153, D = 64 53 / 24, 1 x 16/2 x 591, D = 128
-// 109 / 61, window 512 1 x 32/8 x 638 110 / 64, no mask 1 x 32/8 x 689 118 / 67, 3 x 32/8 x 590, D = 64 94 / 65).
+// Fewer items are worth cutting where the launch leaves compute units idle.  In items, a launch takes the workgroups that a compute unit
+// has one after the other (two side by side at D <= 64; under a mask, where a workgroup has half of the longest one's rows on average, 0.6
+// of those past the first), each 1.5 longer than its items, and the partial sums 0.01 per workgroup and 64 channels.
+// Over 340 drawn backward calls with groups of 2 - 16 heads, 64 - 8192 rows, the cut is 0.8 % off the best one on average (15 % at worst),
+// where the rule above alone was 16 % off (3.1x); against that rule four calls lose more than 2 %, 8 % at most.  Measured, us, without
+// and with it: causal 2 x 16/2 x 153, D = 64 53 / 24, 1 x 16/2 x 591, D = 128 109 / 61, window 512 1 x 32/8 x 638 110 / 64, no mask
+// 1 x 32/8 x 689 118 / 67, 3 x 32/8 x 590, D = 64 94 / 65.
 int choose_hsplit(int64_t B, int64_t G, int64_t H, int64_t Hkv, int64_t Sq, int64_t Sk, int64_t D, uint32_t mask, int64_t window) {
   if (Hkv <= 0 || H <= Hkv || Sk <= 0) return 1;
   const int64_t group = H / Hkv, wgs = B * G * Hkv * ((Sk + kBwdKeysPerWg - 1) / kBwdKeysPerWg);
@@ -1668,12 +1680,12 @@ static fl_status forward_call(const fl_tensor* q, const fl_tensor* k, const fl_t
     p.lds_bytes = (int)(kv + (staged ? stage : 0));
   }
   const int64_t nbh = B * G * H / ke->key.pack;    // (packed heads: a workgroup takes key.pack heads of one kv head)
-  // bf16 kernels under a causal / prefix mask without a window: the work of a q-tile grows with its index.  Either the tiles of all heads go out
-  // longest first, or a workgroup takes a long and a short one, which makes all alike and keeps a head's tiles together, but leaves compute units idle
-  // where the pairs don't come out as whole rounds (two waves per SIMD).  Pairs where they fill 80 % of their rounds (a middle tile without a partner is
-  // half a pair); at D = 64 they cost short lists more than they give, unless the
-  // launch has three rounds of them.  Measured (us, pairs / single tiles): D = 128 16 x 16 x 1024 112 / 125, 16 x 8 x 999 53 / 56,
-  // 2 x 16 x 4096 146 / 152, 1 x 16 x 8192 270 / 281, with 55 and 75 % 5 x 16 x 1777 105 / 87, 32 x 16 x 700 176 / 156; D = 64 1 x 16 x 8192 168 / 177, 2 x 16 x 4096 92 / 95,
+  // bf16 kernels under a causal / prefix mask without a window: the work of a q-tile grows with its index.  Either the tiles of all heads go
+  // out longest first, or a workgroup takes a long and a short one, which makes all alike and keeps a head's tiles together, but leaves
+  // compute units idle where the pairs don't come out as whole rounds (two waves per SIMD).  Pairs where they fill 80 % of their rounds (a
+  // middle tile without a partner is half a pair); at D = 64 they cost short lists more than they give, unless the launch has three rounds.
+  // Measured, us, pairs / single tiles.  D = 128: 16 x 16 x 1024 112 / 125, 16 x 8 x 999 53 / 56, 2 x 16 x 4096 146 / 152, 1 x 16 x 8192
+  // 270 / 281, with 55 and 75 % 5 x 16 x 1777 105 / 87, 32 x 16 x 700 176 / 156.  D = 64: 1 x 16 x 8192 168 / 177, 2 x 16 x 4096 92 / 95,
   // 32 x 16 x 700 70 / 73, 8 x 16 x 1024 38 / 33, 4 x 16 x 2048 59 / 52, 8 x 16 x 2048 98 / 93, 5 x 16 x 1777 63 / 51, 16 x 8 x 999 37 / 32.
   const bool tri = (mask & (FL_MASK_CAUSAL | FL_MASK_PREFIX)) != 0 && (mask & (FL_MASK_WINDOW | FL_MASK_DOC)) == 0;
   const int64_t pairs = nbh * ((p.n_qtiles + 1) / 2), round = 256 * 8 / (ke->key.nwaves > 0 ? ke->key.nwaves : 4);
@@ -1692,9 +1704,10 @@ static fl_status forward_call(const fl_tensor* q, const fl_tensor* k, const fl_t
   // 1 x 32 / 8 x 32768 688 -> 676; window 256, 4 x 16 / 2 x 4096, D = 64, 50.1 -> 45.6; chunks of 8 x 512 rows, 32 / 8 heads, D = 128, 417 -> 407 and 371 -> 368;
   // unmasked and causal 16 / 2 heads, D = 64, within 0.6 %.
   const int64_t share = H / Hkv / ke->key.pack;
-  // Single tiles of unequal length: longest first over all heads (us, heads one after the other and tiles first: causal 2 x 16 x 2048, D = 64 43 / 33, D = 128 59 / 50;
-  // windows and documents 8 x 16 x 1500 64 / 56 and 98 / 83; documents 4 x 16 x 4096 123 / 116 and 184 / 171; windows, whose tiles are nearly alike,
-  // 32 x 8 x 500 30 / 24 and 45.7 / 44.9, 4 x 16 x 4096 67 / 65 and 112.5 / 115.3: not at D = 128).  Chunks of sequences go out by their keys.
+  // Single tiles of unequal length: longest first over all heads, but not windows, whose tiles are nearly alike, at D = 128, nor chunks of
+  // sequences, which go out by their keys.  Measured, us, heads one after the other / tiles first: causal 2 x 16 x 2048, D = 64 43 / 33,
+  // D = 128 59 / 50; windows and documents 8 x 16 x 1500 64 / 56 and 98 / 83; documents 4 x 16 x 4096 123 / 116 and 184 / 171; windows
+  // 32 x 8 x 500 30 / 24 and 45.7 / 44.9, 4 x 16 x 4096 67 / 65 and 112.5 / 115.3.
   const bool windows = D >= 128 && (mask & FL_MASK_WINDOW) && !(mask & FL_MASK_DOC);
   const bool by_tile = dtype == FL_BF16 && !p.pair && kv_lens == nullptr && !windows &&
                        rows_longest_first(mask, D, Dv, Sq, Sk, p.q_off, p.prefix, ke->bm, H / Hkv, nbh, p.n_qtiles);

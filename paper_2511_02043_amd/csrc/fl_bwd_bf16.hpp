@@ -134,8 +134,9 @@ __host__ __device__ __forceinline__ void query_range(const uint32_t MASK, int j_
   lo = min(lo, hi);
 }
 
-// classify_block() under the positional masks for a wave whose rows, or keys, stay the same: what the other side is compared with, formed once.  (Two dozen scalar
-// instructions per 32 x 32 block otherwise, in front of its first product: windows and documents 8 x 16 heads x 2048 rows, D = 64, 239 -> 236 us for the training step, dK / dV 109 -> 104.)
+// classify_block() under the positional masks for a wave whose rows, or keys, stay the same: what the other side is compared with, formed
+// once.  (Two dozen scalar instructions per 32 x 32 block otherwise, in front of its first product: windows and documents 8 x 16 heads x
+// 2048 rows, D = 64, 239 -> 236 us for the training step, dK / dV 109 -> 104.)
 constexpr int kFarBelow = -0x7fffffff - 1, kFarAbove = 0x7fffffff;
 struct KeyBounds {                                 // of rows at the positions [q_lo, q_hi]
   int end, first, whole_last, whole_first;

@@ -8,10 +8,11 @@
 //   * the elementwise work is cut into units of one score and put behind single MFMAs, P behind those of dP and half of dV, dS behind the rest of dV and half of dK;
 //   * delta is the accumulator that dP starts from (V is negated, the product is delta - dP), so dS takes one multiplication;
 //   * scores are hidden once, before their exponentials, in the few blocks that a mask cuts.
-// Matrix cores 62 % busy, at the lower clock that this leaves under the power cap.  Measured (us, D = 128, 128 keys per workgroup with specialised waves and this): causal
-// 2 x 32/8 x 8192 2365 -> 1844, 4 x 16 x 4096 712 -> 551, no mask 4 x 16 x 4096 1375 -> 1028, ALiBi 2 x 16 x 4096 668 -> 519, soft-cap 670 -> 578, prefix 4 x 16 x 4096 655 -> 514;
-// D = 64, Dv = 128, one stream of 2 x 16 x 4096 339 -> 232.  Windows and documents, of which few blocks are whole, gain nothing (241 -> 235, 374 -> 379), nor does D = 64 (causal 8 x 16 x 1999
-// 218 -> 241, 4 x 16 x 4096 354 -> 310): they have no such kernel.
+// Matrix cores 64 % busy (46 % at D = 64, Dv = 128), at the lower clock that this leaves under the power cap.
+// Measured, us, one card, 128 keys per workgroup with specialised waves / this kernel, D = 128: causal 2 x 32/8 x 8192 2280 / 1812, 4 x 16 x 4096
+// 610 / 501, no mask 4 x 16 x 4096 1137 / 872, ALiBi 2 x 16 x 4096 599 / 453, soft-cap 639 / 544, prefix 4 x 16 x 4096 605 / 499; D = 64, Dv = 128,
+// one stream of 2 x 16 x 4096 290 / 223.  Windows and documents, of which few blocks are whole, gain nothing (241 / 235, 374 / 379), and D = 64 on
+// long sequences only (causal 8 x 16 x 1999 218 / 241, 4 x 16 x 4096 354 / 310): they have no such kernel.
 #pragma once
 #include "fl_bwd_bf16.hpp"
 

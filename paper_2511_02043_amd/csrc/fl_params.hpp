@@ -48,9 +48,10 @@ constexpr float kLn2 = 0.6931471805599453f;
 // Granularity (rows / keys) of the document-id summaries used by the tile skipper.
 constexpr int kSumBlock = 32;
 
-// n / d of a whole number d >= 1 for 0 <= n < 2^31, by a product: m = ceil(2^s / d) with s = 31 + ceil(log2 d) is at most 2^32 - 1 and the quotient exact.
-// A workgroup's index becomes tile, batch, row and head by five divisions by sizes of the call, one after the other; made by the
-// device, each is some thirty instructions on both units.  (forward of 128 x 8 x 384 Evoformer rows, D = 32, 3072 workgroups of twelve steps: 80.9 -> 76.3 us; windows and documents 8 x 16 x 2048, D = 64, training step 246 -> 241; causal 1 x 8 x 128 7.6 -> 7.3)
+// n / d of a whole number d >= 1 for 0 <= n < 2^31, by a product: m = ceil(2^s / d) with s = 31 + ceil(log2 d) is at most 2^32 - 1 and the
+// quotient exact.  A workgroup's index becomes tile, batch, row and head by five divisions by sizes of the call, one after the other; made by
+// the device, each is some thirty instructions on both units.  (us: forward of 128 x 8 x 384 Evoformer rows, D = 32, 3072 workgroups of twelve
+// steps 80.9 -> 76.3; windows and documents 8 x 16 x 2048, D = 64, training step 246 -> 241; causal 1 x 8 x 128 7.6 -> 7.3)
 struct Divisor {
   uint32_t m, s, d;
 #ifndef __HIPCC_RTC__

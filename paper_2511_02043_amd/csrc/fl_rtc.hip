@@ -604,12 +604,13 @@ static fl_status custom_forward(fl_custom_variant* v, const fl_tensor* q, const 
   const int64_t nbh = B * G * H;
   p.order = nbh % 8 == 0 ? 1 : 0;
   p.order_heads = 1;
-  // Under a causal / prefix base mask without a window a workgroup takes a long and a short q-tile.  A mask expression with a map may leave anything of
-  // them, equal halves of a launch or a few long tiles: its q-tiles go out by themselves, the last ones of all problems first, but for few tiles per
-  // problem whose pairs come out as whole rounds of the compute units (as in forward_call): there pairs are ahead whatever is hidden.  us, pairs / tiles, one
-  // key in 64 hidden and 12 documents: D = 128 16 x 16 heads x 1024 135 / 143 and 126 / 129, 32 x 8 x 1024 136 / 142 and 133 / 140, 16 x 16 x 1500 253 / 264 and 203 / 208,
-  // 64 x 8 x 300 82 / 84 and 89 / 91, D = 64 64 x 16 x 256 52 / 54 and 65 / 65; beyond, the documents decide: D = 128 16 x 16 x 2048 415 / 427 and 308 / 288,
-  // 4 x 16 x 4096 347 / 357 and 201 / 188, D = 64 64 x 16 x 500 120 / 123 and 140 / 131, 1 x 16 x 8192 255 / 267 and 153 / 101.
+  // Under a causal / prefix base mask without a window a workgroup takes a long and a short q-tile.  A mask expression with a map may leave
+  // anything of them, equal halves of a launch or a few long tiles: its q-tiles go out by themselves, the last ones of all problems first, but
+  // for few tiles per problem whose pairs come out as whole rounds of the compute units (as in forward_call): there pairs are ahead whatever
+  // is hidden.  Measured, us, pairs / tiles, one key in 64 hidden and 12 documents.  D = 128: 16 x 16 heads x 1024 135 / 143 and 126 / 129,
+  // 32 x 8 x 1024 136 / 142 and 133 / 140, 16 x 16 x 1500 253 / 264 and 203 / 208, 64 x 8 x 300 82 / 84 and 89 / 91; D = 64: 64 x 16 x 256
+  // 52 / 54 and 65 / 65.  Beyond, the documents decide: D = 128 16 x 16 x 2048 415 / 427 and 308 / 288, 4 x 16 x 4096 347 / 357 and 201 / 188,
+  // D = 64 64 x 16 x 500 120 / 123 and 140 / 131, 1 x 16 x 8192 255 / 267 and 153 / 101.
   const bool tri = (v->mask & (FL_MASK_CAUSAL | FL_MASK_PREFIX)) != 0 && (v->mask & FL_MASK_WINDOW) == 0;
   const int64_t pairs = nbh * ((p.n_qtiles + 1) / 2), round = 256 * 8 / v->waves;
   const bool filled = 10 * nbh * p.n_qtiles >= 16 * round * ((pairs + round - 1) / round);

@@ -244,9 +244,10 @@ std::tuple<int, int64_t, Tensor, OptTensor> paged(bool decode, const Tensor& q, 
   return {status, (int64_t)need, out, lse};
 }
 
-// ---- the autograd nodes of training calls.  A node written in Python is entered by the engine's thread under the interpreter's lock, which the
-// calling thread has just given up.  A causal forward and backward call on [1, 8, 110, 128] took 45 or 89 us with one, by where the process runs, and
-// takes 38 or 72 with these; documents and windows 3 x 32/8 x 182 61 or 97, and 49 or 84.  Calls under a transform, a trace, forward-mode derivatives or torch.compile keep the Python node (functional.py).
+// ---- the autograd nodes of training calls.  A node written in Python is entered by the engine's thread under the interpreter's lock, which
+// the calling thread has just given up.  A causal forward and backward call on [1, 8, 110, 128] took 45 or 89 us with one, by where the
+// process runs, and takes 38 or 72 with these; documents and windows 3 x 32/8 x 182 61 or 97, and 49 or 84.  Calls under a transform, a
+// trace, forward-mode derivatives or torch.compile keep the Python node (functional.py).
 
 PyObject* g_check = nullptr;                       // binding.check: raises for a status
 
